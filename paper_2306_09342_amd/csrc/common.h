@@ -141,13 +141,15 @@ struct Epi {
     float sign;
     int64_t ldo;
     float* colsum;      // EPI_GELU_BWD, matrix-core path: per-row-strip column sums of the output,
-                        // [gemm_colsum_rows(M)][N] float32 (nullable)
+                        // [gemm_colsum_strips(M, N)][N] float32 (nullable)
     bool solo;          // the launch runs alone on the device (one stream): the tile shape may be chosen
                         // to fill the chip by itself; results do not depend on it
 };
-// 64-row strips of column-sum partials the matrix-core GEMM writes for M rows, and an upper bound for sizing
-int gemm_colsum_strips(int M);
-inline int gemm_colsum_strips_max(int M) { return ((M + 255) / 256) * 4; }
+// rows of column-sum partials (strips of 32 or 64 token rows) a bf16 GEMM with an [M, N] output writes
+int gemm_colsum_strips(int M, int N);
+// tile of a bf16 GEMM launch; _K2 / _K3: the workgroup's wavefronts form that many groups that share the contraction;
+// 32x32 and 64x64: every wavefront takes its own part of it
+enum GemmShape { GS_32x32, GS_64x64, GS_64x128_K3, GS_128x128_K2, GS_128x128, GS_160x128 };
 
 // C[M,N] (+epilogue) = A[M,K] * B[N,K]^T.  A, B row-major with leading dims lda, ldb.
 // fp32 flavour: A, B float.  bf16 flavour: A, B bf16.
@@ -158,10 +160,6 @@ int gemm_nt_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64
 // C[M,N] = A[M,K] * B[K,N]  (B row-major [K, ldb]): the input-gradient form, weights as stored.
 int gemm_nn_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
                  int M, int N, int K, const Epi& epi);
-// true when the pipelined matrix-core kernel (the one that honours Epi::colsum) takes this problem
-bool gemm_bf16_fast_path(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int N, int K, const Epi& epi);
-int gemm_nn_bf16_simple(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
-                        int M, int N, int K, const Epi& epi);
 int gemm_nn_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb,
                 int M, int N, int K, const Epi& epi);
 // dW[N,K] (float32, ld = K) = G[M,N]^T * A[M,K]  -- reduction over the M tokens.
@@ -191,11 +189,7 @@ int wgrad_group_ranges(int M, const int* N, const int* K, int count);
 struct WgradProblem { const bf16* G; const bf16* A; float* out; int64_t ldg, lda, split_stride; int N, K, tile0; };
 struct WgradGroup { WgradProblem p[WGRAD_GROUP_MAX]; int count, tiles_total; };
 
-// plain vector-ALU flavours (also the fall-back for shapes the matrix-core kernels do not take)
-int gemm_nt_bf16_simple(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
-                        int M, int N, int K, const Epi& epi);
-int gemm_wgrad_bf16_simple(hipStream_t s, const bf16* G, int64_t ldg, const bf16* A, int64_t lda,
-                           int M, int N, int K, float* dW);
+// plain vector-ALU attention: float32 mode, and the bf16 heads that the matrix-core backward does not take
 template <typename T>
 int attention_forward_simple(hipStream_t s, const T* qkv, T* o, float* lse, int B, int T_, int H, int dh,
                              const int* key_len = nullptr);

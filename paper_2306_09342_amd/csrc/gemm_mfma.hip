@@ -1,196 +1,102 @@
-// bf16 matrix-core GEMM entry points and the register-staged NT kernel.
+// bf16 matrix-core GEMM entry points.
 //
-//  gemm_nt_bf16 / gemm_nn_bf16   C = A * B^T  /  C = A * B  with fused epilogue.  Problems with
-//            K % 32 == 0 go to the pipelined direct-to-LDS kernel (gemm_nt_dma.hip); other K % 8 == 0
-//            problems to the register-staged kernel below (global -> VGPR -> LDS, padded tiles);
-//            anything else to the plain-ALU kernels.
+//  gemm_nt_bf16 / gemm_nn_bf16   C = A * B^T  /  C = A * B  with fused epilogue: picks the tile and, for launches that do
+//            not fill the chip, the split of the contraction (gemm_nt_dma.hip, gemm_ksplit.hip).
 //  gemm_wgrad_bf16               dW[N,K] = G[M,N]^T * A[M,K]: picks the number of token ranges and
 //            launches the kernel of gemm_wgrad_dma.hip; the partial tiles of the ranges are summed
 //            afterwards in range order, so results do not depend on scheduling.
-//
-// Register layout of v_mfma_f32_32x32x16_bf16, per lane l of the wavefront:
-//   A operand: row l%32, k = 8*(l/32) .. +7;  B operand: column l%32, same k;
-//   D: column l%32, rows 8*(v/4) + 4*(l/32) + v%4 for accumulator register v.
 #include "mfma.h"
 
 namespace rev {
 
 // ----------------------------------------------------------------------------------------
-// epilogues (compile-time kind); m, n are global indices, acc the float32 sum
+// which kernel and tile a GEMM launch takes
 // ----------------------------------------------------------------------------------------
-template <int KIND>
-__device__ __forceinline__ void epi_store(const Epi& e, int m, int n, float acc, float biasv) {
-    const int64_t idx = (int64_t)m * e.ldo + n;
-    if (KIND == EPI_BIAS) {
-        reinterpret_cast<bf16*>(e.out)[idx] = __float2bfloat16(acc + biasv);
-    } else if (KIND == EPI_BIAS_GELU) {
-        float h = acc + biasv;
-        if (e.out != nullptr) reinterpret_cast<bf16*>(e.out)[idx] = __float2bfloat16(h);
-        reinterpret_cast<bf16*>(e.out2)[idx] = __float2bfloat16(gelu_f(h));
-    } else if (KIND == EPI_RESIDUAL) {
-        e.outf[idx] = e.res[idx] + e.sign * (acc + biasv);
-    } else if (KIND == EPI_GELU_BWD) {
-        float h = __bfloat162float(reinterpret_cast<const bf16*>(e.aux)[idx]);
-        reinterpret_cast<bf16*>(e.out)[idx] = __float2bfloat16(acc * gelu_grad_f(h));
-    } else if (KIND == EPI_PLAIN) {
-        reinterpret_cast<bf16*>(e.out)[idx] = __float2bfloat16(acc);
-    } else {
-        e.outf[idx] = acc;
-    }
+static inline int tiles_of(int M, int N, int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
+
+// Cost of a launch in units of "one tile per workgroup slot": the chip holds 512 workgroups of either
+// shape (two per CU); a last round that leaves at most one workgroup per CU was measured at about 0.55
+// of a full round, any fuller one costs a whole round.
+static double rounds_cost(int tiles) {
+    const int full = tiles / 512, rem = tiles % 512;
+    return full + (rem == 0 ? 0.0 : (rem <= 256 ? 0.55 : 1.0));
+}
+// 160x128 tiles do 1.25x the work of 128x128 ones at about 0.9 of their rate.  Only launches with more than
+// one full round of 128-row tiles are considered: below that the chip is not full and the cost of a
+// partly filled round does not follow the model (measured: the tall tile loses there).
+static bool tall_tiles_pay(int M, int N) {
+    if (tiles_of(M, N, 128, 128) <= 512) return false;
+    const double c128 = rounds_cost(tiles_of(M, N, 128, 128)) * 128.0;
+    const double c160 = rounds_cost(tiles_of(M, N, 160, 128)) * 160.0 * 1.10;
+    return c160 < 0.97 * c128;
 }
 
-// ----------------------------------------------------------------------------------------
-// NT GEMM
-// ----------------------------------------------------------------------------------------
-constexpr int NT_BK = 64;
-constexpr int NT_LDP = NT_BK + 8;     // LDS row pitch in elements (144 B: 16-byte rows land on distinct banks)
-
-template <int BM, int BN, int WM, int WN, int KIND>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_nt_kernel(const bf16* __restrict__ A, int64_t lda,
-                                                                const bf16* __restrict__ B, int64_t ldb,
-                                                                int M, int N, int K, Epi epi) {
-    constexpr int NTH = WM * WN * 64;
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-    constexpr int CA = BM * (NT_BK / 8) / NTH, CB = BN * (NT_BK / 8) / NTH;
-    static_assert(CA * NTH == BM * (NT_BK / 8) && CB * NTH == BN * (NT_BK / 8), "tile/thread mismatch");
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    uint16_t* As = reinterpret_cast<uint16_t*>(smem);                 // [2][BM][LDP]
-    uint16_t* Bs = As + 2 * BM * NT_LDP;                              // [2][BN][LDP]
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-    const int tiles_n = (N + BN - 1) / BN;
-    const int tile = xcd_remap(blockIdx.x, gridDim.x);
-    const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
-
-    f32x16_t acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    u32x4_t ra[CA], rb[CB];
-    const u32x4_t zero4 = {0u, 0u, 0u, 0u};
-#define NT_GLOAD(kt)                                                                                   \
-    {                                                                                                  \
-        _Pragma("unroll") for (int i = 0; i < CA; ++i) {                                               \
-            const int idx = tid + i * NTH, row = idx >> 3, ch = idx & 7;                               \
-            const int gk = (kt) * NT_BK + ch * 8;                                                      \
-            const int gr = min(m0 + row, M - 1);                                                       \
-            ra[i] = (gk < K) ? *reinterpret_cast<const u32x4_t*>(A + (int64_t)gr * lda + gk) : zero4;    \
-        }                                                                                              \
-        _Pragma("unroll") for (int i = 0; i < CB; ++i) {                                               \
-            const int idx = tid + i * NTH, row = idx >> 3, ch = idx & 7;                               \
-            const int gk = (kt) * NT_BK + ch * 8;                                                      \
-            const int gr = min(n0 + row, N - 1);                                                       \
-            rb[i] = (gk < K) ? *reinterpret_cast<const u32x4_t*>(B + (int64_t)gr * ldb + gk) : zero4;    \
-        }                                                                                              \
-    }
-#define NT_LSTORE(buf)                                                                                 \
-    {                                                                                                  \
-        _Pragma("unroll") for (int i = 0; i < CA; ++i) {                                               \
-            const int idx = tid + i * NTH, row = idx >> 3, ch = idx & 7;                               \
-            *reinterpret_cast<u32x4_t*>(As + ((buf) * BM + row) * NT_LDP + ch * 8) = ra[i];              \
-        }                                                                                              \
-        _Pragma("unroll") for (int i = 0; i < CB; ++i) {                                               \
-            const int idx = tid + i * NTH, row = idx >> 3, ch = idx & 7;                               \
-            *reinterpret_cast<u32x4_t*>(Bs + ((buf) * BN + row) * NT_LDP + ch * 8) = rb[i];              \
-        }                                                                                              \
-    }
-
-    const int nk = (K + NT_BK - 1) / NT_BK;
-    NT_GLOAD(0);
-    NT_LSTORE(0);
-    __syncthreads();
-    const int fr = lane & 31, fk = (lane >> 5) * 8;
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) NT_GLOAD(kt + 1);
-        const uint16_t* Ab = As + (buf * BM + wm * TM * 32 + fr) * NT_LDP + fk;
-        const uint16_t* Bb = Bs + (buf * BN + wn * TN * 32 + fr) * NT_LDP + fk;
-#pragma unroll
-        for (int kk = 0; kk < NT_BK / 16; ++kk) {
-            bf16x8_t a[TM], b[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const bf16x8_t*>(Ab + i * 32 * NT_LDP + kk * 16);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const bf16x8_t*>(Bb + j * 32 * NT_LDP + kk * 16);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        if (kt + 1 < nk) NT_LSTORE(buf ^ 1);
-        __syncthreads();
-    }
-
-    // epilogue straight from the accumulator layout
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int n = n0 + wn * TN * 32 + j * 32 + (lane & 31);
-        if (n >= N) continue;
-        float biasv = 0.f;
-        if (KIND == EPI_BIAS || KIND == EPI_BIAS_GELU || KIND == EPI_RESIDUAL)
-            biasv = __bfloat162float(reinterpret_cast<const bf16*>(epi.bias)[n]);
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int mb = m0 + wm * TM * 32 + i * 32 + 4 * (lane >> 5);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int m = mb + 8 * (v >> 2) + (v & 3);
-                if (m < M) epi_store<KIND>(epi, m, n, acc[i][j][v], biasv);
-            }
-        }
-    }
+// A launch that cannot give every CU a workgroup is bound by the serial chain of one tile (K stages) and by the rate at
+// which one CU takes in operands; so the smallest tile is taken whose workgroups all run at once (32x32: two per CU,
+// the others one), each splitting K among its wavefronts.  Measured at 49 ... 7289 rows, N and K from 384 to 3072: every
+// choice is the best of the seven shapes or within 10 % of it.  From more than 256 tiles of 128x128 on, whole-K tiles fill the chip.
+// These lines depend on M and N only, never on what else runs: the split of K fixes the order of the sums.  Training
+// batches (more than 3072 rows, where splitting would still gain up to 15 % on narrow outputs) always sum K in one
+// order, so that a sample's results do not depend on how many others are in its batch.
+constexpr int SPLIT_MAX_ROWS = 3072;
+static GemmShape split_shape(int M, int N) {
+    if (M > SPLIT_MAX_ROWS) return GS_128x128;
+    if (tiles_of(M, N, 32, 32) <= 512) return GS_32x32;
+    if (tiles_of(M, N, 64, 64) <= 256) return GS_64x64;
+    if (tiles_of(M, N, 64, 128) <= 256) return GS_64x128_K3;
+    if (tiles_of(M, N, 128, 128) <= 256) return GS_128x128_K2;
+    return GS_128x128;
+}
+// 160-row tiles (two wavefronts of 160x64) when they turn a short ragged second round of 128-row tiles into a single
+// round.  Only for launches that have the device to themselves: next to another stream's kernels that round is filled
+// anyway and the larger LDS footprint keeps the neighbour out (measured: sequential schedule faster, parallel schedule
+// 5 % slower).  Each output element sums the same products in the same order under both tiles, so the choice does
+// not change a bit of the result.  Not with fused column sums (their strips are 64 rows) and not with a short last
+// stage (the extra address registers would not fit next to 160 accumulators).
+static GemmShape pick_gemm_shape(int M, int N, int K, const Epi& epi) {
+    const GemmShape sh = split_shape(M, N);
+    if (sh == GS_128x128 && epi.solo && epi.colsum == nullptr && K % 64 == 0 && tall_tiles_pay(M, N)) return GS_160x128;
+    return sh;
 }
 
-template <int BM, int BN, int WM, int WN, int KIND>
-static int launch_nt(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
-                     const Epi& epi) {
-    constexpr size_t shmem = (size_t)2 * (BM + BN) * NT_LDP * sizeof(uint16_t);
-    static LdsLimit lim;
-    auto kern = gemm_nt_kernel<BM, BN, WM, WN, KIND>;
-    if (int rc = lim.ensure(reinterpret_cast<const void*>(kern), (int)shmem)) return rc;
-    const int tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-    hipLaunchKernelGGL(kern, dim3(tiles), dim3(WM * WN * 64), shmem, s, A, lda, B, ldb, M, N, K, epi);
-    REV_HIP(hipGetLastError());
-    return REV_OK;
+int gemm_colsum_strips(int M, int N) {
+    switch (split_shape(M, N)) {
+        case GS_32x32: return (M + 31) / 32;
+        case GS_64x64: return (M + 63) / 64;
+        case GS_64x128_K3: return (M + 63) / 64 * 2;      // 32-row strips
+        case GS_128x128_K2: return (M + 127) / 128 * 4;
+        default: return (M + 127) / 128 * 2;              // 64-row strips
+    }
 }
 
 int gemm_bf16_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
-                  int M, int N, int K, const Epi& epi, bool b_kmajor);
+                  int M, int N, int K, const Epi& epi, bool b_kmajor, GemmShape shape);
+int gemm_bf16_ksplit(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
+                     const Epi& epi, bool b_kmajor, int tile);
 
-bool gemm_bf16_fast_path(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int N, int K, const Epi& epi) {
+static int gemm_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
+                     const Epi& epi, bool b_kmajor) {
     const uintptr_t ptrs = (uintptr_t)A | (uintptr_t)B | (uintptr_t)epi.out | (uintptr_t)epi.out2 | (uintptr_t)epi.outf |
-                           (uintptr_t)epi.bias | (uintptr_t)epi.res | (uintptr_t)epi.aux;
-    return K % 32 == 0 && N % 8 == 0 && (lda & 7) == 0 && (ldb & 7) == 0 && epi.ldo % 4 == 0 && (ptrs & 15) == 0;
+                           (uintptr_t)epi.bias | (uintptr_t)epi.res | (uintptr_t)epi.aux | (uintptr_t)epi.colsum;
+    if (K % 8 || N % 8 || (lda & 7) || (ldb & 7) || epi.ldo % 8 || (ptrs & 15)) {
+        set_error("gemm_bf16: sizes must be multiples of 8 and every buffer 16-byte aligned");
+        return REV_EINVAL;
+    }
+    ProfScope ps(K_GEMM_NT, s, 2.0 * M * N * K);
+    const GemmShape shape = pick_gemm_shape(M, N, K, epi);
+    if (shape == GS_32x32 || shape == GS_64x64)
+        return gemm_bf16_ksplit(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape == GS_32x32 ? 32 : 64);
+    return gemm_bf16_dma(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
 }
 
 // C[M,N] = A[M,K] * B[K,N]   (B row-major [K, ldb]): the input-gradient form, weights as stored
 int gemm_nn_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
                  int M, int N, int K, const Epi& epi) {
-    if (!gemm_bf16_fast_path(A, lda, B, ldb, N, K, epi)) return gemm_nn_bf16_simple(s, A, lda, B, ldb, M, N, K, epi);
-    ProfScope ps(K_GEMM_NT, s, 2.0 * M * N * K);
-    return gemm_bf16_dma(s, A, lda, B, ldb, M, N, K, epi, true);
+    return gemm_bf16(s, A, lda, B, ldb, M, N, K, epi, true);
 }
-
 int gemm_nt_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
                  int M, int N, int K, const Epi& epi) {
-    if ((lda & 7) || (ldb & 7) || (K & 7) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15)) {
-        return gemm_nt_bf16_simple(s, A, lda, B, ldb, M, N, K, epi);
-    }
-    ProfScope ps(K_GEMM_NT, s, 2.0 * M * N * K);
-    if (gemm_bf16_fast_path(A, lda, B, ldb, N, K, epi)) return gemm_bf16_dma(s, A, lda, B, ldb, M, N, K, epi, false);
-    switch (epi.kind) {
-#define CASE(KIND) case KIND: return launch_nt<128, 128, 2, 2, KIND>(s, A, lda, B, ldb, M, N, K, epi);
-        CASE(EPI_BIAS) CASE(EPI_BIAS_GELU) CASE(EPI_RESIDUAL) CASE(EPI_GELU_BWD) CASE(EPI_PLAIN) CASE(EPI_PLAIN_F32)
-#undef CASE
-    }
-    set_error("gemm_nt_bf16: unknown epilogue");
-    return REV_EINVAL;
+    return gemm_bf16(s, A, lda, B, ldb, M, N, K, epi, false);
 }
 
 // ----------------------------------------------------------------------------------------
@@ -229,7 +135,8 @@ int gemm_wgrad_bf16(hipStream_t s, const bf16* G, int64_t ldg, const bf16* A, in
                     int M, int N, int K, float* dW, float* partial, int64_t partial_elems, RedSeg* defer) {
     if (defer) defer->P = 0;            // P == 0: nothing left to reduce
     if ((ldg & 7) || (lda & 7) || (N & 7) || (K & 7) || ((uintptr_t)G & 15) || ((uintptr_t)A & 15)) {
-        return gemm_wgrad_bf16_simple(s, G, ldg, A, lda, M, N, K, dW);
+        set_error("gemm_wgrad_bf16: sizes must be multiples of 8 and every buffer 16-byte aligned");
+        return REV_EINVAL;
     }
     const int S = wgrad_splits(M, N, K);
     if (S > 1 && (partial == nullptr || partial_elems < (int64_t)S * N * K)) {

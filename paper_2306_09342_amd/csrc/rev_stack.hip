@@ -166,7 +166,7 @@ static Layout make_layout(const rev_cfg& c, bool compact) {
         // [0]: fc1 bias gradient (column-sum strips of the GELU' epilogue, or a plain column sum);
         // [1]: QKV bias gradient; also the top block's fc2 bias gradient
         int64_t e0 = colsum_partial_elems((int)M, (int)Dm);
-        int64_t e0b = (int64_t)gemm_colsum_strips_max((int)M) * Dm;
+        int64_t e0b = (int64_t)gemm_colsum_strips((int)M, (int)Dm) * Dm;
         if (e0b > e0) e0 = e0b;
         int64_t e1 = colsum_partial_elems((int)M, (int)(3 * D));
         int64_t e1b = colsum_partial_elems((int)M, (int)D);
@@ -347,12 +347,10 @@ struct Runner {
         // ---- G branch: dh = (dY2 W2) * gelu'(h); the bias gradient of fc1 (column sums of dh) rides
         // in the epilogue of the matrix-core kernel, otherwise it is a separate pass
         Epi e = epi0(); e.kind = EPI_GELU_BWD; e.out = dhb; e.aux = sl.h; e.ldo = Dm;
-        bool fused_db1 = false;
-        if constexpr (kBf16) fused_db1 = gemm_bf16_fast_path(d2b, D, P(blk, T_WFC2), Dm, Dm, D, e);
-        if (fused_db1) e.colsum = pcol0;
+        if (kBf16) e.colsum = pcol0;
         RC(dgrad(s, blk, T_WFC2, d2b, D, Dm, e));
         if (ev) REV_HIP(hipEventRecord(ev[0], s));
-        if (fused_db1) segs[nseg++] = {pcol0, G(blk, T_BFC1), nullptr, (int64_t)Dm, (int64_t)Dm, (int64_t)Dm, gemm_colsum_strips(M)};
+        if (kBf16) segs[nseg++] = {pcol0, G(blk, T_BFC1), nullptr, (int64_t)Dm, (int64_t)Dm, (int64_t)Dm, gemm_colsum_strips(M, Dm)};
         else RC(colsum<T>(s, dhb, Dm, M, Dm, G(blk, T_BFC1), pcol0, &segs[nseg++]));
         Epi p = epi0(); p.kind = EPI_PLAIN; p.out = dn; p.ldo = D;
         RC(dgrad(s, blk, T_WFC1, dhb, Dm, D, p));

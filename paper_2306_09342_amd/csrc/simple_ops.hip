@@ -108,14 +108,6 @@ int gemm_nn_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int6
                 int M, int N, int K, const Epi& epi) {
     return launch_simple<float, false, false>(s, K_GEMM_NT, A, lda, B, ldb, M, N, K, epi);
 }
-int gemm_nt_bf16_simple(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
-                        int M, int N, int K, const Epi& epi) {
-    return launch_simple<bf16, false, true>(s, K_GEMM_NT, A, lda, B, ldb, M, N, K, epi);
-}
-int gemm_nn_bf16_simple(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
-                        int M, int N, int K, const Epi& epi) {
-    return launch_simple<bf16, false, false>(s, K_GEMM_NT, A, lda, B, ldb, M, N, K, epi);
-}
 int gemm_wgrad_f32(hipStream_t s, const float* G, int64_t ldg, const float* A, int64_t lda,
                    int M, int N, int K, float* dW, float*, int64_t, RedSeg* defer) {
     if (defer) defer->P = 0;
@@ -123,12 +115,6 @@ int gemm_wgrad_f32(hipStream_t s, const float* G, int64_t ldg, const float* A, i
     e.kind = EPI_PLAIN_F32; e.outf = dW; e.ldo = K;
     // dW[n,k] = sum_m G[m,n] * A[m,k]
     return launch_simple<float, true, false>(s, K_GEMM_WGRAD, G, ldg, A, lda, N, K, M, e);
-}
-int gemm_wgrad_bf16_simple(hipStream_t s, const bf16* G, int64_t ldg, const bf16* A, int64_t lda,
-                           int M, int N, int K, float* dW) {
-    Epi e = {};
-    e.kind = EPI_PLAIN_F32; e.outf = dW; e.ldo = K;
-    return launch_simple<bf16, true, false>(s, K_GEMM_WGRAD, G, ldg, A, lda, N, K, M, e);
 }
 
 // ---- attention, one wavefront per query (or key) row ------------------------------------------

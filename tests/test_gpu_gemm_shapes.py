@@ -1,0 +1,50 @@
+"""bf16 GEMMs at the edges of every tile and contraction split of the dispatch, through whole blocks against the
+float64 oracle: K shorter than one stage, a short last stage in each kernel, contraction groups with unequal and with no
+stages, ragged rows and columns, the fused column sums of each strip height.  PaReprop must equal Reprop bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import rev_oracle as O
+from paper_2306_09342_amd import binding as B
+
+from parity_util import TOL, compare_backward, gpu_cfg, make_case, oracle_forward, rel_err, to_dev
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    # 32x32 and 64x64 tiles, wavefronts splitting K
+    "one_token_K8": dict(n_blocks=1, d_model=8, n_heads=1, d_mlp=8, seq_len=1, batch=1),
+    "ragged_K40": dict(n_blocks=2, d_model=40, n_heads=1, d_mlp=72, seq_len=33, batch=1),
+    "tiles64_K328": dict(n_blocks=1, d_model=328, n_heads=1 + 40, d_mlp=2248, seq_len=197, batch=1),
+    # 64x128 by three contraction groups: 4 stages (2, 2, 0) and 5 with a short last one (2, 2, 1)
+    "groups3_K256": dict(n_blocks=1, d_model=256, n_heads=4, d_mlp=2048, seq_len=75, batch=8),
+    "groups3_K264": dict(n_blocks=1, d_model=264, n_heads=3, d_mlp=2056, seq_len=75, batch=8),
+    # 128x128 by two groups: 3 stages (2, 1), the last one short
+    "groups2_K144": dict(n_blocks=1, d_model=144, n_heads=2, d_mlp=2056, seq_len=150, batch=10),
+    # whole-K tiles with a short last stage, and the first row count that takes them for narrow outputs
+    "whole_K72": dict(n_blocks=1, d_model=72, n_heads=1, d_mlp=200, seq_len=31, batch=100),
+    "whole_rows3073": dict(n_blocks=1, d_model=64, n_heads=1, d_mlp=136, seq_len=439, batch=7),
+}
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_gemm_shapes_match_the_oracle(name):
+    cfg = dict(SHAPES[name], mode="bf16")
+    print(f"[case] {name} {cfg}", flush=True)
+    flat, blocks, x, dy1, dy2 = make_case(cfg, seed=3)
+    x2 = x[:, ::-1].copy()
+    y1, y2 = oracle_forward(cfg, blocks, x, x2)
+    y1f, y2f = y1.astype(np.float32), y2.astype(np.float32)
+    ref = O.stack_backward_reversible_chunked(y1f, y2f, blocks, cfg["n_heads"], dy1, dy2)
+    c = gpu_cfg(cfg)
+    params = to_dev(flat, B.param_dtype(c))
+    gy1, gy2 = B.rev_stack_forward(c, params, to_dev(x), to_dev(x2))
+    args = [to_dev(a) for a in (y1f, y2f, dy1, dy2)]
+    rep = B.rev_stack_backward_reprop(c, params, *args, want_inputs=True)
+    par = B.rev_stack_backward_pareprop(c, params, *args, torch.cuda.Stream(), want_inputs=True)
+    torch.cuda.synchronize()
+    assert rel_err(gy1.cpu().numpy(), y1) <= TOL["bf16"] and rel_err(gy2.cpu().numpy(), y2) <= TOL["bf16"]
+    compare_backward(cfg, rep, ref, TOL["bf16"], what=name)
+    for k in ("dX1", "dX2", "dparams", "X1", "X2"):
+        assert torch.equal(rep[k], par[k]), f"PaReprop differs from Reprop in {k}"
