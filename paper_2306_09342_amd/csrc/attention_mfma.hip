@@ -962,7 +962,7 @@ static bool mfma_ok(const void* a, const void* b, const void* c, const void* d) 
 template <>
 int attention_forward<bf16>(hipStream_t s, const bf16* qkv, bf16* o, float* lse, int B, int T, int H, int dh, const int* key_len) {
     if ((dh & 7) || dh > 128 || !mfma_ok(qkv, o, nullptr, nullptr))
-        return attention_forward_simple<bf16>(s, qkv, o, lse, B, T, H, dh, key_len);
+        { set_error("attention: head_dim must be a multiple of 8 up to 128 and every buffer 16-byte aligned"); return REV_EINVAL; }
     ProfScope ps(K_ATTN_FWD, s, 4.0 * B * H * (double)T * T * dh);
     if (dh <= 32) return fwd_launch<32>(s, qkv, o, lse, B, T, H, dh, key_len);
     if (dh <= 64) return fwd_launch<64>(s, qkv, o, lse, B, T, H, dh, key_len);
@@ -971,16 +971,19 @@ int attention_forward<bf16>(hipStream_t s, const bf16* qkv, bf16* o, float* lse,
 }
 template <>
 int attention_forward<float>(hipStream_t s, const float* qkv, float* o, float* lse, int B, int T, int H, int dh, const int* key_len) {
-    return attention_forward_simple<float>(s, qkv, o, lse, B, T, H, dh, key_len);
+    return attention_forward_f32(s, qkv, o, lse, B, T, H, dh, key_len);
 }
 
 template <>
 int attention_backward<bf16>(hipStream_t s, const bf16* qkv, const bf16* o, const bf16* dout, const float* lse,
                              bf16* dqkv, float* delta, int B, int T, int H, int dh, const int* key_len, bool solo) {
-    // Heads wider than 96 take the plain-ALU kernels: the matrix-core dK/dV kernel would need more registers
-    // than a wavefront has for a 128-wide head (it spilled), and no workload of the path has such heads.
-    if ((dh & 7) || dh > 96 || !mfma_ok(qkv, o, dout, dqkv))
-        return attention_backward_simple<bf16>(s, qkv, o, dout, lse, dqkv, delta, B, T, H, dh, key_len);
+    if ((dh & 7) || dh > 128 || !mfma_ok(qkv, o, dout, dqkv)) {
+        set_error("attention: head_dim must be a multiple of 8 up to 128 and every buffer 16-byte aligned");
+        return REV_EINVAL;
+    }
+    // Heads wider than 96 take the float32 products: the bf16 dK/dV kernel would need more registers
+    // than a wavefront has for a 128-wide head (it spilled).
+    if (dh > 96) return attention_backward_f32<bf16>(s, qkv, o, dout, lse, dqkv, B, T, H, dh, key_len);
     ProfScope ps(K_ATTN_BWD, s, 8.0 * B * H * (double)T * T * dh);
     if (dh <= 32) return bwd_launch<32>(s, qkv, o, dout, lse, dqkv, delta, B, T, H, dh, key_len, solo);
     if (dh <= 64) return bwd_launch<64>(s, qkv, o, dout, lse, dqkv, delta, B, T, H, dh, key_len, solo);
@@ -988,8 +991,8 @@ int attention_backward<bf16>(hipStream_t s, const bf16* qkv, const bf16* o, cons
 }
 template <>
 int attention_backward<float>(hipStream_t s, const float* qkv, const float* o, const float* dout, const float* lse,
-                              float* dqkv, float* delta, int B, int T, int H, int dh, const int* key_len, bool) {
-    return attention_backward_simple<float>(s, qkv, o, dout, lse, dqkv, delta, B, T, H, dh, key_len);
+                              float* dqkv, float*, int B, int T, int H, int dh, const int* key_len, bool) {
+    return attention_backward_f32<float>(s, qkv, o, dout, lse, dqkv, B, T, H, dh, key_len);
 }
 
 }  // namespace rev

@@ -162,10 +162,10 @@ int gemm_nn_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64
                  int M, int N, int K, const Epi& epi);
 int gemm_nn_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb,
                 int M, int N, int K, const Epi& epi);
+// rows of column-sum partials a float32 GEMM with an [M, N] output writes
+int gemm_f32_colsum_strips(int M, int N);
 // dW[N,K] (float32, ld = K) = G[M,N]^T * A[M,K]  -- reduction over the M tokens.
 // `partial` is scratch for the fixed-order split of the reduction (may be unused).
-int gemm_wgrad_f32(hipStream_t s, const float* G, int64_t ldg, const float* A, int64_t lda,
-                   int M, int N, int K, float* dW, float* partial, int64_t partial_elems, RedSeg* defer = nullptr);
 int gemm_wgrad_bf16(hipStream_t s, const bf16* G, int64_t ldg, const bf16* A, int64_t lda,
                     int M, int N, int K, float* dW, float* partial, int64_t partial_elems, RedSeg* defer = nullptr);
 
@@ -185,17 +185,18 @@ int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int 
 // token ranges the group launch uses for these shapes (1: no pieces, no scratch); item k then needs ranges * N[k] * K[k]
 // floats of scratch
 int wgrad_group_ranges(int M, const int* N, const int* K, int count);
+// The float32 flavour: up to WGRAD_GROUP_MAX weight gradients in one launch, no pieces.
+struct WgradF32Item { const float* G; int64_t ldg; const float* A; int64_t lda; int N, K; float* dW; };
+int gemm_wgrad_f32_group(hipStream_t s, const WgradF32Item* items, int count, int M);
 // device-side description of the launch (gemm_wgrad_dma.hip)
 struct WgradProblem { const bf16* G; const bf16* A; float* out; int64_t ldg, lda, split_stride; int N, K, tile0; };
 struct WgradGroup { WgradProblem p[WGRAD_GROUP_MAX]; int count, tiles_total; };
 
-// plain vector-ALU attention: float32 mode, and the bf16 heads that the matrix-core backward does not take
+// attention with float32 products (attention_f32.hip): float32 mode, and the backward of bf16 heads wider than 96
+int attention_forward_f32(hipStream_t s, const float* qkv, float* o, float* lse, int B, int T, int H, int dh, const int* key_len);
 template <typename T>
-int attention_forward_simple(hipStream_t s, const T* qkv, T* o, float* lse, int B, int T_, int H, int dh,
-                             const int* key_len = nullptr);
-template <typename T>
-int attention_backward_simple(hipStream_t s, const T* qkv, const T* o, const T* dout, const float* lse,
-                              T* dqkv, float* delta, int B, int T_, int H, int dh, const int* key_len = nullptr);
+int attention_backward_f32(hipStream_t s, const T* qkv, const T* o, const T* dout, const float* lse, T* dqkv, int B, int Tn, int H,
+                           int dh, const int* key_len);
 
 // ---- memory-bound kernels ---------------------------------------------------------
 // y = LN(x; g, b), stats[2*row] = mean, stats[2*row+1] = rstd

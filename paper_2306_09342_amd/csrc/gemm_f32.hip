@@ -1,0 +1,304 @@
+// float32 GEMMs on the float32 matrix cores (v_mfma_f32_32x32x2_f32: float32 products and sums), three operand forms:
+//   gemm_nt_f32      C = A[M,K] * B[N,K]^T      (activation x weight)
+//   gemm_nn_f32      C = A[M,K] * B[K,N]        (input gradients, the weight as stored)
+//   gemm_wgrad_f32   dW[N,K] = G[M,N]^T * A[M,K] (weight gradients, several per launch)
+//
+// A workgroup owns one output tile of 32x32 or 64x64; its four wavefronts split the contraction: wavefront w takes the
+// 32-wide chunks w, w + 4, ... for the whole tile, out of a two-stage ring in LDS that only it uses (direct-to-LDS
+// loads, waited for with its own counter), so the main loop has no barrier.  The four partial tiles are added in
+// wavefront order through LDS and leave through the fused epilogue.  A chunk costs 1024 matrix-core cycles per 32x32
+// and 8 KB (32x32) or 16 KB (64x64, a quarter of the bytes per product) of operands.
+//
+// An operand whose rows run along the contraction is read 4 floats per lane (lane group g = lane / 32 of product step
+// s takes k = 8q + 4g + s); one that is stored contraction-major is read a float per lane from two of its rows, with
+// the same assignment of k to steps.
+//
+// 32x32 tiles unless there are 512 of 64x64: below that the chip is not full and the shorter chain wins.  Both sum the
+// same products in the same order.  Against the plain-ALU kernel (64x64, 6 TFLOP/s on these sizes) measured at 591 rows:
+// see the numbers at the launchers.
+#include "gemm_epilogue.h"
+
+namespace rev {
+
+__device__ __forceinline__ f32x16_t mfma_f32(float a, float b, f32x16_t c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+template <int KIND>
+__device__ __forceinline__ f32x4_t epi_store4_f32(const Epi& e, int m, int n, f32x4_t acc, f32x4_t bv) {
+    const int64_t idx = (int64_t)m * e.ldo + n;
+    if (KIND == EPI_BIAS || KIND == EPI_BIAS_GELU || KIND == EPI_RESIDUAL) acc += bv;
+    if (KIND == EPI_BIAS_GELU) {
+        if (e.out != nullptr) *reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(e.out) + idx) = acc;
+        f32x4_t a;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a[k] = gelu_f(acc[k]);
+        *reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(e.out2) + idx) = a;
+    } else if (KIND == EPI_RESIDUAL) {
+        *reinterpret_cast<f32x4_t*>(e.outf + idx) = *reinterpret_cast<const f32x4_t*>(e.res + idx) + e.sign * acc;
+    } else if (KIND == EPI_GELU_BWD) {
+        const f32x4_t h = *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(e.aux) + idx);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] = acc[k] * gelu_grad_f(h[k]);
+        *reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(e.out) + idx) = acc;
+    } else if (KIND == EPI_PLAIN_F32) {
+        *reinterpret_cast<f32x4_t*>(e.outf + idx) = acc;
+    } else {
+        *reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(e.out) + idx) = acc;
+    }
+    return acc;
+}
+
+constexpr int F_NW = 4, F_NS = 2, F_KC = 32;           // wavefronts, stages per wavefront, chunk depth
+template <int TM, int TN> struct FCfg {
+    static constexpr int BM = 32 * TM, BN = 32 * TN;
+    static constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
+    static constexpr int PITCH = BN + 4;
+    static constexpr int RED_BYTES = F_NW * BM * PITCH * 4;
+    static constexpr int RING_BYTES = F_NW * F_NS * STAGE;
+    static constexpr int SHMEM = RING_BYTES > RED_BYTES ? RING_BYTES : RED_BYTES;
+};
+
+// One output tile (m0, n0).  AKM / BKM: the operand is stored contraction-major ([K, ld]).
+template <int TM, int TN, int KIND, bool AKM, bool BKM>
+__device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
+                                              int M, int N, int K, const Epi& epi, int m0, int n0) {
+    using C = FCfg<TM, TN>;
+    constexpr int BM = C::BM, BN = C::BN, LA = BM / 8, LB = BN / 8, LPS = LA + LB;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 5, fr = lane & 31;
+    unsigned char* ring = smem + wave * (F_NS * C::STAGE);
+    const unsigned lds0 = (unsigned)(uintptr_t)LDS_PTR(unsigned char, ring);
+    const char* zero = reinterpret_cast<const char*>(g_zero_chunk);
+
+    // per-lane source and contraction index (within a chunk) of each wavefront-wide load of 1 KB.  Row-wise operands:
+    // 8 rows of 8 chunks, chunk c of row r at position c ^ ((r >> 1) & 7); contraction-major ones: 8 or 4 rows of 32 or 64
+    // columns as they lie.  Rows / columns beyond the matrix re-read valid ones (never stored).
+    const char* src[LPS];
+    int ks[LPS];
+    auto setup = [&](int t, const float* X, int64_t ld, int r0, int rows, bool km, int cols_tile, int idx) {
+        if (!km) {
+            const int row = t * 8 + (lane >> 3), ch = (lane & 7) ^ ((row >> 1) & 7);
+            ks[idx] = ch * 4;
+            src[idx] = reinterpret_cast<const char*>(X + (int64_t)min(r0 + row, rows - 1) * ld + ch * 4);
+        } else {
+            const int cpr = cols_tile / 4, row = t * (64 / cpr) + lane / cpr;
+            ks[idx] = row;
+            src[idx] = reinterpret_cast<const char*>(X + min(r0 + (lane % cpr) * 4, rows - 4));
+        }
+    };
+#pragma unroll
+    for (int t = 0; t < LA; ++t) setup(t, A, lda, m0, M, AKM, BM, t);
+#pragma unroll
+    for (int t = 0; t < LB; ++t) setup(t, B, ldb, n0, N, BKM, BN, LA + t);
+    auto issue = [&](int c, int stage) {
+        const int k0 = c * F_KC;
+        const unsigned sb = lds0 + stage * C::STAGE;
+#pragma unroll
+        for (int t = 0; t < LPS; ++t) {
+            const bool isA = t < LA, km = isA ? AKM : BKM;
+            const int k = k0 + ks[t];
+            const char* p = km ? src[t] + (int64_t)k * (isA ? lda : ldb) * 4 : src[t] + (int64_t)k0 * 4;
+            dma16_ptr(k < K ? p : zero, sb + t * 1024);
+        }
+    };
+
+    f32x16_t acc[TN][TM];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[j][i][v] = 0.f;
+
+    const int nch = (K + F_KC - 1) / F_KC;
+    const int mine = wave < nch ? (nch - wave + F_NW - 1) / F_NW : 0;
+#pragma unroll
+    for (int s = 0; s < F_NS; ++s)
+        if (s < mine) issue(wave + s * F_NW, s);
+    // fragment of product group q (8 contraction indices, 4 product steps)
+    auto frag = [&](const unsigned char* tile, bool km, int cols, int t, int q, float (&f)[4]) {
+        if (!km) {
+            const f32x4_t v = *reinterpret_cast<const f32x4_t*>(tile + (t * 32 + fr) * 128 + (((2 * q + g) ^ ((fr >> 1) & 7)) << 4));
+#pragma unroll
+            for (int s = 0; s < 4; ++s) f[s] = v[s];
+        } else {
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                f[s] = *reinterpret_cast<const float*>(tile + ((8 * q + 4 * g + s) * cols + t * 32 + fr) * 4);
+        }
+    };
+    for (int i = 0; i < mine; ++i) {
+        // the stage's loads are older than those of the stage requested after it
+        if (i + F_NS <= mine) wait_vm<(F_NS - 1) * LPS>();
+        else wait_vm<0>();
+        const unsigned char* st = ring + (i % F_NS) * C::STAGE;
+#pragma unroll
+        for (int q = 0; q < F_KC / 8; ++q) {
+            float a[TM][4], b[TN][4];
+#pragma unroll
+            for (int t = 0; t < TM; ++t) frag(st, AKM, BM, t, q, a[t]);
+#pragma unroll
+            for (int t = 0; t < TN; ++t) frag(st + C::A_BYTES, BKM, BN, t, q, b[t]);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int t = 0; t < TM; ++t) acc[j][t] = mfma_f32(b[j][s], a[t][s], acc[j][t]);
+        }
+        wait_lds();                                             // the stage has been read: it may be refilled
+        if (i + F_NS < mine) issue(wave + (i + F_NS) * F_NW, i % F_NS);
+    }
+
+    // ---- partial tiles to LDS, summed in wavefront order, epilogue ----
+    __syncthreads();
+    float* red = reinterpret_cast<float*>(smem);
+    {
+        float* part = red + wave * (BM * C::PITCH);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int vq = 0; vq < 4; ++vq) {
+                    const f32x4_t v = {acc[j][i][4 * vq], acc[j][i][4 * vq + 1], acc[j][i][4 * vq + 2], acc[j][i][4 * vq + 3]};
+                    *reinterpret_cast<f32x4_t*>(part + (i * 32 + fr) * C::PITCH + j * 32 + 8 * vq + 4 * g) = v;
+                }
+    }
+    __syncthreads();
+    constexpr int QPR = BN / 4, ROWS = F_NW * 64 / QPR, PASS = BM / ROWS;
+    const int c4 = tid % QPR, rr = tid / QPR;
+    const int n = n0 + 4 * c4;
+    f32x4_t csum = {0.f, 0.f, 0.f, 0.f};
+    if (n < N) {
+        f32x4_t bv = {0.f, 0.f, 0.f, 0.f};
+        if (KIND == EPI_BIAS || KIND == EPI_BIAS_GELU || KIND == EPI_RESIDUAL)
+            bv = *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(epi.bias) + n);
+#pragma unroll
+        for (int p = 0; p < PASS; ++p) {
+            const int r = rr + p * ROWS, m = m0 + r;
+            if (m < M) {
+                f32x4_t v = *reinterpret_cast<const f32x4_t*>(red + r * C::PITCH + 4 * c4);
+#pragma unroll
+                for (int w = 1; w < F_NW; ++w) v += *reinterpret_cast<const f32x4_t*>(red + (w * BM + r) * C::PITCH + 4 * c4);
+                const f32x4_t o = epi_store4_f32<KIND>(epi, m, n, v, bv);
+                if (KIND == EPI_GELU_BWD) csum += o;
+            }
+        }
+    }
+    if (KIND == EPI_GELU_BWD && epi.colsum != nullptr) {       // one partial row of column sums per m-tile
+        __syncthreads();
+        *reinterpret_cast<f32x4_t*>(red + (rr * QPR + c4) * 4) = csum;
+        __syncthreads();
+        if (rr == 0 && n < N) {
+            f32x4_t s = csum;
+            for (int q = 1; q < ROWS; ++q) s += *reinterpret_cast<const f32x4_t*>(red + (q * QPR + c4) * 4);
+            *reinterpret_cast<f32x4_t*>(epi.colsum + (int64_t)(m0 / BM) * N + n) = s;
+        }
+    }
+}
+
+template <int TM, int TN, int KIND, bool BKM>
+__global__ __launch_bounds__(F_NW * 64) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ B,
+                                                             int64_t ldb, int M, int N, int K, Epi epi) {
+    const int tiles_m = (M + 32 * TM - 1) / (32 * TM);
+    const int tile = xcd_remap(blockIdx.x, gridDim.x);         // m fastest: a run of tiles shares a slice of B
+    gemm_f32_tile<TM, TN, KIND, false, BKM>(A, lda, B, ldb, M, N, K, epi, (tile % tiles_m) * 32 * TM, (tile / tiles_m) * 32 * TN);
+}
+
+struct WgradF32Problem { const float* G; const float* A; float* out; int64_t ldg, lda; int N, K, tile0; };
+struct WgradF32Group { WgradF32Problem p[WGRAD_GROUP_MAX]; int count; };
+
+template <int TM, int TN>
+__global__ __launch_bounds__(F_NW * 64) void wgrad_f32_kernel(WgradF32Group grp, int M) {
+    const int lin = xcd_remap(blockIdx.x, gridDim.x);
+    int pi = 0;
+#pragma unroll
+    for (int k = 1; k < WGRAD_GROUP_MAX; ++k)
+        if (k < grp.count && lin >= grp.p[k].tile0) pi = k;
+    const WgradF32Problem& q = grp.p[pi];
+    const int t = lin - q.tile0, tiles_n = (q.N + 32 * TM - 1) / (32 * TM);
+    Epi e = {};
+    e.outf = q.out; e.ldo = q.K;
+    gemm_f32_tile<TM, TN, EPI_PLAIN_F32, true, true>(q.G, q.ldg, q.A, q.lda, q.N, q.K, M, e, (t % tiles_n) * 32 * TM, (t / tiles_n) * 32 * TN);
+}
+
+static inline int64_t f32_tiles(int M, int N, int b) { return (int64_t)((M + b - 1) / b) * ((N + b - 1) / b); }
+static bool f32_wide(int M, int N) { return f32_tiles(M, N, 64) >= 512; }
+
+int gemm_f32_colsum_strips(int M, int N) { return f32_wide(M, N) ? (M + 63) / 64 : (M + 31) / 32; }
+
+template <int TM, int KIND, bool BKM>
+static int launch_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, const Epi& epi) {
+    using C = FCfg<TM, TM>;
+    static LdsLimit lim;
+    auto kern = gemm_f32_kernel<TM, TM, KIND, BKM>;
+    if (int rc = lim.ensure(reinterpret_cast<const void*>(kern), C::SHMEM)) return rc;
+    hipLaunchKernelGGL(kern, dim3((unsigned)f32_tiles(M, N, C::BM)), dim3(F_NW * 64), C::SHMEM, s, A, lda, B, ldb, M, N, K, epi);
+    REV_HIP(hipGetLastError());
+    return REV_OK;
+}
+
+template <bool BKM>
+static int gemm_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, const Epi& epi) {
+    const uintptr_t ptrs = (uintptr_t)A | (uintptr_t)B | (uintptr_t)epi.out | (uintptr_t)epi.out2 | (uintptr_t)epi.outf |
+                           (uintptr_t)epi.bias | (uintptr_t)epi.res | (uintptr_t)epi.aux | (uintptr_t)epi.colsum;
+    if (K % 4 || N % 4 || (lda & 3) || (ldb & 3) || epi.ldo % 4 || (ptrs & 15)) {
+        set_error("gemm_f32: sizes must be multiples of 4 and every buffer 16-byte aligned");
+        return REV_EINVAL;
+    }
+    ProfScope ps(K_GEMM_NT, s, 2.0 * M * N * K);
+    const bool wide = f32_wide(M, N);
+    switch (epi.kind) {
+#define CASE(KIND) case KIND: return wide ? launch_f32<2, KIND, BKM>(s, A, lda, B, ldb, M, N, K, epi) \
+                                          : launch_f32<1, KIND, BKM>(s, A, lda, B, ldb, M, N, K, epi);
+        CASE(EPI_BIAS) CASE(EPI_BIAS_GELU) CASE(EPI_RESIDUAL) CASE(EPI_GELU_BWD) CASE(EPI_PLAIN) CASE(EPI_PLAIN_F32)
+#undef CASE
+    }
+    set_error("gemm_f32: unknown epilogue");
+    return REV_EINVAL;
+}
+int gemm_nt_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, const Epi& epi) {
+    return gemm_f32<false>(s, A, lda, B, ldb, M, N, K, epi);
+}
+int gemm_nn_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, const Epi& epi) {
+    return gemm_f32<true>(s, A, lda, B, ldb, M, N, K, epi);
+}
+
+int gemm_wgrad_f32_group(hipStream_t s, const WgradF32Item* items, int count, int M) {
+    WgradF32Group grp = {};
+    grp.count = count;
+    int64_t t64 = 0, t32 = 0;
+    double flops = 0;
+    for (int k = 0; k < count; ++k) {
+        const WgradF32Item& it = items[k];
+        if (it.N % 4 || it.K % 4 || (it.ldg & 3) || (it.lda & 3) || (((uintptr_t)it.G | (uintptr_t)it.A | (uintptr_t)it.dW) & 15)) {
+            set_error("gemm_wgrad_f32: sizes must be multiples of 4 and every buffer 16-byte aligned");
+            return REV_EINVAL;
+        }
+        t64 += f32_tiles(it.N, it.K, 64);
+        flops += 2.0 * M * it.N * it.K;
+    }
+    const bool wide = t64 >= 512;
+    for (int k = 0; k < count; ++k) {
+        const WgradF32Item& it = items[k];
+        grp.p[k] = {it.G, it.A, it.dW, it.ldg, it.lda, it.N, it.K, (int)t32};
+        t32 += f32_tiles(it.N, it.K, wide ? 64 : 32);
+    }
+    ProfScope ps(K_GEMM_WGRAD, s, flops);
+    static LdsLimit lim1, lim2;
+    if (wide) {
+        if (int rc = lim2.ensure(reinterpret_cast<const void*>(wgrad_f32_kernel<2, 2>), FCfg<2, 2>::SHMEM)) return rc;
+        hipLaunchKernelGGL((wgrad_f32_kernel<2, 2>), dim3((unsigned)t32), dim3(F_NW * 64), (FCfg<2, 2>::SHMEM), s, grp, M);
+    } else {
+        if (int rc = lim1.ensure(reinterpret_cast<const void*>(wgrad_f32_kernel<1, 1>), FCfg<1, 1>::SHMEM)) return rc;
+        hipLaunchKernelGGL((wgrad_f32_kernel<1, 1>), dim3((unsigned)t32), dim3(F_NW * 64), (FCfg<1, 1>::SHMEM), s, grp, M);
+    }
+    REV_HIP(hipGetLastError());
+    return REV_OK;
+}
+
+}  // namespace rev

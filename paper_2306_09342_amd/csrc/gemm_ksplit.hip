@@ -15,12 +15,6 @@
 
 namespace rev {
 
-__device__ __forceinline__ void dma16_ptr(const void* p, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(p), "s"(lds_addr) : "memory", "m0");
-}
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
-__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
 template <int TM, int TN, int NW, int NS> struct KsCfg {
     static constexpr int BM = 32 * TM, BN = 32 * TN;
     static constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;

@@ -99,6 +99,13 @@ __device__ __forceinline__ void dma16_sbase(const void* sbase, unsigned voff, un
                  :: "v"(voff), "s"(sbase), "s"(lds_addr) : "memory", "m0");
 }
 
+// The same with a 64-bit address per lane, for loads that are redirected lane by lane (zeros beyond the contraction).
+__device__ __forceinline__ void dma16_ptr(const void* p, unsigned lds_addr) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(p), "s"(lds_addr) : "memory", "m0");
+}
+template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
 // 64 bytes of zeros (never written): the source of direct-to-LDS loads that fall outside a matrix
 static __device__ u32x4_t g_zero_chunk[4];
 

@@ -163,11 +163,9 @@ static Layout make_layout(const rev_cfg& c, bool compact) {
     L.part_ln[0] = take(ln_bwd_partial_elems((int)M, (int)D) * 4);
     L.part_ln[1] = take(ln_bwd_partial_elems((int)M, (int)D) * 4);
     {
-        // [0]: fc1 bias gradient (column-sum strips of the GELU' epilogue, or a plain column sum);
+        // [0]: fc1 bias gradient (column-sum strips of the GELU' epilogue);
         // [1]: QKV bias gradient; also the top block's fc2 bias gradient
-        int64_t e0 = colsum_partial_elems((int)M, (int)Dm);
-        int64_t e0b = (int64_t)gemm_colsum_strips((int)M, (int)Dm) * Dm;
-        if (e0b > e0) e0 = e0b;
+        const int64_t e0 = (int64_t)(c.mode == REV_MODE_BF16 ? gemm_colsum_strips((int)M, (int)Dm) : gemm_f32_colsum_strips((int)M, (int)Dm)) * Dm;
         int64_t e1 = colsum_partial_elems((int)M, (int)(3 * D));
         int64_t e1b = colsum_partial_elems((int)M, (int)D);
         if (e1b > e1) e1 = e1b;
@@ -224,25 +222,12 @@ struct EventLease {
 // ---------------------------------------------------------------------------------
 #define RC(expr) do { int _rc = (expr); if (_rc != REV_OK) return _rc; } while (0)
 
-template <typename T> struct Ops;
-template <> struct Ops<float> {
-    static int nt(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, const Epi& e) {
-        return gemm_nt_f32(s, A, lda, B, ldb, M, N, K, e);
-    }
-    static int wgrad(hipStream_t s, const float* G, int64_t ldg, const float* A, int64_t lda, int M, int N, int K,
-                     float* dW, float* part, int64_t pe, RedSeg* defer) {
-        return gemm_wgrad_f32(s, G, ldg, A, lda, M, N, K, dW, part, pe, defer);
-    }
-};
-template <> struct Ops<bf16> {
-    static int nt(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& e) {
-        return gemm_nt_bf16(s, A, lda, B, ldb, M, N, K, e);
-    }
-    static int wgrad(hipStream_t s, const bf16* G, int64_t ldg, const bf16* A, int64_t lda, int M, int N, int K,
-                     float* dW, float* part, int64_t pe, RedSeg* defer) {
-        return gemm_wgrad_bf16(s, G, ldg, A, lda, M, N, K, dW, part, pe, defer);
-    }
-};
+static int gemm_nt(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, const Epi& e) {
+    return gemm_nt_f32(s, A, lda, B, ldb, M, N, K, e);
+}
+static int gemm_nt(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& e) {
+    return gemm_nt_bf16(s, A, lda, B, ldb, M, N, K, e);
+}
 
 template <typename T>
 struct Runner {
@@ -275,23 +260,23 @@ struct Runner {
     int f_pre(hipStream_t s, int blk, const float* x2, const Slot& sl) {
         RC((ln_forward<T, T>(s, x2, P(blk, T_LN1G), P(blk, T_LN1B), c.ln_eps, sl.n1, sl.st1, M, D)));
         Epi e = epi0(); e.kind = EPI_BIAS; e.out = sl.qkv; e.bias = P(blk, T_BQKV); e.ldo = 3 * D;
-        RC(Ops<T>::nt(s, sl.n1, D, P(blk, T_WQKV), D, M, 3 * D, D, e));
+        RC(gemm_nt(s, sl.n1, D, P(blk, T_WQKV), D, M, 3 * D, D, e));
         RC((attention_forward<T>(s, sl.qkv, sl.o, sl.lse, B, Tn, H, dh, key_len)));
         return REV_OK;
     }
     // out1 = in1 + sign * (o Wp^T + bp)
     int f_post(hipStream_t s, int blk, const Slot& sl, const float* in1, float* out1, float sign) {
         Epi e = epi0(); e.kind = EPI_RESIDUAL; e.outf = out1; e.res = in1; e.bias = P(blk, T_BPROJ); e.sign = sign; e.ldo = D;
-        return Ops<T>::nt(s, sl.o, D, P(blk, T_WPROJ), D, M, D, D, e);
+        return gemm_nt(s, sl.o, D, P(blk, T_WPROJ), D, M, D, D, e);
     }
     // out2 = in2 + sign * G(y1); the pre-activation of the MLP is kept only where a backward step will read it
     int g_branch(hipStream_t s, int blk, const float* y1, const Slot& sl, const float* in2, float* out2, float sign,
                  bool keep_h = true) {
         RC((ln_forward<T, T>(s, y1, P(blk, T_LN2G), P(blk, T_LN2B), c.ln_eps, sl.n2, sl.st2, M, D)));
         Epi e = epi0(); e.kind = EPI_BIAS_GELU; e.out = keep_h ? sl.h : nullptr; e.out2 = sl.a; e.bias = P(blk, T_BFC1); e.ldo = Dm;
-        RC(Ops<T>::nt(s, sl.n2, D, P(blk, T_WFC1), D, M, Dm, D, e));
+        RC(gemm_nt(s, sl.n2, D, P(blk, T_WFC1), D, M, Dm, D, e));
         Epi r = epi0(); r.kind = EPI_RESIDUAL; r.outf = out2; r.res = in2; r.bias = P(blk, T_BFC2); r.sign = sign; r.ldo = D;
-        return Ops<T>::nt(s, sl.a, Dm, P(blk, T_WFC2), Dm, M, D, Dm, r);
+        return gemm_nt(s, sl.a, Dm, P(blk, T_WFC2), Dm, M, D, Dm, r);
     }
 
     // forward of block blk (0-based): (x1,x2) -> (y1,y2)
@@ -345,13 +330,13 @@ struct Runner {
         int nseg = 0;
 
         // ---- G branch: dh = (dY2 W2) * gelu'(h); the bias gradient of fc1 (column sums of dh) rides
-        // in the epilogue of the matrix-core kernel, otherwise it is a separate pass
+        // in the epilogue
         Epi e = epi0(); e.kind = EPI_GELU_BWD; e.out = dhb; e.aux = sl.h; e.ldo = Dm;
-        if (kBf16) e.colsum = pcol0;
+        e.colsum = pcol0;
         RC(dgrad(s, blk, T_WFC2, d2b, D, Dm, e));
         if (ev) REV_HIP(hipEventRecord(ev[0], s));
-        if (kBf16) segs[nseg++] = {pcol0, G(blk, T_BFC1), nullptr, (int64_t)Dm, (int64_t)Dm, (int64_t)Dm, gemm_colsum_strips(M, Dm)};
-        else RC(colsum<T>(s, dhb, Dm, M, Dm, G(blk, T_BFC1), pcol0, &segs[nseg++]));
+        segs[nseg++] = {pcol0, G(blk, T_BFC1), nullptr, (int64_t)Dm, (int64_t)Dm, (int64_t)Dm,
+                        kBf16 ? gemm_colsum_strips(M, Dm) : gemm_f32_colsum_strips(M, Dm)};
         Epi p = epi0(); p.kind = EPI_PLAIN; p.out = dn; p.ldo = D;
         RC(dgrad(s, blk, T_WFC1, dhb, Dm, D, p));
         // gY1 = dY1 + LN2bwd(dn); its column sums are the bias gradient of the projection
@@ -384,6 +369,7 @@ struct Runner {
         if constexpr (kBf16) for (int w = 0; w < 4; ++w) pwg[w] = at<float>(L.part_wg[w]);
         T* gy1b = gy1_act(blk, o1);
         RedSeg segs[4];
+        if (ev) for (int k = 0; k < 4; ++k) REV_HIP(hipStreamWaitEvent(s, ev[k], 0));
         if constexpr (kBf16) {
             // all four in one launch: together their tiles fill the device without cutting the token range (or with
             // fewer cuts), which saves the float32 pieces and most of their reduction
@@ -392,7 +378,6 @@ struct Runner {
                 {dhb, Dm, sl.n2, D, Dm, D, G(blk, T_WFC1), pwg[1], L.part_wg_elems[1]},
                 {gy1b, D, sl.o, D, D, D, G(blk, T_WPROJ), pwg[2], L.part_wg_elems[2]},
                 {dqkv, 3 * D, sl.n1, D, 3 * D, D, G(blk, T_WQKV), pwg[3], L.part_wg_elems[3]}};
-            if (ev) for (int k = 0; k < 4; ++k) REV_HIP(hipStreamWaitEvent(s, ev[k], 0));
             RC(gemm_wgrad_bf16_group(s, items, 4, M, segs));
             if (done_w2) REV_HIP(hipEventRecord(done_w2, s));
             RedSeg live4[4];
@@ -401,21 +386,14 @@ struct Runner {
                 if (segs[w].P > 0) live4[n4++] = segs[w];
             return reduce_multi(s, live4, n4);
         }
-        if (ev) REV_HIP(hipStreamWaitEvent(s, ev[0], 0));
-        RC(Ops<T>::wgrad(s, d2b, D, sl.a, Dm, M, D, Dm, G(blk, T_WFC2), pwg[0], L.part_wg_elems[0], &segs[0]));
-        if (done_w2) REV_HIP(hipEventRecord(done_w2, s));
-        if (ev) REV_HIP(hipStreamWaitEvent(s, ev[1], 0));
-        RC(Ops<T>::wgrad(s, dhb, Dm, sl.n2, D, M, Dm, D, G(blk, T_WFC1), pwg[1], L.part_wg_elems[1], &segs[1]));
-        if (ev) REV_HIP(hipStreamWaitEvent(s, ev[2], 0));
-        RC(Ops<T>::wgrad(s, gy1b, D, sl.o, D, M, D, D, G(blk, T_WPROJ), pwg[2], L.part_wg_elems[2], &segs[2]));
-        if (ev) REV_HIP(hipStreamWaitEvent(s, ev[3], 0));
-        RC(Ops<T>::wgrad(s, dqkv, 3 * D, sl.n1, D, M, 3 * D, D, G(blk, T_WQKV), pwg[3], L.part_wg_elems[3], &segs[3]));
-        // one launch for the split reductions of all four
-        RedSeg live[4];
-        int nseg = 0;
-        for (int w = 0; w < 4; ++w)
-            if (segs[w].P > 0) live[nseg++] = segs[w];
-        return reduce_multi(s, live, nseg);
+        if constexpr (!kBf16) {
+            const WgradF32Item items[4] = {{d2b, D, sl.a, Dm, D, Dm, G(blk, T_WFC2)}, {dhb, Dm, sl.n2, D, Dm, D, G(blk, T_WFC1)},
+                                           {gy1b, D, sl.o, D, D, D, G(blk, T_WPROJ)},
+                                           {dqkv, 3 * D, sl.n1, D, 3 * D, D, G(blk, T_WQKV)}};
+            RC(gemm_wgrad_f32_group(s, items, 4, M));
+            if (done_w2) REV_HIP(hipEventRecord(done_w2, s));
+            return REV_OK;
+        }
     }
 
     // residual level `lvl` (0..N): stream s1/s2 pointers
@@ -436,8 +414,7 @@ struct Runner {
     //   D_i  after W_{i+2}                  (dh/dqkv/gY1 buffers of the same parity are free again)
     //   D_i  after the fc2 weight gradient of W_{i+1}   (it reads the dY2 copy that D_i's last kernel rewrites)
     //   R_i  after D_{i+2}                  (slot i mod 2 and ring level i+2 are free; W_{i+2} precedes R_i on sr)
-    //   W_i after the kernels of D_i that produce its cotangent operands (bf16 mode: one launch for the four GEMMs,
-    //   so after all of them; float32 mode: each GEMM after its own)
+    //   W_i after the kernels of D_i that produce its cotangent operands (one launch for the four GEMMs)
     // and sv finally waits for W_1, so everything is ordered before later work on sv.
     int backward(int schedule, const float* Y1, const float* Y2, const float* dY1, const float* dY2,
                  float* dX1, float* dX2, float* X1o, float* X2o, hipStream_t sv, hipStream_t sr) {

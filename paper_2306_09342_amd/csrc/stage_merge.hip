@@ -398,7 +398,9 @@ struct MergeRunner {
             RC(gemm_wgrad_bf16(s, at<T>(L.dob), 2 * C, at<T>(L.n), 4 * C, Mo, 2 * C, 4 * C, dW, at<float>(L.part_wg), L.part_wg_elems, &segs[0]));
             RC(gemm_nn_bf16(s, at<T>(L.dob), 2 * C, W(), 4 * C, Mo, 4 * C, 2 * C, e));
         } else {
-            RC(gemm_wgrad_f32(s, at<T>(L.dob), 2 * C, at<T>(L.n), 4 * C, Mo, 2 * C, 4 * C, dW, nullptr, 0, &segs[0]));
+            const WgradF32Item it = {at<T>(L.dob), 2 * C, at<T>(L.n), 4 * C, 2 * C, 4 * C, dW};
+            RC(gemm_wgrad_f32_group(s, &it, 1, Mo));
+            segs[0].P = 0;
             RC(gemm_nn_f32(s, at<T>(L.dob), 2 * C, W(), 4 * C, Mo, 4 * C, 2 * C, e));
         }
         const int rpb = merge_rows_per_block(Mo);
@@ -447,7 +449,9 @@ struct MergeRunner {
             RC(gemm_wgrad_bf16(s, dz0, C, at<T>(L.a), C, M, C, C, dparams + off_wb(), at<float>(L.part_fw[1]), L.part_fw_elems[1], &wseg[1]));
             RC(gemm_nn_bf16(s, dz0, C, params + off_wb(), C, M, C, C, e));
         } else {
-            RC(gemm_wgrad_f32(s, dz0, C, at<T>(L.a), C, M, C, C, dparams + off_wb(), nullptr, 0, &wseg[1]));
+            const WgradF32Item it = {dz0, C, at<T>(L.a), C, C, C, dparams + off_wb()};
+            RC(gemm_wgrad_f32_group(s, &it, 1, M));
+            wseg[1].P = 0;
             RC(gemm_nn_f32(s, dz0, C, params + off_wb(), C, M, C, C, e));
         }
         // hidden layer: db = column sums of dh, dWa = dh^T * [X1 | X2], [dX1 | dX2] = dh * Wa (one GEMM per half:
@@ -458,7 +462,9 @@ struct MergeRunner {
             RC(gemm_nn_bf16(s, dh, C, params + off_wa(), 2 * C, M, C, C, x1));
             RC(gemm_nn_bf16(s, dh, C, params + off_wa() + C, 2 * C, M, C, C, x2));
         } else {
-            RC(gemm_wgrad_f32(s, dh, C, at<T>(L.cat), 2 * C, M, C, 2 * C, dparams + off_wa(), nullptr, 0, &wseg[0]));
+            const WgradF32Item it = {dh, C, at<T>(L.cat), 2 * C, C, 2 * C, dparams + off_wa()};
+            RC(gemm_wgrad_f32_group(s, &it, 1, M));
+            wseg[0].P = 0;
             RC(gemm_nn_f32(s, dh, C, params + off_wa(), 2 * C, M, C, C, x1));
             RC(gemm_nn_f32(s, dh, C, params + off_wa() + C, 2 * C, M, C, C, x2));
         }

@@ -1,6 +1,7 @@
-"""bf16 GEMMs at the edges of every tile and contraction split of the dispatch, through whole blocks against the
-float64 oracle: K shorter than one stage, a short last stage in each kernel, contraction groups with unequal and with no
-stages, ragged rows and columns, the fused column sums of each strip height.  PaReprop must equal Reprop bit for bit."""
+"""GEMMs at the edges of every tile and contraction split of the dispatch, through whole blocks against the
+float64 oracle (bf16): K shorter than one stage, a short last stage in each kernel, contraction groups with unequal and with no
+stages, ragged rows and columns, the fused column sums of each strip height; the float32 products: both tile sizes,
+a token count that is no multiple of anything, heads of every width class with masks.  PaReprop must equal Reprop bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -28,9 +29,18 @@ SHAPES = {
 }
 
 
-@pytest.mark.parametrize("name", list(SHAPES))
-def test_gemm_shapes_match_the_oracle(name):
-    cfg = dict(SHAPES[name], mode="bf16")
+F32_SHAPES = {
+    "f32_wide_output": dict(n_blocks=1, d_model=72, n_heads=3, d_mlp=1544, seq_len=67, batch=21),
+    "f32_wide_wgrad": dict(n_blocks=1, d_model=512, n_heads=16, d_mlp=2048, seq_len=37, batch=1),
+    "f32_heads104": dict(n_blocks=1, d_model=208, n_heads=2, d_mlp=16, seq_len=161, batch=2),
+    "f32_heads72": dict(n_blocks=2, d_model=72, n_heads=1, d_mlp=40, seq_len=129, batch=2),
+}
+
+
+@pytest.mark.parametrize("name,mode", [(n, "bf16") for n in SHAPES] + [(n, "fp32") for n in F32_SHAPES] + [("f32_heads104", "bf16")])
+def test_gemm_shapes_match_the_oracle(name, mode):
+    cfg = dict(SHAPES.get(name) or F32_SHAPES[name], mode=mode)
+    tol = TOL[mode]
     print(f"[case] {name} {cfg}", flush=True)
     flat, blocks, x, dy1, dy2 = make_case(cfg, seed=3)
     x2 = x[:, ::-1].copy()
@@ -44,7 +54,24 @@ def test_gemm_shapes_match_the_oracle(name):
     rep = B.rev_stack_backward_reprop(c, params, *args, want_inputs=True)
     par = B.rev_stack_backward_pareprop(c, params, *args, torch.cuda.Stream(), want_inputs=True)
     torch.cuda.synchronize()
-    assert rel_err(gy1.cpu().numpy(), y1) <= TOL["bf16"] and rel_err(gy2.cpu().numpy(), y2) <= TOL["bf16"]
-    compare_backward(cfg, rep, ref, TOL["bf16"], what=name)
+    assert rel_err(gy1.cpu().numpy(), y1) <= tol and rel_err(gy2.cpu().numpy(), y2) <= tol
+    compare_backward(cfg, rep, ref, tol, what=name)
     for k in ("dX1", "dX2", "dparams", "X1", "X2"):
         assert torch.equal(rep[k], par[k]), f"PaReprop differs from Reprop in {k}"
+
+
+@pytest.mark.parametrize("mode", ["fp32", "bf16"])
+def test_masked_wide_heads_match_the_oracle(mode):
+    cfg = dict(n_blocks=1, d_model=224, n_heads=2, d_mlp=64, seq_len=100, batch=3, mode=mode)
+    lens = np.asarray([100, 1, 65], dtype=np.int32)
+    flat, blocks, x, dy1, dy2 = make_case(cfg, seed=4)
+    ref = [O.stack_backward_reversible(x[b:b + 1].astype(np.float64), x[b:b + 1, ::-1].astype(np.float64), blocks, 2,
+                                       dy1[b:b + 1].astype(np.float64), dy2[b:b + 1].astype(np.float64), key_len=lens[b:b + 1])
+           for b in range(3)]
+    c = gpu_cfg(cfg)
+    args = [to_dev(a) for a in (x, x[:, ::-1].copy())]
+    res = B.rev_stack_backward_reprop_masked(c, to_dev(flat, B.param_dtype(c)), *args, torch.from_numpy(lens).cuda(), to_dev(dy1),
+                                             to_dev(dy2))
+    torch.cuda.synchronize()
+    for i, k in enumerate(("dX1", "dX2")):
+        assert rel_err(res[k].cpu().numpy(), np.concatenate([r[i] for r in ref])) <= TOL[mode], k
