@@ -116,7 +116,7 @@ struct RedSeg {
     int64_t stride, n, split;
     int P;
 };
-constexpr int RED_MAX_SEGS = 6;
+constexpr int RED_MAX_SEGS = 8;
 // All segments in one launch (every length a multiple of 4, nseg <= RED_MAX_SEGS).
 int reduce_multi(hipStream_t s, const RedSeg* segs, int nseg);
 
@@ -164,33 +164,40 @@ int gemm_nn_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int6
                 int M, int N, int K, const Epi& epi);
 // rows of column-sum partials a float32 GEMM with an [M, N] output writes
 int gemm_f32_colsum_strips(int M, int N);
-// dW[N,K] (float32, ld = K) = G[M,N]^T * A[M,K]  -- reduction over the M tokens.
-// `partial` is scratch for the fixed-order split of the reduction (may be unused).
-int gemm_wgrad_bf16(hipStream_t s, const bf16* G, int64_t ldg, const bf16* A, int64_t lda,
-                    int M, int N, int K, float* dW, float* partial, int64_t partial_elems, RedSeg* defer = nullptr);
-
-// Several weight gradients over the same M tokens in ONE launch (the four of a transformer block): together their
-// tiles fill the device, so the token range is cut into fewer pieces (none for Rev-ViT-B) than each would need alone.
-// segs[k] receives the deferred fixed-order reduction of item k's pieces (P == 0: nothing to reduce).
+// dW[N,K] (float32, ld = K) = G[M,N]^T * A[M,K], reduction over the M tokens: up to WGRAD_GROUP_MAX of them over the same
+// tokens in ONE launch (the four of a transformer block), whose tiles together fill the device, so that the token
+// range is cut into fewer pieces than each would need alone.  segs receives the fixed-order reductions of the pieces
+// that are left for a reduce_multi (at most one per item and per column sum), their number in *nseg.
 constexpr int WGRAD_GROUP_MAX = 4;
 struct WgradItem {
     const bf16* G; int64_t ldg;        // cotangent [M, N]
     const bf16* A; int64_t lda;        // activation [M, K]
     int N, K;
     float* dW;                         // [N, K]
-    float* partial; int64_t partial_elems;   // scratch for the pieces (may be null / 0: then this item allows no cut)
+    float* colsum;                     // column sums of G [N] (nullable, at most WGRAD_SUMS_MAX of a group): the bias gradient
 };
-// max_ranges > 0 caps the number of token ranges (1: never cut, whatever share of the device the tiles fill).
-int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int M, RedSeg* segs, int max_ranges = 0);
-// token ranges the group launch uses for these shapes (1: no pieces, no scratch); item k then needs ranges * N[k] * K[k]
-// floats of scratch
-int wgrad_group_ranges(int M, const int* N, const int* K, int count);
+int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int M, float* scratch, int64_t scratch_elems,
+                          RedSeg* segs, int* nseg);
+int64_t wgrad_scratch_elems(int M, const int* N, const int* K, int count);   // floats of scratch it needs for these shapes
 // The float32 flavour: up to WGRAD_GROUP_MAX weight gradients in one launch, no pieces.
 struct WgradF32Item { const float* G; int64_t ldg; const float* A; int64_t lda; int N, K; float* dW; };
 int gemm_wgrad_f32_group(hipStream_t s, const WgradF32Item* items, int count, int M);
+// Column sums that ride in a weight-gradient launch: its last workgroups take 512 columns of one of `chunks` runs of `rows`
+// tokens each (n = 0: none); the chunks' sums go to out[chunk * n + column].
+// At most two cotangents; block0: the first of a cotangent's workgroups, counted from the first behind the tiles.
+constexpr int WGRAD_SUMS_MAX = 2;
+struct WgradSums { const bf16* g; float* out; float* total; int64_t ld; int n, rows, chunks, block0; };
 // device-side description of the launch (gemm_wgrad_dma.hip)
 struct WgradProblem { const bf16* G; const bf16* A; float* out; int64_t ldg, lda, split_stride; int N, K, tile0; };
-struct WgradGroup { WgradProblem p[WGRAD_GROUP_MAX]; int count, tiles_total; };
+struct WgradGroup { WgradProblem p[WGRAD_GROUP_MAX]; WgradSums sums[WGRAD_SUMS_MAX]; int count, tiles_total, tile_blocks, sum_blocks; };
+// The same in 256x256 tiles (gemm_wgrad_big.hip): `full` tiles run over all tokens, the others over `splits` ranges of them.
+struct WgradBigProblem { const bf16* G; const bf16* A; float* dW; int64_t ldg, lda; int N, K, tile0; };
+struct WgradBig {
+    WgradBigProblem p[WGRAD_GROUP_MAX];
+    WgradSums sums[WGRAD_SUMS_MAX];
+    float* partial;               // 256x256 blocks [(tile - full) * splits + range]
+    int M, count, tiles, full, splits, stages, stages_per_split, tile_blocks, sum_blocks;
+};
 
 // attention with float32 products (attention_f32.hip): float32 mode, and the backward of bf16 heads wider than 96
 int attention_forward_f32(hipStream_t s, const float* qkv, float* o, float* lse, int B, int T, int H, int dh, const int* key_len);

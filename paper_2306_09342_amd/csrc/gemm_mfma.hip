@@ -2,9 +2,9 @@
 //
 //  gemm_nt_bf16 / gemm_nn_bf16   C = A * B^T  /  C = A * B  with fused epilogue: picks the tile and, for launches that do
 //            not fill the chip, the split of the contraction (gemm_nt_dma.hip, gemm_ksplit.hip).
-//  gemm_wgrad_bf16               dW[N,K] = G[M,N]^T * A[M,K]: picks the number of token ranges and
-//            launches the kernel of gemm_wgrad_dma.hip; the partial tiles of the ranges are summed
-//            afterwards in range order, so results do not depend on scheduling.
+//  gemm_wgrad_bf16_group         dW[N,K] = G[M,N]^T * A[M,K], up to four in a launch: picks the tile (gemm_wgrad_dma.hip,
+//            gemm_wgrad_big.hip) and the number of token ranges; the pieces of the ranges are summed afterwards in
+//            range order, so results do not depend on scheduling.
 #include "mfma.h"
 
 namespace rev {
@@ -106,66 +106,54 @@ constexpr int WG_BP = 128;            // tile rows (n)
 constexpr int WG_BQ = 128;            // tile cols (k)
 constexpr int WG_BR = 64;             // tokens per step
 
-// The token reduction is cut into S ranges so that tiles * S fills, but does not exceed, the
-// workgroup slots of the chip (256 CUs x 2 resident workgroups): one full round, no ragged second one.
-// Narrow layers with very many tokens (window-attention stages: a handful of tiles, thousands of
-// steps) get up to 128 ranges; the partial sums stay below 64 MB.
-static int wgrad_splits(int M, int N, int K) {
-    const int tiles = ((N + WG_BP - 1) / WG_BP) * ((K + WG_BQ - 1) / WG_BQ);
-    int S = 512 / tiles;
-    const int steps = (M + WG_BR - 1) / WG_BR;
-    if (S > steps / 4) S = steps / 4;                          // at least 4 steps per range
-    const int64_t cap = ((int64_t)64 << 20) / ((int64_t)N * K * 4);   // at most 64 MB of partial sums
-    if (S > cap) S = (int)cap;
-    if (S > 128) S = 128;
-    if (S < 1) S = 1;
-    const int sps = (steps + S - 1) / S;
-    return (steps + sps - 1) / sps;                            // no empty ranges
+// How a group of weight gradients over the same M tokens is cut.
+//
+// 128x128 tiles (gemm_wgrad_dma.hip): the token reduction of all of them is cut into S ranges so that tiles * S fills, but
+// does not exceed, the 512 workgroup slots of the chip (two per CU); at least 4 steps per range, at most 64 MB of pieces per
+// weight.  Narrow layers with very many tokens (window-attention stages: a handful of tiles, thousands of steps) get up to
+// 128 ranges.
+//
+// 256x256 tiles (gemm_wgrad_big.hip): whole rounds of 256 tiles run over all tokens; what is left over (or a group with
+// fewer than 256 tiles) is cut into the number of ranges that keeps the CUs busiest, its pieces counted at the time of
+// writing and reading them.
+//
+// The cheaper of the two by measured times (us): a step of 64 tokens takes a round of 512 small tiles 1.0 and a round of 256
+// large ones 1.3, a piece costs 0.015 / 0.1 to write and read, a round's fill and last stores 4 / 7, a launch for the
+// pieces 4 / 5.  Measured, small and large (with the column sums): 12608 tokens, D = 768: 199 and 158; 8224, 1280: 360 and 266;
+// 16384, 768: 277 and 200; 8192, 1024: 228 and 177; 6000, 512: 57 and 56; 25216, 384: 109 and 117; 1500, 1280: 85 and 86.
+struct WgradPlan {
+    bool big;
+    int S, sps;                       // 128x128: token ranges and steps per range
+    int tiles, full, splits, stages, stages_per_split;   // 256x256
+    int tile_blocks;
+    int64_t piece_elems, elems;       // floats of scratch: the pieces, and with the column sums' chunks
+};
+// Column sums of n columns behind `blocks` tile workgroups of `steps` stages each: as many workgroups as the last round of
+// tiles leaves slots idle, but no more rows for one than it reads (at about 20 GB/s, 40 with 8 wavefronts) in the time of
+// a tile; in one chunk where that is short anyway.
+static WgradSums sums_plan(int M, int n, int blocks, int steps, bool big) {
+    WgradSums p = {};
+    const int slots = big ? 256 : 512, idle = (slots - blocks % slots) % slots, groups = (n + 511) / 512;
+    p.n = n;
+    const int most_rows = steps * (big ? 36 : 13), least = (M + most_rows - 1) / most_rows;
+    p.chunks = M <= 256 ? 1 : (idle / groups > least ? idle / groups : least);
+    if (p.chunks > (M + 63) / 64) p.chunks = (M + 63) / 64;
+    if (p.chunks < 1) p.chunks = 1;
+    p.rows = (M + p.chunks - 1) / p.chunks;
+    p.chunks = (M + p.rows - 1) / p.rows;
+    return p;
 }
-int64_t wgrad_partial_elems(int M, int N, int K) {
-    const int S = wgrad_splits(M, N, K);
-    return S > 1 ? (int64_t)S * N * K : 0;
-}
-
-int launch_wgrad_dma(hipStream_t s, const bf16* G, int64_t ldg, const bf16* A, int64_t lda, int M, int N, int K,
-                     int S, int sps, float* out);
-int launch_wgrad_dma_group(hipStream_t s, WgradGroup grp, int M, int S, int sps);
-
-int gemm_wgrad_bf16(hipStream_t s, const bf16* G, int64_t ldg, const bf16* A, int64_t lda,
-                    int M, int N, int K, float* dW, float* partial, int64_t partial_elems, RedSeg* defer) {
-    if (defer) defer->P = 0;            // P == 0: nothing left to reduce
-    if ((ldg & 7) || (lda & 7) || (N & 7) || (K & 7) || ((uintptr_t)G & 15) || ((uintptr_t)A & 15)) {
-        set_error("gemm_wgrad_bf16: sizes must be multiples of 8 and every buffer 16-byte aligned");
-        return REV_EINVAL;
-    }
-    const int S = wgrad_splits(M, N, K);
-    if (S > 1 && (partial == nullptr || partial_elems < (int64_t)S * N * K)) {
-        set_error("gemm_wgrad_bf16: split scratch too small");
-        return REV_EWORKSPACE;
-    }
+static WgradPlan wgrad_plan(int M, const int* N, const int* K, int count) {
+    WgradPlan p = {};
     const int steps = (M + WG_BR - 1) / WG_BR;
-    const int sps = (steps + S - 1) / S;
-    const int tiles = ((N + WG_BP - 1) / WG_BP) * ((K + WG_BQ - 1) / WG_BQ);
-    {
-        ProfScope ps(K_GEMM_WGRAD, s, 2.0 * M * N * K);
-        int rc = launch_wgrad_dma(s, G, ldg, A, lda, M, N, K, S, sps, S > 1 ? partial : dW);
-        if (rc) return rc;
+    int t128 = 0;
+    int64_t nk = 0;
+    for (int k = 0; k < count; ++k) {
+        t128 += tiles_of(N[k], K[k], WG_BP, WG_BQ);
+        p.tiles += tiles_of(N[k], K[k], 256, 256);
+        nk += (int64_t)N[k] * K[k];
     }
-    if (S > 1) {
-        const RedSeg g = {partial, dW, nullptr, (int64_t)N * K, (int64_t)N * K, (int64_t)N * K, S};
-        if (defer) { *defer = g; return REV_OK; }
-        return reduce_multi(s, &g, 1);
-    }
-    return REV_OK;
-}
-
-// Token ranges of a group launch: tiles of all items x S fills, but does not exceed, the 512 workgroup slots; at
-// least 4 steps per range; at most 64 MB of pieces per item.
-int wgrad_group_ranges(int M, const int* N, const int* K, int count) {
-    int tiles_total = 0;
-    for (int k = 0; k < count; ++k) tiles_total += ((N[k] + WG_BP - 1) / WG_BP) * ((K[k] + WG_BQ - 1) / WG_BQ);
-    const int steps = (M + WG_BR - 1) / WG_BR;
-    int S = 512 / (tiles_total > 0 ? tiles_total : 1);
+    int S = 512 / (t128 > 0 ? t128 : 1);
     if (S > steps / 4) S = steps / 4;
     if (S > 128) S = 128;
     for (int k = 0; k < count; ++k) {
@@ -173,60 +161,101 @@ int wgrad_group_ranges(int M, const int* N, const int* K, int count) {
         if (S > cap) S = (int)cap;
     }
     if (S < 1) S = 1;
-    const int sps = (steps + S - 1) / S;
-    return (steps + sps - 1) / sps;                            // no empty ranges
-}
+    p.sps = (steps + S - 1) / S;
+    p.S = (steps + p.sps - 1) / p.sps;                         // no empty ranges
+    const double small = 4.0 + (double)((t128 * p.S + 511) / 512) * p.sps + (p.S > 1 ? 4.0 + (double)p.S * nk / 16384 * 0.015 : 0.0);
 
-int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int M, RedSeg* segs, int max_ranges) {
-    bool fast = count >= 1 && count <= WGRAD_GROUP_MAX;
-    for (int k = 0; k < count && fast; ++k) {
-        const WgradItem& it = items[k];
-        if ((it.ldg & 7) || (it.lda & 7) || (it.N & 7) || (it.K & 7) || ((uintptr_t)it.G & 15) || ((uintptr_t)it.A & 15))
-            fast = false;
+    p.stages = (M + 127) / 128 * 2;                            // an even number; tokens beyond M count as zeros
+    p.full = p.tiles / 256 * 256;
+    const int rem = p.tiles - p.full;
+    double best = rem > 0 ? 1e30 : 0.0;
+    p.splits = 1;
+    p.stages_per_split = p.stages;
+    for (int q = 1; rem > 0 && q <= 16; ++q) {
+        const int sps = ((p.stages + q - 1) / q + 1) / 2 * 2;
+        if (q > 1 && (sps < 16 || (p.stages + sps - 1) / sps != q || rem * q > 320)) continue;
+        const double c = (double)((rem * q + 255) / 256) * (7.0 + sps * 1.3) + (q > 1 ? 5.0 + rem * q * 0.1 : 0.0);
+        if (c < best) { best = c; p.splits = q; p.stages_per_split = sps; }
     }
-    if (!fast) {                          // one at a time (any shape)
-        for (int k = 0; k < count; ++k) {
-            const WgradItem& it = items[k];
-            int rc = gemm_wgrad_bf16(s, it.G, it.ldg, it.A, it.lda, M, it.N, it.K, it.dW, it.partial, it.partial_elems, &segs[k]);
-            if (rc) return rc;
-        }
-        return REV_OK;
-    }
-    // token ranges: tiles of all items x S fills, but does not exceed, the 512 workgroup slots; at least 4 steps per
-    // range; no more ranges than every item's scratch holds
-    WgradGroup grp = {};
-    grp.count = count;
-    int tiles_total = 0;
+    const double large = (double)(p.full / 256) * (7.0 + p.stages * 1.3) + best;
+    p.tile_blocks = p.full + rem * p.splits;
+    p.big = M >= 64 && large < 0.95 * small;
+    p.piece_elems = p.big ? (p.splits > 1 ? (int64_t)rem * p.splits * 65536 : 0) : (p.S > 1 ? p.S * nk : 0);
+    if (!p.big) p.tile_blocks = t128 * p.S;
+    p.elems = p.piece_elems;
+    for (int k = 0; k < count; ++k) p.elems += (int64_t)sums_plan(M, N[k], p.tile_blocks, p.big ? p.stages_per_split : p.sps, p.big).chunks * N[k];
+    return p;
+}
+int64_t wgrad_scratch_elems(int M, const int* N, const int* K, int count) { return wgrad_plan(M, N, K, count).elems; }
+
+int launch_wgrad_dma_group(hipStream_t s, const WgradGroup& grp, int M, int sps);
+int launch_wgrad_big(hipStream_t s, const WgradBig& p);
+
+int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int M, float* scratch, int64_t scratch_elems,
+                          RedSeg* segs, int* nseg) {
+    *nseg = 0;
+    if (count < 1 || count > WGRAD_GROUP_MAX) { set_error("gemm_wgrad_bf16: 1 to 4 weight gradients per launch"); return REV_EINVAL; }
+    int N[WGRAD_GROUP_MAX], K[WGRAD_GROUP_MAX];
     double flops = 0;
     for (int k = 0; k < count; ++k) {
-        grp.p[k].tile0 = tiles_total;
-        tiles_total += ((items[k].N + WG_BP - 1) / WG_BP) * ((items[k].K + WG_BQ - 1) / WG_BQ);
-        flops += 2.0 * M * items[k].N * items[k].K;
+        const WgradItem& it = items[k];
+        if ((it.ldg & 7) || (it.lda & 7) || (it.N & 7) || (it.K & 7) || (((uintptr_t)it.G | (uintptr_t)it.A | (uintptr_t)it.dW) & 15)) {
+            set_error("gemm_wgrad_bf16: sizes must be multiples of 8 and every buffer 16-byte aligned");
+            return REV_EINVAL;
+        }
+        N[k] = it.N; K[k] = it.K;
+        flops += 2.0 * M * it.N * it.K;
     }
-    grp.tiles_total = tiles_total;
-    const int steps = (M + WG_BR - 1) / WG_BR;
-    int Ns[WGRAD_GROUP_MAX], Ks[WGRAD_GROUP_MAX];
-    for (int k = 0; k < count; ++k) { Ns[k] = items[k].N; Ks[k] = items[k].K; }
-    int S = wgrad_group_ranges(M, Ns, Ks, count);
-    if (max_ranges > 0 && S > max_ranges) S = max_ranges;
-    for (int k = 0; k < count; ++k) {
-        const int64_t cap = items[k].partial ? items[k].partial_elems / ((int64_t)items[k].N * items[k].K) : 0;
-        if (S > cap) S = (int)cap;
+    const WgradPlan pl = wgrad_plan(M, N, K, count);
+    if (pl.elems > 0 && (scratch == nullptr || scratch_elems < pl.elems)) {
+        set_error("gemm_wgrad_bf16: scratch too small");
+        return REV_EWORKSPACE;
     }
-    if (S < 1) S = 1;
-    const int sps = (steps + S - 1) / S;
-    S = (steps + sps - 1) / sps;                               // no empty ranges
+    WgradSums sums[WGRAD_SUMS_MAX] = {};
+    int nsums = 0, sum_blocks = 0;
+    float* sums_scratch = scratch + pl.piece_elems;
+    for (int k = 0; k < count; ++k)
+        if (items[k].colsum) {
+            if (nsums == WGRAD_SUMS_MAX) { set_error("gemm_wgrad_bf16: too many column sums"); return REV_EINVAL; }
+            WgradSums& q = sums[nsums++];
+            q = sums_plan(M, N[k], pl.tile_blocks, pl.big ? pl.stages_per_split : pl.sps, pl.big);
+            q.g = items[k].G; q.ld = items[k].ldg; q.total = items[k].colsum; q.block0 = sum_blocks;
+            q.out = pl.big || q.chunks > 1 ? sums_scratch : q.total;
+            sums_scratch += (int64_t)q.chunks * q.n;
+            sum_blocks += q.chunks * ((q.n + 511) / 512);
+        }
+    for (int k = nsums; k < WGRAD_SUMS_MAX; ++k) sums[k].block0 = sum_blocks;
+    ProfScope ps(K_GEMM_WGRAD, s, flops);
+    if (pl.big) {
+        WgradBig b = {};
+        b.count = count; b.M = M; b.tiles = pl.tiles; b.full = pl.full; b.splits = pl.splits;
+        b.stages = pl.stages; b.stages_per_split = pl.stages_per_split; b.tile_blocks = pl.tile_blocks;
+        b.partial = scratch; b.sum_blocks = sum_blocks;
+        for (int k = 0; k < WGRAD_SUMS_MAX; ++k) b.sums[k] = sums[k];
+        for (int k = 0, t = 0; k < count; ++k) {
+            const WgradItem& it = items[k];
+            b.p[k] = {it.G, it.A, it.dW, it.ldg, it.lda, it.N, it.K, t};
+            t += tiles_of(it.N, it.K, 256, 256);
+        }
+        return launch_wgrad_big(s, b);
+    }
+    WgradGroup grp = {};
+    grp.count = count; grp.tile_blocks = pl.tile_blocks; grp.sum_blocks = sum_blocks;
+    for (int k = 0; k < WGRAD_SUMS_MAX; ++k) grp.sums[k] = sums[k];
+    float* part = scratch;
     for (int k = 0; k < count; ++k) {
         const WgradItem& it = items[k];
         const int64_t nk = (int64_t)it.N * it.K;
-        grp.p[k].G = it.G; grp.p[k].A = it.A; grp.p[k].ldg = it.ldg; grp.p[k].lda = it.lda;
-        grp.p[k].N = it.N; grp.p[k].K = it.K;
-        grp.p[k].out = S > 1 ? it.partial : it.dW;
-        grp.p[k].split_stride = nk;
-        segs[k] = {it.partial, it.dW, nullptr, nk, nk, nk, S > 1 ? S : 0};
+        grp.p[k] = {it.G, it.A, pl.S > 1 ? part : it.dW, it.ldg, it.lda, nk, it.N, it.K, grp.tiles_total};
+        grp.tiles_total += tiles_of(it.N, it.K, WG_BP, WG_BQ);
+        if (pl.S > 1) {
+            segs[(*nseg)++] = {part, it.dW, nullptr, nk, nk, nk, pl.S};
+            part += pl.S * nk;
+        }
     }
-    ProfScope ps(K_GEMM_WGRAD, s, flops);
-    return launch_wgrad_dma_group(s, grp, M, S, sps);
+    for (int k = 0; k < nsums; ++k)
+        if (sums[k].chunks > 1) segs[(*nseg)++] = {sums[k].out, sums[k].total, nullptr, sums[k].n, sums[k].n, sums[k].n, sums[k].chunks};
+    return launch_wgrad_dma_group(s, grp, M, pl.sps);
 }
 
 }  // namespace rev

@@ -22,8 +22,7 @@ constexpr int WD_TILE = WD_BR * 256;            // bytes of one operand tile
 constexpr int WD_STAGE = 2 * WD_TILE;
 
 // One 128 x 128 tile of dW over one token range: `tile` counts the tiles of this weight gradient, `split` its token
-// ranges (range `split` covers steps_per_split 64-token steps and goes to out + split * split_stride).
-template <int NS>
+// ranges (range `split` covers steps_per_split 64-token steps and goes to out + split * split_stride). 
 __device__ __forceinline__ void wgrad_dma_tile(const bf16* __restrict__ G, int64_t ldg,
                                                const bf16* __restrict__ A, int64_t lda,
                                                int M, int N, int K, int steps_per_split,
@@ -39,6 +38,8 @@ __device__ __forceinline__ void wgrad_dma_tile(const bf16* __restrict__ G, int64
     int tp, tq;
     if (K > N) { tq = tile / tiles_p; tp = tile - tq * tiles_p; }
     else { tp = tile / tiles_q; tq = tile - tp * tiles_q; }
+    tp = __builtin_amdgcn_readfirstlane(tp);                       // the quotients come from vector registers
+    tq = __builtin_amdgcn_readfirstlane(tq);
     const int p0 = tp * WD_BP, q0 = tq * WD_BQ;
     const int total_steps = (M + WD_BR - 1) / WD_BR;
     const int step0 = split * steps_per_split;
@@ -46,7 +47,6 @@ __device__ __forceinline__ void wgrad_dma_tile(const bf16* __restrict__ G, int64
 
     // Each operand tile is 16 wavefront-wide loads of 4 token rows; wavefront w issues loads
     // w, w+4, w+8, w+12 of G and the same of A.  Lane l: row 4*i + l/16, LDS position l%16.
-    constexpr int LPW = 8;
     int rowl[4], chunk[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -77,11 +77,9 @@ __device__ __forceinline__ void wgrad_dma_tile(const bf16* __restrict__ G, int64
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-#pragma unroll
-    for (int s = 0; s < NS - 1; ++s)
-        if (s < nsteps) issue(s, s);
+    if (nsteps > 0) issue(0, 0);
 
-    if constexpr (NS == 2) {
+    {
         // Hand-placed fragment reads (see mfma.h): one step ahead, every product group waits only
         // for its own 8 transpose reads.  Stage parity and "is there a next stage" are compile-time
         // tags so that the loop body has no branch.
@@ -172,26 +170,6 @@ __device__ __forceinline__ void wgrad_dma_tile(const bf16* __restrict__ G, int64
         } else if (st + 1 == nsteps) {
             body(S0{}, std::false_type{}, st);
         }
-    } else
-    for (int st = 0; st < nsteps; ++st) {
-        if (st + NS - 2 < nsteps) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 2) * LPW));
-        else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
-        __builtin_amdgcn_s_barrier();
-        if (st + NS - 1 < nsteps) issue(st + NS - 1, (st + NS - 1) % NS);
-        const unsigned char* Gt = smem + (st % NS) * WD_STAGE;
-        const unsigned char* At = Gt + WD_TILE;
-#pragma unroll
-        for (int kk = 0; kk < WD_BR / 16; ++kk) {
-            bf16x8_t a[2], b[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = tr_frag_swz(Gt, kk * 16, wp * 64 + i * 32, lane);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) b[j] = tr_frag_swz(At, kk * 16, wq * 64 + j * 32, lane);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = mfma32(a[i], b[j], acc[i][j]);
-        }
     }
 
     float* o = out + (int64_t)split * split_stride;
@@ -211,51 +189,34 @@ __device__ __forceinline__ void wgrad_dma_tile(const bf16* __restrict__ G, int64
     }
 }
 
+// Several weight gradients over the same M tokens in one launch (the four of a transformer block): the tiles of all
+// of them form one list, so that together they fill the device where each alone would have to cut its token range
+// into pieces (and sum the pieces afterwards) to do so.
 // Each XCD takes one contiguous run of the (token range, tile) order, token range slowest: an XCD
 // then works on one or two token ranges and on a block of tiles inside them, so both operands are
 // partitioned over the XCDs' L2s (with every XCD walking all ranges of its tiles, each of them read
 // the whole of one operand).
-template <int NS>
-__global__ __launch_bounds__(256) void wgrad_dma_kernel(const bf16* __restrict__ G, int64_t ldg,
-                                                        const bf16* __restrict__ A, int64_t lda,
-                                                        int M, int N, int K, int steps_per_split,
-                                                        float* __restrict__ out, int64_t split_stride) {
-    const int tiles = ((N + WD_BP - 1) / WD_BP) * ((K + WD_BQ - 1) / WD_BQ);
-    const int lin = xcd_remap(blockIdx.x, gridDim.x);
-    const int split = lin / tiles;
-    wgrad_dma_tile<NS>(G, ldg, A, lda, M, N, K, steps_per_split, out, split_stride, lin - split * tiles, split);
-}
-
-// Several weight gradients over the same M tokens in one launch (the four of a transformer block): the tiles of all
-// of them form one list, so that together they fill the device where each alone would have to cut its token range
-// into pieces (and sum the pieces afterwards) to do so.
-template <int NS>
 __global__ __launch_bounds__(256) void wgrad_dma_group_kernel(WgradGroup grp, int M, int steps_per_split) {
-    const int lin = xcd_remap(blockIdx.x, gridDim.x);
-    const int split = lin / grp.tiles_total;
+    if ((int)blockIdx.x >= grp.tile_blocks) {
+        extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+        wgrad_tail_sums<4>(grp.sums, M, blockIdx.x - grp.tile_blocks, reinterpret_cast<float*>(smem));
+        return;
+    }
+    const int lin = xcd_remap(blockIdx.x, grp.tile_blocks);
+    const int split = __builtin_amdgcn_readfirstlane(lin / grp.tiles_total);
     const int gt = lin - split * grp.tiles_total;
     int pi = 0;
 #pragma unroll
     for (int k = 1; k < WGRAD_GROUP_MAX; ++k)
         if (k < grp.count && gt >= grp.p[k].tile0) pi = k;
     const WgradProblem& q = grp.p[pi];
-    wgrad_dma_tile<NS>(q.G, q.ldg, q.A, q.lda, M, q.N, q.K, steps_per_split, q.out, q.split_stride, gt - q.tile0, split);
+    wgrad_dma_tile(q.G, q.ldg, q.A, q.lda, M, q.N, q.K, steps_per_split, q.out, q.split_stride, gt - q.tile0, split);
 }
 
-int launch_wgrad_dma_group(hipStream_t s, WgradGroup grp, int M, int S, int sps) {
+int launch_wgrad_dma_group(hipStream_t s, const WgradGroup& grp, int M, int sps) {
     static LdsLimit lim;
-    if (int rc = lim.ensure(reinterpret_cast<const void*>(wgrad_dma_group_kernel<2>), 2 * WD_STAGE)) return rc;
-    hipLaunchKernelGGL(wgrad_dma_group_kernel<2>, dim3(grp.tiles_total * S), dim3(256), 2 * WD_STAGE, s, grp, M, sps);
-    REV_HIP(hipGetLastError());
-    return REV_OK;
-}
-
-int launch_wgrad_dma(hipStream_t s, const bf16* G, int64_t ldg, const bf16* A, int64_t lda, int M, int N, int K,
-                     int S, int sps, float* out) {
-    const int tiles = ((N + WD_BP - 1) / WD_BP) * ((K + WD_BQ - 1) / WD_BQ);
-    static LdsLimit lim;
-    if (int rc = lim.ensure(reinterpret_cast<const void*>(wgrad_dma_kernel<2>), 2 * WD_STAGE)) return rc;
-    hipLaunchKernelGGL(wgrad_dma_kernel<2>, dim3(tiles * S), dim3(256), 2 * WD_STAGE, s, G, ldg, A, lda, M, N, K, sps, out, (int64_t)N * K);
+    if (int rc = lim.ensure(reinterpret_cast<const void*>(wgrad_dma_group_kernel), 2 * WD_STAGE)) return rc;
+    hipLaunchKernelGGL(wgrad_dma_group_kernel, dim3(grp.tile_blocks + grp.sum_blocks), dim3(256), 2 * WD_STAGE, s, grp, M, sps);
     REV_HIP(hipGetLastError());
     return REV_OK;
 }

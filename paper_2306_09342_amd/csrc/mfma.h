@@ -113,6 +113,48 @@ static __device__ u32x4_t g_zero_chunk[4];
 // s_waitcnt immediate for gfx9: vmcnt in bits [3:0] and [15:14], expcnt [6:4] (no wait), lgkmcnt [11:8] = 0
 constexpr int waitcnt_vm_lgkm0(int vm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4); }
 
+// Column sums of a cotangent (a bias gradient) in the last workgroups of a weight-gradient launch, for the CUs that its tiles
+// leave idle: workgroup b takes 512 columns of one chunk of tokens, a wavefront every NW-th token, a lane 8 columns;
+// the wavefronts are added in order through sh (NW * 512 floats).  (Summing the fragments inside the tiles was measured:
+// v_dot2 between the products costs the launch 10 to 25 %, more than a launch of its own.)
+template <int NW>
+__device__ __forceinline__ void wgrad_tail_sums(const WgradSums (&sums)[WGRAD_SUMS_MAX], int M, int b, float* sh) {
+    const WgradSums& p = b >= sums[1].block0 ? sums[1] : sums[0];
+    b -= p.block0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int groups = (p.n + 511) / 512, chunk = b / groups, c0 = (b - chunk * groups) * 512, c = c0 + lane * 8;
+    const int r1 = min(M, (chunk + 1) * p.rows);
+    float s[8] = {};
+    if (c < p.n) {
+        const bf16* src = p.g + c;
+        int r = chunk * p.rows + wave;
+        auto add = [&](u32x4_t v) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                s[2 * e] += __uint_as_float(v[e] << 16);
+                s[2 * e + 1] += __uint_as_float(v[e] & 0xFFFF0000u);
+            }
+        };
+        for (; r + 7 * NW < r1; r += 8 * NW) {
+            u32x4_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const u32x4_t*>(src + (int64_t)(r + NW * u) * p.ld);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) add(v[u]);
+        }
+        for (; r < r1; r += NW) add(*reinterpret_cast<const u32x4_t*>(src + (int64_t)r * p.ld));
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sh[wave * 512 + lane * 8 + e] = s[e];
+    __syncthreads();
+    for (int i = threadIdx.x; i < 512 && c0 + i < p.n; i += NW * 64) {
+        float t = sh[i];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t += sh[w * 512 + i];
+        p.out[(int64_t)chunk * p.n + c0 + i] = t;
+    }
+}
+
 // Workgroups go round-robin over the 8 XCDs, each with its own L2: give every
 // XCD one contiguous run of tiles so that neighbouring tiles (which share an
 // operand panel) meet in the same L2.

@@ -109,9 +109,9 @@ struct Layout {
     int64_t gy1b[2];       // act-typed copy of gY1 (bf16 mode), by block parity
     int64_t dh[2], dqkv[2]; // by block parity: read by the weight-gradient kernels of the block
     int64_t dn, dO, delta;
-    int64_t part_ln[2], part_col[2], part_wg[4];   // one per deferred reduction of a block
+    int64_t part_ln[2], part_col[2], part_wg;   // partial sums of the deferred reductions of a block
     int64_t total;
-    int64_t part_wg_elems[4];
+    int64_t part_wg_elems;
     int64_t slot_bytes;
     int ring_levels;
 };
@@ -164,9 +164,9 @@ static Layout make_layout(const rev_cfg& c, bool compact) {
     L.part_ln[1] = take(ln_bwd_partial_elems((int)M, (int)D) * 4);
     {
         // [0]: fc1 bias gradient (column-sum strips of the GELU' epilogue);
-        // [1]: QKV bias gradient; also the top block's fc2 bias gradient
+        // [1]: the top block's fc2 bias gradient; float32 mode: the QKV bias gradients too
         const int64_t e0 = (int64_t)(c.mode == REV_MODE_BF16 ? gemm_colsum_strips((int)M, (int)Dm) : gemm_f32_colsum_strips((int)M, (int)Dm)) * Dm;
-        int64_t e1 = colsum_partial_elems((int)M, (int)(3 * D));
+        int64_t e1 = c.mode == REV_MODE_BF16 ? 0 : colsum_partial_elems((int)M, (int)(3 * D));
         int64_t e1b = colsum_partial_elems((int)M, (int)D);
         if (e1b > e1) e1 = e1b;
         L.part_col[0] = take(e0 * 4);
@@ -176,11 +176,8 @@ static Layout make_layout(const rev_cfg& c, bool compact) {
         // scratch for the pieces of the four weight gradients (fc2, fc1, proj, qkv), which go out as one launch: none
         // where their tiles fill the device without cutting the token range
         const int nn[4] = {(int)D, (int)Dm, (int)D, (int)(3 * D)}, kk[4] = {(int)Dm, (int)D, (int)D, (int)D};
-        const int S = wgrad_group_ranges((int)M, nn, kk, 4);
-        for (int w = 0; w < 4; ++w) {
-            L.part_wg_elems[w] = S > 1 ? (int64_t)S * nn[w] * kk[w] : 0;
-            L.part_wg[w] = take((L.part_wg_elems[w] > 0 ? L.part_wg_elems[w] : 64) * 4);
-        }
+        L.part_wg_elems = wgrad_scratch_elems((int)M, nn, kk, 4);
+        L.part_wg = take(L.part_wg_elems * 4);
     }
     L.total = off;
     return L;
@@ -323,7 +320,6 @@ struct Runner {
         T* dn = at<T>(L.dn);
         T* dO = at<T>(L.dO);
         float* pcol0 = at<float>(L.part_col[0]);
-        float* pcol1 = at<float>(L.part_col[1]);
         T* gy1b = gy1_act(blk, o1);
         // second stages of the block's fixed-order sums are gathered and run as one launch at the end
         RedSeg segs[4];
@@ -350,7 +346,8 @@ struct Runner {
         if (ev) REV_HIP(hipEventRecord(ev[2], s));
         Epi r = epi0(); r.kind = EPI_PLAIN; r.out = dn; r.ldo = D;
         RC(dgrad(s, blk, T_WQKV, dqkv, 3 * D, D, r));
-        RC(colsum<T>(s, dqkv, 3 * D, M, 3 * D, G(blk, T_BQKV), pcol1, &segs[nseg++]));
+        // (bf16: the weight-gradient kernel, which reads dqkv anyway, sums its columns)
+        if constexpr (!kBf16) RC(colsum<T>(s, dqkv, 3 * D, M, 3 * D, G(blk, T_BQKV), at<float>(L.part_col[1]), &segs[nseg++]));
         // dX2 = dY2 + LN1bwd(dn); dX2 is the block below's dY2, so its column sums are that block's
         // fc2 bias gradient
         RC((ln_backward<T, T>(s, dn, x2, sl.st1, P(blk, T_LN1G), d2, o2, kBf16 ? o2b : nullptr,
@@ -365,26 +362,20 @@ struct Runner {
         Slot sl = slot(blk);
         T* dhb = at<T>(L.dh[blk & 1]);
         T* dqkv = at<T>(L.dqkv[blk & 1]);
-        float* pwg[4] = {nullptr, nullptr, nullptr, nullptr};
-        if constexpr (kBf16) for (int w = 0; w < 4; ++w) pwg[w] = at<float>(L.part_wg[w]);
         T* gy1b = gy1_act(blk, o1);
-        RedSeg segs[4];
         if (ev) for (int k = 0; k < 4; ++k) REV_HIP(hipStreamWaitEvent(s, ev[k], 0));
         if constexpr (kBf16) {
             // all four in one launch: together their tiles fill the device without cutting the token range (or with
             // fewer cuts), which saves the float32 pieces and most of their reduction
-            const WgradItem items[4] = {
-                {d2b, D, sl.a, Dm, D, Dm, G(blk, T_WFC2), pwg[0], L.part_wg_elems[0]},
-                {dhb, Dm, sl.n2, D, Dm, D, G(blk, T_WFC1), pwg[1], L.part_wg_elems[1]},
-                {gy1b, D, sl.o, D, D, D, G(blk, T_WPROJ), pwg[2], L.part_wg_elems[2]},
-                {dqkv, 3 * D, sl.n1, D, 3 * D, D, G(blk, T_WQKV), pwg[3], L.part_wg_elems[3]}};
-            RC(gemm_wgrad_bf16_group(s, items, 4, M, segs));
+            const WgradItem items[4] = {{d2b, D, sl.a, Dm, D, Dm, G(blk, T_WFC2), nullptr},
+                                        {dhb, Dm, sl.n2, D, Dm, D, G(blk, T_WFC1), nullptr},
+                                        {gy1b, D, sl.o, D, D, D, G(blk, T_WPROJ), nullptr},
+                                        {dqkv, 3 * D, sl.n1, D, 3 * D, D, G(blk, T_WQKV), G(blk, T_BQKV)}};
+            RedSeg segs[RED_MAX_SEGS];
+            int nseg = 0;
+            RC(gemm_wgrad_bf16_group(s, items, 4, M, at<float>(L.part_wg), L.part_wg_elems, segs, &nseg));
             if (done_w2) REV_HIP(hipEventRecord(done_w2, s));
-            RedSeg live4[4];
-            int n4 = 0;
-            for (int w = 0; w < 4; ++w)
-                if (segs[w].P > 0) live4[n4++] = segs[w];
-            return reduce_multi(s, live4, n4);
+            return reduce_multi(s, segs, nseg);
         }
         if constexpr (!kBf16) {
             const WgradF32Item items[4] = {{d2b, D, sl.a, Dm, D, Dm, G(blk, T_WFC2)}, {dhb, Dm, sl.n2, D, Dm, D, G(blk, T_WFC1)},

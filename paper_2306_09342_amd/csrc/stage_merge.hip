@@ -245,7 +245,6 @@ static int merge_rows_per_block(int Mo) {
     return rpb;
 }
 
-int64_t wgrad_partial_elems(int M, int N, int K);   // gemm_mfma.hip
 
 // ---- workspace ---------------------------------------------------------------------------------
 struct MergeLayout {
@@ -253,8 +252,8 @@ struct MergeLayout {
     int64_t part_wg_elems;
     // fusion by a small MLP only: [X1 | X2], hidden pre-activation and activation, fused map, its cotangent, the
     // hidden cotangent (all [M, .] in the activation type), and the partial sums of the four parameter gradients
-    int64_t cat, h, a, z0, dz0, dh, part_col[2], part_fw[2];
-    int64_t part_fw_elems[2];
+    int64_t cat, h, a, z0, dz0, dh, part_col[2], part_fw;
+    int64_t part_fw_elems;
 };
 static MergeLayout merge_layout(const rev_merge_cfg& c) {
     MergeLayout L = {};
@@ -268,7 +267,9 @@ static MergeLayout merge_layout(const rev_merge_cfg& c) {
     L.dn = take(Mo * 4 * C * es);
     const int rpb = merge_rows_per_block((int)Mo);
     L.part_ln = take(((Mo + rpb - 1) / rpb) * 8 * C * 4);
-    L.part_wg_elems = (c.mode == REV_MODE_BF16) ? wgrad_partial_elems((int)Mo, (int)(2 * C), (int)(4 * C)) : 0;
+    const bool bf = c.mode == REV_MODE_BF16;
+    const int wn = (int)(2 * C), wk = (int)(4 * C), fn[2] = {(int)C, (int)C}, fk[2] = {(int)C, (int)(2 * C)};
+    L.part_wg_elems = bf ? wgrad_scratch_elems((int)Mo, &wn, &wk, 1) : 0;
     L.part_wg = take(L.part_wg_elems * 4);
     if (c.fusion == REV_FUSION_MLP) {
         const int64_t M = 4 * Mo;
@@ -278,12 +279,10 @@ static MergeLayout merge_layout(const rev_merge_cfg& c) {
         L.z0 = take(M * C * es);
         L.dz0 = take(M * C * es);
         L.dh = take(M * C * es);
-        L.part_col[0] = take(colsum_partial_elems((int)M, (int)C) * 4);
-        L.part_col[1] = take(colsum_partial_elems((int)M, (int)C) * 4);
-        L.part_fw_elems[0] = (c.mode == REV_MODE_BF16) ? wgrad_partial_elems((int)M, (int)C, (int)(2 * C)) : 0;
-        L.part_fw_elems[1] = (c.mode == REV_MODE_BF16) ? wgrad_partial_elems((int)M, (int)C, (int)C) : 0;
-        L.part_fw[0] = take((L.part_fw_elems[0] > 0 ? L.part_fw_elems[0] : 64) * 4);
-        L.part_fw[1] = take((L.part_fw_elems[1] > 0 ? L.part_fw_elems[1] : 64) * 4);
+        L.part_col[0] = take(bf ? 0 : colsum_partial_elems((int)M, (int)C) * 4);
+        L.part_col[1] = take(bf ? 0 : colsum_partial_elems((int)M, (int)C) * 4);
+        L.part_fw_elems = bf ? wgrad_scratch_elems((int)M, fn, fk, 2) : 0;
+        L.part_fw = take(L.part_fw_elems * 4);
     }
     L.total = pos;
     return L;
@@ -391,16 +390,17 @@ struct MergeRunner {
             hipLaunchKernelGGL((add2_kernel<T>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, dA, dB, at<T>(L.dob), n4);
             REV_HIP(hipGetLastError());
         }
-        RedSeg segs[2];
+        RedSeg segs[RED_MAX_SEGS];
+        int nseg = 0;
         float* dW = dparams + 8 * C;
         Epi e = {}; e.kind = EPI_PLAIN; e.out = at<T>(L.dn); e.ldo = 4 * C; e.solo = true;
         if constexpr (kBf16) {
-            RC(gemm_wgrad_bf16(s, at<T>(L.dob), 2 * C, at<T>(L.n), 4 * C, Mo, 2 * C, 4 * C, dW, at<float>(L.part_wg), L.part_wg_elems, &segs[0]));
+            const WgradItem it = {at<T>(L.dob), 2 * C, at<T>(L.n), 4 * C, 2 * C, 4 * C, dW, nullptr};
+            RC(gemm_wgrad_bf16_group(s, &it, 1, Mo, at<float>(L.part_wg), L.part_wg_elems, segs, &nseg));
             RC(gemm_nn_bf16(s, at<T>(L.dob), 2 * C, W(), 4 * C, Mo, 4 * C, 2 * C, e));
         } else {
             const WgradF32Item it = {at<T>(L.dob), 2 * C, at<T>(L.n), 4 * C, 2 * C, 4 * C, dW};
             RC(gemm_wgrad_f32_group(s, &it, 1, Mo));
-            segs[0].P = 0;
             RC(gemm_nn_f32(s, at<T>(L.dob), 2 * C, W(), 4 * C, Mo, 4 * C, 2 * C, e));
         }
         const int rpb = merge_rows_per_block(Mo);
@@ -425,52 +425,42 @@ struct MergeRunner {
             REV_HIP(hipGetLastError());
         }
         // d gamma | d beta are adjacent in the packed layout
-        segs[1] = {at<float>(L.part_ln), dparams, nullptr, (int64_t)8 * C, (int64_t)8 * C, (int64_t)8 * C, nblk};
-        if (segs[0].P > 0) RC(reduce_multi(s, segs, 2));
-        else RC(reduce_multi(s, &segs[1], 1));
-        return mlp() ? fuse_mlp_backward(s, dX1, dX2, dparams) : REV_OK;
+        segs[nseg++] = {at<float>(L.part_ln), dparams, nullptr, (int64_t)8 * C, (int64_t)8 * C, (int64_t)8 * C, nblk};
+        if (mlp()) RC(fuse_mlp_backward(s, dX1, dX2, dparams, segs, &nseg));
+        return reduce_multi(s, segs, nseg);
     }
 
     // dz0 (cotangent of the fused map) -> dX1, dX2 and the gradients of the fusion MLP; cat, h, a are those
-    // the forward half of this call left in the workspace
-    int fuse_mlp_backward(hipStream_t s, float* dX1, float* dX2, float* dparams) {
+    // the forward half of this call left in the workspace.  The fixed-order sums that are left are added to segs.
+    int fuse_mlp_backward(hipStream_t s, float* dX1, float* dX2, float* dparams, RedSeg* segs, int* nseg) {
         const int M = Mi();
         T* dz0 = at<T>(L.dz0);
         T* dh = at<T>(L.dh);
-        RedSeg segs[4];
-        int nseg = 0;
-        RedSeg wseg[2];
-        // output layer: db = column sums, dWb = dz0^T * a, da = dz0 * Wb, dh = da * gelu'(h)
-        RC(colsum<T>(s, dz0, C, M, C, dparams + off_bb(), at<float>(L.part_col[0]), &segs[nseg++]));
+        // output layer: db = column sums, dWb = dz0^T * a, da = dz0 * Wb, dh = da * gelu'(h);
+        // hidden layer: db = column sums of dh, dWa = dh^T * [X1 | X2], [dX1 | dX2] = dh * Wa (one GEMM per half:
+        // the two streams' cotangents are separate buffers)
         Epi e = {}; e.kind = EPI_GELU_BWD; e.out = dh; e.aux = at<T>(L.h); e.ldo = C; e.solo = true;
         Epi x1 = {}; x1.kind = EPI_PLAIN_F32; x1.outf = dX1; x1.ldo = C; x1.solo = true;
         Epi x2 = x1; x2.outf = dX2;
         if constexpr (kBf16) {
-            RC(gemm_wgrad_bf16(s, dz0, C, at<T>(L.a), C, M, C, C, dparams + off_wb(), at<float>(L.part_fw[1]), L.part_fw_elems[1], &wseg[1]));
             RC(gemm_nn_bf16(s, dz0, C, params + off_wb(), C, M, C, C, e));
-        } else {
-            const WgradF32Item it = {dz0, C, at<T>(L.a), C, C, C, dparams + off_wb()};
-            RC(gemm_wgrad_f32_group(s, &it, 1, M));
-            wseg[1].P = 0;
-            RC(gemm_nn_f32(s, dz0, C, params + off_wb(), C, M, C, C, e));
-        }
-        // hidden layer: db = column sums of dh, dWa = dh^T * [X1 | X2], [dX1 | dX2] = dh * Wa (one GEMM per half:
-        // the two streams' cotangents are separate buffers)
-        RC(colsum<T>(s, dh, C, M, C, dparams + off_ba(), at<float>(L.part_col[1]), &segs[nseg++]));
-        if constexpr (kBf16) {
-            RC(gemm_wgrad_bf16(s, dh, C, at<T>(L.cat), 2 * C, M, C, 2 * C, dparams + off_wa(), at<float>(L.part_fw[0]), L.part_fw_elems[0], &wseg[0]));
+            const WgradItem items[2] = {{dz0, C, at<T>(L.a), C, C, C, dparams + off_wb(), dparams + off_bb()},
+                                        {dh, C, at<T>(L.cat), 2 * C, C, 2 * C, dparams + off_wa(), dparams + off_ba()}};
+            int n = 0;
+            RC(gemm_wgrad_bf16_group(s, items, 2, M, at<float>(L.part_fw), L.part_fw_elems, segs + *nseg, &n));
+            *nseg += n;
             RC(gemm_nn_bf16(s, dh, C, params + off_wa(), 2 * C, M, C, C, x1));
-            RC(gemm_nn_bf16(s, dh, C, params + off_wa() + C, 2 * C, M, C, C, x2));
+            return gemm_nn_bf16(s, dh, C, params + off_wa() + C, 2 * C, M, C, C, x2);
         } else {
-            const WgradF32Item it = {dh, C, at<T>(L.cat), 2 * C, C, 2 * C, dparams + off_wa()};
-            RC(gemm_wgrad_f32_group(s, &it, 1, M));
-            wseg[0].P = 0;
+            RC(colsum<T>(s, dz0, C, M, C, dparams + off_bb(), at<float>(L.part_col[0]), &segs[(*nseg)++]));
+            RC(gemm_nn_f32(s, dz0, C, params + off_wb(), C, M, C, C, e));
+            RC(colsum<T>(s, dh, C, M, C, dparams + off_ba(), at<float>(L.part_col[1]), &segs[(*nseg)++]));
+            const WgradF32Item items[2] = {{dz0, C, at<T>(L.a), C, C, C, dparams + off_wb()},
+                                           {dh, C, at<T>(L.cat), 2 * C, C, 2 * C, dparams + off_wa()}};
+            RC(gemm_wgrad_f32_group(s, items, 2, M));
             RC(gemm_nn_f32(s, dh, C, params + off_wa(), 2 * C, M, C, C, x1));
-            RC(gemm_nn_f32(s, dh, C, params + off_wa() + C, 2 * C, M, C, C, x2));
+            return gemm_nn_f32(s, dh, C, params + off_wa() + C, 2 * C, M, C, C, x2);
         }
-        for (int w = 0; w < 2; ++w)
-            if (wseg[w].P > 0) segs[nseg++] = wseg[w];
-        return reduce_multi(s, segs, nseg);
     }
 };
 

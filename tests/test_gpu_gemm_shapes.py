@@ -26,6 +26,11 @@ SHAPES = {
     # whole-K tiles with a short last stage, and the first row count that takes them for narrow outputs
     "whole_K72": dict(n_blocks=1, d_model=72, n_heads=1, d_mlp=200, seq_len=31, batch=100),
     "whole_rows3073": dict(n_blocks=1, d_model=64, n_heads=1, d_mlp=136, seq_len=439, batch=7),
+    # weight gradients in 256x256 tiles: one token beyond the last full stage; ragged in every direction; three token ranges,
+    # the last one short
+    "wgrad256_one_token_over": dict(n_blocks=1, d_model=1024, n_heads=16, d_mlp=4096, seq_len=683, batch=3),
+    "wgrad256_ragged": dict(n_blocks=1, d_model=776, n_heads=97, d_mlp=3080, seq_len=125, batch=20),
+    "wgrad256_ranges": dict(n_blocks=1, d_model=520, n_heads=13, d_mlp=2056, seq_len=353, batch=17),
 }
 
 
