@@ -105,7 +105,7 @@ struct Layout {
     int64_t s_n2, s_h, s_a, s_n1, s_qkv, s_o, s_lse, s_st1, s_st2;   // relative to a slot
     int64_t ring[3][2];
     int64_t cot[2][2];     // float32 cotangent levels
-    int64_t cot2b[2];      // act-typed copy of the stream-2 cotangent (bf16 mode)
+    int64_t cot2b[3];      // act-typed copies of the stream-2 cotangent (bf16 mode), by block index mod 3
     int64_t gy1b[2];       // act-typed copy of gY1 (bf16 mode), by block parity
     int64_t dh[2], dqkv[2]; // by block parity: read by the weight-gradient kernels of the block
     int64_t dn, dO, delta;
@@ -150,6 +150,7 @@ static Layout make_layout(const rev_cfg& c, bool compact) {
     if (c.mode == REV_MODE_BF16) {
         L.cot2b[0] = take(M * D * es);
         L.cot2b[1] = take(M * D * es);
+        L.cot2b[2] = compact ? 0 : take(M * D * es);
         L.gy1b[0] = take(M * D * es);
         L.gy1b[1] = compact ? L.gy1b[0] : take(M * D * es);
     }
@@ -242,6 +243,7 @@ struct Runner {
         : c(cfg), L(make_layout(cfg, compact)), ws((char*)w), params((const T*)p), dparams(dp), solo(compact) {
         M = c.batch * c.seq_len; D = c.d_model; Dm = c.d_mlp; H = c.n_heads; dh = D / H; B = c.batch; Tn = c.seq_len;
     }
+    int c2b(int i) const { return solo ? i & 1 : i % 3; }   // compact layout: two copies in turn
     Epi epi0() const { Epi e = {}; e.solo = solo; return e; }
     template <typename U> U* at(int64_t off) const { return reinterpret_cast<U*>(ws + off); }
     const T* P(int blk, int t) const { return params + (int64_t)blk * block_params(c) + tensor_offset(c, t); }
@@ -309,11 +311,11 @@ struct Runner {
     // y1: first stream of the block's outputs, x2: second stream of its inputs.
     // d1, d2: incoming cotangents (float32); d2b: act-typed copy of d2.
     // o1, o2: outgoing cotangents; o2b: act-typed copy of o2 (nullable).
-    // ev (nullable): 3 events recorded on s when dh / gY1 / dqkv are complete.
+    // done_dqkv (nullable): recorded on s when dh, gY1 and dqkv are complete.
     T* gy1_act(int blk, float* o1) const { return kBf16 ? at<T>(L.gy1b[blk & 1]) : reinterpret_cast<T*>(o1); }
 
     int grad_d(hipStream_t s, int blk, const float* y1, const float* x2, const float* d1, const float* d2,
-               const T* d2b, float* o1, float* o2, T* o2b, const hipEvent_t* ev) {
+               const T* d2b, float* o1, float* o2, T* o2b, hipEvent_t done_dqkv) {
         Slot sl = slot(blk);
         T* dhb = at<T>(L.dh[blk & 1]);
         T* dqkv = at<T>(L.dqkv[blk & 1]);
@@ -330,7 +332,6 @@ struct Runner {
         Epi e = epi0(); e.kind = EPI_GELU_BWD; e.out = dhb; e.aux = sl.h; e.ldo = Dm;
         e.colsum = pcol0;
         RC(dgrad(s, blk, T_WFC2, d2b, D, Dm, e));
-        if (ev) REV_HIP(hipEventRecord(ev[0], s));
         segs[nseg++] = {pcol0, G(blk, T_BFC1), nullptr, (int64_t)Dm, (int64_t)Dm, (int64_t)Dm,
                         kBf16 ? gemm_colsum_strips(M, Dm) : gemm_f32_colsum_strips(M, Dm)};
         Epi p = epi0(); p.kind = EPI_PLAIN; p.out = dn; p.ldo = D;
@@ -338,12 +339,11 @@ struct Runner {
         // gY1 = dY1 + LN2bwd(dn); its column sums are the bias gradient of the projection
         RC((ln_backward<T, T>(s, dn, y1, sl.st2, P(blk, T_LN2G), d1, o1, kBf16 ? gy1b : nullptr,
                               G(blk, T_LN2G), G(blk, T_BPROJ), at<float>(L.part_ln[0]), M, D, &segs[nseg++])));
-        if (ev) REV_HIP(hipEventRecord(ev[1], s));
         // ---- F branch
         Epi q = epi0(); q.kind = EPI_PLAIN; q.out = dO; q.ldo = D;
         RC(dgrad(s, blk, T_WPROJ, gy1b, D, D, q));
         RC((attention_backward<T>(s, sl.qkv, sl.o, dO, sl.lse, dqkv, at<float>(L.delta), B, Tn, H, dh, key_len, solo)));
-        if (ev) REV_HIP(hipEventRecord(ev[2], s));
+        if (done_dqkv) REV_HIP(hipEventRecord(done_dqkv, s));
         Epi r = epi0(); r.kind = EPI_PLAIN; r.out = dn; r.ldo = D;
         RC(dgrad(s, blk, T_WQKV, dqkv, 3 * D, D, r));
         // (bf16: the weight-gradient kernel, which reads dqkv anyway, sums its columns)
@@ -356,14 +356,11 @@ struct Runner {
         return reduce_multi(s, segs, nseg);
     }
 
-    // ev (nullable): events to wait for on s before the kernels that read dY2 copy / dh / gY1 / dqkv
-    // (4 events); done_w2 (nullable) is recorded after the fc2 weight gradient.
-    int grad_w(hipStream_t s, int blk, const T* d2b, float* o1, const hipEvent_t* ev, hipEvent_t done_w2) {
+    int grad_w(hipStream_t s, int blk, const T* d2b, float* o1) {
         Slot sl = slot(blk);
         T* dhb = at<T>(L.dh[blk & 1]);
         T* dqkv = at<T>(L.dqkv[blk & 1]);
         T* gy1b = gy1_act(blk, o1);
-        if (ev) for (int k = 0; k < 4; ++k) REV_HIP(hipStreamWaitEvent(s, ev[k], 0));
         if constexpr (kBf16) {
             // all four in one launch: together their tiles fill the device without cutting the token range (or with
             // fewer cuts), which saves the float32 pieces and most of their reduction
@@ -374,18 +371,20 @@ struct Runner {
             RedSeg segs[RED_MAX_SEGS];
             int nseg = 0;
             RC(gemm_wgrad_bf16_group(s, items, 4, M, at<float>(L.part_wg), L.part_wg_elems, segs, &nseg));
-            if (done_w2) REV_HIP(hipEventRecord(done_w2, s));
             return reduce_multi(s, segs, nseg);
         }
         if constexpr (!kBf16) {
             const WgradF32Item items[4] = {{d2b, D, sl.a, Dm, D, Dm, G(blk, T_WFC2)}, {dhb, Dm, sl.n2, D, Dm, D, G(blk, T_WFC1)},
                                            {gy1b, D, sl.o, D, D, D, G(blk, T_WPROJ)},
                                            {dqkv, 3 * D, sl.n1, D, 3 * D, D, G(blk, T_WQKV)}};
-            RC(gemm_wgrad_f32_group(s, items, 4, M));
-            if (done_w2) REV_HIP(hipEventRecord(done_w2, s));
-            return REV_OK;
+            return gemm_wgrad_f32_group(s, items, 4, M);
         }
     }
+
+    // Two streams cost the host three events and three waits per block.  A block whose kernels are bound by launch latency
+    // gains nothing that pays for them: 64 tokens, D = 64 (7 MFLOP per block forward): 4 blocks 254 us on one stream, 351 on
+    // two; 197 tokens, D = 768 (2.9 GFLOP): two streams are faster.  Same kernels in the same order, so the same results.
+    bool one_stream_is_faster() const { return 2.0 * M * D * (4.0 * D + 2.0 * Dm) + 4.0 * M * (double)Tn * D < 3e8; }
 
     // residual level `lvl` (0..N): stream s1/s2 pointers
     struct Ptrs { const float* in1; const float* in2; float* out1; float* out2; };
@@ -400,24 +399,25 @@ struct Runner {
     // PaReprop, stream by stream (block indices 1-based, N at the top):
     //   sr:  R_N | R_{N-1}  W_N | R_{N-2}  W_{N-1} | ...      (W_i = grad_w of block i)
     //   sv:  D_N | D_{N-1}      | D_{N-2}          | ...      (D_i = grad_d of block i)
-    // Orderings across the streams (events):
-    //   D_i  after R_i                      (activations of block i exist)
-    //   D_i  after W_{i+2}                  (dh/dqkv/gY1 buffers of the same parity are free again)
-    //   D_i  after the fc2 weight gradient of W_{i+1}   (it reads the dY2 copy that D_i's last kernel rewrites)
+    // Orderings across the streams (three events and three waits per block: each costs the host about as much as a launch):
+    //   D_i  after R_i                      (activations of block i exist; W_{i+2} precedes R_i on sr, so the dh/dqkv/gY1
+    //                                        buffers of the same parity and the dY2 copy of W_{i+2} are free again)
     //   R_i  after D_{i+2}                  (slot i mod 2 and ring level i+2 are free; W_{i+2} precedes R_i on sr)
-    //   W_i after the kernels of D_i that produce its cotangent operands (one launch for the four GEMMs)
-    // and sv finally waits for W_1, so everything is ordered before later work on sv.
+    //   W_i  after the attention backward of D_i, the last of its kernels that produce an operand of W_i
+    // and sv finally waits for W_1, so everything is ordered before later work on sv.  The dY2 copies rotate over three
+    // buffers, so that D_i does not have to wait for W_{i+1}, which reads the copy before the last; in float32 mode W reads
+    // the two alternating cotangent levels themselves, and D_i does wait.
     int backward(int schedule, const float* Y1, const float* Y2, const float* dY1, const float* dY2,
                  float* dX1, float* dX2, float* X1o, float* X2o, hipStream_t sv, hipStream_t sr) {
         const int N = c.n_blocks;
         const bool doR = schedule != 3, doV = schedule != 2;
-        // per block: 0 R done, 1 D done, 2 W done, 3 dY2 copy ready (= D start), 4 dh, 5 gY1, 6 dqkv, 7 fc2 wgrad done
-        constexpr int EPB = 8;
+        enum { E_R = 0, E_D, E_DQKV, E_W, EPB };
         EventLease lease;
         std::vector<hipEvent_t>& ev = lease.ev;
         auto E = [&](int i, int k) { return ev[(i - 1) * EPB + k]; };
-        if (schedule == 1) {
-            RC(lease.take(EPB * N + 1));
+        const bool two = schedule == 1 && !one_stream_is_faster();
+        if (two) {
+            RC(lease.take(EPB * N + 2));
             REV_HIP(hipEventRecord(ev[EPB * N], sv));            // fork
             REV_HIP(hipStreamWaitEvent(sr, ev[EPB * N], 0));
         } else {
@@ -429,7 +429,7 @@ struct Runner {
             // theirs from the LayerNorm-backward kernel that produces their dY2)
             RC(colsum<float>(sv, dY2, D, M, D, G(N - 1, T_BFC2), at<float>(L.part_col[1])));
             if constexpr (kBf16) {
-                T* b = at<T>(L.cot2b[N & 1]);
+                T* b = at<T>(L.cot2b[c2b(N)]);
                 RC(convert_f32_to_bf16(sv, dY2, b, (int64_t)M * D));
                 top2b = b;
             } else {
@@ -442,49 +442,47 @@ struct Runner {
             return recompute(sr, i - 1, y1, y2, res(i - 1, 0, X1o, X2o), res(i - 1, 1, X1o, X2o));
         };
         auto d2b_of = [&](int i) -> const T* {
-            if constexpr (kBf16) return (i == N) ? top2b : at<T>(L.cot2b[i & 1]);
+            if constexpr (kBf16) return (i == N) ? top2b : at<T>(L.cot2b[c2b(i)]);
             else return reinterpret_cast<const T*>((i == N) ? dY2 : at<float>(L.cot[i & 1][1]));
         };
         auto o1_of = [&](int i) -> float* { return (i == 1) ? dX1 : at<float>(L.cot[(i - 1) & 1][0]); };
-        auto run_D = [&](int i, const hipEvent_t* evs) -> int {
+        auto run_D = [&](int i, hipEvent_t done_dqkv) -> int {
             const float* y1 = (i == N) ? Y1 : res(i, 0, X1o, X2o);
             const float* x2 = res(i - 1, 1, X1o, X2o);
             const float* d1 = (i == N) ? dY1 : at<float>(L.cot[i & 1][0]);
             const float* d2 = (i == N) ? dY2 : at<float>(L.cot[i & 1][1]);
             float* o2 = (i == 1) ? dX2 : at<float>(L.cot[(i - 1) & 1][1]);
             T* o2b = nullptr;
-            if constexpr (kBf16) o2b = (i == 1) ? nullptr : at<T>(L.cot2b[(i - 1) & 1]);
-            return grad_d(sv, i - 1, y1, x2, d1, d2, d2b_of(i), o1_of(i), o2, o2b, evs);
+            if constexpr (kBf16) o2b = (i == 1) ? nullptr : at<T>(L.cot2b[c2b(i - 1)]);
+            return grad_d(sv, i - 1, y1, x2, d1, d2, d2b_of(i), o1_of(i), o2, o2b, done_dqkv);
         };
-        if (schedule == 1) {
+        if (two) {
             RC(run_R(N));
-            REV_HIP(hipEventRecord(E(N, 0), sr));
+            REV_HIP(hipEventRecord(E(N, E_R), sr));
             for (int i = N; i >= 1; --i) {
                 // ---- D_i on the gradient stream
-                REV_HIP(hipStreamWaitEvent(sv, E(i, 0), 0));
-                if (i + 2 <= N) REV_HIP(hipStreamWaitEvent(sv, E(i + 2, 2), 0));
-                if (i + 1 <= N) REV_HIP(hipStreamWaitEvent(sv, E(i + 1, 7), 0));
-                REV_HIP(hipEventRecord(E(i, 3), sv));
-                const hipEvent_t dev[3] = {E(i, 4), E(i, 5), E(i, 6)};
-                RC(run_D(i, dev));
-                REV_HIP(hipEventRecord(E(i, 1), sv));
+                REV_HIP(hipStreamWaitEvent(sv, E(i, E_R), 0));
+                if (!kBf16 && i + 1 <= N) REV_HIP(hipStreamWaitEvent(sv, E(i + 1, E_W), 0));
+                RC(run_D(i, E(i, E_DQKV)));
+                if (i > 2) REV_HIP(hipEventRecord(E(i, E_D), sv));
                 // ---- R_{i-1}, then W_i, on the recompute stream
                 if (i - 1 >= 1) {
-                    if (i + 1 <= N) REV_HIP(hipStreamWaitEvent(sr, E(i + 1, 1), 0));
+                    if (i + 1 <= N) REV_HIP(hipStreamWaitEvent(sr, E(i + 1, E_D), 0));
                     RC(run_R(i - 1));
-                    REV_HIP(hipEventRecord(E(i - 1, 0), sr));
+                    REV_HIP(hipEventRecord(E(i - 1, E_R), sr));
                 }
-                const hipEvent_t wev[4] = {E(i, 3), E(i, 4), E(i, 5), E(i, 6)};
-                RC(grad_w(sr, i - 1, d2b_of(i), o1_of(i), wev, E(i, 7)));
-                REV_HIP(hipEventRecord(E(i, 2), sr));
+                REV_HIP(hipStreamWaitEvent(sr, E(i, E_DQKV), 0));
+                RC(grad_w(sr, i - 1, d2b_of(i), o1_of(i)));
+                if (!kBf16 && i > 1) REV_HIP(hipEventRecord(E(i, E_W), sr));
             }
-            REV_HIP(hipStreamWaitEvent(sv, E(1, 2), 0));          // join (W_2 precedes W_1 on sr)
+            REV_HIP(hipEventRecord(ev[EPB * N + 1], sr));         // join
+            REV_HIP(hipStreamWaitEvent(sv, ev[EPB * N + 1], 0));
         } else {
             for (int i = N; i >= 1; --i) {
                 if (doR) RC(run_R(i));
                 if (doV) {
                     RC(run_D(i, nullptr));
-                    RC(grad_w(sv, i - 1, d2b_of(i), o1_of(i), nullptr, nullptr));
+                    RC(grad_w(sv, i - 1, d2b_of(i), o1_of(i)));
                 }
             }
         }
