@@ -150,7 +150,7 @@ static Layout make_layout(const rev_cfg& c, bool compact) {
     if (c.mode == REV_MODE_BF16) {
         L.cot2b[0] = take(M * D * es);
         L.cot2b[1] = take(M * D * es);
-        L.cot2b[2] = compact ? 0 : take(M * D * es);
+        L.cot2b[2] = take(M * D * es);
         L.gy1b[0] = take(M * D * es);
         L.gy1b[1] = compact ? L.gy1b[0] : take(M * D * es);
     }
@@ -159,7 +159,7 @@ static Layout make_layout(const rev_cfg& c, bool compact) {
         L.dqkv[r] = (compact && r) ? L.dqkv[0] : take(M * 3 * D * es);
     }
     L.dn = take(M * D * es);
-    L.dO = take(M * D * es);
+    L.dO = L.dn;           // dn is consumed by LN2's backward before dO is written, and dO by attention's before dn is again
     L.delta = take((int64_t)c.batch * c.n_heads * c.seq_len * 4);
     L.part_ln[0] = take(ln_bwd_partial_elems((int)M, (int)D) * 4);
     L.part_ln[1] = take(ln_bwd_partial_elems((int)M, (int)D) * 4);
@@ -243,7 +243,6 @@ struct Runner {
         : c(cfg), L(make_layout(cfg, compact)), ws((char*)w), params((const T*)p), dparams(dp), solo(compact) {
         M = c.batch * c.seq_len; D = c.d_model; Dm = c.d_mlp; H = c.n_heads; dh = D / H; B = c.batch; Tn = c.seq_len;
     }
-    int c2b(int i) const { return solo ? i & 1 : i % 3; }   // compact layout: two copies in turn
     Epi epi0() const { Epi e = {}; e.solo = solo; return e; }
     template <typename U> U* at(int64_t off) const { return reinterpret_cast<U*>(ws + off); }
     const T* P(int blk, int t) const { return params + (int64_t)blk * block_params(c) + tensor_offset(c, t); }
@@ -429,7 +428,7 @@ struct Runner {
             // theirs from the LayerNorm-backward kernel that produces their dY2)
             RC(colsum<float>(sv, dY2, D, M, D, G(N - 1, T_BFC2), at<float>(L.part_col[1])));
             if constexpr (kBf16) {
-                T* b = at<T>(L.cot2b[c2b(N)]);
+                T* b = at<T>(L.cot2b[N % 3]);
                 RC(convert_f32_to_bf16(sv, dY2, b, (int64_t)M * D));
                 top2b = b;
             } else {
@@ -442,7 +441,7 @@ struct Runner {
             return recompute(sr, i - 1, y1, y2, res(i - 1, 0, X1o, X2o), res(i - 1, 1, X1o, X2o));
         };
         auto d2b_of = [&](int i) -> const T* {
-            if constexpr (kBf16) return (i == N) ? top2b : at<T>(L.cot2b[c2b(i)]);
+            if constexpr (kBf16) return (i == N) ? top2b : at<T>(L.cot2b[i % 3]);
             else return reinterpret_cast<const T*>((i == N) ? dY2 : at<float>(L.cot[i & 1][1]));
         };
         auto o1_of = [&](int i) -> float* { return (i == 1) ? dX1 : at<float>(L.cot[(i - 1) & 1][0]); };
@@ -453,7 +452,7 @@ struct Runner {
             const float* d2 = (i == N) ? dY2 : at<float>(L.cot[i & 1][1]);
             float* o2 = (i == 1) ? dX2 : at<float>(L.cot[(i - 1) & 1][1]);
             T* o2b = nullptr;
-            if constexpr (kBf16) o2b = (i == 1) ? nullptr : at<T>(L.cot2b[c2b(i - 1)]);
+            if constexpr (kBf16) o2b = (i == 1) ? nullptr : at<T>(L.cot2b[(i - 1) % 3]);
             return grad_d(sv, i - 1, y1, x2, d1, d2, d2b_of(i), o1_of(i), o2, o2b, done_dqkv);
         };
         if (two) {
