@@ -86,8 +86,8 @@ static int check_cfg(const rev_cfg* c) {
     }
     if (dh > 128) { set_error("cfg: head_dim must be <= 128"); return REV_EINVAL; }
     if (c->d_model > 8192 || c->d_mlp > 32768) { set_error("cfg: d_model <= 8192 and d_mlp <= 32768"); return REV_EINVAL; }
-    // launch-grid limits: the attention kernels put (sample, head) pairs on the grid's y axis and the plain-ALU
-    // GEMM 64-row strips of tokens; y holds at most 65535
+    // launch-grid limits: the attention kernels put (sample, head) pairs on the grid's y axis, which holds at most 65535;
+    // the token limit keeps tile counts and row offsets of every launch within 32 bits
     if ((int64_t)c->batch * c->seq_len > (int64_t)65535 * 64) {
         set_error("cfg: batch*seq_len must be <= 4194240"); return REV_EINVAL;
     }
@@ -415,10 +415,15 @@ struct Runner {
         std::vector<hipEvent_t>& ev = lease.ev;
         auto E = [&](int i, int k) { return ev[(i - 1) * EPB + k]; };
         const bool two = schedule == 1 && !one_stream_is_faster();
-        if (two) {
-            RC(lease.take(EPB * N + 2));
-            REV_HIP(hipEventRecord(ev[EPB * N], sv));            // fork
-            REV_HIP(hipStreamWaitEvent(sr, ev[EPB * N], 0));
+        const int per = two ? EPB * N : 0;
+        const hipStream_t sv_caller = sv;
+        if (schedule == 1) {
+            RC(lease.take(per + 2));
+            REV_HIP(hipEventRecord(ev[per], sv));                 // fork
+            REV_HIP(hipStreamWaitEvent(sr, ev[per], 0));
+            // One stream: it is the recompute stream, so that the call keeps its order with the caller's work on both (254 us
+            // becomes 268 on the four blocks above, the price of the fork and the join).
+            if (!two) sv = sr;
         } else {
             sr = sv;
         }
@@ -474,8 +479,6 @@ struct Runner {
                 RC(grad_w(sr, i - 1, d2b_of(i), o1_of(i)));
                 if (!kBf16 && i > 1) REV_HIP(hipEventRecord(E(i, E_W), sr));
             }
-            REV_HIP(hipEventRecord(ev[EPB * N + 1], sr));         // join
-            REV_HIP(hipStreamWaitEvent(sv, ev[EPB * N + 1], 0));
         } else {
             for (int i = N; i >= 1; --i) {
                 if (doR) RC(run_R(i));
@@ -484,6 +487,10 @@ struct Runner {
                     RC(grad_w(sv, i - 1, d2b_of(i), o1_of(i)));
                 }
             }
+        }
+        if (schedule == 1) {
+            REV_HIP(hipEventRecord(ev[per + 1], sr));             // join
+            REV_HIP(hipStreamWaitEvent(sv_caller, ev[per + 1], 0));
         }
         return REV_OK;
     }

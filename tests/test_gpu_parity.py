@@ -303,3 +303,33 @@ def test_two_host_threads_issue_pareprop_calls_concurrently():
         for r in j["results"]:
             for k, v in j["alone"].items():
                 assert torch.equal(r[k], v), k
+
+
+@pytest.mark.parametrize("name", ["tiny", "vit_s_slice"])
+def test_pareprop_keeps_its_order_with_work_on_the_recompute_stream(name):
+    """The outputs Y1, Y2 are produced late on the recompute stream, and the recomputed inputs are read there right after the
+    call; blocks small enough to be issued on one stream keep the same order as larger ones."""
+    cfg = synth.CONFIGS["tiny"] if name == "tiny" else dict(SHAPES[name], mode="bf16")
+    flat, _, x, dy1, dy2 = make_case(cfg, seed=31)
+    c = gpu_cfg(cfg)
+    params = to_dev(flat, B.param_dtype(c))
+    X, dY1, dY2 = to_dev(x), to_dev(dy1), to_dev(dy2)
+    Y1, Y2 = B.rev_stack_forward(c, params, X, X)
+    ref = B.rev_stack_backward_reprop(c, params, Y1, Y2, dY1, dY2, want_inputs=True)
+    late1, late2 = torch.zeros_like(Y1), torch.zeros_like(Y2)
+    big = torch.ones(4096, 4096, device="cuda") / 4096
+    ws, sr = B.alloc_workspace(c), torch.cuda.Stream()
+    out = {k: torch.zeros_like(v) for k, v in ref.items() if v is not None}
+    torch.cuda.synchronize()
+    with torch.cuda.stream(sr):
+        for _ in range(10):
+            big = big @ big
+        late1.copy_(Y1)
+        late2.copy_(Y2)
+    B.rev_stack_backward_pareprop(c, params, late1, late2, dY1, dY2, sr, workspace=ws, want_inputs=True, out=out)
+    with torch.cuda.stream(sr):
+        seen = out["X1"].clone(), out["X2"].clone()
+    torch.cuda.synchronize()
+    assert torch.equal(seen[0], ref["X1"]) and torch.equal(seen[1], ref["X2"])
+    for k, v in out.items():
+        assert torch.equal(v, ref[k]), k
