@@ -40,14 +40,19 @@ __device__ __forceinline__ f32x16_t rows_product(const float (&a)[DHP / 2], cons
     for (int k = 0; k < DHP / 2; ++k) acc = mfma_f32(a[k], b[k], acc);
     return acc;
 }
-// acc[d, owned] += sum over the tile's rows r of X[r0 + r][32*dt + d] * p[r, owned]; p in accumulator order
+// acc[d, owned] += sum over the tile's rows r of X[r0 + r][32*dt + d] * p[r, owned]; p in accumulator order.  Rows from `rows`
+// on count as zeros whatever they hold: their p is 0, but 0 times an infinity or a NaN would not be.
 template <typename T>
 __device__ __forceinline__ f32x16_t cols_product(const T* __restrict__ base, int64_t ld, int r0, int rows, int dh, int dt, int lane,
                                                  const float (&p)[16], f32x16_t acc) {
     const int c = min(dt * 32 + (lane & 31), dh - 1), g = lane >> 5;
     float x[16];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) x[v] = to_f(base[(int64_t)min(r0 + 8 * (v >> 2) + 4 * g + (v & 3), rows - 1) * ld + c]);
+    for (int v = 0; v < 16; ++v) {
+        const int r = r0 + 8 * (v >> 2) + 4 * g + (v & 3);
+        const float y = to_f(base[(int64_t)min(r, rows - 1) * ld + c]);
+        x[v] = r < rows ? y : 0.f;
+    }
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc = mfma_f32(x[v], p[v], acc);
     return acc;
@@ -114,11 +119,11 @@ __global__ __launch_bounds__(AF_NW * 64) void attn_fwd_f32(const float* __restri
             mloc = fmaxf(mloc, p[v]);
         }
         mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
-        const float mn = fmaxf(m, mloc), corr = __expf(m - mn);
+        const float mn = fmaxf(m, mloc), ms = mn == -INFINITY ? 0.f : mn, corr = __expf(m - ms);    // (no finite score yet)
         float lsum = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            p[v] = __expf(p[v] - mn);
+            p[v] = __expf(p[v] - ms);
             lsum += p[v];
         }
         l = l * corr + lsum + __shfl_xor(lsum, 32, 64);
@@ -127,7 +132,7 @@ __global__ __launch_bounds__(AF_NW * 64) void attn_fwd_f32(const float* __restri
         for (int dt = 0; dt < DT; ++dt) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[dt][v] *= corr;
-            acc[dt] = cols_product(base + 2 * D, ld, k0, T, dh, dt, lane, p, acc[dt]);
+            acc[dt] = cols_product(base + 2 * D, ld, k0, Tk, dh, dt, lane, p, acc[dt]);
         }
     }
     if (g == 0) { sm[wave][lane] = m; sl[wave][lane] = l; }
@@ -204,7 +209,7 @@ __global__ __launch_bounds__(AF_NW * 64) void attn_bwd_f32(const T* __restrict__
                 ds[v] = key < Tk ? __expf(s[v] * scale - L) * (dp[v] - dl) * scale : 0.f;
             }
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) acc[dt] = cols_product(base + D, ld, k0, Tn, dh, dt, lane, ds, acc[dt]);
+            for (int dt = 0; dt < DT; ++dt) acc[dt] = cols_product(base + D, ld, k0, Tk, dh, dt, lane, ds, acc[dt]);
         }
     } else {
         float bk[DHP / 2], bv[DHP / 2];
@@ -221,7 +226,8 @@ __global__ __launch_bounds__(AF_NW * 64) void attn_bwd_f32(const T* __restrict__
             for (int v = 0; v < 16; ++v) {
                 const int r = 8 * (v >> 2) + 4 * g + (v & 3), i = t0 + r;
                 p[v] = i < Tn ? __expf(s[v] * scale - lrow[min(i, Tn - 1)]) : 0.f;
-                ds[v] = p[v] * (dp[v] - __shfl(dl, r, 64)) * scale;
+                const float d = __shfl(dl, r, 64);
+                ds[v] = i < Tn ? p[v] * (dp[v] - d) * scale : 0.f;
             }
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {

@@ -119,3 +119,39 @@ def test_masked_calls_reject_a_missing_or_misshapen_mask():
                                           ctypes.c_void_p(Y.data_ptr()), ctypes.c_void_p(Y.data_ptr()),
                                           ctypes.c_void_p(ws.data_ptr()), ws.numel(), None)
     assert rc == -1 and "key_len" in B.rev_last_error()
+
+
+# heads of every width class of the float32 kernels; lengths inside, at and just beyond a 32-key tile
+NON_FINITE = [
+    (dict(n_blocks=2, d_model=96, n_heads=3, d_mlp=128, seq_len=49, batch=4), [1, 31, 32, 33]),
+    (dict(n_blocks=2, d_model=128, n_heads=2, d_mlp=256, seq_len=197, batch=3), [65, 130, 196]),
+    (dict(n_blocks=1, d_model=160, n_heads=2, d_mlp=160, seq_len=300, batch=2), [290, 129]),
+    (dict(n_blocks=1, d_model=208, n_heads=2, d_mlp=64, seq_len=70, batch=2), [69, 3]),
+]
+
+
+def _non_finite_padding(shape, lens, mode):
+    """Padded rows may hold anything (uninitialised memory): the outputs at valid positions are, bit for bit, those of a
+    call whose padded rows are zeros."""
+    cfg = dict(shape, mode=mode)
+    print(f"[case] non-finite padding {cfg} key_len={lens}", flush=True)
+    flat, _, x, _, _ = make_case(cfg, seed=6)
+    c = gpu_cfg(cfg)
+    params = to_dev(flat, B.param_dtype(c))
+    klen = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    valid = torch.arange(cfg["seq_len"], device="cuda")[None, :] < klen[:, None]
+    X1, X2 = to_dev(x), to_dev(x[:, ::-1].copy())
+    want = B.rev_stack_forward_masked(c, params, X1 * valid[..., None], X2 * valid[..., None], klen)
+    for fill in (float("nan"), float("inf")):
+        P1, P2 = X1.clone(), X2.clone()
+        P1[~valid] = fill
+        P2[~valid] = fill
+        got = B.rev_stack_forward_masked(c, params, P1, P2, klen)
+        torch.cuda.synchronize()
+        for g, w in zip(got, want):
+            assert torch.equal(g[valid], w[valid]), fill
+
+
+@pytest.mark.parametrize("shape,lens", NON_FINITE)
+def test_non_finite_padding_does_not_reach_valid_positions_fp32(shape, lens):
+    _non_finite_padding(shape, lens, "fp32")
