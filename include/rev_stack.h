@@ -49,6 +49,11 @@
  * residual streams, cotangent streams, LayerNorm statistics, softmax
  * statistics and all parameter gradients stay float32.
  *
+ * Reproducibility.  Every sum has a fixed order.  The outputs, reconstructed
+ * inputs and input gradients of a sample have the same bits in a batch of any
+ * size and under every schedule; a parameter gradient, which sums over all
+ * tokens, has the same bits in every call with the same sizes.
+ *
  * Limits (anything else returns REV_EINVAL before any work is enqueued):
  * all six sizes positive; d_model % n_heads == 0; d_model % 8 == 0;
  * d_mlp % 8 == 0; head_dim % 8 == 0 and head_dim <= 128; d_model <= 8192;

@@ -141,15 +141,14 @@ struct Epi {
     float sign;
     int64_t ldo;
     float* colsum;      // EPI_GELU_BWD, matrix-core path: per-row-strip column sums of the output,
-                        // [gemm_colsum_strips(M, N)][N] float32 (nullable)
+                        // [gemm_colsum_strips(M, N, K)][N] float32 (nullable)
     bool solo;          // the launch runs alone on the device (one stream): the tile shape may be chosen
                         // to fill the chip by itself; results do not depend on it
 };
-// rows of column-sum partials (strips of 32 or 64 token rows) a bf16 GEMM with an [M, N] output writes
-int gemm_colsum_strips(int M, int N);
-// tile of a bf16 GEMM launch; _K2 / _K3: the workgroup's wavefronts form that many groups that share the contraction;
-// 32x32 and 64x64: every wavefront takes its own part of it
-enum GemmShape { GS_32x32, GS_64x64, GS_64x128_K3, GS_128x128_K2, GS_128x128, GS_160x128 };
+// rows of column-sum partials (strips of 32 or 64 token rows) that a bf16 GEMM writes
+int gemm_colsum_strips(int M, int N, int K);
+// tile of a bf16 GEMM launch: gemm_ring.hip (the first three) and gemm_nt_dma.hip
+enum GemmShape { GS_32x32, GS_64x64, GS_64x128_RING, GS_64x128, GS_128x128, GS_160x128 };
 
 // C[M,N] (+epilogue) = A[M,K] * B[N,K]^T.  A, B row-major with leading dims lda, ldb.
 // fp32 flavour: A, B float.  bf16 flavour: A, B bf16.

@@ -1,7 +1,7 @@
 // bf16 matrix-core GEMM entry points.
 //
-//  gemm_nt_bf16 / gemm_nn_bf16   C = A * B^T  /  C = A * B  with fused epilogue: picks the tile and, for launches that do
-//            not fill the chip, the split of the contraction (gemm_nt_dma.hip, gemm_ksplit.hip).
+//  gemm_nt_bf16 / gemm_nn_bf16   C = A * B^T  /  C = A * B  with fused epilogue: picks the tile (gemm_nt_dma.hip,
+//            gemm_ring.hip).  No choice changes the order of an output's sums.
 //  gemm_wgrad_bf16_group         dW[N,K] = G[M,N]^T * A[M,K], up to four in a launch: picks the tile (gemm_wgrad_dma.hip,
 //            gemm_wgrad_big.hip) and the number of token ranges; the pieces of the ranges are summed afterwards in
 //            range order, so results do not depend on scheduling.
@@ -31,48 +31,47 @@ static bool tall_tiles_pay(int M, int N) {
     return c160 < 0.97 * c128;
 }
 
-// A launch that cannot give every CU a workgroup is bound by the serial chain of one tile (K stages) and by the rate at
-// which one CU takes in operands; so the smallest tile is taken whose workgroups all run at once (32x32: two per CU,
-// the others one), each splitting K among its wavefronts.  Measured at 49 ... 7289 rows, N and K from 384 to 3072: every
-// choice is the best of the seven shapes or within 10 % of it.  From more than 256 tiles of 128x128 on, whole-K tiles fill the chip.
-// These lines depend on M and N only, never on what else runs: the split of K fixes the order of the sums.  Training
-// batches (more than 3072 rows, where splitting would still gain up to 15 % on narrow outputs) always sum K in one
-// order, so that a sample's results do not depend on how many others are in its batch.
-constexpr int SPLIT_MAX_ROWS = 3072;
-static GemmShape split_shape(int M, int N) {
-    if (M > SPLIT_MAX_ROWS) return GS_128x128;
-    if (tiles_of(M, N, 32, 32) <= 512) return GS_32x32;
-    if (tiles_of(M, N, 64, 64) <= 256) return GS_64x64;
-    if (tiles_of(M, N, 64, 128) <= 256) return GS_64x128_K3;
-    if (tiles_of(M, N, 128, 128) <= 256) return GS_128x128_K2;
+// A launch that cannot give every CU a workgroup is bound by the serial chain of one tile and by the rate at
+// which one CU takes in operands; so it takes the smallest tile whose workgroups all run at once.  All tiles sum the products
+// of an output in the same order, so a sample's results do not depend on how many others are in its batch, and the lines
+// below are free to follow the clock.  Measured at 16 ... 7289 rows, N and K from 384 to 5120 (us, activation x weight):
+//   32x32 up to 288 tiles (a little over one per CU).  197 rows, N = K = 768 (168 tiles): 4.4, 64x64 5.5, 64x128 8.3; K = 3072:
+//     9.1, 12.3, 28.  At 456 tiles 5.9 against 6.1, and 6.6 against 5.8 for weights stored K x N.
+//   64x64 up to 384 tiles, and up to the 512 that run at once for short contractions.  1182 rows, N = 768, K = 3072 (228): 14.1,
+//     128x128 34.6.  2364 rows, N = K = 768 (444): 11.1, 64x128 11.7; K = 3072: 28.6 against 24.6.
+//   64x128 in the ring up to 256 tiles.  2364 rows, N = 768, K = 3072 (222): 24.6, the two-stage kernel 29.8.
+//   64x128 in two stages while 128x128 would leave CUs idle and the contraction is long enough to feel it.  2570 rows, N = 1280,
+//     K = 3840 (410): 39.8, 128x128 45.2.  At K = 768 the two are within 5 % of each other, either way.
+static GemmShape small_shape(int M, int N, int K) {
+    if (tiles_of(M, N, 32, 32) <= 288) return GS_32x32;
+    if (tiles_of(M, N, 64, 64) <= (K < 1536 ? 512 : 384)) return GS_64x64;
+    if (tiles_of(M, N, 64, 128) <= 256) return GS_64x128_RING;
+    if (tiles_of(M, N, 128, 128) <= 256 && K >= 1024) return GS_64x128;
     return GS_128x128;
 }
 // 160-row tiles (two wavefronts of 160x64) when they turn a short ragged second round of 128-row tiles into a single
 // round.  Only for launches that have the device to themselves: next to another stream's kernels that round is filled
 // anyway and the larger LDS footprint keeps the neighbour out (measured: sequential schedule faster, parallel schedule
-// 5 % slower).  Each output element sums the same products in the same order under both tiles, so the choice does
-// not change a bit of the result.  Not with fused column sums (their strips are 64 rows) and not with a short last
+// 5 % slower).  Not with fused column sums (their strips are 64 rows) and not with a short last
 // stage (the extra address registers would not fit next to 160 accumulators).
 static GemmShape pick_gemm_shape(int M, int N, int K, const Epi& epi) {
-    const GemmShape sh = split_shape(M, N);
+    const GemmShape sh = small_shape(M, N, K);
     if (sh == GS_128x128 && epi.solo && epi.colsum == nullptr && K % 64 == 0 && tall_tiles_pay(M, N)) return GS_160x128;
     return sh;
 }
 
-int gemm_colsum_strips(int M, int N) {
-    switch (split_shape(M, N)) {
+int gemm_colsum_strips(int M, int N, int K) {
+    switch (small_shape(M, N, K)) {
         case GS_32x32: return (M + 31) / 32;
-        case GS_64x64: return (M + 63) / 64;
-        case GS_64x128_K3: return (M + 63) / 64 * 2;      // 32-row strips
-        case GS_128x128_K2: return (M + 127) / 128 * 4;
+        case GS_64x64: case GS_64x128_RING: case GS_64x128: return (M + 63) / 64;
         default: return (M + 127) / 128 * 2;              // 64-row strips
     }
 }
 
 int gemm_bf16_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
                   int M, int N, int K, const Epi& epi, bool b_kmajor, GemmShape shape);
-int gemm_bf16_ksplit(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
-                     const Epi& epi, bool b_kmajor, int tile);
+int gemm_bf16_ring(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
+                   const Epi& epi, bool b_kmajor, GemmShape shape);
 
 static int gemm_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
                      const Epi& epi, bool b_kmajor) {
@@ -84,8 +83,7 @@ static int gemm_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, i
     }
     ProfScope ps(K_GEMM_NT, s, 2.0 * M * N * K);
     const GemmShape shape = pick_gemm_shape(M, N, K, epi);
-    if (shape == GS_32x32 || shape == GS_64x64)
-        return gemm_bf16_ksplit(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape == GS_32x32 ? 32 : 64);
+    if (shape == GS_32x32 || shape == GS_64x64 || shape == GS_64x128_RING) return gemm_bf16_ring(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
     return gemm_bf16_dma(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
 }
 

@@ -22,12 +22,8 @@
 //
 // Tile shapes: 128x128 with four wavefronts of 64x64 (two workgroups per CU, the general case); 160x128 with two
 // wavefronts of 160x64 (7 fragment reads per 10 products, one wavefront per SIMD), which a launch that
-// has the device to itself picks when 128-row tiles would leave a short, ragged last round of workgroups.  Launches
-// whose tiles do not fill the chip split the contraction inside the workgroup as well (KG groups of wavefronts, each
-// with its own stages, their partial tiles added in group order at the end): 128x128 by two groups, 64x128 by three.
-// The K stages of a tile are a serial chain of about 0.6 us each whatever the other CUs do, so with one workgroup per CU
-// the groups shorten it (M = 1576, N = 768, K = 3072: 28.4 -> 21.7 us; M = 3152: 33.9 -> 28.9 us), up to the
-// 60 GB/s or so at which a CU takes in operands.
+// has the device to itself picks when 128-row tiles would leave a short, ragged last round of workgroups; 64x128 with
+// two wavefronts of 64x64 for launches that would leave CUs without a workgroup otherwise.
 #include "gemm_epilogue.h"
 #include <type_traits>
 
@@ -36,11 +32,11 @@ namespace rev {
 constexpr int GD_NS = 2;                                 // stages in flight
 
 // BK: contraction depth of a stage (64: 128-byte rows; 32)
-template <int BM, int BN, int WM, int WN, int BK, int KG, int KIND, bool BKM, bool TAIL>
-__global__ __launch_bounds__(WM * WN * KG * 64) void gemm_nt_dma_kernel(const bf16* __restrict__ A, int64_t lda,
+template <int BM, int BN, int WM, int WN, int BK, int KIND, bool BKM, bool TAIL>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_nt_dma_kernel(const bf16* __restrict__ A, int64_t lda,
                                                                          const bf16* __restrict__ B, int64_t ldb,
                                                                          int M, int N, int K, Epi epi, int gn) {
-    constexpr int NW = WM * WN;                          // wavefronts of one contraction group
+    constexpr int NW = WM * WN;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int NS = GD_NS;
     static_assert(BK == 64 || (BK == 32 && !TAIL), "BK");
@@ -51,7 +47,6 @@ __global__ __launch_bounds__(WM * WN * KG * 64) void gemm_nt_dma_kernel(const bf
     // is BK rows of BN columns, kept as it lies in memory and read with the LDS transpose read
     static_assert(!BKM || BN == 128, "K-major B tiles have 256-byte rows");
     static_assert(TN == 2 && (TM == 2 || TM == 5), "64x64 or 160x64 per wavefront");
-    static_assert(KG == 1 || TM == 2, "contraction groups: 64x64 per wavefront");
     constexpr int A_BYTES = BM * ROWB, B_BYTES = BN * ROWB, STAGE = A_BYTES + B_BYTES;
     constexpr int IA = BM / RPI, IB = B_BYTES / 1024;    // wavefront-wide loads per stage
     constexpr int LPW = (IA + IB) / NW;                  // ... per wavefront
@@ -61,9 +56,7 @@ __global__ __launch_bounds__(WM * WN * KG * 64) void gemm_nt_dma_kernel(const bf
     const int tid = threadIdx.x, lane = tid & 63;
     // the wavefront index as a scalar: LDS destinations of the direct-to-LDS loads (M0) then need no
     // per-load lane read-out
-    const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kg = KG == 1 ? 0 : wave_all / NW;          // contraction group of this wavefront
-    const int wave = KG == 1 ? wave_all : wave_all - kg * NW;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int g = lane >> 5;
     // Tile order: column groups of `gn` n-tiles, each group walked over all m-tiles, n fastest inside
@@ -79,13 +72,8 @@ __global__ __launch_bounds__(WM * WN * KG * 64) void gemm_nt_dma_kernel(const bf
     // chunk c of row r is kept at position c ^ swz(r): 16 consecutive rows x one chunk -> 16 distinct bank groups
     auto swz = [](int r) { return BK == 64 ? ((r >> 1) & 7) : ((r >> 2) & 3); };
 
-    // stages of the contraction: all of them, or the share of this contraction group
-    const int nk_all = (K + BK - 1) / BK;
-    const int nk_max = KG == 1 ? nk_all : (nk_all + KG - 1) / KG;
-    const int kt0 = KG == 1 ? 0 : min(kg * nk_max, nk_all);
-    const int nk = KG == 1 ? nk_all : min(nk_max, nk_all - kt0);
+    const int nk = (K + BK - 1) / BK;
     const int kvalid = (K & (BK - 1)) >> 3;                  // TAIL: valid 16-byte chunks per row of the last stage
-    const bool has_tail = TAIL && kt0 + nk == nk_all && nk > 0;   // the last stage of this group is the short one
 
     // Sources of this wavefront's loads: a scalar base per operand (the tile's first row / column,
     // advanced along K per stage) plus a 32-bit per-lane byte offset inside the tile's panel, which
@@ -117,8 +105,8 @@ __global__ __launch_bounds__(WM * WN * KG * 64) void gemm_nt_dma_kernel(const bf
         dst[t] = (isA ? 0 : A_BYTES) + ii * 1024;
     }
     const int64_t bstep = BKM ? (int64_t)BK * ldb * 2 : (int64_t)BK * 2;       // B advance per stage, bytes
-    const char* a_base = reinterpret_cast<const char*>(A + (int64_t)m0 * lda) + (int64_t)kt0 * (BK * 2);
-    const char* b_base = reinterpret_cast<const char*>(BKM ? B + n0 : B + (int64_t)n0 * ldb) + kt0 * bstep;
+    const char* a_base = reinterpret_cast<const char*>(A + (int64_t)m0 * lda);
+    const char* b_base = reinterpret_cast<const char*>(BKM ? B + n0 : B + (int64_t)n0 * ldb);
 
     // Epilogue geometry (32-row panels leave through LDS in full rows) and, for the
     // epilogues that read a second operand (residual stream, saved pre-activation), that operand:
@@ -132,7 +120,7 @@ __global__ __launch_bounds__(WM * WN * KG * 64) void gemm_nt_dma_kernel(const bf
     const int n = n0 + wn * CW + 4 * c4;
     // (float32 residual rows cost 4 registers each: only the first panel's are held across the main
     // loop, the second panel's are requested when the epilogue starts)
-    constexpr int PRE = KG > 1 || BK == 32 ? 0 : (KIND == EPI_GELU_BWD ? 2 : (KIND == EPI_RESIDUAL ? 1 : 0));
+    constexpr int PRE = BK == 32 ? 0 : (KIND == EPI_GELU_BWD ? 2 : (KIND == EPI_RESIDUAL ? 1 : 0));
     f32x4_t opnd_pre[TM][NP];
     if (PRE > 0 && n < N) {
 #pragma unroll
@@ -150,18 +138,18 @@ __global__ __launch_bounds__(WM * WN * KG * 64) void gemm_nt_dma_kernel(const bf
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][i][v] = 0.f;
 
-    const unsigned lds0 = (unsigned)(uintptr_t)LDS_PTR(unsigned char, smem) + kg * (NS * STAGE);
-    // requests stage kt (of this group) in the scalar-base form
+    const unsigned lds0 = (unsigned)(uintptr_t)LDS_PTR(unsigned char, smem);
+    // requests stage kt in the scalar-base form
     auto issue = [&](int kt, int stage) {
         const char* ak = a_base + (int64_t)kt * (BK * 2);
         const char* bk = b_base + kt * bstep;
         const unsigned sbase = lds0 + stage * STAGE;
-        const bool short_stage = TAIL && has_tail && kt == nk - 1;
+        const bool short_stage = TAIL && kt == nk - 1;
 #pragma unroll
         for (int t = 0; t < LPW; ++t)
             dma16_sbase((NW * t) < IA ? ak : bk, TAIL && short_stage ? voff_t[TAIL ? t : 0] : voff[t], sbase + dst[t]);
     };
-    if (KG == 1 || nk > 0) issue(0, 0);
+    issue(0, 0);
 
     // fragment addressing: row r of a tile region, chunk (2*kk + g) swizzled
     const int fr = lane & 31;
@@ -196,13 +184,11 @@ __global__ __launch_bounds__(WM * WN * KG * 64) void gemm_nt_dma_kernel(const bf
         __builtin_amdgcn_s_barrier();
         if (TAIL && !has_next) {
             // A beyond K contributes exact zeros whatever B holds there
-            if (has_tail) {
-                unsigned char* at = smem + kg * (NS * STAGE) + SOFF;
-                const u32x4_t z = {0u, 0u, 0u, 0u};
-                for (int idx = tid - kg * (NW * 64); idx < BM * CPR; idx += NW * 64) {
-                    const int r = idx / CPR, pos = idx % CPR;
-                    if ((pos ^ swz(r)) >= kvalid) *reinterpret_cast<u32x4_t*>(at + r * ROWB + pos * 16) = z;
-                }
+            unsigned char* at = smem + SOFF;
+            const u32x4_t z = {0u, 0u, 0u, 0u};
+            for (int idx = tid; idx < BM * CPR; idx += NW * 64) {
+                const int r = idx / CPR, pos = idx % CPR;
+                if ((pos ^ swz(r)) >= kvalid) *reinterpret_cast<u32x4_t*>(at + r * ROWB + pos * 16) = z;
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
@@ -296,14 +282,9 @@ __global__ __launch_bounds__(WM * WN * KG * 64) void gemm_nt_dma_kernel(const bf
         if (kt + 2 == nk) {
             stage_body(S0{}, std::true_type{}, kt);
             stage_body(S1{}, std::false_type{}, kt + 1);
-        } else if (KG == 1 || kt + 1 == nk) {
+        } else {
             stage_body(S0{}, std::false_type{}, kt);
         }
-    }
-    if (KG > 1) {
-        // every wavefront passes the same barriers: one per stage of the longest group (and one more with TAIL)
-        for (int e = nk; e < nk_max; ++e) __builtin_amdgcn_s_barrier();
-        if (TAIL && nk == 0) __builtin_amdgcn_s_barrier();
     }
 
     // ---- epilogue through LDS, 32 rows at a time: [32][TN*32 + 4] float32 per panel ----
@@ -330,38 +311,6 @@ __global__ __launch_bounds__(WM * WN * KG * 64) void gemm_nt_dma_kernel(const bf
             for (int k = 0; k < 4; ++k) csum[k] += __shfl_xor(csum[k], off, 64);
         if (rr == 0 && n < N) *reinterpret_cast<f32x4_t*>(epi.colsum + (int64_t)strip * N + n) = csum;
     };
-    if constexpr (KG > 1) {
-        // every group leaves its partial tile; panel i of a wavefront position is then summed (in group order) and
-        // stored by group i
-        float* part = reinterpret_cast<float*>(smem);     // [kg][wave][panel][32][CP]
-#pragma unroll
-        for (int i = 0; i < TM; ++i) put_panel(part + ((kg * NW + wave) * TM + i) * (32 * CP), i);
-        __syncthreads();
-        if (kg < TM && n < N) {
-            const int i = kg;
-            f32x4_t opnd[NP], v[NP];
-            const int mrow = m0 + wm * TM * 32 + i * 32 + rr;
-#pragma unroll
-            for (int p = 0; p < NP; ++p) opnd[p] = epi_load4<KIND>(epi, min(mrow + p * RPP, M - 1), n);
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const float* q = part + (wave * TM + i) * (32 * CP) + (p * RPP + rr) * CP + 4 * c4;
-                v[p] = *reinterpret_cast<const f32x4_t*>(q);
-#pragma unroll
-                for (int k = 1; k < KG; ++k) v[p] += *reinterpret_cast<const f32x4_t*>(q + k * (NW * TM * 32 * CP));
-            }
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const int m = mrow + p * RPP;
-                if (m < M) {
-                    const f32x4_t o = epi_store4<KIND>(epi, m, n, v[p], bv, opnd[p]);
-                    if (KIND == EPI_GELU_BWD) csum += o;
-                }
-            }
-        }
-        if (KIND == EPI_GELU_BWD && epi.colsum != nullptr && kg < TM) put_colsum((m0 + wm * TM * 32 + kg * 32) >> 5);   // 32-row strips
-        return;
-    }
     float* ct = reinterpret_cast<float*>(smem) + wave * (32 * CP);
     if ((KIND == EPI_RESIDUAL || KIND == EPI_GELU_BWD) && n < N) {
 #pragma unroll
@@ -396,15 +345,15 @@ __global__ __launch_bounds__(WM * WN * KG * 64) void gemm_nt_dma_kernel(const bf
     if (KIND == EPI_GELU_BWD && TM * 32 == 64 && epi.colsum != nullptr) put_colsum((m0 + wm * TM * 32) >> 6);   // 64-row strips
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int KG, int KIND, bool BKM, bool TAIL>
+template <int BM, int BN, int WM, int WN, int BK, int KIND, bool BKM, bool TAIL>
 static int launch_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
                       const Epi& epi) {
-    constexpr int NW = WM * WN * KG;
-    constexpr size_t stage_bytes = (size_t)KG * GD_NS * (BM + BN) * BK * 2;
-    constexpr size_t epi_bytes = (size_t)NW * (KG > 1 ? BM / WM : 32) * (BN / WN + 4) * 4;
+    constexpr int NW = WM * WN;
+    constexpr size_t stage_bytes = (size_t)GD_NS * (BM + BN) * BK * 2;
+    constexpr size_t epi_bytes = (size_t)NW * 32 * (BN / WN + 4) * 4;
     constexpr size_t shmem = stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
     static LdsLimit lim;
-    auto kern = gemm_nt_dma_kernel<BM, BN, WM, WN, BK, KG, KIND, BKM, TAIL>;
+    auto kern = gemm_nt_dma_kernel<BM, BN, WM, WN, BK, KIND, BKM, TAIL>;
     if (int rc = lim.ensure(reinterpret_cast<const void*>(kern), (int)shmem)) return rc;
     const int tiles_n = (N + BN - 1) / BN;
     const int tiles = ((M + BM - 1) / BM) * tiles_n;
@@ -423,10 +372,9 @@ template <int KIND, bool BKM, bool TAIL>
 static int dispatch_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
                         const Epi& epi, GemmShape shape) {
     switch (shape) {
-        case GS_64x128_K3: return launch_dma<64, 128, 1, 2, 64, 3, KIND, BKM, TAIL>(s, A, lda, B, ldb, M, N, K, epi);
-        case GS_128x128_K2: return launch_dma<128, 128, 2, 2, 64, 2, KIND, BKM, TAIL>(s, A, lda, B, ldb, M, N, K, epi);
+        case GS_64x128: return launch_dma<64, 128, 1, 2, 64, KIND, BKM, TAIL>(s, A, lda, B, ldb, M, N, K, epi);
         case GS_160x128:
-            if constexpr (!TAIL) return launch_dma<160, 128, 1, 2, 64, 1, KIND, BKM, false>(s, A, lda, B, ldb, M, N, K, epi);
+            if constexpr (!TAIL) return launch_dma<160, 128, 1, 2, 64, KIND, BKM, false>(s, A, lda, B, ldb, M, N, K, epi);
             break;
         default: break;
     }
@@ -434,8 +382,8 @@ static int dispatch_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B
     // (these launches are bound by memory traffic: width 96, 200 704 rows: a backward pass 4 % faster than with a
     // half-empty 64-wide stage)
     if constexpr (TAIL)
-        if (K % 32 == 0 && K < 128) return launch_dma<128, 128, 2, 2, 32, 1, KIND, BKM, false>(s, A, lda, B, ldb, M, N, K, epi);
-    return launch_dma<128, 128, 2, 2, 64, 1, KIND, BKM, TAIL>(s, A, lda, B, ldb, M, N, K, epi);
+        if (K % 32 == 0 && K < 128) return launch_dma<128, 128, 2, 2, 32, KIND, BKM, false>(s, A, lda, B, ldb, M, N, K, epi);
+    return launch_dma<128, 128, 2, 2, 64, KIND, BKM, TAIL>(s, A, lda, B, ldb, M, N, K, epi);
 }
 
 // The caller has checked K % 8 == 0, N % 8 == 0 and 16-byte alignment of every row.

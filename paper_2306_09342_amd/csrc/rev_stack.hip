@@ -166,7 +166,7 @@ static Layout make_layout(const rev_cfg& c, bool compact) {
     {
         // [0]: fc1 bias gradient (column-sum strips of the GELU' epilogue);
         // [1]: the top block's fc2 bias gradient; float32 mode: the QKV bias gradients too
-        const int64_t e0 = (int64_t)(c.mode == REV_MODE_BF16 ? gemm_colsum_strips((int)M, (int)Dm) : gemm_f32_colsum_strips((int)M, (int)Dm)) * Dm;
+        const int64_t e0 = (int64_t)(c.mode == REV_MODE_BF16 ? gemm_colsum_strips((int)M, (int)Dm, (int)D) : gemm_f32_colsum_strips((int)M, (int)Dm)) * Dm;
         int64_t e1 = c.mode == REV_MODE_BF16 ? 0 : colsum_partial_elems((int)M, (int)(3 * D));
         int64_t e1b = colsum_partial_elems((int)M, (int)D);
         if (e1b > e1) e1 = e1b;
@@ -332,7 +332,7 @@ struct Runner {
         e.colsum = pcol0;
         RC(dgrad(s, blk, T_WFC2, d2b, D, Dm, e));
         segs[nseg++] = {pcol0, G(blk, T_BFC1), nullptr, (int64_t)Dm, (int64_t)Dm, (int64_t)Dm,
-                        kBf16 ? gemm_colsum_strips(M, Dm) : gemm_f32_colsum_strips(M, Dm)};
+                        kBf16 ? gemm_colsum_strips(M, Dm, D) : gemm_f32_colsum_strips(M, Dm)};
         Epi p = epi0(); p.kind = EPI_PLAIN; p.out = dn; p.ldo = D;
         RC(dgrad(s, blk, T_WFC1, dhb, Dm, D, p));
         // gY1 = dY1 + LN2bwd(dn); its column sums are the bias gradient of the projection

@@ -1,6 +1,6 @@
-"""GEMMs at the edges of every tile and contraction split of the dispatch, through whole blocks against the
-float64 oracle (bf16): K shorter than one stage, a short last stage in each kernel, contraction groups with unequal and with no
-stages, ragged rows and columns, the fused column sums of each strip height; the float32 products: both tile sizes,
+"""GEMMs at the edges of every tile of the dispatch, through whole blocks against the
+float64 oracle (bf16): K shorter than one stage, a short last stage in each kernel, stages whose second half is empty,
+ragged rows and columns, the fused column sums of each strip height; the float32 products: both tile sizes,
 a token count that is no multiple of anything, heads of every width class with masks.  PaReprop must equal Reprop bit for bit."""
 import numpy as np
 import pytest
@@ -14,16 +14,19 @@ from parity_util import TOL, compare_backward, gpu_cfg, make_case, oracle_forwar
 pytestmark = pytest.mark.gpu
 
 SHAPES = {
-    # 32x32 and 64x64 tiles, wavefronts splitting K
+    # 32x32 and 64x64 tiles
     "one_token_K8": dict(n_blocks=1, d_model=8, n_heads=1, d_mlp=8, seq_len=1, batch=1),
     "ragged_K40": dict(n_blocks=2, d_model=40, n_heads=1, d_mlp=72, seq_len=33, batch=1),
     "tiles64_K328": dict(n_blocks=1, d_model=328, n_heads=1 + 40, d_mlp=2248, seq_len=197, batch=1),
-    # 64x128 by three contraction groups: 4 stages (2, 2, 0) and 5 with a short last one (2, 2, 1)
+    # 32x32 tiles at K = 256 / 264 (the last of three stages holds one chunk of 8) and 2048, 64x64 tiles at the same short K
     "groups3_K256": dict(n_blocks=1, d_model=256, n_heads=4, d_mlp=2048, seq_len=75, batch=8),
     "groups3_K264": dict(n_blocks=1, d_model=264, n_heads=3, d_mlp=2056, seq_len=75, batch=8),
-    # 128x128 by two groups: 3 stages (2, 1), the last one short
+    # 128x128 tiles at K = 144, 64x64 at 2056
     "groups2_K144": dict(n_blocks=1, d_model=144, n_heads=2, d_mlp=2056, seq_len=150, batch=10),
-    # whole-K tiles with a short last stage, and the first row count that takes them for narrow outputs
+    # 64x128 tiles in the ring (fc2 and its transpose; a last chunk of 8) and in two stages (proj, fc1, its transpose with column sums)
+    "ring64x128_K1544": dict(n_blocks=1, d_model=384, n_heads=6, d_mlp=1544, seq_len=197, batch=23),
+    "two_stage64x128_K1032": dict(n_blocks=1, d_model=1032, n_heads=43, d_mlp=1032, seq_len=95, batch=20),
+    # few output columns at many rows
     "whole_K72": dict(n_blocks=1, d_model=72, n_heads=1, d_mlp=200, seq_len=31, batch=100),
     "whole_rows3073": dict(n_blocks=1, d_model=64, n_heads=1, d_mlp=136, seq_len=439, batch=7),
     # weight gradients in 256x256 tiles: one token beyond the last full stage; ragged in every direction; three token ranges,
