@@ -16,7 +16,8 @@
  * sqrt(head_dim)) v with no mask and no dropout; GELU is the erf form x*Phi(x)
  * (REV_MODE_FP32 evaluates erf; REV_MODE_BF16 evaluates Phi with a fitted
  * polynomial of absolute error < 6.5e-5 on |x| <= 3.8 and takes exactly 0 / 1
- * beyond); every linear map has a bias.
+ * beyond if d_model is a multiple of 32, and evaluates erf if it is not); every
+ * linear map has a bias.
  *
  * All pointers except `cfg` are DEVICE pointers owned by the caller; the library
  * allocates no device memory, frees none, and keeps no state between calls

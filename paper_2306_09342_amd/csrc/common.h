@@ -127,7 +127,8 @@ enum EpiKind {
     EPI_RESIDUAL,      // outf = res[m,n] + sign * (acc + bias[n])          (float32)
     EPI_GELU_BWD,      // out = acc * gelu'(aux[m,n])                       (act type)
     EPI_PLAIN,         // out = acc                                         (act type)
-    EPI_PLAIN_F32      // outf = acc                                        (float32)
+    EPI_PLAIN_F32,     // outf = acc                                        (float32)
+    EPI_ERF = 16       // added to a GELU kind by the bf16 dispatch: the normal CDF by erff instead of the polynomial
 };
 
 struct Epi {

@@ -25,6 +25,10 @@ __device__ __forceinline__ float gelu_cdf(float x) {
     r = x > 3.8f ? 1.f : r;
     return r;
 }
+// EPI_ERF: the erf form instead.  It goes with contractions that are no multiple of 32 (gemm_mfma.hip).
+template <bool ERF> __device__ __forceinline__ float gelu_cdf_of(float x) {
+    return ERF ? 0.5f * (1.0f + erff(x * 0.70710678118654752f)) : gelu_cdf(x);
+}
 __device__ __forceinline__ float gelu_pdf(float x) { return 0.39894228040143268f * __expf(-0.5f * x * x); }
 
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
@@ -62,8 +66,10 @@ __device__ __forceinline__ f32x4_t epi_load4(const Epi& e, int m, int n) {
 
 // 4 consecutive output columns n..n+3 of row m; `opnd` is what epi_load4 returned for them
 // (returns the float32 values behind the stored output, for the fused column sums)
-template <int KIND>
+template <int EPI>
 __device__ __forceinline__ f32x4_t epi_store4(const Epi& e, int m, int n, f32x4_t acc, f32x4_t bv, f32x4_t opnd) {
+    constexpr int KIND = EPI & ~EPI_ERF;
+    constexpr bool ERF = (EPI & EPI_ERF) != 0;
     const int64_t idx = (int64_t)m * e.ldo + n;
     if (KIND == EPI_BIAS || KIND == EPI_BIAS_GELU || KIND == EPI_RESIDUAL) acc += bv;
     if (KIND == EPI_BIAS) {
@@ -72,7 +78,7 @@ __device__ __forceinline__ f32x4_t epi_store4(const Epi& e, int m, int n, f32x4_
         if (e.out != nullptr) st_bf16x4(reinterpret_cast<bf16*>(e.out) + idx, acc);   // the pre-activation is optional
         f32x4_t a;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) a[k] = acc[k] * gelu_cdf(acc[k]);
+        for (int k = 0; k < 4; ++k) a[k] = acc[k] * gelu_cdf_of<ERF>(acc[k]);
         st_bf16x4(reinterpret_cast<bf16*>(e.out2) + idx, a);
     } else if (KIND == EPI_RESIDUAL) {
         *reinterpret_cast<f32x4_t*>(e.outf + idx) = opnd + e.sign * acc;
@@ -82,7 +88,7 @@ __device__ __forceinline__ f32x4_t epi_store4(const Epi& e, int m, int n, f32x4_
                            __uint_as_float(u1 << 16), __uint_as_float(u1 & 0xFFFF0000u)};
         f32x4_t o;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) o[k] = acc[k] * (gelu_cdf(h[k]) + h[k] * gelu_pdf(h[k]));
+        for (int k = 0; k < 4; ++k) o[k] = acc[k] * (gelu_cdf_of<ERF>(h[k]) + h[k] * gelu_pdf(h[k]));
         st_bf16x4(reinterpret_cast<bf16*>(e.out) + idx, o);
         return o;
     } else if (KIND == EPI_PLAIN) {

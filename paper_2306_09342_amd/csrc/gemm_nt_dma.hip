@@ -32,10 +32,11 @@ namespace rev {
 constexpr int GD_NS = 2;                                 // stages in flight
 
 // BK: contraction depth of a stage (64: 128-byte rows; 32)
-template <int BM, int BN, int WM, int WN, int BK, int KIND, bool BKM, bool TAIL>
+template <int BM, int BN, int WM, int WN, int BK, int EPI, bool BKM, bool TAIL>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_nt_dma_kernel(const bf16* __restrict__ A, int64_t lda,
                                                                          const bf16* __restrict__ B, int64_t ldb,
                                                                          int M, int N, int K, Epi epi, int gn) {
+    constexpr int KIND = EPI & ~EPI_ERF;
     constexpr int NW = WM * WN;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int NS = GD_NS;
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_nt_dma_kernel(const bf16* _
             for (int p = 0; p < NP; ++p) {
                 const int m = mrow + p * RPP;
                 if (m < M) {
-                    const f32x4_t o = epi_store4<KIND>(epi, m, n, v[p], bv, opnd[p]);
+                    const f32x4_t o = epi_store4<EPI>(epi, m, n, v[p], bv, opnd[p]);
                     if (KIND == EPI_GELU_BWD) csum += o;
                 }
             }
@@ -345,7 +346,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_nt_dma_kernel(const bf16* _
     if (KIND == EPI_GELU_BWD && TM * 32 == 64 && epi.colsum != nullptr) put_colsum((m0 + wm * TM * 32) >> 6);   // 64-row strips
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int KIND, bool BKM, bool TAIL>
+template <int BM, int BN, int WM, int WN, int BK, int EPI, bool BKM, bool TAIL>
 static int launch_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
                       const Epi& epi) {
     constexpr int NW = WM * WN;
@@ -353,7 +354,7 @@ static int launch_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, 
     constexpr size_t epi_bytes = (size_t)NW * 32 * (BN / WN + 4) * 4;
     constexpr size_t shmem = stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
     static LdsLimit lim;
-    auto kern = gemm_nt_dma_kernel<BM, BN, WM, WN, BK, KIND, BKM, TAIL>;
+    auto kern = gemm_nt_dma_kernel<BM, BN, WM, WN, BK, EPI, BKM, TAIL>;
     if (int rc = lim.ensure(reinterpret_cast<const void*>(kern), (int)shmem)) return rc;
     const int tiles_n = (N + BN - 1) / BN;
     const int tiles = ((M + BM - 1) / BM) * tiles_n;
@@ -368,22 +369,22 @@ static int launch_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, 
 }
 
 // Tile and split of a launch: see pick_gemm_shape (gemm_mfma.hip)
-template <int KIND, bool BKM, bool TAIL>
+template <int EPI, bool BKM, bool TAIL>
 static int dispatch_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
                         const Epi& epi, GemmShape shape) {
     switch (shape) {
-        case GS_64x128: return launch_dma<64, 128, 1, 2, 64, KIND, BKM, TAIL>(s, A, lda, B, ldb, M, N, K, epi);
+        case GS_64x128: return launch_dma<64, 128, 1, 2, 64, EPI, BKM, TAIL>(s, A, lda, B, ldb, M, N, K, epi);
         case GS_160x128:
-            if constexpr (!TAIL) return launch_dma<160, 128, 1, 2, 64, KIND, BKM, false>(s, A, lda, B, ldb, M, N, K, epi);
+            if constexpr (!TAIL) return launch_dma<160, 128, 1, 2, 64, EPI, BKM, false>(s, A, lda, B, ldb, M, N, K, epi);
             break;
         default: break;
     }
     // K = 32 and 96: 32-wide stages read nothing that is not there, and their 32 KB of LDS let four workgroups share a CU
     // (these launches are bound by memory traffic: width 96, 200 704 rows: a backward pass 4 % faster than with a
     // half-empty 64-wide stage)
-    if constexpr (TAIL)
-        if (K % 32 == 0 && K < 128) return launch_dma<128, 128, 2, 2, 32, KIND, BKM, false>(s, A, lda, B, ldb, M, N, K, epi);
-    return launch_dma<128, 128, 2, 2, 64, KIND, BKM, TAIL>(s, A, lda, B, ldb, M, N, K, epi);
+    if constexpr (TAIL && !(EPI & EPI_ERF))
+        if (K % 32 == 0 && K < 128) return launch_dma<128, 128, 2, 2, 32, EPI, BKM, false>(s, A, lda, B, ldb, M, N, K, epi);
+    return launch_dma<128, 128, 2, 2, 64, EPI, BKM, TAIL>(s, A, lda, B, ldb, M, N, K, epi);
 }
 
 // The caller has checked K % 8 == 0, N % 8 == 0 and 16-byte alignment of every row.
@@ -393,10 +394,14 @@ int gemm_bf16_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int6
     const bool tail = K % 64 != 0;
     switch (epi.kind) {
 #define ARGS s, A, lda, B, ldb, M, N, K, epi, shape
-#define CASE(KIND) case KIND: return b_kmajor ? (tail ? dispatch_dma<KIND, true, true>(ARGS) : dispatch_dma<KIND, true, false>(ARGS)) \
-                                              : (tail ? dispatch_dma<KIND, false, true>(ARGS) : dispatch_dma<KIND, false, false>(ARGS));
+#define TAILED(EPI) return b_kmajor ? dispatch_dma<EPI, true, true>(ARGS) : dispatch_dma<EPI, false, true>(ARGS);
+#define CASE(KIND) case KIND: if (tail) TAILED(KIND) \
+                              return b_kmajor ? dispatch_dma<KIND, true, false>(ARGS) : dispatch_dma<KIND, false, false>(ARGS);
         CASE(EPI_BIAS) CASE(EPI_BIAS_GELU) CASE(EPI_RESIDUAL) CASE(EPI_GELU_BWD) CASE(EPI_PLAIN) CASE(EPI_PLAIN_F32)
+        case EPI_BIAS_GELU | EPI_ERF: if (tail) TAILED(EPI_BIAS_GELU | EPI_ERF) break;
+        case EPI_GELU_BWD | EPI_ERF: if (tail) TAILED(EPI_GELU_BWD | EPI_ERF) break;
 #undef CASE
+#undef TAILED
 #undef ARGS
     }
     set_error("gemm_bf16: unknown epilogue");

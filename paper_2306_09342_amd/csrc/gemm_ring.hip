@@ -30,10 +30,11 @@ template <int TM, int TN, int WM, int WN, int SUB, int NS> struct RingCfg {
     static_assert(LA % NW == 0 && LB % NW == 0 && WM * WN <= NW && (NS - 2) * LPW < 64, "RingCfg");
 };
 
-template <int TM, int TN, int WM, int WN, int SUB, int NS, int KIND, bool BKM>
+template <int TM, int TN, int WM, int WN, int SUB, int NS, int EPI, bool BKM>
 __global__ __launch_bounds__(256) void gemm_ring_kernel(const bf16* __restrict__ A, int64_t lda, const bf16* __restrict__ B, int64_t ldb,
                                                         int M, int N, int K, Epi epi) {
     using C = RingCfg<TM, TN, WM, WN, SUB, NS>;
+    constexpr int KIND = EPI & ~EPI_ERF;
     constexpr int BM = C::BM, BN = C::BN, NW = C::NW, LPW = C::LPW;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const bf16* __restrict__
             if (m < M) {
                 const f32x4_t v = *reinterpret_cast<const f32x4_t*>(ct + r * C::PITCH + 4 * c4);
                 const f32x4_t x = PASS <= 4 ? opnd[p] : epi_load4<KIND>(epi, m, n);
-                const f32x4_t o = epi_store4<KIND>(epi, m, n, v, bv, x);
+                const f32x4_t o = epi_store4<EPI>(epi, m, n, v, bv, x);
                 if (KIND == EPI_GELU_BWD) csum += o;
             }
         }
@@ -252,11 +253,11 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const bf16* __restrict__
     }
 }
 
-template <int TM, int TN, int WM, int WN, int SUB, int NS, int KIND, bool BKM>
+template <int TM, int TN, int WM, int WN, int SUB, int NS, int EPI, bool BKM>
 static int launch_ring(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi) {
     using C = RingCfg<TM, TN, WM, WN, SUB, NS>;
     static LdsLimit lim;
-    auto kern = gemm_ring_kernel<TM, TN, WM, WN, SUB, NS, KIND, BKM>;
+    auto kern = gemm_ring_kernel<TM, TN, WM, WN, SUB, NS, EPI, BKM>;
     if (int rc = lim.ensure(reinterpret_cast<const void*>(kern), C::SHMEM)) return rc;
     const int tiles = ((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
     hipLaunchKernelGGL(kern, dim3(tiles), dim3(256), C::SHMEM, s, A, lda, B, ldb, M, N, K, epi);
@@ -264,13 +265,13 @@ static int launch_ring(hipStream_t s, const bf16* A, int64_t lda, const bf16* B,
     return REV_OK;
 }
 
-template <int KIND, bool BKM>
+template <int EPI, bool BKM>
 static int dispatch_ring(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
                          const Epi& epi, GemmShape shape) {
     switch (shape) {
-        case GS_32x32: return launch_ring<1, 1, 1, 1, 2, 4, KIND, BKM>(s, A, lda, B, ldb, M, N, K, epi);     // 64 to 72 KB of LDS:
-        case GS_64x64: return launch_ring<1, 1, 2, 2, 1, 4, KIND, BKM>(s, A, lda, B, ldb, M, N, K, epi);     // two workgroups
-        case GS_64x128_RING: return launch_ring<1, 2, 2, 2, 1, 3, KIND, BKM>(s, A, lda, B, ldb, M, N, K, epi);   // per CU
+        case GS_32x32: return launch_ring<1, 1, 1, 1, 2, 4, EPI, BKM>(s, A, lda, B, ldb, M, N, K, epi);     // 64 to 72 KB of LDS:
+        case GS_64x64: return launch_ring<1, 1, 2, 2, 1, 4, EPI, BKM>(s, A, lda, B, ldb, M, N, K, epi);     // two workgroups
+        case GS_64x128_RING: return launch_ring<1, 2, 2, 2, 1, 3, EPI, BKM>(s, A, lda, B, ldb, M, N, K, epi);   // per CU
         default: set_error("gemm_bf16: no such tile"); return REV_EINVAL;
     }
 }
@@ -281,6 +282,7 @@ int gemm_bf16_ring(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int
 #define CASE(KIND) case KIND: return b_kmajor ? dispatch_ring<KIND, true>(s, A, lda, B, ldb, M, N, K, epi, shape) \
                                               : dispatch_ring<KIND, false>(s, A, lda, B, ldb, M, N, K, epi, shape);
         CASE(EPI_BIAS) CASE(EPI_BIAS_GELU) CASE(EPI_RESIDUAL) CASE(EPI_GELU_BWD) CASE(EPI_PLAIN) CASE(EPI_PLAIN_F32)
+        CASE(EPI_BIAS_GELU | EPI_ERF) CASE(EPI_GELU_BWD | EPI_ERF)
 #undef CASE
     }
     set_error("gemm_bf16: unknown epilogue");
