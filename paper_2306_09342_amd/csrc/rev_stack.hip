@@ -380,10 +380,17 @@ struct Runner {
         }
     }
 
-    // Two streams cost the host three events and three waits per block.  A block whose kernels are bound by launch latency
-    // gains nothing that pays for them: 64 tokens, D = 64 (7 MFLOP per block forward): 4 blocks 254 us on one stream, 351 on
-    // two; 197 tokens, D = 768 (2.9 GFLOP): two streams are faster.  Same kernels in the same order, so the same results.
-    bool one_stream_is_faster() const { return 2.0 * M * D * (4.0 * D + 2.0 * Dm) + 4.0 * M * (double)Tn * D < 3e8; }
+    // Two streams cost the host three events and three waits per block, so where the line lies depends on the host's speed.
+    // Measured (us a call, one stream / two, calls back to back) on a slow host, 12 blocks, and on a fast one, 6 blocks, by FLOP
+    // of a block's forward:
+    //              slow: bf16         float32         fast: bf16      float32
+    //    6.6e6       769 / 1018       848 / 1249        450 / 443      537 / 478
+    //    2.9e7      1047 / 1006      1142 / 1262        538 / 453      616 / 500
+    //    5.5e7      1039 / 1010      1164 / 1241        522 / 435      608 / 503
+    //    9.7e7      1202 /  976      1296 / 1270        635 / 460      724 / 546
+    //    2.0e8      1240 / 1043      1418 / 1241        657 / 465      796 / 618
+    // From 8e7 on two streams win on both.  Same kernels in the same order, so the same results.
+    bool one_stream_is_faster() const { return 2.0 * M * D * (4.0 * D + 2.0 * Dm) + 4.0 * M * (double)Tn * D < 8e7; }
 
     // residual level `lvl` (0..N): stream s1/s2 pointers
     struct Ptrs { const float* in1; const float* in2; float* out1; float* out2; };
@@ -398,7 +405,8 @@ struct Runner {
     // PaReprop, stream by stream (block indices 1-based, N at the top):
     //   sr:  R_N | R_{N-1}  W_N | R_{N-2}  W_{N-1} | ...      (W_i = grad_w of block i)
     //   sv:  D_N | D_{N-1}      | D_{N-2}          | ...      (D_i = grad_d of block i)
-    // Orderings across the streams (three events and three waits per block: each costs the host about as much as a launch):
+    // Orderings across the streams (three events and three waits per block, in float32 mode four: each costs the host about
+    // as much as a launch):
     //   D_i  after R_i                      (activations of block i exist; W_{i+2} precedes R_i on sr, so the dh/dqkv/gY1
     //                                        buffers of the same parity and the dY2 copy of W_{i+2} are free again)
     //   R_i  after D_{i+2}                  (slot i mod 2 and ring level i+2 are free; W_{i+2} precedes R_i on sr)
@@ -410,7 +418,8 @@ struct Runner {
                  float* dX1, float* dX2, float* X1o, float* X2o, hipStream_t sv, hipStream_t sr) {
         const int N = c.n_blocks;
         const bool doR = schedule != 3, doV = schedule != 2;
-        enum { E_R = 0, E_D, E_DQKV, E_W, EPB };
+        enum { E_R = 0, E_D, E_DQKV, E_W };                       // E_W: float32 mode only
+        constexpr int EPB = kBf16 ? 3 : 4;
         EventLease lease;
         std::vector<hipEvent_t>& ev = lease.ev;
         auto E = [&](int i, int k) { return ev[(i - 1) * EPB + k]; };
@@ -421,8 +430,7 @@ struct Runner {
             RC(lease.take(per + 2));
             REV_HIP(hipEventRecord(ev[per], sv));                 // fork
             REV_HIP(hipStreamWaitEvent(sr, ev[per], 0));
-            // One stream: it is the recompute stream, so that the call keeps its order with the caller's work on both (254 us
-            // becomes 268 on the four blocks above, the price of the fork and the join).
+            // One stream: it is the recompute stream, so that the call keeps its order with the caller's work on both.
             if (!two) sv = sr;
         } else {
             sr = sv;

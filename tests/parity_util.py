@@ -43,6 +43,14 @@ def oracle_forward(cfg, blocks, x1, x2, chunk=8):
     return y1, y2
 
 
+def takes_two_streams(cfg):
+    """Whether the parallel schedule issues this stack on both streams: from 8e7 FLOP per block forward on (smaller blocks
+    run in turn on the recompute stream).  Tests of the cross-stream ordering assert it, so that they cannot become
+    comparisons of two serial runs."""
+    rows, D, Dm = cfg["batch"] * cfg["seq_len"], cfg["d_model"], cfg["d_mlp"]
+    return 2.0 * rows * D * (4.0 * D + 2.0 * Dm) + 4.0 * rows * cfg["seq_len"] * D >= 8e7
+
+
 def to_dev(a, dtype=torch.float32):
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda").to(dtype).contiguous()
 

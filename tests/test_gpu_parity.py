@@ -10,7 +10,7 @@ from oracle import rev_oracle as O
 from paper_2306_09342_amd import binding as B
 from paper_2306_09342_amd import synth
 
-from parity_util import TOL, compare_backward, gpu_cfg, make_case, oracle_forward, rel_err, to_dev
+from parity_util import TOL, compare_backward, gpu_cfg, make_case, oracle_forward, rel_err, takes_two_streams, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -23,6 +23,9 @@ SHAPES = {
     "dh128_T1": dict(n_blocks=2, d_model=256, n_heads=2, d_mlp=264, seq_len=1, batch=5),
     "vit_s_slice": dict(n_blocks=3, d_model=384, n_heads=6, d_mlp=1536, seq_len=197, batch=3),
     "one_sample_T300": dict(n_blocks=1, d_model=64, n_heads=2, d_mlp=64, seq_len=300, batch=1),
+    # six blocks on two streams: every buffer that the streams hand each other is used again (in float32 mode a cotangent
+    # level, from the fourth block on)
+    "six_blocks": dict(n_blocks=6, d_model=256, n_heads=4, d_mlp=1024, seq_len=197, batch=2),
     # window-attention shaped stages (49 tokens, head_dim 32): narrow first stage, many-headed last stage
     "window_stage1": dict(n_blocks=2, d_model=96, n_heads=3, d_mlp=384, seq_len=49, batch=7),
     "window_stage4": dict(n_blocks=1, d_model=768, n_heads=24, d_mlp=3072, seq_len=49, batch=2),
@@ -79,6 +82,11 @@ def test_fp32_mode_matches_oracle(name):
     _run_case(name, "fp32")
 
 
+def test_shapes_of_several_blocks_lie_on_both_sides_of_the_two_stream_line():
+    several = {n: takes_two_streams(s) for n, s in SHAPES.items() if s["n_blocks"] > 1}
+    assert several["six_blocks"] and several["vit_s_slice"] and not several["tiny"], several
+
+
 @pytest.mark.parametrize("name", list(SHAPES))
 def test_bf16_mode_matches_oracle(name):
     _run_case(name, "bf16")
@@ -120,7 +128,8 @@ def test_paper_recipe_inputs_tiny_fp32():
 
 def test_outputs_do_not_depend_on_stale_workspace_or_repeat():
     """Two calls in a row on a workspace filled with NaN bytes give identical bits."""
-    cfg = dict(SHAPES["ragged_dh64"], mode="bf16")
+    cfg = dict(SHAPES["six_blocks"], mode="bf16")
+    assert takes_two_streams(cfg)
     flat, blocks, x, dy1, dy2 = make_case(cfg, seed=3)
     c = gpu_cfg(cfg)
     params = to_dev(flat, B.param_dtype(c))
@@ -180,11 +189,13 @@ def test_reprop_in_its_smaller_workspace_gives_the_same_bits(name, mode):
         B.rev_stack_backward_pareprop(c, params, Y1, Y2, dY1, dY2, side, workspace=ws_small)
 
 
-def test_pareprop_call_can_be_captured_into_a_graph_and_replayed():
+@pytest.mark.parametrize("mode", ["bf16", "fp32"])
+def test_pareprop_call_can_be_captured_into_a_graph_and_replayed(mode):
     """The two-stream call enqueues only kernels and event waits, so a caller may capture it into a
     HIP graph (both streams join the capture through the call's own fork / join events).  Replays,
     with eager work and a scrambled workspace in between, reproduce the eager bits."""
-    cfg = dict(SHAPES["ragged_dh64"], mode="bf16")
+    cfg = dict(SHAPES["six_blocks"], mode=mode)
+    assert takes_two_streams(cfg)
     flat, blocks, x, dy1, dy2 = make_case(cfg, seed=7)
     c = gpu_cfg(cfg)
     params = to_dev(flat, B.param_dtype(c))
@@ -262,7 +273,8 @@ def test_two_host_threads_issue_pareprop_calls_concurrently():
     at the same time (each call leases its own events): every result equals, bit for bit, what the same call
     returns when it is the only one in flight."""
     import threading
-    cfgs = [dict(SHAPES["ragged_dh64"], mode="bf16"), dict(SHAPES["vit_s_slice"], mode="bf16")]
+    cfgs = [dict(SHAPES["six_blocks"], mode="bf16"), dict(SHAPES["vit_s_slice"], mode="bf16")]
+    assert all(takes_two_streams(cfg) for cfg in cfgs)
     jobs = []
     for i, cfg in enumerate(cfgs):
         flat, _, x, dy1, dy2 = make_case(cfg, seed=20 + i)
@@ -310,6 +322,7 @@ def test_pareprop_keeps_its_order_with_work_on_the_recompute_stream(name):
     """The outputs Y1, Y2 are produced late on the recompute stream, and the recomputed inputs are read there right after the
     call; blocks small enough to be issued on one stream keep the same order as larger ones."""
     cfg = synth.CONFIGS["tiny"] if name == "tiny" else dict(SHAPES[name], mode="bf16")
+    assert takes_two_streams(cfg) == (name != "tiny")
     flat, _, x, dy1, dy2 = make_case(cfg, seed=31)
     c = gpu_cfg(cfg)
     params = to_dev(flat, B.param_dtype(c))
