@@ -1,9 +1,11 @@
 """The static check for hand-issued loads (paper_2306_09342_amd/asm_check.py): it must see a planted misuse in
 a small assembly text, accept the correct form, and find nothing in the library's own kernels."""
 import os
+import re
 import tempfile
 
 from paper_2306_09342_amd import asm_check
+from paper_2306_09342_amd import build as _b
 
 GOOD = """
 _Z4kernPf:
@@ -63,6 +65,18 @@ def test_spill_of_a_hand_issued_global_load_is_found_and_compiler_loads_are_left
     got = _check(BAD_VM)
     assert len(got) == 1 and "scratch_store" in got[0][2]
     assert _check(COMPILER_VM) == []
+
+
+def test_every_source_with_a_hand_issued_load_into_registers_is_checked():
+    """Sources that call the helpers of mfma.h which issue such a load, or that issue one themselves."""
+    hand_issued = re.compile(r"\blds_read_(b128|tr16_b64)\(|asm volatile\(\"(ds_read|global_load_dword|buffer_load_dword)")
+    found = set()
+    for name in os.listdir(_b.CSRC):
+        if name.endswith(".hip"):
+            with open(os.path.join(_b.CSRC, name)) as f:
+                if hand_issued.search(f.read()):
+                    found.add(name)
+    assert found == set(asm_check.SOURCES)
 
 
 def test_library_kernels_use_no_hand_issued_load_before_its_wait():
