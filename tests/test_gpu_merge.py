@@ -36,6 +36,10 @@ MLP_CASES = {
     "mlp_width192_bf16": dict(batch=5, grid_h=28, grid_w=28, window=7, d_in=192, mode="bf16", ln_eps=1e-6, fusion="mlp"),
     "mlp_width384_fp32": dict(batch=1, grid_h=14, grid_w=28, window=7, d_in=384, mode="fp32", ln_eps=1e-5, fusion="mlp"),
     "mlp_wide_bf16": dict(batch=1, grid_h=14, grid_w=14, window=7, d_in=768, mode="bf16", ln_eps=1e-5, fusion="mlp"),
+    # the two bias gradients as column sums that ride in the weight-gradient launch, 62 720 rows: 128x128 tiles whose last
+    # round leaves too few idle slots for them (70 tiles x 7 ranges = 490 of 512; 35 chunks x 2), and 256x256 tiles
+    "mlp_sums_beyond_idle_bf16": dict(batch=20, grid_h=56, grid_w=56, window=7, d_in=576, mode="bf16", ln_eps=1e-5, fusion="mlp"),
+    "mlp_sums_tiles256_bf16": dict(batch=20, grid_h=56, grid_w=56, window=7, d_in=608, mode="bf16", ln_eps=1e-5, fusion="mlp"),
 }
 
 
