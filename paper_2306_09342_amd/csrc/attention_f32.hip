@@ -16,10 +16,6 @@ namespace rev {
 
 constexpr int AF_NW = 4;
 
-__device__ __forceinline__ f32x16_t mfma_f32(float a, float b, f32x16_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
-
 // Rows r0 + l%32 (clamped) of a [rows, ld] matrix: f[4*q + e] = X[row][8q + 4g + e], 0 beyond dh
 template <int DHP, typename T>
 __device__ __forceinline__ void rows_frag(const T* __restrict__ base, int64_t ld, int r0, int rows, int dh, int lane, float (&f)[DHP / 2]) {

@@ -416,7 +416,6 @@ int colsum(hipStream_t s, const T* in, int64_t ld, int M, int N, float* out, flo
     return reduce_multi(s, &g, 1);
 }
 template int colsum<float>(hipStream_t, const float*, int64_t, int, int, float*, float*, RedSeg*);
-template int colsum<bf16>(hipStream_t, const bf16*, int64_t, int, int, float*, float*, RedSeg*);
 
 // ---- conversion ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void cvt_kernel(const float* __restrict__ in, bf16* __restrict__ out, int64_t n4) {

@@ -1,7 +1,7 @@
 // float32 GEMMs on the float32 matrix cores (v_mfma_f32_32x32x2_f32: float32 products and sums), three operand forms:
-//   gemm_nt_f32      C = A[M,K] * B[N,K]^T      (activation x weight)
-//   gemm_nn_f32      C = A[M,K] * B[K,N]        (input gradients, the weight as stored)
-//   gemm_wgrad_f32   dW[N,K] = G[M,N]^T * A[M,K] (weight gradients, several per launch)
+//   gemm_nt_f32            C = A[M,K] * B[N,K]^T      (activation x weight)
+//   gemm_nn_f32            C = A[M,K] * B[K,N]        (input gradients, the weight as stored)
+//   gemm_wgrad_f32_group   dW[N,K] = G[M,N]^T * A[M,K] (weight gradients, several per launch)
 //
 // A workgroup owns one output tile of 32x32 or 64x64; its four wavefronts split the contraction: wavefront w takes the
 // 32-wide chunks w, w + 4, ... for the whole tile, out of a two-stage ring in LDS that only it uses (direct-to-LDS
@@ -18,10 +18,6 @@
 #include "gemm_epilogue.h"
 
 namespace rev {
-
-__device__ __forceinline__ f32x16_t mfma_f32(float a, float b, f32x16_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
 
 template <int KIND>
 __device__ __forceinline__ f32x4_t epi_store4_f32(const Epi& e, int m, int n, f32x4_t acc, f32x4_t bv) {

@@ -1,5 +1,5 @@
 // Weight gradients of a block in 256x256 tiles:  dW[N,K] = sum over tokens m of G[m,n] * A[m,k], up to four of them in one
-// launch, for token counts and widths at which such tiles fill the chip (wgrad_big_plan).
+// launch, for token counts and widths at which such tiles fill the chip (wgrad_plan, gemm_mfma.hip).
 //
 // One workgroup of 8 wavefronts per CU, 128x64 of the tile per wavefront.  Both operands have the token as their slow
 // index: a stage is 64 tokens of 256 columns of each, kept in LDS as it lies in memory and read with the transpose read.

@@ -11,7 +11,8 @@
 // token rows x 64 bytes per 32 lanes; the swizzle spreads those 4 rows over
 // the 4 quarters of the bank space.
 //
-// Tokens beyond M and columns beyond N / K are fetched from a block of zeros.
+// Tokens beyond M are fetched from a block of zeros; columns beyond N / K re-read the last valid ones (never stored), in
+// the step of the last tokens zeros.
 #include "mfma.h"
 #include <type_traits>
 

@@ -21,6 +21,11 @@ __device__ __forceinline__ f32x16_t mfma32(bf16x8_t a, bf16x8_t b, f32x16_t c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// v_mfma_f32_32x32x2_f32, lane l: A row l%32, B column l%32, both k = l / 32; D as above
+__device__ __forceinline__ f32x16_t mfma_f32(float a, float b, f32x16_t c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
 // LDS transpose read (ds_read_b64_tr_b16): the 16 lanes of a group hand in a 4x4
 // arrangement of 8-byte chunks (lane 4e+q: row e, columns 4q..4q+3 of a 4x16 patch)
 // and lane j of the group receives column j of the patch: 4 consecutive rows.

@@ -160,7 +160,8 @@ static Layout make_layout(const rev_cfg& c, bool compact) {
     }
     L.dn = take(M * D * es);
     L.dO = L.dn;           // dn is consumed by LN2's backward before dO is written, and dO by attention's before dn is again
-    L.delta = take((int64_t)c.batch * c.n_heads * c.seq_len * 4);
+    // read by the bf16 attention backward (heads up to 96 wide); the float32 products form it in registers
+    L.delta = take(c.mode == REV_MODE_BF16 && D / c.n_heads <= 96 ? (int64_t)c.batch * c.n_heads * c.seq_len * 4 : 0);
     L.part_ln[0] = take(ln_bwd_partial_elems((int)M, (int)D) * 4);
     L.part_ln[1] = take(ln_bwd_partial_elems((int)M, (int)D) * 4);
     {
