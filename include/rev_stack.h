@@ -229,7 +229,10 @@ int rev_adamw_step(int64_t n, float* master, void* params_bf16, const float* gra
  * returned, padded positions included: they flow through the blocks like any
  * token but no valid position ever reads them, so with cotangents that vanish
  * on the padded positions every result at a valid position and every parameter
- * gradient equals that of the unpadded sequences.  Everything else (arguments,
+ * gradient equals that of the unpadded sequences.  In the forward call the
+ * padded positions may hold anything, infinities and NaN included; the backward
+ * calls need finite values there, because a parameter gradient sums over all
+ * positions.  Everything else (arguments,
  * workspace sizes, ordering, errors, bit-identity of the two schedules) is as
  * for the unmasked calls; key_len must not be null here. */
 int rev_stack_forward_masked(const rev_cfg* cfg, const void* params,

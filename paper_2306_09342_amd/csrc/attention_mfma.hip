@@ -240,7 +240,8 @@ __global__ __launch_bounds__(512) void attn_fwd_mfma(const bf16* __restrict__ qk
     const int q0 = (blockIdx.x * nw + wave) * 32;
     // scores are kept in the base-2 domain (scale * log2 e folded into one multiply, exp2 is one instruction)
     const float c2 = rsqrtf((float)dh) * 1.4426950408889634f;
-    // key-padding mask: keys at positions >= Tk take no part in the softmax (Tk = T without a mask)
+    // key-padding mask: keys at positions >= Tk take no part in the softmax (Tk = T without a mask).  Their rows are not
+    // read: their probability is 0, but 0 times an infinity or a NaN would not be.
     const int Tk = key_len ? min(max(key_len[b], 1), T) : T;
 
     bf16x8_t bq[C::KS];
@@ -257,8 +258,8 @@ __global__ __launch_bounds__(512) void attn_fwd_mfma(const bf16* __restrict__ qk
     constexpr bool pipe = PIPE;
     TilePre<DHP> pk, pv;
     if constexpr (pipe) {
-        tile_fetch<DHP>(pk, base + D, ld, 0, T, dh);
-        tile_fetch<DHP>(pv, base + 2 * D, ld, 0, T, dh);
+        tile_fetch<DHP>(pk, base + D, ld, 0, Tk, dh);
+        tile_fetch<DHP>(pv, base + 2 * D, ld, 0, Tk, dh);
     }
     for (int t0 = 0; t0 < Tk; t0 += trows) {
       __syncthreads();
@@ -266,13 +267,13 @@ __global__ __launch_bounds__(512) void attn_fwd_mfma(const bf16* __restrict__ qk
           tile_store<DHP>(Ks0, pk);
           tile_store<DHP>(Vs0, pv);
       } else {
-          load_tile<DHP>(Ks0, base + D, ld, t0, T, dh, trows);
-          load_tile<DHP>(Vs0, base + 2 * D, ld, t0, T, dh, trows);
+          load_tile<DHP>(Ks0, base + D, ld, t0, Tk, dh, trows);
+          load_tile<DHP>(Vs0, base + 2 * D, ld, t0, Tk, dh, trows);
       }
       __syncthreads();
       if (pipe) if (t0 + trows < Tk) {
-          tile_fetch<DHP>(pk, base + D, ld, t0 + trows, T, dh);
-          tile_fetch<DHP>(pv, base + 2 * D, ld, t0 + trows, T, dh);
+          tile_fetch<DHP>(pk, base + D, ld, t0 + trows, Tk, dh);
+          tile_fetch<DHP>(pv, base + 2 * D, ld, t0 + trows, Tk, dh);
       }
       for (int k0 = t0; k0 < min(Tk, t0 + trows); k0 += AT_ROWS) {
         const uint16_t* Ks = Ks0 + (k0 - t0) * C::PITCH;
@@ -383,7 +384,8 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_mfma(const bf16* __restrict__
     const int q = q0 + (lane & 31), qc = min(q, T - 1);
     const float scale = rsqrtf((float)dh);
     const float c2 = scale * 1.4426950408889634f;
-    // key-padding mask: keys at positions >= Tk take no part in the softmax (Tk = T without a mask)
+    // key-padding mask: keys at positions >= Tk take no part in the softmax (Tk = T without a mask).  Their rows are not
+    // read: their probability is 0, but 0 times an infinity or a NaN would not be.
     const int Tk = key_len ? min(max(key_len[b], 1), T) : T;
 
     bf16x8_t bq[C::KS], bdo[C::KS];
@@ -412,8 +414,8 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_mfma(const bf16* __restrict__
     constexpr bool pipe = PIPE;
     TilePre<DHP> pk, pv;
     if constexpr (pipe) {
-        tile_fetch<DHP>(pk, base + D, ld, 0, T, dh);
-        tile_fetch<DHP>(pv, base + 2 * D, ld, 0, T, dh);
+        tile_fetch<DHP>(pk, base + D, ld, 0, Tk, dh);
+        tile_fetch<DHP>(pv, base + 2 * D, ld, 0, Tk, dh);
     }
     for (int t0 = 0; t0 < Tk; t0 += trows) {
       __syncthreads();
@@ -421,13 +423,13 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_mfma(const bf16* __restrict__
           tile_store<DHP>(Ks0, pk);
           tile_store<DHP>(Vs0, pv);
       } else {
-          load_tile<DHP>(Ks0, base + D, ld, t0, T, dh, trows);
-          load_tile<DHP>(Vs0, base + 2 * D, ld, t0, T, dh, trows);
+          load_tile<DHP>(Ks0, base + D, ld, t0, Tk, dh, trows);
+          load_tile<DHP>(Vs0, base + 2 * D, ld, t0, Tk, dh, trows);
       }
       __syncthreads();
       if (pipe) if (t0 + trows < Tk) {
-          tile_fetch<DHP>(pk, base + D, ld, t0 + trows, T, dh);
-          tile_fetch<DHP>(pv, base + 2 * D, ld, t0 + trows, T, dh);
+          tile_fetch<DHP>(pk, base + D, ld, t0 + trows, Tk, dh);
+          tile_fetch<DHP>(pv, base + 2 * D, ld, t0 + trows, Tk, dh);
       }
       for (int k0 = t0; k0 < min(Tk, t0 + trows); k0 += AT_ROWS) {
         const uint16_t* Ks = Ks0 + (k0 - t0) * C::PITCH;
@@ -677,7 +679,7 @@ __global__ __launch_bounds__(512) void attn_bwd_fused(const bf16* __restrict__ q
     res_load_owned<KS>(ob, D, r0, T, lane, fo);
     float Lraw = res_load4(lse + (int64_t)bh * T + qc);
     int rem[4], nkv, nqo;
-    res_request<DH>(Ks0, base + D, ld, Vs0, base + 2 * D, ld, T, tp, wave, nw, lane, rem, nkv);
+    res_request<DH>(Ks0, base + D, ld, Vs0, base + 2 * D, ld, Tk, tp, wave, nw, lane, rem, nkv);   // masked rows: the last valid one
     {
         int rem2[4];
         res_request<DH>(Qs0, base, ld, Os0, dob, D, T, tp, wave, nw, lane, rem2, nqo);

@@ -121,7 +121,7 @@ def test_masked_calls_reject_a_missing_or_misshapen_mask():
     assert rc == -1 and "key_len" in B.rev_last_error()
 
 
-# heads of every width class of the float32 kernels; lengths inside, at and just beyond a 32-key tile
+# heads of every width class; lengths inside, at and just beyond a 32-key tile
 NON_FINITE = [
     (dict(n_blocks=2, d_model=96, n_heads=3, d_mlp=128, seq_len=49, batch=4), [1, 31, 32, 33]),
     (dict(n_blocks=2, d_model=128, n_heads=2, d_mlp=256, seq_len=197, batch=3), [65, 130, 196]),
@@ -155,3 +155,10 @@ def _non_finite_padding(shape, lens, mode):
 @pytest.mark.parametrize("shape,lens", NON_FINITE)
 def test_non_finite_padding_does_not_reach_valid_positions_fp32(shape, lens):
     _non_finite_padding(shape, lens, "fp32")
+
+
+# and one that streams 64-row tiles
+@pytest.mark.parametrize("shape,lens", NON_FINITE + [(dict(n_blocks=1, d_model=128, n_heads=2, d_mlp=128, seq_len=700, batch=2),
+                                                      [577, 70])])
+def test_non_finite_padding_does_not_reach_valid_positions_bf16(shape, lens):
+    _non_finite_padding(shape, lens, "bf16")
