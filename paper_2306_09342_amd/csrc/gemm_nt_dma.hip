@@ -1,5 +1,5 @@
 // NT GEMM, pipelined flavour:  C[M,N] (+epilogue) = A[M,K] * B[N,K]^T  for K % 8 == 0, in 64-wide stages of K (a last
-// stage that K does not fill has its part of A beyond K zeroed in LDS).
+// stage that K does not fill has what lies beyond K zeroed in LDS).
 //
 // Operand tiles travel HBM -> LDS with the direct-to-LDS loads of gfx950
 // (global_load_lds_dwordx4): no staging registers, no LDS store instructions.
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_nt_dma_kernel(const bf16* _
     // is what the scalar-base addressing form of the load takes: no 64-bit vector adds per load.
     // Rows beyond M or N re-read the last valid row; K-major B columns beyond N re-read the last
     // valid 8 columns (such output rows / columns are never stored).  TAIL: in the short last stage chunks (rows of
-    // K-major B) beyond K re-read the last valid one; A's are zeroed in LDS before they are used.
+    // K-major B) beyond K re-read the last valid one; they are zeroed in LDS before they are used.
     unsigned voff[LPW], voff_t[TAIL ? LPW : 1];
     int dst[LPW];
 #pragma unroll
@@ -184,12 +184,20 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_nt_dma_kernel(const bf16* _
         __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
         __builtin_amdgcn_s_barrier();
         if (TAIL && !has_next) {
-            // A beyond K contributes exact zeros whatever B holds there
+            // what the loads left beyond K counts as zeros, in both operands (0 times a re-read infinity would not be 0)
             unsigned char* at = smem + SOFF;
             const u32x4_t z = {0u, 0u, 0u, 0u};
             for (int idx = tid; idx < BM * CPR; idx += NW * 64) {
                 const int r = idx / CPR, pos = idx % CPR;
                 if ((pos ^ swz(r)) >= kvalid) *reinterpret_cast<u32x4_t*>(at + r * ROWB + pos * 16) = z;
+            }
+            if (BKM) {
+                for (int idx = kvalid * 8 * 16 + tid; idx < BK * 16; idx += NW * 64) *reinterpret_cast<u32x4_t*>(at + A_BYTES + idx * 16) = z;
+            } else {
+                for (int idx = tid; idx < BN * CPR; idx += NW * 64) {
+                    const int r = idx / CPR, pos = idx % CPR;
+                    if ((pos ^ swz(r)) >= kvalid) *reinterpret_cast<u32x4_t*>(at + A_BYTES + r * ROWB + pos * 16) = z;
+                }
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();

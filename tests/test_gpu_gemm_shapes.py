@@ -83,3 +83,22 @@ def test_masked_wide_heads_match_the_oracle(mode):
     torch.cuda.synchronize()
     for i, k in enumerate(("dX1", "dX2")):
         assert rel_err(res[k].cpu().numpy(), np.concatenate([r[i] for r in ref])) <= TOL[mode], k
+
+
+@pytest.mark.parametrize("tokens,batch", [(3, 1), (100, 64), (100, 200)])
+def test_an_infinite_weight_stays_infinite_in_a_contraction_that_ends_inside_a_stage(tokens, batch):
+    """What a short last stage reads beyond the contraction counts as zeros, not as 0 times the weights it re-reads: with one
+    infinite weight at the last index, Y2 is infinite in its column and finite elsewhere.  32x32, 64x64 and 128x128 tiles."""
+    D = 72
+    c = B.make_cfg(n_blocks=1, d_model=D, n_heads=1, d_mlp=D, seq_len=tokens, batch=batch, mode="bf16")
+    params = torch.zeros(B.rev_stack_param_count(c), device="cuda", dtype=torch.bfloat16)
+    b_fc1, n = B.rev_stack_param_offset(c, 0, 9)
+    params[b_fc1:b_fc1 + n] = 1.0                                   # the activation is gelu(1) everywhere
+    w_fc2, _ = B.rev_stack_param_offset(c, 0, 10)
+    params[w_fc2 + 5 * D + D - 1] = float("inf")
+    X = torch.ones(batch, tokens, D, device="cuda")
+    _, Y2 = B.rev_stack_forward(c, params, X, X)
+    torch.cuda.synchronize()
+    want = torch.ones(D, device="cuda")
+    want[5] = float("inf")
+    assert bool((Y2 == want).all())
