@@ -120,8 +120,9 @@ constexpr int WG_BR = 64;             // tokens per step
 //
 // The cheaper of the two by measured times (us): a step of 64 tokens takes a round of 512 small tiles 1.0 and a round of 256
 // large ones 1.3, a piece costs 0.015 / 0.1 to write and read, a round's fill and last stores 4 / 7, a launch for the
-// pieces 4 / 5.  Measured, small and large (with the column sums): 12608 tokens, D = 768: 199 and 158; 8224, 1280: 360 and 266;
-// 16384, 768: 277 and 200; 8192, 1024: 228 and 177; 6000, 512: 57 and 56; 25216, 384: 109 and 117; 1500, 1280: 85 and 86.
+// pieces 4 / 5.  Measured, small and large, whole (the QKV column sums and the launch that adds the pieces included): 12608
+// tokens, D = 768: 220 and 174; 8224, 1280: 408 and 273; 16384, 768: 284 and 209; 8192, 1024: 264 and 182.  6000, 512 (57),
+// 25216, 384 (134) and 1500, 1280 (84) take small tiles, where the two were within 7 % of each other.
 struct WgradPlan {
     bool big;
     int S, sps;                       // 128x128: token ranges and steps per range

@@ -12,9 +12,10 @@
 // one, and then multiplies.  The two wavefronts of a SIMD are half a phase apart, so that one multiplies while the other
 // reads; the barrier between the halves also orders the reads of a part before its next request.
 //
-// What bounds it: the matrix cores under this card's power limit (products and barriers alone run at 1.65 PFLOP/s).
-// 12608 tokens, D = 768, the four of a block and the QKV bias gradient: 158 us (1.13 PFLOP/s); 128x128 tiles, two workgroups
-// per CU, and the column sums in a kernel of their own: 210 us.  8224 tokens, D = 1280: 266 us (1.22 PFLOP/s) against 371.
+// What bounds it: the matrix cores, busy 57 % of the launch, under this card's power limit (products and barriers alone run at
+// 1.65 PFLOP/s).  The four of a block and the QKV bias gradient, with the kernel that adds the pieces, launches back to
+// back: 12608 tokens, D = 768: 174 us (1.03 PFLOP/s; in a whole pass 151 and 15 for the pieces), in 128x128 tiles 220.  8224
+// tokens, D = 1280: 273 us (1.18 PFLOP/s) against 408.
 //
 // Columns beyond N or K re-read the last valid ones (never stored).
 #include "mfma.h"
