@@ -40,13 +40,14 @@ static bool tall_tiles_pay(int M, int N) {
 //   64x64 up to 384 tiles, and up to the 512 that run at once for short contractions.  1182 rows, N = 768, K = 3072 (228): 14.1,
 //     128x128 34.6.  2364 rows, N = K = 768 (444): 11.1, 64x128 11.7; K = 3072: 28.6 against 24.6.
 //   64x128 in the ring up to 256 tiles.  2364 rows, N = 768, K = 3072 (222): 24.6, the two-stage kernel 29.8.
-//   64x128 in two stages while 128x128 would leave CUs idle and the contraction is long enough to feel it.  2570 rows, N = 1280,
-//     K = 3840 (410): 39.8, 128x128 45.2.  At K = 768 the two are within 5 % of each other, either way.
+//   64x128 in two stages up to 440 tiles of long contractions.  2570 rows, N = 1280, K = 3840 (410): 39.8, 128x128 45.2; 4728
+//     rows, N = 640, K = 2560 (370): 29.4, 32.2; 5300 rows, N = 768, K = 2304 (498): 30.3, 29.6.  At K = 768 and 1024 the
+//     two are within 5 % of each other, either way.
 static GemmShape small_shape(int M, int N, int K) {
     if (tiles_of(M, N, 32, 32) <= 288) return GS_32x32;
     if (tiles_of(M, N, 64, 64) <= (K < 1536 ? 512 : 384)) return GS_64x64;
     if (tiles_of(M, N, 64, 128) <= 256) return GS_64x128_RING;
-    if (tiles_of(M, N, 128, 128) <= 256 && K >= 1024) return GS_64x128;
+    if (tiles_of(M, N, 64, 128) <= 440 && K >= 1280) return GS_64x128;
     return GS_128x128;
 }
 // 160-row tiles (two wavefronts of 160x64) when they turn a short ragged second round of 128-row tiles into a single

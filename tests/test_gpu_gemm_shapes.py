@@ -25,7 +25,7 @@ SHAPES = {
     "groups2_K144": dict(n_blocks=1, d_model=144, n_heads=2, d_mlp=2056, seq_len=150, batch=10),
     # 64x128 tiles in the ring (fc2 and its transpose; a last chunk of 8) and in two stages (proj, fc1, its transpose with column sums)
     "ring64x128_K1544": dict(n_blocks=1, d_model=384, n_heads=6, d_mlp=1544, seq_len=197, batch=23),
-    "two_stage64x128_K1032": dict(n_blocks=1, d_model=1032, n_heads=43, d_mlp=1032, seq_len=95, batch=20),
+    "two_stage64x128_K1288": dict(n_blocks=1, d_model=1288, n_heads=23, d_mlp=1288, seq_len=95, batch=20),
     # few output columns at many rows
     "whole_K72": dict(n_blocks=1, d_model=72, n_heads=1, d_mlp=200, seq_len=31, batch=100),
     "whole_rows3073": dict(n_blocks=1, d_model=64, n_heads=1, d_mlp=136, seq_len=439, batch=7),
