@@ -104,6 +104,12 @@ __device__ __forceinline__ void dma16_sbase(const void* sbase, unsigned voff, un
                  :: "v"(voff), "s"(sbase), "s"(lds_addr) : "memory", "m0");
 }
 
+// The same for 4 bytes per lane (LDS destination + 4 * lane).
+__device__ __forceinline__ void dma4_sbase(const void* sbase, unsigned voff, unsigned lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+                 :: "v"(voff), "s"(sbase), "s"(lds_addr) : "memory", "m0");
+}
+
 // The same with a 64-bit address per lane, for loads that are redirected lane by lane (zeros beyond the contraction).
 __device__ __forceinline__ void dma16_ptr(const void* p, unsigned lds_addr) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(p), "s"(lds_addr) : "memory", "m0");
