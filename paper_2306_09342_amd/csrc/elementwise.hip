@@ -9,17 +9,18 @@
 namespace rev {
 
 // ---- LayerNorm forward -----------------------------------------------------------
-// Lane l of the row's wavefront holds 4-element chunks l, l+64, ... (MAXJ of them).  A wavefront
-// handles two rows (rows w and w + M/2-ish apart are both requested before either is reduced), so
-// every lane has two independent memory round trips in flight.
-template <typename TA, typename TP, int MAXJ>
+// LPR lanes hold a row: lane l of them the 4-element chunks l, l + LPR, ... (MAXJ of them).  Rows of up to 256 floats share a
+// wavefront (pick_row), wider ones have it to themselves.  Every lane handles two rows, half of all rows apart and both
+// requested before either is reduced, so it has two independent memory round trips in flight.  Bound by HBM.  200704 rows
+// of 96: 49 us with a wavefront per row (24 of 64 lanes at work), now 28; 100000 rows of 64: 22 -> 9.6.
+template <typename TA, typename TP, int LPR, int MAXJ>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(const float* __restrict__ x, const TP* __restrict__ g,
                                                      const TP* __restrict__ b, float eps,
                                                      TA* __restrict__ y, float* __restrict__ stats,
                                                      int M, int D) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & (LPR - 1);
     const int half = (M + 1) >> 1;
-    const int r0 = blockIdx.x * 4 + wave;          // rows r0 and r0 + half
+    const int r0 = (blockIdx.x * 256 + threadIdx.x) / LPR;         // rows r0 and r0 + half
     if (r0 >= half) return;
     const int nch = D >> 2;
     int rows[2] = {r0, r0 + half};
@@ -31,34 +32,34 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float* __restrict__ x
         if (k == 1 && !live1) break;
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
-            int c = lane + 64 * j;
+            int c = lane + LPR * j;
             if (c < nch) v[k][j] = load4(xr + 4 * c);
         }
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         if (k == 1 && !live1) break;
-        float s = 0.f;
+        float s[MAXJ], q[MAXJ];
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
-            int c = lane + 64 * j;
-            if (c < nch) s += (v[k][j].x + v[k][j].y) + (v[k][j].z + v[k][j].w);
+            int c = lane + LPR * j;
+            s[j] = c < nch ? (v[k][j].x + v[k][j].y) + (v[k][j].z + v[k][j].w) : 0.f;
         }
-        const float mean = wave_sum(s) / (float)D;
-        float q = 0.f;
+        const float mean = row_sum<LPR, MAXJ>(s) / (float)D;
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
-            int c = lane + 64 * j;
+            int c = lane + LPR * j;
+            q[j] = 0.f;
             if (c < nch) {
                 float a0 = v[k][j].x - mean, a1 = v[k][j].y - mean, a2 = v[k][j].z - mean, a3 = v[k][j].w - mean;
-                q += (a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3);
+                q[j] = (a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3);
             }
         }
-        const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
+        const float rstd = 1.0f / sqrtf(row_sum<LPR, MAXJ>(q) / (float)D + eps);
         TA* yr = y + (int64_t)rows[k] * D;
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
-            int c = lane + 64 * j;
+            int c = lane + LPR * j;
             if (c < nch) {
                 f4 gg = load4(g + 4 * c), bb = load4(b + 4 * c), o;
                 o.x = (v[k][j].x - mean) * rstd * gg.x + bb.x;
@@ -79,13 +80,11 @@ template <typename TA, typename TP>
 int ln_forward(hipStream_t s, const float* x, const TP* g, const TP* b, float eps,
                TA* y, float* stats, int M, int D) {
     ProfScope ps(K_LN_FWD, s, (double)M * D * (4 + sizeof(TA)));
-    dim3 grid(((M + 1) / 2 + 3) / 4), block(256);
-    switch (pick_maxj(D)) {
-#define CASE(J) case J: hipLaunchKernelGGL((ln_fwd_kernel<TA, TP, J>), grid, block, 0, s, x, g, b, eps, y, stats, M, D); break;
-        CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(8) CASE(12) CASE(16) CASE(24) CASE(32)
+    const RowSplit rs = pick_row(D, M >= 16384);       // shared wavefronts only where there are enough of them
+    dim3 grid((unsigned)(((int64_t)((M + 1) / 2) * rs.lpr + 255) / 256)), block(256);
+#define CASE(L, J) if (rs.lpr == L && rs.maxj == J) { hipLaunchKernelGGL((ln_fwd_kernel<TA, TP, L, J>), grid, block, 0, s, x, g, b, eps, y, stats, M, D); } else
+    ROW_SPLITS_WIDE(CASE) ROW_SPLITS_8(CASE) ROW_SPLITS_16(CASE) { set_error("ln_forward: d_model too large"); return REV_EINVAL; }
 #undef CASE
-        default: set_error("ln_forward: d_model too large"); return REV_EINVAL;
-    }
     REV_HIP(hipGetLastError());
     return REV_OK;
 }
@@ -102,36 +101,43 @@ template int ln_forward<bf16, bf16>(hipStream_t, const float*, const bf16*, cons
 constexpr int LNB_ROWS = 32;
 // Rows per block (a multiple of 4): LNB_ROWS for 32 k rows and more; fewer, down to 8, for shorter
 // inputs so that about 1024 blocks (4 per CU) are in flight; more once LNB_ROWS would give above 2048
-// partial rows.
-static int ln_bwd_rows_per_block(int M) {
+// partial rows, and for rows of 772 to 2048 floats (2 to 4 blocks share a CU) where that makes one round of blocks: 8224 rows
+// of 1280 45.8 -> 41.4 us, 16384 of 1024 54 -> 43.
+static int ln_bwd_rows_per_block(int M, int D) {
     int rpb = LNB_ROWS;
     if ((M + rpb - 1) / rpb > 2048) rpb = (((M + 2047) / 2048) + 3) / 4 * 4;
     else if (M < 1024 * LNB_ROWS) rpb = ((M + 1023) / 1024 + 3) / 4 * 4;
     if (rpb < 8) rpb = 8;
+    if (rpb > 8 && D > 768 && D <= 2048) {                          // accumulators in LDS: a second, short round costs a whole one
+        const int slots = 256 * (160 * 1024 / (48 * D)), one_round = ((M + slots - 1) / slots + 3) / 4 * 4;
+        if (one_round > rpb && one_round <= LNB_ROWS) rpb = one_round;
+    }
+    if (rpb > 8 && D <= 128) rpb = (rpb + 31) / 32 * 32;            // shared wavefronts: 32 rows of a block at a time
     return rpb;
 }
 
 // Rows of 1024 floats and more (4+ register chunks per lane): the three column accumulators of a
 // wavefront live in its own slice of LDS instead of registers (lane-private slots, no synchronisation),
 // which roughly halves the register count and doubles the wavefronts in flight.
-template <int MAXJ> struct LnBwdCfg { static constexpr bool ACC_LDS = (MAXJ >= 4 && MAXJ <= 8); };
+template <int LPR, int MAXJ> struct LnBwdCfg { static constexpr bool ACC_LDS = (LPR == 64 && MAXJ >= 4 && MAXJ <= 8); };
 
-template <typename TA, typename TP, int MAXJ>
+template <typename TA, typename TP, int LPR, int MAXJ>
 __global__ __launch_bounds__(256) void ln_bwd_kernel(const TA* __restrict__ dn, const float* __restrict__ x,
                                                      const float* __restrict__ stats, const TP* __restrict__ g,
                                                      const float* __restrict__ r, float* __restrict__ out,
                                                      TA* __restrict__ outb, float* __restrict__ partial,
                                                      int M, int D, int rows_per_block) {
-    constexpr bool ACC_LDS = LnBwdCfg<MAXJ>::ACC_LDS;
+    constexpr bool ACC_LDS = LnBwdCfg<LPR, MAXJ>::ACC_LDS;
+    constexpr int G = 64 / LPR;                                  // rows of a wavefront at a time
     extern __shared__ float lds[];   // [3 * D], or [4][3 * D] with ACC_LDS
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & (LPR - 1), grp = (threadIdx.x & 63) / LPR;
     const int nch = D >> 2;
     constexpr int NACC = ACC_LDS ? 1 : MAXJ;
     f4 ag[NACC], ab[NACC], ao[NACC], gg[MAXJ];
     float* wacc = lds + (ACC_LDS ? wave * 3 * D : 0);            // [dgamma | dbeta | colsum(out)] of this wavefront
 #pragma unroll
     for (int j = 0; j < MAXJ; ++j) {
-        int c = lane + 64 * j;
+        int c = lane + LPR * j;
         gg[j] = (c < nch) ? load4(g + 4 * c) : f4{0.f, 0.f, 0.f, 0.f};
         if (ACC_LDS) {
             if (c < nch) {
@@ -148,20 +154,20 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TA* __restrict__ dn, 
     }
     const int row0 = blockIdx.x * rows_per_block;
     const int row1 = min(M, row0 + rows_per_block);
-    for (int row = row0 + wave; row < row1; row += 4) {
+    for (int row = row0 + wave * G + grp; row < row1; row += 4 * G) {
         const float mean = stats[2 * (int64_t)row], rstd = stats[2 * (int64_t)row + 1];
         const int64_t base = (int64_t)row * D;
         f4 xh[MAXJ], dh[MAXJ], rv[MAXJ];
-        float c1 = 0.f, c2 = 0.f;
+        float p1[MAXJ] = {}, p2[MAXJ] = {};
         // all three input rows are requested up front: one memory round trip per row, not two
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
-            int c = lane + 64 * j;
+            int c = lane + LPR * j;
             if (c < nch) rv[j] = load4(r + base + 4 * c);
         }
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
-            int c = lane + 64 * j;
+            int c = lane + LPR * j;
             if (c < nch) {
                 f4 xv = load4(x + base + 4 * c), d = load4(dn + base + 4 * c);
                 xh[j] = {(xv.x - mean) * rstd, (xv.y - mean) * rstd, (xv.z - mean) * rstd, (xv.w - mean) * rstd};
@@ -177,15 +183,14 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TA* __restrict__ dn, 
                     ag[j % NACC].z += d.z * xh[j].z; ag[j % NACC].w += d.w * xh[j].w;
                 }
                 dh[j] = {d.x * gg[j].x, d.y * gg[j].y, d.z * gg[j].z, d.w * gg[j].w};
-                c1 += (dh[j].x + dh[j].y) + (dh[j].z + dh[j].w);
-                c2 += (dh[j].x * xh[j].x + dh[j].y * xh[j].y) + (dh[j].z * xh[j].z + dh[j].w * xh[j].w);
+                p1[j] = (dh[j].x + dh[j].y) + (dh[j].z + dh[j].w);
+                p2[j] = (dh[j].x * xh[j].x + dh[j].y * xh[j].y) + (dh[j].z * xh[j].z + dh[j].w * xh[j].w);
             }
         }
-        c1 = wave_sum(c1) / (float)D;
-        c2 = wave_sum(c2) / (float)D;
+        const float c1 = row_sum<LPR, MAXJ>(p1) / (float)D, c2 = row_sum<LPR, MAXJ>(p2) / (float)D;
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
-            int c = lane + 64 * j;
+            int c = lane + LPR * j;
             if (c < nch) {
                 f4 o;
                 o.x = rv[j].x + rstd * (dh[j].x - c1 - xh[j].x * c2);
@@ -212,13 +217,26 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TA* __restrict__ dn, 
             prow[i] = ((lds[i] + lds[3 * D + i]) + lds[6 * D + i]) + lds[9 * D + i];
         return;
     }
+    // the rows that shared the wavefront, by halves
+    if constexpr (G > 1) {
+#pragma unroll
+        for (int j = 0; j < NACC; ++j)
+#pragma unroll
+            for (int off = 32; off >= LPR; off >>= 1) {
+                auto fold = [&](f4& v) {
+                    v.x += __shfl_xor(v.x, off, 64); v.y += __shfl_xor(v.y, off, 64);
+                    v.z += __shfl_xor(v.z, off, 64); v.w += __shfl_xor(v.w, off, 64);
+                };
+                fold(ag[j]); fold(ab[j]); fold(ao[j]);
+            }
+    }
     // fold the 4 wavefronts' column accumulators in wavefront order
     for (int w = 0; w < 4; ++w) {
         if (wave == w) {
 #pragma unroll
             for (int j = 0; j < MAXJ; ++j) {
-                int c = lane + 64 * j;
-                if (c < nch) {
+                int c = lane + LPR * j;
+                if (c < nch && grp == 0) {
                     float* pg = lds + 4 * c;
                     float* pb = lds + D + 4 * c;
                     float* po = lds + 2 * D + 4 * c;
@@ -239,6 +257,76 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TA* __restrict__ dn, 
     for (int i = threadIdx.x; i < 3 * D; i += 256) prow[i] = lds[i];
 }
 
+// The same for short inputs (up to 8192 rows of up to 1280 floats): a row per wavefront, 8 in a block, which leave their
+// contributions to the column sums in LDS at once.  A chain of one memory round trip, one barrier and the stores; the kernel above
+// takes its rows in turn and adds its wavefronts one after the other (197 rows of 768: 6.7 us, here 3.8; 1000 of 640:
+// 7.4 -> 4.4).
+constexpr int LNB_SMALL_MAXD = 1280;
+template <typename TA, typename TP, int MAXJ>
+__global__ __launch_bounds__(512) void ln_bwd_small_kernel(const TA* __restrict__ dn, const float* __restrict__ x,
+                                                           const float* __restrict__ stats, const TP* __restrict__ g,
+                                                           const float* __restrict__ r, float* __restrict__ out,
+                                                           TA* __restrict__ outb, float* __restrict__ partial, int M, int D) {
+    extern __shared__ float lds[];   // [8][3 * D]
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nch = D >> 2;
+    const int row = blockIdx.x * 8 + wave;
+    float* slot = lds + wave * 3 * D;
+    const f4 z = {0.f, 0.f, 0.f, 0.f};
+    if (row < M) {
+        const int64_t base = (int64_t)row * D;
+        f4 xv[MAXJ], d[MAXJ], rv[MAXJ], gg[MAXJ];
+#pragma unroll
+        for (int j = 0; j < MAXJ; ++j) {
+            const int c = lane + 64 * j;
+            xv[j] = d[j] = rv[j] = gg[j] = z;
+            if (c < nch) { xv[j] = load4(x + base + 4 * c); d[j] = load4(dn + base + 4 * c); gg[j] = load4(g + 4 * c); rv[j] = load4(r + base + 4 * c); }
+        }
+        const float mean = stats[2 * (int64_t)row], rstd = stats[2 * (int64_t)row + 1];
+        float c1 = 0.f, c2 = 0.f;
+#pragma unroll
+        for (int j = 0; j < MAXJ; ++j) {
+            const int c = lane + 64 * j;
+            xv[j] = {(xv[j].x - mean) * rstd, (xv[j].y - mean) * rstd, (xv[j].z - mean) * rstd, (xv[j].w - mean) * rstd};
+            const f4 h = {d[j].x * gg[j].x, d[j].y * gg[j].y, d[j].z * gg[j].z, d[j].w * gg[j].w};
+            c1 += (h.x + h.y) + (h.z + h.w);
+            c2 += (h.x * xv[j].x + h.y * xv[j].y) + (h.z * xv[j].z + h.w * xv[j].w);
+            if (c < nch) {
+                store4(slot + 4 * c, f4{d[j].x * xv[j].x, d[j].y * xv[j].y, d[j].z * xv[j].z, d[j].w * xv[j].w});
+                store4(slot + D + 4 * c, d[j]);
+            }
+            d[j] = h;
+        }
+        c1 = wave_sum(c1) / (float)D;
+        c2 = wave_sum(c2) / (float)D;
+#pragma unroll
+        for (int j = 0; j < MAXJ; ++j) {
+            const int c = lane + 64 * j;
+            if (c < nch) {
+                f4 o;
+                o.x = rv[j].x + rstd * (d[j].x - c1 - xv[j].x * c2);
+                o.y = rv[j].y + rstd * (d[j].y - c1 - xv[j].y * c2);
+                o.z = rv[j].z + rstd * (d[j].z - c1 - xv[j].z * c2);
+                o.w = rv[j].w + rstd * (d[j].w - c1 - xv[j].w * c2);
+                store4(slot + 2 * D + 4 * c, o);
+                store4(out + base + 4 * c, o);
+                if (outb) store4(outb + base + 4 * c, o);
+            }
+        }
+    } else {
+        for (int c = lane; c < 3 * nch; c += 64) store4(slot + 4 * c, z);
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < 3 * nch; c += 512) {
+        f4 s = z;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+            const f4 v = load4(lds + w * 3 * D + 4 * c);
+            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+        }
+        store4(partial + (int64_t)blockIdx.x * 3 * D + 4 * c, s);
+    }
+}
+
 // out[i] = sum over p (ascending) of partial[p * stride + i]; 4 elements per thread.
 // Elements at or beyond `split4` (in units of 4) go to out2 instead (nullable: dropped).
 __device__ __forceinline__ void reduce_store(float* out, float* out2, int64_t split4, int64_t i, float4 acc) {
@@ -250,8 +338,12 @@ __device__ __forceinline__ void reduce_store(float* out, float* out2, int64_t sp
 struct RedSegDev { const float* partial; float* out; float* out2; int64_t stride, n4, split4; int P, first_block; };
 struct RedArgs { RedSegDev seg[RED_MAX_SEGS]; int nseg; };
 
-// Segments with many partial rows (P > 32) use 16 row-lanes per group of 16 column quads, folded in
-// lane order through LDS; the others one thread per column quad.  Either way the order is fixed.
+// Segments with many partial rows, or few columns and more than 8 rows, use 16 row-lanes per group of 16 column quads, folded
+// in lane order through LDS; the others one thread per column quad.  Either way the order is fixed.  8 loads of a
+// thread are in flight together: with few blocks the launch is a chain of memory round trips (two segments of 25 rows by 2304,
+// one thread per quad, loads one by one: 4.4 us, now 2.6; 1024 rows: 4.7 -> 4.2).
+__host__ __device__ __forceinline__ bool reduce_by_lanes(int P, int64_t n4) { return P > 32 || (P > 8 && n4 <= 16384); }
+
 __global__ __launch_bounds__(256) void reduce_multi_kernel(RedArgs a) {
     __shared__ float4 sh[256];
     int si = 0;
@@ -260,32 +352,37 @@ __global__ __launch_bounds__(256) void reduce_multi_kernel(RedArgs a) {
         if (k < a.nseg && (int)blockIdx.x >= a.seg[k].first_block) si = k;
     const RedSegDev g = a.seg[si];
     const int lb = blockIdx.x - g.first_block;
-    if (g.P > 32) {
+    // adds rows p, p + step, ... of column quad i, ascending
+    auto sum_rows = [&](int p, int step, int64_t i) {
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        const float* q = g.partial + 4 * i;
+        for (; p + 7 * step < g.P; p += 8 * step) {
+            float4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(q + (int64_t)(p + u * step) * g.stride);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
+        }
+        if (p < g.P) {
+            float4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (p + u * step < g.P) v[u] = *reinterpret_cast<const float4*>(q + (int64_t)(p + u * step) * g.stride);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (p + u * step < g.P) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
+        }
+        return acc;
+    };
+    if (reduce_by_lanes(g.P, g.n4)) {
         const int cg = threadIdx.x & 15, pl = threadIdx.x >> 4;
         const int64_t i = (int64_t)lb * 16 + cg;
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (i < g.n4) {
-            // 4 loads in flight per thread; the additions stay in ascending row order
-            int p = pl;
-            for (; p + 48 < g.P; p += 64) {
-                const float* q = g.partial + (int64_t)p * g.stride + 4 * i;
-                const float4 v0 = *reinterpret_cast<const float4*>(q);
-                const float4 v1 = *reinterpret_cast<const float4*>(q + 16 * g.stride);
-                const float4 v2 = *reinterpret_cast<const float4*>(q + 32 * g.stride);
-                const float4 v3 = *reinterpret_cast<const float4*>(q + 48 * g.stride);
-                acc.x += v0.x; acc.y += v0.y; acc.z += v0.z; acc.w += v0.w;
-                acc.x += v1.x; acc.y += v1.y; acc.z += v1.z; acc.w += v1.w;
-                acc.x += v2.x; acc.y += v2.y; acc.z += v2.z; acc.w += v2.w;
-                acc.x += v3.x; acc.y += v3.y; acc.z += v3.z; acc.w += v3.w;
-            }
-            for (; p < g.P; p += 16) {
-                float4 v = *reinterpret_cast<const float4*>(g.partial + (int64_t)p * g.stride + 4 * i);
-                acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-            }
-        }
+        if (i < g.n4) acc = sum_rows(pl, 16, i);
         sh[threadIdx.x] = acc;
         __syncthreads();
         if (pl == 0 && i < g.n4) {
+#pragma unroll
             for (int q = 1; q < 16; ++q) {
                 float4 v = sh[q * 16 + cg];
                 acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
@@ -295,11 +392,7 @@ __global__ __launch_bounds__(256) void reduce_multi_kernel(RedArgs a) {
     } else {
         const int64_t i = (int64_t)lb * 256 + threadIdx.x;
         if (i >= g.n4) return;
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int p = 0; p < g.P; ++p) {
-            float4 v = *reinterpret_cast<const float4*>(g.partial + (int64_t)p * g.stride + 4 * i);
-            acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-        }
+        const float4 acc = sum_rows(0, 1, i);
         reduce_store(g.out, g.out2, g.split4, i, acc);
     }
 }
@@ -316,7 +409,7 @@ int reduce_multi(hipStream_t s, const RedSeg* segs, int nseg) {
         if (g.n % 4 != 0 || g.split % 4 != 0) { set_error("reduce_multi: lengths must be multiples of 4"); return REV_EINVAL; }
         const int64_t n4 = g.n / 4;
         a.seg[k] = {g.partial, g.out, g.out2, g.stride, n4, g.split / 4, g.P, blocks};
-        blocks += (int)(g.P > 32 ? (n4 + 15) / 16 : (n4 + 255) / 256);
+        blocks += (int)(reduce_by_lanes(g.P, n4) ? (n4 + 15) / 16 : (n4 + 255) / 256);
         bytes += (double)(g.P + 1) * g.n * 4;
     }
     ProfScope ps(K_REDUCE, s, bytes);
@@ -326,7 +419,7 @@ int reduce_multi(hipStream_t s, const RedSeg* segs, int nseg) {
 }
 
 int64_t ln_bwd_partial_elems(int M, int D) {
-    const int rpb = ln_bwd_rows_per_block(M);
+    const int rpb = ln_bwd_rows_per_block(M, D);
     return (int64_t)((M + rpb - 1) / rpb) * 3 * D;
 }
 
@@ -334,24 +427,32 @@ template <typename TA, typename TP>
 int ln_backward(hipStream_t s, const TA* dn, const float* x, const float* stats, const TP* g,
                 const float* r, float* out, TA* outb, float* dgb, float* dbias,
                 float* partial, int M, int D, RedSeg* defer) {
-    const int rpb = ln_bwd_rows_per_block(M);
+    const int rpb = ln_bwd_rows_per_block(M, D);
     const int nblk = (M + rpb - 1) / rpb;
     {
         ProfScope ps(K_LN_BWD, s, (double)M * D * (sizeof(TA) + 4 + 4 + 4 + (outb ? sizeof(TA) : 0)));
         dim3 grid(nblk), block(256);
-        switch (pick_maxj(D)) {
-#define CASE(J) case J: {                                                                                            \
-            auto kern = ln_bwd_kernel<TA, TP, J>;                                                                       \
-            constexpr int copies = LnBwdCfg<J>::ACC_LDS ? 4 : 1;                                                        \
+        const bool small = rpb == 8 && D <= LNB_SMALL_MAXD;
+        // rows of 160 to 256 floats, four to a wavefront: 31 us against 28 (50176 rows of 192)
+        const RowSplit rs = pick_row(D, D <= 128 && rpb > 8);
+#define SMALL(J) if (rs.maxj == J) {                                                                                   \
+            auto kern = ln_bwd_small_kernel<TA, TP, J>;                                                                 \
+            static LdsLimit lim;                                                                                        \
+            if (int rc = lim.ensure(reinterpret_cast<const void*>(kern), 96 * LNB_SMALL_MAXD)) return rc;               \
+            hipLaunchKernelGGL(kern, grid, dim3(512), (size_t)96 * D, s, dn, x, stats, g, r, out, outb, partial, M, D); \
+        }
+#define CASE(L, J) if (rs.lpr == L && rs.maxj == J) {                                                                  \
+            auto kern = ln_bwd_kernel<TA, TP, L, J>;                                                                    \
+            constexpr int copies = LnBwdCfg<L, J>::ACC_LDS ? 4 : 1;                                                     \
             const size_t shmem = (size_t)copies * 3 * D * sizeof(float);                                                \
             static LdsLimit lim;                                                                                        \
-            if (int rc = lim.ensure(reinterpret_cast<const void*>(kern), copies * 3 * 64 * J * 16)) return rc;          \
-            hipLaunchKernelGGL(kern, grid, block, shmem, s, dn, x, stats, g, r, out, outb, partial, M, D, rpb);     \
-        } break;
-            CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(8) CASE(12) CASE(16) CASE(24) CASE(32)
+            if (int rc = lim.ensure(reinterpret_cast<const void*>(kern), copies * 3 * L * J * 16)) return rc;           \
+            hipLaunchKernelGGL(kern, grid, block, shmem, s, dn, x, stats, g, r, out, outb, partial, M, D, rpb);         \
+        } else
+        if (small) { SMALL(2) SMALL(3) SMALL(4) SMALL(5) } else
+        ROW_SPLITS_WIDE(CASE) ROW_SPLITS_8(CASE) { set_error("ln_backward: d_model too large"); return REV_EINVAL; }
 #undef CASE
-            default: set_error("ln_backward: d_model too large"); return REV_EINVAL;
-        }
+#undef SMALL
         REV_HIP(hipGetLastError());
     }
     // partial rows are [dgamma(D) | dbeta(D) | colsum(out)(D)]; gamma and beta gradients are adjacent in dgb
