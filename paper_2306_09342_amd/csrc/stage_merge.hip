@@ -13,9 +13,10 @@
 //
 // Tokens are stored window by window (the windows are the attention sequences of the stages), on
 // both sides of the block.  The gather, the average and the LayerNorm are one kernel (a wavefront
-// per output row, the row in registers); its backward is one kernel too, which recomputes the
-// gathered row, applies the LayerNorm backward and scatters the halves to both streams.  The three
-// contractions are the library's GEMM kernels.
+// per output row, the row in registers); its backward is one kernel too, which gathers and normalises the row
+// again, leaves it for the weight gradient, applies the LayerNorm backward and scatters the halves to both streams.  The
+// three contractions are the library's GEMM kernels; dn = dout * W needs no activation, so it goes first and a
+// backward call gathers the rows once.
 #include "common.h"
 #include "rowwise.h"
 
@@ -57,7 +58,7 @@ template <typename TA, typename TP, int MAXJ, bool FUSED>
 __global__ __launch_bounds__(256) void merge_ln_fwd_kernel(const float* __restrict__ X1, const float* __restrict__ X2,
                                                            const TA* __restrict__ Z0,
                                                            const TP* __restrict__ gam, const TP* __restrict__ bet, float eps,
-                                                           TA* __restrict__ n, float* __restrict__ stats, MergeGeom g, int Mo) {
+                                                           TA* __restrict__ n, MergeGeom g, int Mo) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int o = blockIdx.x * 4 + wave;
     if (o >= Mo) return;
@@ -106,22 +107,20 @@ __global__ __launch_bounds__(256) void merge_ln_fwd_kernel(const float* __restri
             store4(nr + 4 * c, r);
         }
     }
-    if (lane == 0) {
-        stats[2 * (int64_t)o] = mean;
-        stats[2 * (int64_t)o + 1] = rstd;
-    }
 }
 
-// ---- LayerNorm backward on the re-gathered row + scatter of the halves to both streams -------------
+// ---- gather, LayerNorm and its backward, scatter of the halves to both streams -------------
 // Each block walks rows_per_block consecutive output rows (4 wavefronts, one row each at a time) and
 // writes one partial row [d gamma | d beta], its wavefronts folded in wavefront order.
-// FUSED: rows are re-gathered from the fused map z0 and their cotangent goes, whole, to dZ0 (activation type);
+// FUSED: rows are gathered from the fused map z0 and their cotangent goes, whole, to dZ0 (activation type);
 // otherwise from the average of X1 and X2, and half of it goes to each of dX1, dX2.
+// Bound by HBM.  It writes the normalised row n here instead of a pass of its own over X1 and X2 (50176 rows of 384, us: 38 and
+// 67 before, now 91 together; with the next row requested a row ahead 87, but 45 instead of 38 for 1536-wide rows).
 template <typename TA, typename TP, int MAXJ, bool FUSED>
 __global__ __launch_bounds__(256) void merge_ln_bwd_kernel(const TA* __restrict__ dn, const float* __restrict__ X1,
                                                            const float* __restrict__ X2, const TA* __restrict__ Z0,
-                                                           const float* __restrict__ stats,
-                                                           const TP* __restrict__ gam, float* __restrict__ dX1,
+                                                           const TP* __restrict__ gam, const TP* __restrict__ bet, float eps,
+                                                           TA* __restrict__ n, float* __restrict__ dX1,
                                                            float* __restrict__ dX2, TA* __restrict__ dZ0,
                                                            float* __restrict__ partial,
                                                            MergeGeom g, int Mo, int rows_per_block) {
@@ -139,26 +138,44 @@ __global__ __launch_bounds__(256) void merge_ln_bwd_kernel(const TA* __restrict_
     const int row0 = blockIdx.x * rows_per_block;
     const int row1 = min(Mo, row0 + rows_per_block);
     for (int o = row0 + wave; o < row1; o += 4) {
-        const float mean = stats[2 * (int64_t)o], rstd = stats[2 * (int64_t)o + 1];
         int src[4];
         merge_sources(g, o, src);
         f4 xh[MAXJ], dh[MAXJ];
-        float c1 = 0.f, c2 = 0.f;
+        float s = 0.f, qs = 0.f, c1 = 0.f, c2 = 0.f;
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
             const int c = lane + 64 * j;
             if (c < nch) {
                 const int q = (4 * c) / C, col = 4 * c - q * C;
                 const int64_t off = (int64_t)src[q] * C + col;
-                const f4 d = load4(dn + (int64_t)o * D4 + 4 * c);
-                f4 zz;
+                dh[j] = load4(dn + (int64_t)o * D4 + 4 * c);
                 if (FUSED) {
-                    zz = load4(Z0 + off);
+                    xh[j] = load4(Z0 + off);
                 } else {
                     const f4 a = load4(X1 + off), b = load4(X2 + off);
-                    zz = {0.5f * (a.x + b.x), 0.5f * (a.y + b.y), 0.5f * (a.z + b.z), 0.5f * (a.w + b.w)};
+                    xh[j] = {0.5f * (a.x + b.x), 0.5f * (a.y + b.y), 0.5f * (a.z + b.z), 0.5f * (a.w + b.w)};
                 }
-                xh[j] = {(zz.x - mean) * rstd, (zz.y - mean) * rstd, (zz.z - mean) * rstd, (zz.w - mean) * rstd};
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < MAXJ; ++j)
+            if (lane + 64 * j < nch) s += (xh[j].x + xh[j].y) + (xh[j].z + xh[j].w);
+        const float mean = wave_sum(s) / (float)D4;
+#pragma unroll
+        for (int j = 0; j < MAXJ; ++j)
+            if (lane + 64 * j < nch) {
+                xh[j] = {xh[j].x - mean, xh[j].y - mean, xh[j].z - mean, xh[j].w - mean};
+                qs += (xh[j].x * xh[j].x + xh[j].y * xh[j].y) + (xh[j].z * xh[j].z + xh[j].w * xh[j].w);
+            }
+        const float rstd = 1.0f / sqrtf(wave_sum(qs) / (float)D4 + eps);
+#pragma unroll
+        for (int j = 0; j < MAXJ; ++j) {
+            const int c = lane + 64 * j;
+            if (c < nch) {
+                const f4 d = dh[j], bb = load4(bet + 4 * c);
+                xh[j] = {xh[j].x * rstd, xh[j].y * rstd, xh[j].z * rstd, xh[j].w * rstd};
+                store4(n + (int64_t)o * D4 + 4 * c, f4{xh[j].x * gg[j].x + bb.x, xh[j].y * gg[j].y + bb.y, xh[j].z * gg[j].z + bb.z,
+                                                       xh[j].w * gg[j].w + bb.w});
                 ab[j].x += d.x; ab[j].y += d.y; ab[j].z += d.z; ab[j].w += d.w;
                 ag[j].x += d.x * xh[j].x; ag[j].y += d.y * xh[j].y; ag[j].z += d.z * xh[j].z; ag[j].w += d.w * xh[j].w;
                 dh[j] = {d.x * gg[j].x, d.y * gg[j].y, d.z * gg[j].z, d.w * gg[j].w};
@@ -248,7 +265,7 @@ static int merge_rows_per_block(int Mo) {
 
 // ---- workspace ---------------------------------------------------------------------------------
 struct MergeLayout {
-    int64_t n, stats, dob, dn, part_ln, part_wg, total;
+    int64_t n, dob, dn, part_ln, part_wg, total;
     int64_t part_wg_elems;
     // fusion by a small MLP only: [X1 | X2], hidden pre-activation and activation, fused map, its cotangent, the
     // hidden cotangent (all [M, .] in the activation type), and the partial sums of the four parameter gradients
@@ -262,7 +279,6 @@ static MergeLayout merge_layout(const rev_merge_cfg& c) {
     int64_t pos = 0;
     auto take = [&](int64_t bytes) { int64_t at = pos; pos += (bytes + 255) / 256 * 256; return at; };
     L.n = take(Mo * 4 * C * es);
-    L.stats = take(Mo * 2 * 4);
     L.dob = take(Mo * 2 * C * es);
     L.dn = take(Mo * 4 * C * es);
     const int rpb = merge_rows_per_block((int)Mo);
@@ -355,16 +371,15 @@ struct MergeRunner {
     }
 
     int gather_ln(hipStream_t s, const float* X1, const float* X2) {
-        if (mlp()) RC(fuse_mlp(s, X1, X2));
         ProfScope ps(K_LN_FWD, s, (double)Mo * 4 * C * (8 + sizeof(T)));
         dim3 grid((Mo + 3) / 4), block(256);
         const T* z0 = mlp() ? at<T>(L.z0) : nullptr;
         switch (pick_maxj(4 * C)) {
 #define CASE(J) case J:                                                                                                      \
             if (mlp()) hipLaunchKernelGGL((merge_ln_fwd_kernel<T, T, J, true>), grid, block, 0, s, X1, X2, z0, gam(), bet(),   \
-                                          c.ln_eps, at<T>(L.n), at<float>(L.stats), g, Mo);                                    \
+                                          c.ln_eps, at<T>(L.n), g, Mo);                                    \
             else hipLaunchKernelGGL((merge_ln_fwd_kernel<T, T, J, false>), grid, block, 0, s, X1, X2, z0, gam(), bet(),        \
-                                    c.ln_eps, at<T>(L.n), at<float>(L.stats), g, Mo);                                          \
+                                    c.ln_eps, at<T>(L.n), g, Mo);                                          \
             break;
             CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(8) CASE(12) CASE(16) CASE(24) CASE(32)
 #undef CASE
@@ -375,6 +390,7 @@ struct MergeRunner {
     }
 
     int forward(hipStream_t s, const float* X1, const float* X2, float* out) {
+        if (mlp()) RC(fuse_mlp(s, X1, X2));
         RC(gather_ln(s, X1, X2));
         Epi e = {}; e.kind = EPI_PLAIN_F32; e.outf = out; e.ldo = 2 * C; e.solo = true;
         if constexpr (kBf16) return gemm_nt_bf16(s, at<T>(L.n), 4 * C, W(), 4 * C, Mo, 2 * C, 4 * C, e);
@@ -383,7 +399,7 @@ struct MergeRunner {
 
     int backward(hipStream_t s, const float* X1, const float* X2, const float* dA, const float* dB,
                  float* dX1, float* dX2, float* dparams) {
-        RC(gather_ln(s, X1, X2));
+        if (mlp()) RC(fuse_mlp(s, X1, X2));
         {
             const int64_t n4 = (int64_t)Mo * 2 * C / 4;
             ProfScope ps(K_CONVERT, s, (double)n4 * 4 * (8 + sizeof(T)));
@@ -395,12 +411,8 @@ struct MergeRunner {
         float* dW = dparams + 8 * C;
         Epi e = {}; e.kind = EPI_PLAIN; e.out = at<T>(L.dn); e.ldo = 4 * C; e.solo = true;
         if constexpr (kBf16) {
-            const WgradItem it = {at<T>(L.dob), 2 * C, at<T>(L.n), 4 * C, 2 * C, 4 * C, dW, nullptr};
-            RC(gemm_wgrad_bf16_group(s, &it, 1, Mo, at<float>(L.part_wg), L.part_wg_elems, segs, &nseg));
             RC(gemm_nn_bf16(s, at<T>(L.dob), 2 * C, W(), 4 * C, Mo, 4 * C, 2 * C, e));
         } else {
-            const WgradF32Item it = {at<T>(L.dob), 2 * C, at<T>(L.n), 4 * C, 2 * C, 4 * C, dW};
-            RC(gemm_wgrad_f32_group(s, &it, 1, Mo));
             RC(gemm_nn_f32(s, at<T>(L.dob), 2 * C, W(), 4 * C, Mo, 4 * C, 2 * C, e));
         }
         const int rpb = merge_rows_per_block(Mo);
@@ -412,10 +424,10 @@ struct MergeRunner {
             switch (pick_maxj(4 * C)) {
 #define CASE(J) case J:                                                                                                      \
                 if (mlp()) hipLaunchKernelGGL((merge_ln_bwd_kernel<T, T, J, true>), grid, block, shmem, s, at<T>(L.dn), X1, X2, \
-                                              at<T>(L.z0), at<float>(L.stats), gam(), dX1, dX2, at<T>(L.dz0),                  \
+                                              at<T>(L.z0), gam(), bet(), c.ln_eps, at<T>(L.n), dX1, dX2, at<T>(L.dz0),         \
                                               at<float>(L.part_ln), g, Mo, rpb);                                               \
                 else hipLaunchKernelGGL((merge_ln_bwd_kernel<T, T, J, false>), grid, block, shmem, s, at<T>(L.dn), X1, X2,     \
-                                        (const T*)nullptr, at<float>(L.stats), gam(), dX1, dX2, (T*)nullptr,                  \
+                                        (const T*)nullptr, gam(), bet(), c.ln_eps, at<T>(L.n), dX1, dX2, (T*)nullptr,         \
                                         at<float>(L.part_ln), g, Mo, rpb);                                                     \
                 break;
                 CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(8) CASE(12) CASE(16) CASE(24) CASE(32)
@@ -423,6 +435,13 @@ struct MergeRunner {
                 default: set_error("merge: d_in too large"); return REV_EINVAL;
             }
             REV_HIP(hipGetLastError());
+        }
+        if constexpr (kBf16) {
+            const WgradItem it = {at<T>(L.dob), 2 * C, at<T>(L.n), 4 * C, 2 * C, 4 * C, dW, nullptr};
+            RC(gemm_wgrad_bf16_group(s, &it, 1, Mo, at<float>(L.part_wg), L.part_wg_elems, segs, &nseg));
+        } else {
+            const WgradF32Item it = {at<T>(L.dob), 2 * C, at<T>(L.n), 4 * C, 2 * C, 4 * C, dW};
+            RC(gemm_wgrad_f32_group(s, &it, 1, Mo));
         }
         // d gamma | d beta are adjacent in the packed layout
         segs[nseg++] = {at<float>(L.part_ln), dparams, nullptr, (int64_t)8 * C, (int64_t)8 * C, (int64_t)8 * C, nblk};
