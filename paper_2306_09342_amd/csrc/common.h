@@ -116,7 +116,7 @@ struct RedSeg {
     int64_t stride, n, split;
     int P;
 };
-constexpr int RED_MAX_SEGS = 8;
+constexpr int RED_MAX_SEGS = 12;
 // All segments in one launch (every length a multiple of 4, nseg <= RED_MAX_SEGS).
 int reduce_multi(hipStream_t s, const RedSeg* segs, int nseg);
 
@@ -225,7 +225,9 @@ template <typename T>
 int colsum(hipStream_t s, const T* in, int64_t ld, int M, int N, float* out, float* partial, RedSeg* defer = nullptr);
 int64_t colsum_partial_elems(int M, int N);
 
-int convert_f32_to_bf16(hipStream_t s, const float* in, bf16* out, int64_t n);
+// out = in in bf16 (nullable) and the column sums of in; their second stage is left for a reduce_multi.  partial:
+// colsum_partial_elems floats, at most M * N
+int convert_colsum(hipStream_t s, const float* in, bf16* out, int M, int N, float* sums, float* partial, RedSeg* defer);
 
 // ---- attention ----------------------------------------------------------------------
 // qkv [B*T, 3D] (q|k|v, head-major inside each), o [B*T, D], lse [B, H, T].

@@ -165,12 +165,9 @@ static Layout make_layout(const rev_cfg& c, bool compact) {
     L.part_ln[0] = take(ln_bwd_partial_elems((int)M, (int)D) * 4);
     L.part_ln[1] = take(ln_bwd_partial_elems((int)M, (int)D) * 4);
     {
-        // [0]: fc1 bias gradient (column-sum strips of the GELU' epilogue);
-        // [1]: the top block's fc2 bias gradient; float32 mode: the QKV bias gradients too
+        // [0]: fc1 bias gradient (column-sum strips of the GELU' epilogue); [1]: float32 mode, the QKV bias gradients
         const int64_t e0 = (int64_t)(c.mode == REV_MODE_BF16 ? gemm_colsum_strips((int)M, (int)Dm, (int)D) : gemm_f32_colsum_strips((int)M, (int)Dm)) * Dm;
-        int64_t e1 = c.mode == REV_MODE_BF16 ? 0 : colsum_partial_elems((int)M, (int)(3 * D));
-        int64_t e1b = colsum_partial_elems((int)M, (int)D);
-        if (e1b > e1) e1 = e1b;
+        const int64_t e1 = c.mode == REV_MODE_BF16 ? 0 : colsum_partial_elems((int)M, (int)(3 * D));
         L.part_col[0] = take(e0 * 4);
         L.part_col[1] = take(e1 * 4);
     }
@@ -311,11 +308,12 @@ struct Runner {
     // y1: first stream of the block's outputs, x2: second stream of its inputs.
     // d1, d2: incoming cotangents (float32); d2b: act-typed copy of d2.
     // o1, o2: outgoing cotangents; o2b: act-typed copy of o2 (nullable).
+    // The second stages of the fixed-order sums are left in segs (five at most from grad_d, six from grad_w) for one launch.
     // done_dqkv (nullable): recorded on s when dh, gY1 and dqkv are complete.
     T* gy1_act(int blk, float* o1) const { return kBf16 ? at<T>(L.gy1b[blk & 1]) : reinterpret_cast<T*>(o1); }
 
     int grad_d(hipStream_t s, int blk, const float* y1, const float* x2, const float* d1, const float* d2,
-               const T* d2b, float* o1, float* o2, T* o2b, hipEvent_t done_dqkv) {
+               const T* d2b, float* o1, float* o2, T* o2b, hipEvent_t done_dqkv, RedSeg* segs, int* n) {
         Slot sl = slot(blk);
         T* dhb = at<T>(L.dh[blk & 1]);
         T* dqkv = at<T>(L.dqkv[blk & 1]);
@@ -323,9 +321,7 @@ struct Runner {
         T* dO = at<T>(L.dO);
         float* pcol0 = at<float>(L.part_col[0]);
         T* gy1b = gy1_act(blk, o1);
-        // second stages of the block's fixed-order sums are gathered and run as one launch at the end
-        RedSeg segs[4];
-        int nseg = 0;
+        int& nseg = *n;
 
         // ---- G branch: dh = (dY2 W2) * gelu'(h); the bias gradient of fc1 (column sums of dh) rides
         // in the epilogue
@@ -353,10 +349,10 @@ struct Runner {
         RC((ln_backward<T, T>(s, dn, x2, sl.st1, P(blk, T_LN1G), d2, o2, kBf16 ? o2b : nullptr,
                               G(blk, T_LN1G), blk > 0 ? G(blk - 1, T_BFC2) : nullptr, at<float>(L.part_ln[1]), M, D,
                               &segs[nseg++])));
-        return reduce_multi(s, segs, nseg);
+        return REV_OK;
     }
 
-    int grad_w(hipStream_t s, int blk, const T* d2b, float* o1) {
+    int grad_w(hipStream_t s, int blk, const T* d2b, float* o1, RedSeg* segs, int* nseg) {
         Slot sl = slot(blk);
         T* dhb = at<T>(L.dh[blk & 1]);
         T* dqkv = at<T>(L.dqkv[blk & 1]);
@@ -368,10 +364,10 @@ struct Runner {
                                         {dhb, Dm, sl.n2, D, Dm, D, G(blk, T_WFC1), nullptr},
                                         {gy1b, D, sl.o, D, D, D, G(blk, T_WPROJ), nullptr},
                                         {dqkv, 3 * D, sl.n1, D, 3 * D, D, G(blk, T_WQKV), G(blk, T_BQKV)}};
-            RedSeg segs[RED_MAX_SEGS];
-            int nseg = 0;
-            RC(gemm_wgrad_bf16_group(s, items, 4, M, at<float>(L.part_wg), L.part_wg_elems, segs, &nseg));
-            return reduce_multi(s, segs, nseg);
+            int n = 0;
+            RC(gemm_wgrad_bf16_group(s, items, 4, M, at<float>(L.part_wg), L.part_wg_elems, segs + *nseg, &n));
+            *nseg += n;
+            return REV_OK;
         }
         if constexpr (!kBf16) {
             const WgradF32Item items[4] = {{d2b, D, sl.a, Dm, D, Dm, G(blk, T_WFC2)}, {dhb, Dm, sl.n2, D, Dm, D, G(blk, T_WFC1)},
@@ -437,17 +433,20 @@ struct Runner {
             sr = sv;
         }
         const T* top2b = nullptr;
+        RedSeg segs[RED_MAX_SEGS];
+        int nseg = 0;
+        auto reduce = [&](hipStream_t s, RedSeg* which, int* n) -> int {
+            const int rc = reduce_multi(s, which, *n);
+            *n = 0;
+            return rc;
+        };
         if (doV) {
-            // fc2 bias gradient of the top block: column sums of the incoming dY2 (lower blocks get
-            // theirs from the LayerNorm-backward kernel that produces their dY2)
-            RC(colsum<float>(sv, dY2, D, M, D, G(N - 1, T_BFC2), at<float>(L.part_col[1])));
-            if constexpr (kBf16) {
-                T* b = at<T>(L.cot2b[N % 3]);
-                RC(convert_f32_to_bf16(sv, dY2, b, (int64_t)M * D));
-                top2b = b;
-            } else {
-                top2b = reinterpret_cast<const T*>(dY2);
-            }
+            // the incoming dY2 in the activation type, and the fc2 bias gradient of the top block: its column sums (lower
+            // blocks get theirs from the LayerNorm-backward kernel that produces their dY2).  The partial sums are added with
+            // those of D_N; until then they lie in the cotangent level that D_{N-1} is the first to write.
+            T* b = kBf16 ? at<T>(L.cot2b[N % 3]) : nullptr;
+            RC(convert_colsum(sv, dY2, reinterpret_cast<bf16*>(b), M, D, G(N - 1, T_BFC2), at<float>(L.cot[N & 1][0]), &segs[nseg++]));
+            top2b = kBf16 ? b : reinterpret_cast<const T*>(dY2);
         }
         auto run_R = [&](int i) -> int {   // i = N..1 (1-based block index)
             const float* y1 = (i == N) ? Y1 : res(i, 0, X1o, X2o);
@@ -467,7 +466,7 @@ struct Runner {
             float* o2 = (i == 1) ? dX2 : at<float>(L.cot[(i - 1) & 1][1]);
             T* o2b = nullptr;
             if constexpr (kBf16) o2b = (i == 1) ? nullptr : at<T>(L.cot2b[(i - 1) % 3]);
-            return grad_d(sv, i - 1, y1, x2, d1, d2, d2b_of(i), o1_of(i), o2, o2b, done_dqkv);
+            return grad_d(sv, i - 1, y1, x2, d1, d2, d2b_of(i), o1_of(i), o2, o2b, done_dqkv, segs, &nseg);
         };
         if (two) {
             RC(run_R(N));
@@ -477,6 +476,7 @@ struct Runner {
                 REV_HIP(hipStreamWaitEvent(sv, E(i, E_R), 0));
                 if (!kBf16 && i + 1 <= N) REV_HIP(hipStreamWaitEvent(sv, E(i + 1, E_W), 0));
                 RC(run_D(i, E(i, E_DQKV)));
+                RC(reduce(sv, segs, &nseg));
                 if (i > 2) REV_HIP(hipEventRecord(E(i, E_D), sv));
                 // ---- R_{i-1}, then W_i, on the recompute stream
                 if (i - 1 >= 1) {
@@ -485,7 +485,10 @@ struct Runner {
                     REV_HIP(hipEventRecord(E(i - 1, E_R), sr));
                 }
                 REV_HIP(hipStreamWaitEvent(sr, E(i, E_DQKV), 0));
-                RC(grad_w(sr, i - 1, d2b_of(i), o1_of(i)));
+                RedSeg wsegs[RED_MAX_SEGS];
+                int nw = 0;
+                RC(grad_w(sr, i - 1, d2b_of(i), o1_of(i), wsegs, &nw));
+                RC(reduce(sr, wsegs, &nw));
                 if (!kBf16 && i > 1) REV_HIP(hipEventRecord(E(i, E_W), sr));
             }
         } else {
@@ -493,7 +496,8 @@ struct Runner {
                 if (doR) RC(run_R(i));
                 if (doV) {
                     RC(run_D(i, nullptr));
-                    RC(grad_w(sv, i - 1, d2b_of(i), o1_of(i)));
+                    RC(grad_w(sv, i - 1, d2b_of(i), o1_of(i), segs, &nseg));
+                    RC(reduce(sv, segs, &nseg));
                 }
             }
         }
