@@ -1,7 +1,7 @@
 // bf16 matrix-core GEMM entry points.
 //
 //  gemm_nt_bf16 / gemm_nn_bf16   C = A * B^T  /  C = A * B  with fused epilogue: picks the tile (gemm_nt_dma.hip,
-//            gemm_ring.hip).  No choice changes the order of an output's sums.
+//            gemm_ring.hip, gemm_big.hip).  No choice changes the order of an output's sums.
 //  gemm_wgrad_bf16_group         dW[N,K] = G[M,N]^T * A[M,K], up to four in a launch: picks the tile (gemm_wgrad_dma.hip,
 //            gemm_wgrad_big.hip) and the number of token ranges; the pieces of the ranges are summed afterwards in
 //            range order, so results do not depend on scheduling.
@@ -55,14 +55,47 @@ static GemmShape small_shape(int M, int N, int K) {
 // anyway and the larger LDS footprint keeps the neighbour out (measured: sequential schedule faster, parallel schedule
 // 5 % slower).  Not with fused column sums (their strips are 64 rows) and not with a short last
 // stage (the extra address registers would not fit next to 160 accumulators).
+// 256x256 tiles (gemm_big.hip), one workgroup per CU, against 128x128 or 160x128 ones, two per CU.  Times in us, fitted to 93
+// launches of M = 3000 ... 40000, D = 384 ... 1280 (the eight products of a block): a stage of 64 of K takes a round of 512
+// small tiles 1.12 and a round of 256 large ones 0.78 + 0.5 * (the share of the CUs that have one: the power limit); the
+// rest of a round (first loads, epilogue) by what the epilogue does.  Measured, 160x128 or 128x128 / 256x256: M = 16384, N = 768, K =
+// 3072: 92 / 64 (input gradient), 103 / 78 (residual); N = 3072, K = 768: 114 / 92 (GELU), 116 / 102 (GELU'); M = 8224, N = 1280, K =
+// 5120: 125 / 90, 156 / 104; M = 8192, N = 1024, K = 4096 (128 tiles): 66 / 72; M = 12608, N = K = 768 (150 tiles): 27.1 /
+// 28.7; M = 25216, N = 384, K = 1536: 40 / 43.
+// Next to another stream's kernels a partly filled round costs only the CUs it takes, so there the work per CU decides, unless the
+// launch by itself would take much longer.  A launch with column sums decides like that under both schedules: their
+// strips depend on the tile, so that both add the same ones.
+static bool big_tiles_pay(int M, int N, int K, int kind, bool solo, bool tall) {
+    if (M < 256 || N < 256 || K % 128 != 0) return false;
+    const int st = K / 64, t128 = tiles_of(M, N, 128, 128), t256 = tiles_of(M, N, 256, 256), rounds = (t256 + 255) / 256;
+    double small_rest = 4.4, big_rest = 8.0;
+    switch (kind) {
+        case EPI_BIAS: small_rest = 3.0; break;
+        case EPI_BIAS_GELU: small_rest = 7.0; big_rest = 15.0; break;
+        case EPI_RESIDUAL: case EPI_PLAIN_F32: small_rest = 8.0; big_rest = 17.0; break;
+        case EPI_GELU_BWD: small_rest = 7.0; big_rest = 18.0; break;
+        default: break;
+    }
+    const double small = rounds_cost(t128) * (st * 1.12 + small_rest);
+    const double big = rounds * (st * (0.78 + 0.5 * t256 / (256.0 * rounds)) + big_rest);
+    if (!solo) return t256 * (st * 1.28 + big_rest) < 0.85 * 0.5 * t128 * (st * 1.12 + small_rest) && big < 1.1 * small;
+    return big < (tall ? std::fmin(small, rounds_cost(tiles_of(M, N, 160, 128)) * (st * 1.13 + 1.6 * small_rest)) : small);
+}
 static GemmShape pick_gemm_shape(int M, int N, int K, const Epi& epi) {
     const GemmShape sh = small_shape(M, N, K);
-    if (sh == GS_128x128 && epi.solo && epi.colsum == nullptr && K % 64 == 0 && tall_tiles_pay(M, N)) return GS_160x128;
-    return sh;
+    if (sh != GS_128x128) return sh;
+    const bool tall = epi.solo && epi.colsum == nullptr && K % 64 == 0 && tall_tiles_pay(M, N);
+    if (big_tiles_pay(M, N, K, epi.kind, epi.solo && epi.colsum == nullptr, tall)) return GS_256x256;
+    return tall ? GS_160x128 : sh;
 }
 
 int gemm_colsum_strips(int M, int N, int K) {
-    switch (small_shape(M, N, K)) {
+    Epi e = {};
+    e.kind = EPI_GELU_BWD;
+    float sums;
+    e.colsum = &sums;                                         // a launch with column sums
+    switch (pick_gemm_shape(M, N, K, e)) {
+        case GS_256x256: return (M + 255) / 256 * 4;
         case GS_32x32: return (M + 31) / 32;
         case GS_64x64: case GS_64x128_RING: case GS_64x128: return (M + 63) / 64;
         default: return (M + 127) / 128 * 2;              // 64-row strips
@@ -71,6 +104,7 @@ int gemm_colsum_strips(int M, int N, int K) {
 
 int gemm_bf16_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
                   int M, int N, int K, const Epi& epi, bool b_kmajor, GemmShape shape);
+int gemm_bf16_big(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi, bool b_kmajor);
 int gemm_bf16_ring(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
                    const Epi& epi, bool b_kmajor, GemmShape shape);
 
@@ -88,6 +122,7 @@ static int gemm_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, i
     // than half a bf16 step below -2 (12 of them at -3), and pays only where the epilogue is a large share of the launch.
     if (K % 32 && (epi.kind == EPI_BIAS_GELU || epi.kind == EPI_GELU_BWD)) epi.kind |= EPI_ERF;
     if (shape == GS_32x32 || shape == GS_64x64 || shape == GS_64x128_RING) return gemm_bf16_ring(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
+    if (shape == GS_256x256) return gemm_bf16_big(s, A, lda, B, ldb, M, N, K, epi, b_kmajor);
     return gemm_bf16_dma(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
 }
 
