@@ -615,7 +615,8 @@ __global__ __launch_bounds__(512) void attn_bwd_fused(const bf16* __restrict__ q
     const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 5;
-    const int bh = blockIdx.x, b = bh / H, h = bh % H;
+    // two heads of 32 features share a cache line: neighbours go to one XCD's L2 (a stage of 49-token windows: 1886 -> 1869 us)
+    const int bh = DH == 32 ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x, b = bh / H, h = bh % H;
     const int D = H * dh;
     const int64_t ld = 3 * (int64_t)D;
     const bf16* base = qkv + (int64_t)b * T * ld + h * dh;
