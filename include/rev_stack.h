@@ -15,7 +15,7 @@
  * uses the biased variance and eps = cfg.ln_eps; attention is softmax(q k^T /
  * sqrt(head_dim)) v with no mask and no dropout; GELU is the erf form x*Phi(x)
  * (REV_MODE_FP32 evaluates erf; REV_MODE_BF16 evaluates Phi with a fitted
- * polynomial of absolute error < 6.5e-5 on |x| <= 3.8 and takes exactly 0 / 1
+ * polynomial of absolute error < 3.3e-5 on |x| <= 4 and takes exactly 0 / 1
  * beyond if d_model is a multiple of 32, and evaluates erf if it is not); every
  * linear map has a bias.
  *

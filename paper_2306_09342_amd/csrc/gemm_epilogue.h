@@ -5,31 +5,31 @@
 
 namespace rev {
 
-// Normal CDF for the bf16 GELU epilogues: Phi(x) = 1/2 + x * P(x^2) on |x| <= 3.8 with a degree-6 minimax-fitted P
-// (absolute error < 6.5e-5 there; plain FMAs, no transcendental), and exactly 0 / 1 beyond, so that gelu(x) is exactly
-// 0 for x < -3.8 (the true value is below 2.8e-4 in magnitude and shrinking) and exactly x for x > 3.8.  The bound is an
-// absolute one: relative to the small negative-tail values of gelu it is not small (4.6 % at x = -3).
-// The density, needed by the derivative only, is one exp.
+// Normal CDF for the bf16 GELU epilogues: Phi(x) = 1/2 + x * P(x^2) on |x| <= 4 with a degree-7 minimax P that is held to 1/8 at
+// x^2 = 16, so that it is exactly 0 / 1 from there on without a comparison: gelu(x) is exactly 0 for x <= -4 (the true value
+// is below 1.3e-4 in magnitude and shrinking) and exactly x for x >= 4.  Absolute error < 3.3e-5 (one instruction per
+// term, no transcendental; degree 6 on |x| <= 3.8 with two comparisons: 7.2e-5 and four instructions more, which the
+// epilogues of the wide GEMMs are bound by).  The bound is an absolute one: relative to the small negative-tail values of gelu it
+// is not small (2.4 % at x = -3).  The density, needed by the derivative only, is one exp2.
 __device__ __forceinline__ float gelu_cdf(float x) {
-    const float xc = fminf(fmaxf(x, -3.8f), 3.8f);
+    const float xc = __builtin_amdgcn_fmed3f(x, -4.0f, 4.0f);
     const float u = xc * xc;
-    float p = 3.665773107e-08f;
-    p = p * u - 2.272460051e-06f;
-    p = p * u + 6.068476796e-05f;
-    p = p * u - 9.315473144e-04f;
-    p = p * u + 9.316634387e-03f;
-    p = p * u - 6.571978331e-02f;
-    p = p * u + 3.986767530e-01f;
-    float r = 0.5f + xc * p;
-    r = x < -3.8f ? 0.f : r;
-    r = x > 3.8f ? 1.f : r;
-    return r;
+    float p = -1.275765493e-09f;
+    p = fmaf(p, u, 1.043133153e-07f);
+    p = fmaf(p, u, -3.706616098e-06f);
+    p = fmaf(p, u, 7.615501090e-05f);
+    p = fmaf(p, u, -1.020826516e-03f);
+    p = fmaf(p, u, 9.580695070e-03f);
+    p = fmaf(p, u, -6.606313586e-02f);
+    p = fmaf(p, u, 3.988051414e-01f);
+    return fmaf(xc, p, 0.5f);
 }
 // EPI_ERF: the erf form instead.  It goes with contractions that are no multiple of 32 (gemm_mfma.hip).
 template <bool ERF> __device__ __forceinline__ float gelu_cdf_of(float x) {
     return ERF ? 0.5f * (1.0f + erff(x * 0.70710678118654752f)) : gelu_cdf(x);
 }
-__device__ __forceinline__ float gelu_pdf(float x) { return 0.39894228040143268f * __expf(-0.5f * x * x); }
+// exp(-x^2 / 2) / sqrt(2 pi), both constants in the exponent
+__device__ __forceinline__ float gelu_pdf(float x) { return __builtin_amdgcn_exp2f(fmaf(x * x, -0.72134752044448170f, -1.3257480647361593f)); }
 
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));

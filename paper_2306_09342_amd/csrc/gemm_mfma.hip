@@ -118,8 +118,8 @@ static int gemm_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, i
     }
     ProfScope ps(K_GEMM_NT, s, 2.0 * M * N * K);
     const GemmShape shape = pick_gemm_shape(M, N, K, epi);
-    // Widths that are no multiple of 32 take GELU in its erf form.  The polynomial is off by up to 2.7e-4 in the value, more
-    // than half a bf16 step below -2 (12 of them at -3), and pays only where the epilogue is a large share of the launch.
+    // Widths that are no multiple of 32 take GELU in its erf form.  The polynomial is off by up to 1.3e-4 in the value, more
+    // than half a bf16 step below -2.1 (six of them at -3), and pays only where the epilogue is a large share of the launch.
     if (K % 32 && (epi.kind == EPI_BIAS_GELU || epi.kind == EPI_GELU_BWD)) epi.kind |= EPI_ERF;
     if (shape == GS_32x32 || shape == GS_64x64 || shape == GS_64x128_RING) return gemm_bf16_ring(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
     if (shape == GS_256x256) return gemm_bf16_big(s, A, lda, B, ldb, M, N, K, epi, b_kmajor);
