@@ -25,7 +25,7 @@ import tempfile
 
 from . import build as _b
 
-SOURCES = ("gemm_nt_dma.hip", "gemm_wgrad_dma.hip", "gemm_wgrad_big.hip", "gemm_big.hip", "attention_dma.hip")
+SOURCES = ("gemm_nt_dma.hip", "gemm_wgrad_dma.hip", "gemm_wgrad_big.hip", "gemm_big.hip", "gemm_mid.hip", "attention_dma.hip")
 
 _REG = re.compile(r"\b([va])(?:(\d+)|\[(\d+):(\d+)\])")
 _VM_LOAD = ("global_load", "buffer_load", "scratch_load", "flat_load")

@@ -1,7 +1,7 @@
 // bf16 matrix-core GEMM entry points.
 //
 //  gemm_nt_bf16 / gemm_nn_bf16   C = A * B^T  /  C = A * B  with fused epilogue: picks the tile (gemm_nt_dma.hip,
-//            gemm_ring.hip, gemm_big.hip).  No choice changes the order of an output's sums.
+//            gemm_ring.hip, gemm_big.hip, gemm_mid.hip).  No choice changes the order of an output's sums.
 //  gemm_wgrad_bf16_group         dW[N,K] = G[M,N]^T * A[M,K], up to four in a launch: picks the tile (gemm_wgrad_dma.hip,
 //            gemm_wgrad_big.hip) and the number of token ranges; the pieces of the ranges are summed afterwards in
 //            range order, so results do not depend on scheduling.
@@ -81,9 +81,19 @@ static bool big_tiles_pay(int M, int N, int K, int kind, bool solo, bool tall) {
     if (!solo) return t256 * (st * 1.28 + big_rest) < 0.85 * 0.5 * t128 * (st * 1.12 + small_rest) && big < 1.1 * small;
     return big < (tall ? std::fmin(small, rounds_cost(tiles_of(M, N, 160, 128)) * (st * 1.13 + 1.6 * small_rest)) : small);
 }
+// 256x128 tiles (gemm_mid.hip), two workgroups per CU, whose epilogues run beside the other's products: the GELU epilogues over
+// short contractions, from more than two rounds of 512 on.  256x256 or 128x128 / 256x128, us: GELU' M = 25216, N = 1536, K = 384
+// (1188 tiles): 72 / 63; N = 2048, K = 512: 110 / 94; M = 7289, N = 1536, K = 384 (348): 24.7 / 25.0; M = 12608, N = 3072, K = 768:
+// 97 / 85 alone, but next to the other stream's kernels a pass of Rev-ViT-B takes 9.16 ms with them and 9.00 without.  GELU
+// M = 50000, N = 1024, K = 256: 82 / 71; M = 25216, N = 1536, K = 384: 69 / 67; N = 2048, K = 512: 98 / 99; M = 30000: 106 / 116.
+static bool mid_tiles_pay(int M, int N, int K, int kind) {
+    if (M < 256 || N < 128 || K % 64 != 0 || tiles_of(M, N, 256, 128) <= 1024) return false;
+    return (kind == EPI_GELU_BWD && K <= 512) || (kind == EPI_BIAS_GELU && K <= 384);
+}
 static GemmShape pick_gemm_shape(int M, int N, int K, const Epi& epi) {
     const GemmShape sh = small_shape(M, N, K);
     if (sh != GS_128x128) return sh;
+    if (mid_tiles_pay(M, N, K, epi.kind)) return GS_256x128;
     const bool tall = epi.solo && epi.colsum == nullptr && K % 64 == 0 && tall_tiles_pay(M, N);
     if (big_tiles_pay(M, N, K, epi.kind, epi.solo && epi.colsum == nullptr, tall)) return GS_256x256;
     return tall ? GS_160x128 : sh;
@@ -95,7 +105,7 @@ int gemm_colsum_strips(int M, int N, int K) {
     float sums;
     e.colsum = &sums;                                         // a launch with column sums
     switch (pick_gemm_shape(M, N, K, e)) {
-        case GS_256x256: return (M + 255) / 256 * 4;
+        case GS_256x256: case GS_256x128: return (M + 255) / 256 * 4;
         case GS_32x32: return (M + 31) / 32;
         case GS_64x64: case GS_64x128_RING: case GS_64x128: return (M + 63) / 64;
         default: return (M + 127) / 128 * 2;              // 64-row strips
@@ -105,6 +115,7 @@ int gemm_colsum_strips(int M, int N, int K) {
 int gemm_bf16_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
                   int M, int N, int K, const Epi& epi, bool b_kmajor, GemmShape shape);
 int gemm_bf16_big(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi, bool b_kmajor);
+int gemm_bf16_mid(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi, bool b_kmajor);
 int gemm_bf16_ring(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
                    const Epi& epi, bool b_kmajor, GemmShape shape);
 
@@ -122,6 +133,7 @@ static int gemm_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, i
     // than half a bf16 step below -2.1 (six of them at -3), and pays only where the epilogue is a large share of the launch.
     if (K % 32 && (epi.kind == EPI_BIAS_GELU || epi.kind == EPI_GELU_BWD)) epi.kind |= EPI_ERF;
     if (shape == GS_32x32 || shape == GS_64x64 || shape == GS_64x128_RING) return gemm_bf16_ring(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
+    if (shape == GS_256x128 && b_kmajor == (epi.kind == EPI_GELU_BWD)) return gemm_bf16_mid(s, A, lda, B, ldb, M, N, K, epi, b_kmajor);
     if (shape == GS_256x256) return gemm_bf16_big(s, A, lda, B, ldb, M, N, K, epi, b_kmajor);
     return gemm_bf16_dma(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
 }

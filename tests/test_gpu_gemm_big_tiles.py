@@ -1,5 +1,5 @@
-"""256x256 tiles of the bf16 GEMMs: row and column counts that the last tiles overhang (they are moved back and store only their
-own part), against the oracle, and sample bits against launches that take small tiles."""
+"""256x256 and 256x128 tiles of the bf16 GEMMs: row and column counts that the last tiles overhang (they are moved back and store
+only their own part), against the oracle, and sample bits against launches that take small tiles."""
 import numpy as np
 import pytest
 import torch
@@ -12,8 +12,10 @@ from parity_util import TOL, compare_backward, gpu_cfg, make_case, to_dev
 pytestmark = pytest.mark.gpu
 
 # (width, heads, hidden, tokens, samples): 2561 rows (one beyond ten tiles) and 5128 columns (eight beyond twenty); 4334 rows;
-# 2560 rows and 3840 columns, all tiles whole
-CASES = [(1280, 16, 5128, 197, 13), (768, 12, 3072, 197, 22), (1280, 20, 3840, 64, 40)]
+# 2560 rows and 3840 columns, all tiles whole.  256x128 tiles (fc1 and its transpose): contractions of one, two and three
+# stages, 65807, 33005 and 42007 rows, 520, 1024 and 776 columns
+CASES = [(1280, 16, 5128, 197, 13), (768, 12, 3072, 197, 22), (1280, 20, 3840, 64, 40),
+         (64, 2, 520, 7, 9401), (192, 6, 776, 7, 6001), (128, 2, 1024, 5, 6601)]
 
 
 @pytest.mark.parametrize("width,heads,hidden,tokens,batch", CASES)
@@ -40,5 +42,5 @@ def test_overhanging_tiles_match_the_oracle_and_small_tiles(width, heads, hidden
     assert torch.equal(y1, Y1[:1]) and torch.equal(y2, Y2[:1])
     for k in ("dX1", "dX2", "X1", "X2"):
         assert torch.equal(few[k], res[k][:1]), k
-    ref = O.stack_backward_reversible_chunked(Y1.cpu().numpy(), Y2.cpu().numpy(), blocks, heads, dy1, dy2, chunk=4)
+    ref = O.stack_backward_reversible_chunked(Y1.cpu().numpy(), Y2.cpu().numpy(), blocks, heads, dy1, dy2, chunk=4 if tokens > 50 else 256)
     compare_backward(cfg, res, ref, TOL["bf16"], what=str(cfg))
