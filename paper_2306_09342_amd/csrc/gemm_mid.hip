@@ -1,5 +1,6 @@
-// bf16 GEMM in 256x128 tiles, two workgroups of four wavefronts per CU, for the GELU epilogues over short contractions:
-//   h = A[M,K] * B[N,K]^T + bias, gelu(h)   and, with BKM,   A[M,K] * B[K,N] * gelu'(h);   M >= 256, N >= 128, K a multiple of 64.
+// bf16 GEMM in 256x128 tiles, two workgroups of four wavefronts per CU, for the wide maps over short contractions:
+//   h = A[M,K] * B[N,K]^T + bias, with or without gelu(h)   and, with BKM,   A[M,K] * B[K,N] * gelu'(h);   M >= 256, N >= 128, K
+//   a multiple of 64.
 //
 // 128 columns x 64 rows of each half of the tile per wavefront (weights on the A port, so an accumulator quad holds 4
 // consecutive columns).  A stage is 64 of K in three PARTS of 16 KB (B, rows 0..127 of A, rows 128..255), which travel in that
@@ -11,7 +12,8 @@
 // per product), HBM and vector ALU in the epilogue.  The two workgroups of a CU are not in step, so the epilogue of one runs
 // beside the products of the other: over short contractions that outweighs the slower products.  us, 256x256 or 128x128 tiles
 // / these: M = 25216, N = 1536, K = 384: 72 / 63; N = 2048, K = 512: 110 / 94; with GELU M = 50000, N = 1024, K = 256: 82 / 71.
-// A forward and backward pass of 12 such blocks (width 384, 128 samples of 197): 10.82 -> 10.52 ms.
+// A forward and backward pass of 12 such blocks (width 384, 128 samples of 197): 10.82 -> 10.52 ms.  Without GELU, M = 25216:
+// N = 1152, K = 384: 37.9 / 34.1; N = 1536, K = 512: 59.6 / 51.4 (less than two rounds of these, two and three of the others).
 //
 // The last tile of a row or column of tiles is moved back to end at M or N; what its neighbour also computes is not stored.
 #include "gemm_epilogue.h"
@@ -185,8 +187,8 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(const bf16* __restrict
         for (int p = 0; p < NP; ++p) o[p] = epi_load4<KIND>(epi, row_of(q) + 4 * p, n);
     };
     if (OPND) request(opnd[0], 0);
-    f32x4_t bv = {0.f, 0.f, 0.f, 0.f}, cs = {0.f, 0.f, 0.f, 0.f};
-    if (KIND == EPI_BIAS_GELU) bv = ld_bf16x4(reinterpret_cast<const bf16*>(epi.bias) + n);
+    f32x4_t bv = {0.f, 0.f, 0.f, 0.f}, cs = {0.f, 0.f, 0.f, 0.f}, cs_first = cs;
+    if (KIND == EPI_BIAS || KIND == EPI_BIAS_GELU) bv = ld_bf16x4(reinterpret_cast<const bf16*>(epi.bias) + n);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         if (OPND && q < 3) request(opnd[(q + 1) & 1], q + 1);
@@ -210,13 +212,14 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(const bf16* __restrict
                 }
             }
         }
-        if (KIND == EPI_GELU_BWD && (q & 1) && epi.colsum != nullptr) {
-            // column sums of the wavefront's 64 rows: a strip, four from the tile's first row
+        if (KIND == EPI_GELU_BWD && epi.colsum != nullptr) {
+            // column sums of the wavefront's 64 rows: a strip, four from the tile's first row, in two halves as the 256x256 tiles add them
 #pragma unroll
             for (int off = 16; off < 64; off <<= 1)
 #pragma unroll
                 for (int k = 0; k < 4; ++k) cs[k] += __shfl_xor(cs[k], off, 64);
-            if (rr == 0 && n >= n_first) *reinterpret_cast<f32x4_t*>(epi.colsum + (int64_t)((m_first >> 6) + (q & 2) + wn) * N + n) = cs;
+            if ((q & 1) == 0) cs_first = cs;
+            else if (rr == 0 && n >= n_first) *reinterpret_cast<f32x4_t*>(epi.colsum + (int64_t)((m_first >> 6) + (q & 2) + wn) * N + n) = cs_first + cs;
             cs = f32x4_t{0.f, 0.f, 0.f, 0.f};
         }
     }
@@ -234,8 +237,9 @@ static int launch_mid(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, 
     return REV_OK;
 }
 
-// b_kmajor: the GELU' form; the GELU form otherwise
+// b_kmajor: the GELU' form; the bias or GELU form otherwise
 int gemm_bf16_mid(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi, bool b_kmajor) {
+    if (epi.kind == EPI_BIAS) return launch_mid<EPI_BIAS, false>(s, A, lda, B, ldb, M, N, K, epi);
     return b_kmajor ? launch_mid<EPI_GELU_BWD, true>(s, A, lda, B, ldb, M, N, K, epi) : launch_mid<EPI_BIAS_GELU, false>(s, A, lda, B, ldb, M, N, K, epi);
 }
 
