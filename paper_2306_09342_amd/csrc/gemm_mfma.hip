@@ -105,12 +105,20 @@ static bool mid_fills_better(int M, int N, int K, const Epi& epi) {
     const int t256 = tiles_of(M, N, 256, 256);
     return epi.solo && (epi.kind == EPI_BIAS_GELU || epi.kind == EPI_GELU_BWD) && K <= 768 && t256 > 512 && t256 < 0.85 * 256 * ((t256 + 255) / 256);
 }
+// The narrow outputs of such models beside another stream's kernels, which take the CUs that a partly filled round leaves: fewer
+// operand bytes per product than in 128x128 tiles.  Two-stream backward of six blocks, 128x128 / 256x128, us: D = 384, M = 32000
+// 4423 / 4298, M = 25216 3516 / 3485; D = 192, M = 50176 3051 / 2985; D = 256, M = 50000 4270 / 4247; D = 512, M = 25216 4840 / 4845.
+static bool mid_shares_better(int M, int N, int K, const Epi& epi) {
+    return !epi.solo && (epi.kind == EPI_RESIDUAL || epi.kind == EPI_PLAIN) && M >= 256 && N >= 128 && N <= 384 && K >= 192 && K % 64 == 0 &&
+           tiles_of(M, N, 256, 128) > 256;
+}
 static GemmShape pick_gemm_shape(int M, int N, int K, const Epi& epi) {
     const GemmShape sh = small_shape(M, N, K);
     if (sh != GS_128x128) return sh;
     if (mid_tiles_pay(M, N, K, epi.kind, epi.solo)) return GS_256x128;
     const bool tall = epi.solo && epi.colsum == nullptr && K % 64 == 0 && tall_tiles_pay(M, N);
     if (big_tiles_pay(M, N, K, epi.kind, epi.solo && epi.colsum == nullptr, tall)) return mid_fills_better(M, N, K, epi) ? GS_256x128 : GS_256x256;
+    if (mid_shares_better(M, N, K, epi)) return GS_256x128;
     return tall ? GS_160x128 : sh;
 }
 
@@ -130,7 +138,7 @@ int gemm_colsum_strips(int M, int N, int K) {
 int gemm_bf16_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
                   int M, int N, int K, const Epi& epi, bool b_kmajor, GemmShape shape);
 int gemm_bf16_big(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi, bool b_kmajor);
-int gemm_bf16_mid(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi, bool b_kmajor);
+int gemm_bf16_mid(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi);
 int gemm_bf16_ring(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
                    const Epi& epi, bool b_kmajor, GemmShape shape);
 
@@ -148,7 +156,7 @@ static int gemm_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, i
     // than half a bf16 step below -2.1 (six of them at -3), and pays only where the epilogue is a large share of the launch.
     if (K % 32 && (epi.kind == EPI_BIAS_GELU || epi.kind == EPI_GELU_BWD)) epi.kind |= EPI_ERF;
     if (shape == GS_32x32 || shape == GS_64x64 || shape == GS_64x128_RING) return gemm_bf16_ring(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
-    if (shape == GS_256x128 && b_kmajor == (epi.kind == EPI_GELU_BWD)) return gemm_bf16_mid(s, A, lda, B, ldb, M, N, K, epi, b_kmajor);
+    if (shape == GS_256x128 && b_kmajor == (epi.kind == EPI_GELU_BWD || epi.kind == EPI_PLAIN)) return gemm_bf16_mid(s, A, lda, B, ldb, M, N, K, epi);
     if (shape == GS_256x256) return gemm_bf16_big(s, A, lda, B, ldb, M, N, K, epi, b_kmajor);
     return gemm_bf16_dma(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
 }

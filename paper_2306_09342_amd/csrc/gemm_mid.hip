@@ -1,6 +1,6 @@
 // bf16 GEMM in 256x128 tiles, two workgroups of four wavefronts per CU, for the wide maps over short contractions:
 //   h = A[M,K] * B[N,K]^T + bias, with or without gelu(h)   and, with BKM,   A[M,K] * B[K,N] * gelu'(h);   M >= 256, N >= 128, K
-//   a multiple of 64.
+//   a multiple of 64.  Beside another stream's kernels also for narrow outputs, residual and plain.
 //
 // 128 columns x 64 rows of each half of the tile per wavefront (weights on the A port, so an accumulator quad holds 4
 // consecutive columns).  A stage is 64 of K in three PARTS of 16 KB (B, rows 0..127 of A, rows 128..255), which travel in that
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(const bf16* __restrict
     const int c4 = lane & 15, rr = lane >> 4;
     const int n = n0 + wm * 64 + 4 * c4;
     auto row_of = [&](int q) { return m0 + (q >> 1) * 128 + wn * 64 + (q & 1) * 32 + rr; };
-    constexpr bool OPND = KIND == EPI_GELU_BWD;
+    constexpr bool OPND = KIND == EPI_RESIDUAL || KIND == EPI_GELU_BWD;
     f32x4_t opnd[2][NP];
     auto request = [&](f32x4_t (&o)[NP], int q) {
 #pragma unroll
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(const bf16* __restrict
     };
     if (OPND) request(opnd[0], 0);
     f32x4_t bv = {0.f, 0.f, 0.f, 0.f}, cs = {0.f, 0.f, 0.f, 0.f}, cs_first = cs;
-    if (KIND == EPI_BIAS || KIND == EPI_BIAS_GELU) bv = ld_bf16x4(reinterpret_cast<const bf16*>(epi.bias) + n);
+    if (KIND == EPI_BIAS || KIND == EPI_BIAS_GELU || KIND == EPI_RESIDUAL) bv = ld_bf16x4(reinterpret_cast<const bf16*>(epi.bias) + n);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         if (OPND && q < 3) request(opnd[(q + 1) & 1], q + 1);
@@ -237,10 +237,17 @@ static int launch_mid(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, 
     return REV_OK;
 }
 
-// b_kmajor: the GELU' form; the bias or GELU form otherwise
-int gemm_bf16_mid(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi, bool b_kmajor) {
-    if (epi.kind == EPI_BIAS) return launch_mid<EPI_BIAS, false>(s, A, lda, B, ldb, M, N, K, epi);
-    return b_kmajor ? launch_mid<EPI_GELU_BWD, true>(s, A, lda, B, ldb, M, N, K, epi) : launch_mid<EPI_BIAS_GELU, false>(s, A, lda, B, ldb, M, N, K, epi);
+// GELU' and plain: B as stored, [K, N]; bias, GELU and residual: [N, K]
+int gemm_bf16_mid(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi) {
+    switch (epi.kind) {
+        case EPI_BIAS: return launch_mid<EPI_BIAS, false>(s, A, lda, B, ldb, M, N, K, epi);
+        case EPI_BIAS_GELU: return launch_mid<EPI_BIAS_GELU, false>(s, A, lda, B, ldb, M, N, K, epi);
+        case EPI_RESIDUAL: return launch_mid<EPI_RESIDUAL, false>(s, A, lda, B, ldb, M, N, K, epi);
+        case EPI_GELU_BWD: return launch_mid<EPI_GELU_BWD, true>(s, A, lda, B, ldb, M, N, K, epi);
+        case EPI_PLAIN: return launch_mid<EPI_PLAIN, true>(s, A, lda, B, ldb, M, N, K, epi);
+    }
+    set_error("gemm_bf16: unknown epilogue");
+    return REV_EINVAL;
 }
 
 }  // namespace rev

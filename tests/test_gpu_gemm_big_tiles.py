@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 # (width, heads, hidden, tokens, samples): 2561 rows (one beyond ten tiles) and 5128 columns (eight beyond twenty); 4334 rows;
 # 2560 rows and 3840 columns, all tiles whole.  256x128 tiles (fc1 and its transpose): contractions of one, two and three
-# stages, 65807, 33005 and 42007 rows, 520, 1024 and 776 columns (QKV too in the last, 576 columns); 256x128 tiles on one stream and
+# stages, 65807, 33005 and 42007 rows, 520, 1024 and 776 columns (QKV too in the last, 576 columns, and
+# on two streams its residual and plain products, 192 columns); 256x128 tiles on one stream and
 # 256x256 ones on two, whose column sums have the same bits: 12796 rows, 3064 columns
 CASES = [(1280, 16, 5128, 197, 13), (768, 12, 3072, 197, 22), (1280, 20, 3840, 64, 40),
          (64, 2, 520, 7, 9401), (192, 6, 776, 7, 6001), (128, 2, 1024, 5, 6601), (640, 10, 3064, 7, 1828)]
