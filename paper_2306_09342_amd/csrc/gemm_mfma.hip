@@ -21,9 +21,14 @@ static double rounds_cost(int tiles) {
     const int full = tiles / 512, rem = tiles % 512;
     return full + (rem == 0 ? 0.0 : (rem <= 256 ? 0.55 : 1.0));
 }
-// 160x128 tiles do 1.25x the work of 128x128 ones at about 0.9 of their rate.  Only launches with more than
+// 160-row tiles (two wavefronts of 160x64) when they turn a short ragged second round of 128-row tiles into a single
+// round: they do 1.25x the work of 128x128 ones at about 0.9 of their rate.  Only launches with more than
 // one full round of 128-row tiles are considered: below that the chip is not full and the cost of a
-// partly filled round does not follow the model (measured: the tall tile loses there).
+// partly filled round does not follow the model (measured: the tall tile loses there).  Only for launches that have the device
+// to themselves: next to another stream's kernels that round is filled anyway and the larger LDS footprint keeps the
+// neighbour out (measured: sequential schedule faster, parallel schedule 5 % slower).  Not with fused column sums (their
+// strips are 64 rows) and not with a short last stage (the extra address registers would not fit next to 160 accumulators):
+// pick_gemm_shape.
 static bool tall_tiles_pay(int M, int N) {
     if (tiles_of(M, N, 128, 128) <= 512) return false;
     const double c128 = rounds_cost(tiles_of(M, N, 128, 128)) * 128.0;
@@ -50,36 +55,56 @@ static GemmShape small_shape(int M, int N, int K) {
     if (tiles_of(M, N, 64, 128) <= 440 && K >= 1280) return GS_64x128;
     return GS_128x128;
 }
-// 160-row tiles (two wavefronts of 160x64) when they turn a short ragged second round of 128-row tiles into a single
-// round.  Only for launches that have the device to themselves: next to another stream's kernels that round is filled
-// anyway and the larger LDS footprint keeps the neighbour out (measured: sequential schedule faster, parallel schedule
-// 5 % slower).  Not with fused column sums (their strips are 64 rows) and not with a short last
-// stage (the extra address registers would not fit next to 160 accumulators).
-// 256x256 tiles (gemm_big.hip), one workgroup per CU, against 128x128 or 160x128 ones, two per CU.  Times in us, fitted to 93
-// launches of M = 3000 ... 40000, D = 384 ... 1280 (the eight products of a block): a stage of 64 of K takes a round of 512
-// small tiles 1.12 and a round of 256 large ones 0.78 + 0.5 * (the share of the CUs that have one: the power limit); the
-// rest of a round (first loads, epilogue) by what the epilogue does.  Measured, 160x128 or 128x128 / 256x256: M = 16384, N = 768, K =
-// 3072: 92 / 64 (input gradient), 103 / 78 (residual); N = 3072, K = 768: 114 / 92 (GELU), 116 / 102 (GELU'); M = 8224, N = 1280, K =
-// 5120: 125 / 90, 156 / 104; M = 8192, N = 1024, K = 4096 (128 tiles): 66 / 72; M = 12608, N = K = 768 (150 tiles): 27.1 /
-// 28.7; M = 25216, N = 384, K = 1536: 40 / 43.
-// Next to another stream's kernels a partly filled round costs only the CUs it takes, so there the work per CU decides, unless the
-// launch by itself would take much longer.  A launch with column sums decides like that under both schedules: their
-// strips depend on the tile, so that both add the same ones.
-static bool big_tiles_pay(int M, int N, int K, int kind, bool solo, bool tall) {
+// What a launch takes by itself, in us, by tile: a stage of 64 of K, and what a round spends besides (first loads, epilogue) by
+// what the epilogue does.  Fitted to 1466 launches of M = 400 ... 40000, D = 128 ... 2048 (the products of a block and of a
+// transition; root mean square error 7 %).  A round is 512 workgroups, two per CU, of 128x128 or 160x128 tiles, 256 of 256x256
+// ones.  The workgroups of a launch that does not fill one round run faster, for they share less (two to a CU on some of them;
+// the power limit), and so do those of a last, partly filled round.
+//                                     bias  GELU  residual  GELU'  plain  float32
+static const double REST_128[] =      {5.0,  9.0,  12.0,     10.0,  6.0,   7.5};
+static const double REST_160[] =      {7.7,  13.2, 14.7,     13.2,  8.3,   9.5};
+static const double REST_256[] =      {10.0, 16.0, 22.0,     20.0,  10.5,  11.5};
+static double cost_128(int tiles, double st, int kind) {
+    const int full = tiles / 512;
+    const double x = tiles % 512 / 512.0;
+    const double last = x == 0 ? 0.0 : full ? 0.32 + 0.74 * x : x <= 0.5 ? 0.48 + 0.42 * x : 0.51 + 0.49 * x;
+    return (full + last) * (st * 0.98 + REST_128[kind]);
+}
+static double cost_160(int tiles, double st, int kind) {
+    const int full = tiles / 512;
+    const double x = tiles % 512 / 512.0;
+    const double last = x == 0 ? 0.0 : full ? 0.57 + 0.53 * x : x <= 0.5 ? 0.65 + 0.26 * x : 0.58 + 0.48 * x;
+    return (full + last) * (st * 1.09 + REST_160[kind]);
+}
+static double cost_256(int tiles, double st, int kind) {
+    const int full = tiles / 256;
+    const double x = tiles % 256 / 256.0, rest = REST_256[kind];
+    return full * (st * 1.43 + rest) + (x == 0 ? 0.0 : st * (0.66 + 0.77 * x) + rest * (0.71 + 0.29 * x));
+}
+// 256x256 tiles (gemm_big.hip) for a launch by itself, where they save more than the costs above are off by.  Measured,
+// 128x128 or 160x128 / 256x256, us: M = 16384, N = 768, K = 3072: 92 / 64 (input gradient), 103 / 78 (residual); M = 8224, N = 1280, K =
+// 5120: 125 / 90, 156 / 104; M = 12608, N = K = 1024 (200 tiles), residual: 51 / 44.  Where they leave half of a round empty:
+// M = 1568, N = 2560, K = 1280 (70 tiles; 260 of 128x128): 17.8 / 25.0; M = 8192, N = 1024, K = 4096 (128; 512): 66 / 72; or take a
+// short second one: M = 4100, N = 4096, K = 1024 (272; 1056), GELU: 53 / 59.  Of the 1466 launches they take 589, 18 % faster in
+// the mean; ten of these are 3 to 11 % slower (four of them with column sums, see below).
+// Next to another stream's kernels a partly filled round costs only the CUs it takes, so there the work per CU decides (a tile's
+// time with the chip full of them), unless the launch by itself would take much longer.  Four blocks on two streams, 128x128 /
+// 256x256 tiles, us: D = 1024, M = 5122: 2349 / 2232; D = 1536, M = 4096: 3471 / 3178.
+// A launch with column sums decides by the work per CU under both schedules, and must not take much longer by itself: their strips
+// depend on the tile, so that both add the same ones.  (Rev-ViT-B, two streams, in 128x128 tiles instead: 9.14 ms -> 9.37.)
+enum BigRule { BIG_ALONE, BIG_BESIDE, BIG_SUMS };
+static bool big_tiles_pay(int M, int N, int K, int kind, BigRule rule, bool tall) {
     if (M < 256 || N < 256 || K % 128 != 0) return false;
-    const int st = K / 64, t128 = tiles_of(M, N, 128, 128), t256 = tiles_of(M, N, 256, 256), rounds = (t256 + 255) / 256;
-    double small_rest = 4.4, big_rest = 8.0;
-    switch (kind) {
-        case EPI_BIAS: small_rest = 3.0; break;
-        case EPI_BIAS_GELU: small_rest = 7.0; big_rest = 15.0; break;
-        case EPI_RESIDUAL: case EPI_PLAIN_F32: small_rest = 8.0; big_rest = 17.0; break;
-        case EPI_GELU_BWD: small_rest = 7.0; big_rest = 18.0; break;
-        default: break;
-    }
-    const double small = rounds_cost(t128) * (st * 1.12 + small_rest);
-    const double big = rounds * (st * (0.78 + 0.5 * t256 / (256.0 * rounds)) + big_rest);
-    if (!solo) return t256 * (st * 1.28 + big_rest) < 0.85 * 0.5 * t128 * (st * 1.12 + small_rest) && big < 1.1 * small;
-    return big < (tall ? std::fmin(small, rounds_cost(tiles_of(M, N, 160, 128)) * (st * 1.13 + 1.6 * small_rest)) : small);
+    const double st = K / 64;
+    const int t128 = tiles_of(M, N, 128, 128), t256 = tiles_of(M, N, 256, 256);
+    const double small = cost_128(t128, st, kind), big = cost_256(t256, st, kind);
+    if (rule == BIG_ALONE) return big < 0.95 * (tall ? std::fmin(small, cost_160(tiles_of(M, N, 160, 128), st, kind)) : small);
+    // the constants of the two rules below are those that were fitted next to another stream's kernels
+    static const double small_rest[] = {3.0, 7.0, 8.0, 7.0, 4.4, 8.0}, big_rest[] = {8.0, 15.0, 17.0, 18.0, 8.0, 17.0};
+    const int rounds = (t256 + 255) / 256;
+    const bool work = t256 * (st * 1.28 + big_rest[kind]) < 0.425 * t128 * (st * 1.12 + small_rest[kind]);
+    if (rule == BIG_SUMS) return work && big < 1.05 * small;
+    return work && rounds * (st * (0.78 + 0.5 * t256 / (256.0 * rounds)) + big_rest[kind]) < 1.1 * rounds_cost(t128) * (st * 1.12 + small_rest[kind]);
 }
 // 256x128 tiles (gemm_mid.hip), two workgroups per CU, whose epilogues run beside the other's products.  256x256, 160x128 or
 // 128x128 / 256x128, us:
@@ -117,7 +142,7 @@ static GemmShape pick_gemm_shape(int M, int N, int K, const Epi& epi) {
     if (sh != GS_128x128) return sh;
     if (mid_tiles_pay(M, N, K, epi.kind, epi.solo)) return GS_256x128;
     const bool tall = epi.solo && epi.colsum == nullptr && K % 64 == 0 && tall_tiles_pay(M, N);
-    if (big_tiles_pay(M, N, K, epi.kind, epi.solo && epi.colsum == nullptr, tall)) return mid_fills_better(M, N, K, epi) ? GS_256x128 : GS_256x256;
+    if (big_tiles_pay(M, N, K, epi.kind, epi.colsum ? BIG_SUMS : epi.solo ? BIG_ALONE : BIG_BESIDE, tall)) return mid_fills_better(M, N, K, epi) ? GS_256x128 : GS_256x256;
     if (mid_shares_better(M, N, K, epi)) return GS_256x128;
     return tall ? GS_160x128 : sh;
 }

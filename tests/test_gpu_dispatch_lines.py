@@ -1,0 +1,57 @@
+"""Lines of a dispatch lie where both sides cost about the same: a little more work, or heads twice as wide, must not cost far more
+time in the kernel family that takes it.  Times are the library's own (rev_profile_*), each the least of several passes,
+the two shapes in turn; the limits lie half-way between what a kernel on the wrong side of its line was measured at and what
+the right one takes."""
+import pytest
+import torch
+
+from paper_2306_09342_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _merge(batch, grid, window, width):
+    c = B.make_merge_cfg(batch=batch, grid_h=grid, grid_w=grid, window=window, d_in=width, mode="bf16")
+    rows = batch * grid * grid
+    params = (torch.randn(B.rev_merge_param_count(c), device="cuda") * 0.02).bfloat16()
+    x1, x2 = (torch.randn(rows, width, device="cuda") for _ in range(2))
+    da, db = (torch.randn(rows // 4, 2 * width, device="cuda") for _ in range(2))
+    ws = torch.empty(B.rev_merge_workspace_bytes(c), dtype=torch.uint8, device="cuda")
+    return lambda: B.rev_merge_backward(c, params, x1, x2, da, db, workspace=ws)
+
+
+def _stack(width, heads, tokens, batch):
+    c = B.make_cfg(n_blocks=1, d_model=width, n_heads=heads, d_mlp=64, seq_len=tokens, batch=batch, mode="bf16")
+    params = (torch.randn(B.rev_stack_param_count(c), device="cuda") * 0.02).bfloat16()
+    y1, y2, d1, d2 = (torch.randn(batch, tokens, width, device="cuda") for _ in range(4))
+    ws = B.alloc_workspace(c, reprop_only=True)
+    return lambda: B.rev_stack_backward_reprop(c, params, y1, y2, d1, d2, workspace=ws)
+
+
+def _least(family, runs, passes=12):
+    best = [float("inf")] * len(runs)
+    for i in range(passes + 2):                     # the first two warm up
+        for k, run in enumerate(runs):
+            torch.cuda.synchronize()
+            B.rev_profile_begin()
+            run()
+            torch.cuda.synchronize()
+            ms = B.rev_profile_end()[family][0]
+            if i >= 2:
+                best[k] = min(best[k], 1e3 * ms)
+    return best
+
+
+# name -> (family, smaller shape, larger shape, limit of the ratio of their times)
+CASES = {
+    # input gradient of a transition, 2560 columns, K = 1280: 240 tiles of 128x128 in 1536 rows, 260 in 1568
+    "wide_transition_1536_1568_rows": ("gemm_nt", lambda: _merge(6, 32, 2, 640), lambda: _merge(8, 28, 7, 640), 1.22),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_no_jump_at_the_line(name):
+    family, small, large, limit = CASES[name]
+    a, b = _least(family, (small(), large()))
+    print(f"[case] {name}: {a:.1f} and {b:.1f} us, ratio {b / a:.2f} (limit {limit})", flush=True)
+    assert b <= limit * a, (name, a, b)
