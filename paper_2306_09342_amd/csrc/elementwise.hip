@@ -83,7 +83,7 @@ int ln_forward(hipStream_t s, const float* x, const TP* g, const TP* b, float ep
     const RowSplit rs = pick_row(D, M >= 16384);       // shared wavefronts only where there are enough of them
     dim3 grid((unsigned)(((int64_t)((M + 1) / 2) * rs.lpr + 255) / 256)), block(256);
 #define CASE(L, J) if (rs.lpr == L && rs.maxj == J) { hipLaunchKernelGGL((ln_fwd_kernel<TA, TP, L, J>), grid, block, 0, s, x, g, b, eps, y, stats, M, D); } else
-    ROW_SPLITS_WIDE(CASE) ROW_SPLITS_8(CASE) ROW_SPLITS_16(CASE) { set_error("ln_forward: d_model too large"); return REV_EINVAL; }
+    ROW_SPLITS_WIDE(CASE) ROW_SPLITS_8(CASE) ROW_SPLITS_FWD(CASE) { set_error("ln_forward: d_model too large"); return REV_EINVAL; }
 #undef CASE
     REV_HIP(hipGetLastError());
     return REV_OK;
@@ -103,6 +103,12 @@ constexpr int LNB_ROWS = 32;
 // inputs so that about 1024 blocks (4 per CU) are in flight; more once LNB_ROWS would give above 2048
 // partial rows, and for rows of 772 to 2048 floats (2 to 4 blocks share a CU) where that makes one round of blocks: 8224 rows
 // of 1280 45.8 -> 41.4 us, 16384 of 1024 54 -> 43.
+// Rows of up to 64 floats, and of up to 96 in 100 000 rows and more, share a wavefront (8 lanes each), 32 of a block at a time; beyond,
+// the registers of three and more chunks per lane leave too few wavefronts in flight.  A wavefront per row / shared, us: 64
+// floats, 8200 rows 5.9 / 5.4, 65 536 19 / 17, 200 704 65 / 44; 96 floats, 8200 6.3 / 7.6, 65 536 27 / 30, 100 000 40 / 38, 200 704
+// 75 / 68; 128 floats, 8200 6.4 / 9.8, 65 536 31 / 42, 200 704 88 / 94; rows of 160 to 256 floats, four to a wavefront: 50 176 of
+// 192 28 / 31.
+static bool ln_bwd_shares(int M, int D) { return M > 8192 && (D <= 64 || (D <= 96 && M >= 100000)); }
 static int ln_bwd_rows_per_block(int M, int D) {
     int rpb = LNB_ROWS;
     if ((M + rpb - 1) / rpb > 2048) rpb = (((M + 2047) / 2048) + 3) / 4 * 4;
@@ -112,7 +118,7 @@ static int ln_bwd_rows_per_block(int M, int D) {
         const int slots = 256 * (160 * 1024 / (48 * D)), one_round = ((M + slots - 1) / slots + 3) / 4 * 4;
         if (one_round > rpb && one_round <= LNB_ROWS) rpb = one_round;
     }
-    if (rpb > 8 && D <= 128) rpb = (rpb + 31) / 32 * 32;            // shared wavefronts: 32 rows of a block at a time
+    if (ln_bwd_shares(M, D)) rpb = (rpb + 31) / 32 * 32;
     return rpb;
 }
 
@@ -433,8 +439,7 @@ int ln_backward(hipStream_t s, const TA* dn, const float* x, const float* stats,
         ProfScope ps(K_LN_BWD, s, (double)M * D * (sizeof(TA) + 4 + 4 + 4 + (outb ? sizeof(TA) : 0)));
         dim3 grid(nblk), block(256);
         const bool small = rpb == 8 && D <= LNB_SMALL_MAXD;
-        // rows of 160 to 256 floats, four to a wavefront: 31 us against 28 (50176 rows of 192)
-        const RowSplit rs = pick_row(D, D <= 128 && rpb > 8);
+        const RowSplit rs = pick_row(D, ln_bwd_shares(M, D));
 #define SMALL(J) if (rs.maxj == J) {                                                                                   \
             auto kern = ln_bwd_small_kernel<TA, TP, J>;                                                                 \
             static LdsLimit lim;                                                                                        \

@@ -51,8 +51,8 @@ inline int pick_maxj(int D) {
 // wavefront; row_sum adds the chunks of a row in the same order either way, so the layout is free to follow the clock.
 struct RowSplit { int lpr, maxj; };
 #define ROW_SPLITS_WIDE(X) X(64, 2) X(64, 3) X(64, 4) X(64, 5) X(64, 6) X(64, 8) X(64, 12) X(64, 16) X(64, 24) X(64, 32)
-#define ROW_SPLITS_8(X) X(8, 1) X(8, 2) X(8, 3) X(8, 4)
-#define ROW_SPLITS_16(X) X(16, 3) X(16, 4)
+#define ROW_SPLITS_8(X) X(8, 1) X(8, 2) X(8, 3)
+#define ROW_SPLITS_FWD(X) X(8, 4) X(16, 3) X(16, 4)              // the forward kernel only
 inline RowSplit pick_row(int D, bool shared) {
     const int nch = D / 4;
     if (shared && nch <= 32) return {8, (nch + 7) / 8};

@@ -46,6 +46,8 @@ def _least(family, runs, passes=12):
 CASES = {
     # input gradient of a transition, 2560 columns, K = 1280: 240 tiles of 128x128 in 1536 rows, 260 in 1568
     "wide_transition_1536_1568_rows": ("gemm_nt", lambda: _merge(6, 32, 2, 640), lambda: _merge(8, 28, 7, 640), 1.22),
+    "narrow_rows_128_8192_8200": ("ln_bwd", lambda: _stack(128, 4, 8, 1024), lambda: _stack(128, 4, 8, 1025), 1.3),
+    "narrow_rows_104_8192_8200": ("ln_bwd", lambda: _stack(104, 13, 8, 1024), lambda: _stack(104, 13, 8, 1025), 1.4),
 }
 
 
