@@ -139,6 +139,9 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TA* __restrict__ dn, 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & (LPR - 1), grp = (threadIdx.x & 63) / LPR;
     const int nch = D >> 2;
     constexpr int NACC = ACC_LDS ? 1 : MAXJ;
+    // The chunks' sums: added as they come, or kept apart, whichever is faster (1280 floats, 50176 rows: 238 / 252 us;
+    // 2048 floats, 8192 rows: 101 / 94).  The order is the same.
+    constexpr int NP = LPR == 64 && MAXJ < 8 ? 1 : MAXJ;
     f4 ag[NACC], ab[NACC], ao[NACC], gg[MAXJ];
     float* wacc = lds + (ACC_LDS ? wave * 3 * D : 0);            // [dgamma | dbeta | colsum(out)] of this wavefront
 #pragma unroll
@@ -164,7 +167,7 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TA* __restrict__ dn, 
         const float mean = stats[2 * (int64_t)row], rstd = stats[2 * (int64_t)row + 1];
         const int64_t base = (int64_t)row * D;
         f4 xh[MAXJ], dh[MAXJ], rv[MAXJ];
-        float p1[MAXJ] = {}, p2[MAXJ] = {};
+        float p1[NP] = {}, p2[NP] = {};
         // all three input rows are requested up front: one memory round trip per row, not two
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
@@ -189,11 +192,13 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TA* __restrict__ dn, 
                     ag[j % NACC].z += d.z * xh[j].z; ag[j % NACC].w += d.w * xh[j].w;
                 }
                 dh[j] = {d.x * gg[j].x, d.y * gg[j].y, d.z * gg[j].z, d.w * gg[j].w};
-                p1[j] = (dh[j].x + dh[j].y) + (dh[j].z + dh[j].w);
-                p2[j] = (dh[j].x * xh[j].x + dh[j].y * xh[j].y) + (dh[j].z * xh[j].z + dh[j].w * xh[j].w);
+                const float s1 = (dh[j].x + dh[j].y) + (dh[j].z + dh[j].w);
+                const float s2 = (dh[j].x * xh[j].x + dh[j].y * xh[j].y) + (dh[j].z * xh[j].z + dh[j].w * xh[j].w);
+                p1[j % NP] = NP == 1 ? p1[0] + s1 : s1;
+                p2[j % NP] = NP == 1 ? p2[0] + s2 : s2;
             }
         }
-        const float c1 = row_sum<LPR, MAXJ>(p1) / (float)D, c2 = row_sum<LPR, MAXJ>(p2) / (float)D;
+        const float c1 = row_sum<LPR, NP>(p1) / (float)D, c2 = row_sum<LPR, NP>(p2) / (float)D;
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
             int c = lane + LPR * j;
@@ -265,8 +270,10 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TA* __restrict__ dn, 
 
 // The same for short inputs (up to 8192 rows of up to 1280 floats): a row per wavefront, 8 in a block, which leave their
 // contributions to the column sums in LDS at once.  A chain of one memory round trip, one barrier and the stores; the kernel above
-// takes its rows in turn and adds its wavefronts one after the other (197 rows of 768: 6.7 us, here 3.8; 1000 of 640:
-// 7.4 -> 4.4).
+// takes its rows in turn and adds its wavefronts one after the other.  The kernel above / here, us: 197 rows of 768 6.7 / 3.8; 1000
+// of 640 7.4 / 4.4; 4096 of 768 13.0 / 10.6; 8192 of 640 18.9 / 18.2, of 768 23.1 / 23.3, of 1280 43.3 / 39.8.  Rows of 852 to 1024
+// floats, of which one block here but three or four above fit a CU, only in one round of blocks (2048 rows): 1024 floats,
+// 2000 rows 10.8 / 8.5, 4096 15.2 / 15.7, 6144 24.2 / 25.4, 8192 33.1 / 34.0.
 constexpr int LNB_SMALL_MAXD = 1280;
 template <typename TA, typename TP, int MAXJ>
 __global__ __launch_bounds__(512) void ln_bwd_small_kernel(const TA* __restrict__ dn, const float* __restrict__ x,
@@ -438,7 +445,7 @@ int ln_backward(hipStream_t s, const TA* dn, const float* x, const float* stats,
     {
         ProfScope ps(K_LN_BWD, s, (double)M * D * (sizeof(TA) + 4 + 4 + 4 + (outb ? sizeof(TA) : 0)));
         dim3 grid(nblk), block(256);
-        const bool small = rpb == 8 && D <= LNB_SMALL_MAXD;
+        const bool small = rpb == 8 && D <= LNB_SMALL_MAXD && !(M > 2048 && D > 848 && D <= 1024);
         const RowSplit rs = pick_row(D, ln_bwd_shares(M, D));
 #define SMALL(J) if (rs.maxj == J) {                                                                                   \
             auto kern = ln_bwd_small_kernel<TA, TP, J>;                                                                 \
