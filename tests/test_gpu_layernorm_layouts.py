@@ -13,9 +13,11 @@ from parity_util import TOL, compare_backward, gpu_cfg, make_case, to_dev
 pytestmark = pytest.mark.gpu
 
 # (width, heads, tokens, samples, fewer samples): every layout of narrow rows on both sides of 16384 rows (forward) and 8192
-# (backward); one row, 7, 8 and 9 rows; the widest row of the short kernel and one beyond; accumulators in LDS
+# (backward); one row, 7, 8 and 9 rows; the widest row of the short kernel and one beyond; accumulators in LDS; rows of 1024 on
+# both sides of 2048 rows, of 96 beyond 100000
 CASES = [(32, 1, 7, 2400, 3), (64, 2, 7, 2400, 3), (96, 3, 7, 2400, 1), (128, 4, 7, 2400, 3), (160, 2, 7, 2400, 3), (256, 4, 7, 2400, 3),
-         (264, 11, 7, 1171, 3), (800, 10, 7, 1171, 1), (1280, 16, 9, 1, 1), (1288, 23, 8, 1, 1), (64, 2, 1, 1, 1), (200, 5, 7, 1, 1)]
+         (264, 11, 7, 1171, 3), (800, 10, 7, 1171, 1), (1280, 16, 9, 1, 1), (1288, 23, 8, 1, 1), (64, 2, 1, 1, 1), (200, 5, 7, 1, 1),
+         (1024, 16, 7, 300, 3), (96, 3, 7, 14300, 3)]
 
 
 @pytest.mark.parametrize("mode", ["bf16", "fp32"])
