@@ -141,9 +141,10 @@ __device__ __forceinline__ bf16x8_t res_tr_frag(const unsigned char* tile_r0, in
 // share of a tile; a tile is used after each wavefront has waited for its own share and all have met at a barrier, which
 // is also where the tile before it is known to be free for the next request.  Rows from `rows` on are zeros.
 // NS: 64 floats each of NS row statistics come along (clamped to the last row).
-template <int DH, int NM, int NS>
+// TR: rows a tile has room for (32: only for sequences that are no longer).
+template <int DH, int NM, int NS, int TR = 64>
 struct TileRing {
-    static constexpr int ROWB = 2 * DH, CPR = DH / 8, LPT = DH / 8, TILE = 64 * ROWB, SLOT = NM * TILE + NS * 256;
+    static constexpr int ROWB = 2 * DH, CPR = DH / 8, LPT = DH / 8, TILE = TR * ROWB, SLOT = NM * TILE + NS * 256;
     const bf16* base[NM];
     const float* stat[NS > 0 ? NS : 1];
     int64_t ld[NM];
@@ -203,10 +204,10 @@ struct TileRing {
 };
 
 // ---- forward ----------------------------------------------------------------------------------------------------------
-template <int DH>
+template <int DH, int TR>
 __global__ __launch_bounds__(256, DH == 80 ? 3 : 4) void attn_fwd_dma(const bf16* __restrict__ qkv, bf16* __restrict__ o, float* __restrict__ lse,
                                                     const int* __restrict__ key_len, int T, int H, int nblk) {
-    constexpr int KS = DH / 16, DT = (DH + 31) / 32, ROWB = 2 * DH;
+    constexpr int KS = DH / 16, DT = (DH + 31) / 32, ROWB = 2 * DH, NT = TR / 32;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int lane = threadIdx.x & 63, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(256, DH == 80 ? 3 : 4) void attn_fwd_dma(const bf16
 
     u32x4_t fq[KS];
     res_load_owned<KS>(base, ld, q0, T, lane, fq);
-    TileRing<DH, 2, 0> ring;
+    TileRing<DH, 2, 0, TR> ring;
     ring.base[0] = base + D; ring.base[1] = base + 2 * D; ring.ld[0] = ring.ld[1] = ld;
     ring.init(smem, Tk);
     ring.start();
@@ -244,13 +245,13 @@ __global__ __launch_bounds__(256, DH == 80 ? 3 : 4) void attn_fwd_dma(const bf16
     float m = -INFINITY, l = 0.f;
     for (int j = 0; j < ring.nt; ++j) {
         const unsigned char* Ks = smem + ring.get(j);
-        const unsigned char* Vs = Ks + 64 * ROWB;
+        const unsigned char* Vs = Ks + TR * ROWB;
         const int left = Tk - j * 64;
         if (q0 >= T) continue;
-        f32x16_t s[2];
+        f32x16_t s[NT];
         float mloc = -INFINITY;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
+        for (int t = 0; t < NT; ++t) {
             if (t == 0 || left > 32) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) s[t][v] = 0.f;
@@ -271,7 +272,7 @@ __global__ __launch_bounds__(256, DH == 80 ? 3 : 4) void attn_fwd_dma(const bf16
         const float corr = __builtin_amdgcn_exp2f(m - mn);
         float lsum = 0.f;
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < NT; ++t)
             if (t == 0 || left > 32) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
@@ -287,7 +288,7 @@ __global__ __launch_bounds__(256, DH == 80 ? 3 : 4) void attn_fwd_dma(const bf16
 #pragma unroll
             for (int v = 0; v < 16; ++v) accO[dt][v] *= corr;
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < NT; ++t)
             if (t == 0 || left > 32) {
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
@@ -825,12 +826,12 @@ static void split_rows(int T, int most, int* nblk, int* nw) {
 // 64 bytes more than the tiles: the last transpose reads of 80-wide rows run past the row
 template <typename Ring> static size_t ring_lds(int T) { return (size_t)(T > 64 ? 2 : 1) * Ring::SLOT + 64; }
 
-template <int DH>
+template <int DH, int TR>
 static int fwd_dma(hipStream_t s, const bf16* qkv, bf16* o, float* lse, int B, int T, int H, const int* key_len) {
     int nblk, nw;
     split_rows(T, 4, &nblk, &nw);
-    const size_t lds = ring_lds<TileRing<DH, 2, 0>>(T);
-    hipLaunchKernelGGL(attn_fwd_dma<DH>, dim3(nblk * B * H), dim3(nw * 64), lds, s, qkv, o, lse, key_len, T, H, nblk);
+    const size_t lds = ring_lds<TileRing<DH, 2, 0, TR>>(T);
+    hipLaunchKernelGGL((attn_fwd_dma<DH, TR>), dim3(nblk * B * H), dim3(nw * 64), lds, s, qkv, o, lse, key_len, T, H, nblk);
     REV_HIP(hipGetLastError());
     return REV_OK;
 }
@@ -879,9 +880,15 @@ static int bwd_dma(hipStream_t s, BwdArgs a, int B) {
 
 bool attention_dma_takes(int dh) { return dh == 32 || dh == 64 || dh == 80; }
 int attention_forward_dma(hipStream_t s, const bf16* qkv, bf16* o, float* lse, int B, int T, int H, int dh, const int* key_len) {
-    if (dh == 32) return fwd_dma<32>(s, qkv, o, lse, B, T, H, key_len);
-    if (dh == 64) return fwd_dma<64>(s, qkv, o, lse, B, T, H, key_len);
-    return fwd_dma<80>(s, qkv, o, lse, B, T, H, key_len);
+    // Tiles of 32 rows hold half the LDS, so twice as many one-wavefront workgroups share a CU.  64 rows / 32, us: 64 features, T = 1, 6144
+    // heads 11.5 / 8.5, 49152 69 / 47; T = 16, 3072 heads 8.9 / 7.6, 6144 13.8 / 12.4; but where the rows come from HBM more of
+    // them in flight are slower: T = 16, 49152 heads 108 / 115; T = 24, 12288 heads 41.7 / 46.0; T = 32, 6144 heads 28.4 / 30.7.
+    const bool half = T <= 8 || (T <= 16 && (int64_t)B * H * T <= 131072);
+#define FWD(DH) return half ? fwd_dma<DH, 32>(s, qkv, o, lse, B, T, H, key_len) : fwd_dma<DH, 64>(s, qkv, o, lse, B, T, H, key_len)
+    if (dh == 32) FWD(32);
+    if (dh == 64) FWD(64);
+    FWD(80);
+#undef FWD
 }
 int attention_backward_dma(hipStream_t s, const bf16* qkv, const bf16* o, const bf16* dout, const float* lse, bf16* dqkv, float* delta,
                            int B, int T, int H, int dh, const int* key_len) {

@@ -28,6 +28,10 @@ CASES = [
     (32, 31, (2, 60, 200), False),
     (32, 97, (3, 60, 200), True),
     (32, 257, (2, 70), True),
+    # forward tiles of 32 rows: up to 8 tokens, and up to 16 where heads * tokens <= 131072
+    (32, 8, (2, 60), True),
+    (64, 16, (2, 4200), True),
+    (80, 13, (3, 5100), False),
 ]
 
 

@@ -48,6 +48,7 @@ CASES = {
     "wide_transition_1536_1568_rows": ("gemm_nt", lambda: _merge(6, 32, 2, 640), lambda: _merge(8, 28, 7, 640), 1.22),
     "narrow_rows_128_8192_8200": ("ln_bwd", lambda: _stack(128, 4, 8, 1024), lambda: _stack(128, 4, 8, 1025), 1.3),
     "narrow_rows_104_8192_8200": ("ln_bwd", lambda: _stack(104, 13, 8, 1024), lambda: _stack(104, 13, 8, 1025), 1.4),
+    "one_token_heads_of_32_and_64": ("attn_fwd", lambda: _stack(384, 12, 1, 4096), lambda: _stack(768, 12, 1, 4096), 1.6),
 }
 
 
