@@ -844,6 +844,8 @@ static int fwd_dma(hipStream_t s, const bf16* qkv, bf16* o, float* lse, int B, i
 //   64, 512:  64 (512) - 38.5 29.2;  96 (768) - 45.8 42.3;  192 (1536) - 68.0 73.0
 //   80, 1000: 32 (512) - 74.2 61.8;  48 (768) - 92.1 89.9;  64 (1024) - 101 106
 //   80, 257:  64 (384) - 28.6 23.1;  128 (768) - 37.9 33.1;  384 (2304) - 87.4 84.7
+// So heads of 64 features up to 256 tokens take the pair up to 128 heads (up to 64 tokens, one workgroup of two wavefronts a pass, up to
+// 256), everything else up to 768 workgroups.  (96 to 128 tokens, 192 heads, with the pair 2 to 5 % slower.)
 // Workgroups of two wavefronts instead of four as long as every CU gets at most one of them (12 heads of 197 tokens: 12.0
 // against 12.3; 24 of 128, 64 features: 8.1 against 8.8; where a CU gets two, both use the same two SIMDs: 48 of 197, 14.5
 // against 12.7).
@@ -852,7 +854,7 @@ static int bwd_dma(hipStream_t s, BwdArgs a, int B) {
     const int heads = B * a.H, tiles = (a.T + 31) / 32;
     int nw;
     const bool fits = DH <= 64 && a.T <= 256;
-    if (2 * heads * ((tiles + 3) / 4) <= (fits && DH == 64 ? 512 : 768)) {
+    if (fits && DH == 64 ? heads <= (tiles > 2 ? 128 : 256) : 2 * heads * ((tiles + 3) / 4) <= 768) {
         split_rows(a.T, 2 * heads * ((tiles + 1) / 2) <= 256 ? 2 : 4, &a.nblk, &nw);
         a.delta = nullptr;
         const size_t lds = ring_lds<TileRing<DH, 3, 1>>(a.T) + nw * 128;
