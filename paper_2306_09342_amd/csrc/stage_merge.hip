@@ -115,7 +115,9 @@ __global__ __launch_bounds__(256) void merge_ln_fwd_kernel(const float* __restri
 // FUSED: rows are gathered from the fused map z0 and their cotangent goes, whole, to dZ0 (activation type);
 // otherwise from the average of X1 and X2, and half of it goes to each of dX1, dX2.
 // Bound by HBM.  It writes the normalised row n here instead of a pass of its own over X1 and X2 (50176 rows of 384, us: 38 and
-// 67 before, now 91 together; with the next row requested a row ahead 87, but 45 instead of 38 for 1536-wide rows).
+// 67 before, now 91 together; with the next row requested a row ahead 87, but 45 instead of 38 for 1536-wide rows).  Rows of more
+// than 4096 floats do not fit the registers with everything else, so they read the gains and the cotangent twice instead of
+// spilling them: 784 rows of 8192 floats 253 -> 189 us (242 with the gather in a kernel of its own).
 template <typename TA, typename TP, int MAXJ, bool FUSED>
 __global__ __launch_bounds__(256) void merge_ln_bwd_kernel(const TA* __restrict__ dn, const float* __restrict__ X1,
                                                            const float* __restrict__ X2, const TA* __restrict__ Z0,
@@ -127,11 +129,12 @@ __global__ __launch_bounds__(256) void merge_ln_bwd_kernel(const TA* __restrict_
     extern __shared__ float lds[];                   // [2 * 4C]
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int C = g.C, D4 = 4 * C, nch = C;
-    f4 ag[MAXJ], ab[MAXJ], gg[MAXJ];
+    constexpr bool KEEP = MAXJ <= 16;                // the gains and the cotangent's row stay in registers
+    f4 ag[MAXJ], ab[MAXJ], gg[KEEP ? MAXJ : 1];
 #pragma unroll
     for (int j = 0; j < MAXJ; ++j) {
         const int c = lane + 64 * j;
-        gg[j] = (c < nch) ? load4(gam + 4 * c) : f4{0.f, 0.f, 0.f, 0.f};
+        if (KEEP) gg[KEEP ? j : 0] = (c < nch) ? load4(gam + 4 * c) : f4{0.f, 0.f, 0.f, 0.f};
         ag[j] = {0.f, 0.f, 0.f, 0.f};
         ab[j] = {0.f, 0.f, 0.f, 0.f};
     }
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(256) void merge_ln_bwd_kernel(const TA* __restrict_
     for (int o = row0 + wave; o < row1; o += 4) {
         int src[4];
         merge_sources(g, o, src);
-        f4 xh[MAXJ], dh[MAXJ];
+        f4 xh[MAXJ], dh[KEEP ? MAXJ : 1];
         float s = 0.f, qs = 0.f, c1 = 0.f, c2 = 0.f;
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
@@ -148,7 +151,7 @@ __global__ __launch_bounds__(256) void merge_ln_bwd_kernel(const TA* __restrict_
             if (c < nch) {
                 const int q = (4 * c) / C, col = 4 * c - q * C;
                 const int64_t off = (int64_t)src[q] * C + col;
-                dh[j] = load4(dn + (int64_t)o * D4 + 4 * c);
+                if (KEEP) dh[KEEP ? j : 0] = load4(dn + (int64_t)o * D4 + 4 * c);
                 if (FUSED) {
                     xh[j] = load4(Z0 + off);
                 } else {
@@ -172,31 +175,39 @@ __global__ __launch_bounds__(256) void merge_ln_bwd_kernel(const TA* __restrict_
         for (int j = 0; j < MAXJ; ++j) {
             const int c = lane + 64 * j;
             if (c < nch) {
-                const f4 d = dh[j], bb = load4(bet + 4 * c);
+                const f4 d = KEEP ? dh[KEEP ? j : 0] : load4(dn + (int64_t)o * D4 + 4 * c), bb = load4(bet + 4 * c);
+                const f4 ga = KEEP ? gg[KEEP ? j : 0] : load4(gam + 4 * c);
                 xh[j] = {xh[j].x * rstd, xh[j].y * rstd, xh[j].z * rstd, xh[j].w * rstd};
-                store4(n + (int64_t)o * D4 + 4 * c, f4{xh[j].x * gg[j].x + bb.x, xh[j].y * gg[j].y + bb.y, xh[j].z * gg[j].z + bb.z,
-                                                       xh[j].w * gg[j].w + bb.w});
+                store4(n + (int64_t)o * D4 + 4 * c, f4{xh[j].x * ga.x + bb.x, xh[j].y * ga.y + bb.y, xh[j].z * ga.z + bb.z,
+                                                       xh[j].w * ga.w + bb.w});
                 ab[j].x += d.x; ab[j].y += d.y; ab[j].z += d.z; ab[j].w += d.w;
                 ag[j].x += d.x * xh[j].x; ag[j].y += d.y * xh[j].y; ag[j].z += d.z * xh[j].z; ag[j].w += d.w * xh[j].w;
-                dh[j] = {d.x * gg[j].x, d.y * gg[j].y, d.z * gg[j].z, d.w * gg[j].w};
-                c1 += (dh[j].x + dh[j].y) + (dh[j].z + dh[j].w);
-                c2 += (dh[j].x * xh[j].x + dh[j].y * xh[j].y) + (dh[j].z * xh[j].z + dh[j].w * xh[j].w);
+                const f4 h = {d.x * ga.x, d.y * ga.y, d.z * ga.z, d.w * ga.w};
+                c1 += (h.x + h.y) + (h.z + h.w);
+                c2 += (h.x * xh[j].x + h.y * xh[j].y) + (h.z * xh[j].z + h.w * xh[j].w);
+                if (KEEP) dh[KEEP ? j : 0] = h;
             }
         }
         c1 = wave_sum(c1) / (float)D4;
         c2 = wave_sum(c2) / (float)D4;
         const float hr = FUSED ? rstd : 0.5f * rstd;
+        int ln = lane;
+        if (!KEEP) asm volatile("" : "+v"(ln));      // the chunks' addresses are formed again, not kept
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
-            const int c = lane + 64 * j;
+            const int c = ln + 64 * j;
             if (c < nch) {
                 const int q = (4 * c) / C, col = 4 * c - q * C;
                 const int64_t off = (int64_t)src[q] * C + col;
-                f4 r;
-                r.x = hr * (dh[j].x - c1 - xh[j].x * c2);
-                r.y = hr * (dh[j].y - c1 - xh[j].y * c2);
-                r.z = hr * (dh[j].z - c1 - xh[j].z * c2);
-                r.w = hr * (dh[j].w - c1 - xh[j].w * c2);
+                f4 r, h = dh[KEEP ? j : 0];
+                if (!KEEP) {
+                    const f4 d = load4(dn + (int64_t)o * D4 + 4 * c), ga = load4(gam + 4 * c);
+                    h = {d.x * ga.x, d.y * ga.y, d.z * ga.z, d.w * ga.w};
+                }
+                r.x = hr * (h.x - c1 - xh[j].x * c2);
+                r.y = hr * (h.y - c1 - xh[j].y * c2);
+                r.z = hr * (h.z - c1 - xh[j].z * c2);
+                r.w = hr * (h.w - c1 - xh[j].w * c2);
                 if (FUSED) {
                     store4(dZ0 + off, r);
                 } else {

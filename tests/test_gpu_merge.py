@@ -26,6 +26,13 @@ CASES = {
     "wide_bf16": dict(batch=1, grid_h=14, grid_w=14, window=7, d_in=768, mode="bf16", ln_eps=1e-5),
     "width192_bf16": dict(batch=5, grid_h=28, grid_w=28, window=7, d_in=192, mode="bf16", ln_eps=1e-6),
     "width384_fp32": dict(batch=1, grid_h=14, grid_w=28, window=7, d_in=384, mode="fp32", ln_eps=1e-5),
+    # rows whose gains and cotangents the backward kernel reads twice (beyond 4096 floats), 24 and 32 chunks per lane, and the
+    # widest that keeps them
+    "width1024_bf16": dict(batch=1, grid_h=4, grid_w=12, window=2, d_in=1024, mode="bf16", ln_eps=1e-5),
+    "width1032_bf16": dict(batch=1, grid_h=12, grid_w=4, window=2, d_in=1032, mode="bf16", ln_eps=1e-5),
+    "width1032_fp32": dict(batch=1, grid_h=4, grid_w=8, window=2, d_in=1032, mode="fp32", ln_eps=1e-5),
+    "width2048_bf16": dict(batch=1, grid_h=4, grid_w=12, window=2, d_in=2048, mode="bf16", ln_eps=1e-5),
+    "width2048_fp32": dict(batch=1, grid_h=4, grid_w=8, window=2, d_in=2048, mode="fp32", ln_eps=1e-5),
 }
 
 
@@ -36,6 +43,8 @@ MLP_CASES = {
     "mlp_width192_bf16": dict(batch=5, grid_h=28, grid_w=28, window=7, d_in=192, mode="bf16", ln_eps=1e-6, fusion="mlp"),
     "mlp_width384_fp32": dict(batch=1, grid_h=14, grid_w=28, window=7, d_in=384, mode="fp32", ln_eps=1e-5, fusion="mlp"),
     "mlp_wide_bf16": dict(batch=1, grid_h=14, grid_w=14, window=7, d_in=768, mode="bf16", ln_eps=1e-5, fusion="mlp"),
+    "mlp_width1032_bf16": dict(batch=1, grid_h=12, grid_w=4, window=2, d_in=1032, mode="bf16", ln_eps=1e-5, fusion="mlp"),
+    "mlp_width2048_fp32": dict(batch=1, grid_h=4, grid_w=8, window=2, d_in=2048, mode="fp32", ln_eps=1e-5, fusion="mlp"),
     # the two bias gradients as column sums that ride in the weight-gradient launch, 62 720 rows: 128x128 tiles whose last
     # round leaves too few idle slots for them (70 tiles x 7 ranges = 490 of 512; 35 chunks x 2), and 256x256 tiles
     "mlp_sums_beyond_idle_bf16": dict(batch=20, grid_h=56, grid_w=56, window=7, d_in=576, mode="bf16", ln_eps=1e-5, fusion="mlp"),
