@@ -283,10 +283,12 @@ static int launch_big(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, 
     return REV_OK;
 }
 
+// Bias, GELU and residual: B is [N, K]; GELU' and plain: B as stored, [K, N]; float32: either.
 int gemm_bf16_big(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi, bool b_kmajor) {
-    switch (epi.kind) {
-#define CASE(KIND) case KIND: return b_kmajor ? launch_big<KIND, true>(s, A, lda, B, ldb, M, N, K, epi) : launch_big<KIND, false>(s, A, lda, B, ldb, M, N, K, epi);
-        CASE(EPI_BIAS) CASE(EPI_BIAS_GELU) CASE(EPI_RESIDUAL) CASE(EPI_GELU_BWD) CASE(EPI_PLAIN) CASE(EPI_PLAIN_F32)
+    switch (epi.kind * 2 + b_kmajor) {
+#define CASE(KIND, BKM) case KIND * 2 + BKM: return launch_big<KIND, BKM>(s, A, lda, B, ldb, M, N, K, epi);
+        CASE(EPI_BIAS, false) CASE(EPI_BIAS_GELU, false) CASE(EPI_RESIDUAL, false) CASE(EPI_GELU_BWD, true) CASE(EPI_PLAIN, true)
+        CASE(EPI_PLAIN_F32, false) CASE(EPI_PLAIN_F32, true)
 #undef CASE
     }
     set_error("gemm_bf16: unknown epilogue");

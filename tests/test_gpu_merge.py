@@ -45,6 +45,10 @@ MLP_CASES = {
     "mlp_wide_bf16": dict(batch=1, grid_h=14, grid_w=14, window=7, d_in=768, mode="bf16", ln_eps=1e-5, fusion="mlp"),
     "mlp_width1032_bf16": dict(batch=1, grid_h=12, grid_w=4, window=2, d_in=1032, mode="bf16", ln_eps=1e-5, fusion="mlp"),
     "mlp_width2048_fp32": dict(batch=1, grid_h=4, grid_w=8, window=2, d_in=2048, mode="fp32", ln_eps=1e-5, fusion="mlp"),
+    # input gradients of both streams in 256x256 tiles, the weight's halves as they are stored (row pitch 2 * d_in, the second half
+    # at an offset): 32 004 rows, four beyond the last whole tile, and 384 columns, one tile and a half; 25 236 rows, 512 columns
+    "mlp_big_tiles384_bf16": dict(batch=889, grid_h=6, grid_w=6, window=3, d_in=384, mode="bf16", ln_eps=1e-5, fusion="mlp"),
+    "mlp_big_tiles512_bf16": dict(batch=701, grid_h=6, grid_w=6, window=3, d_in=512, mode="bf16", ln_eps=1e-5, fusion="mlp"),
     # the two bias gradients as column sums that ride in the weight-gradient launch, 62 720 rows: 128x128 tiles whose last
     # round leaves too few idle slots for them (70 tiles x 7 ranges = 490 of 512; 35 chunks x 2), and 256x256 tiles
     "mlp_sums_beyond_idle_bf16": dict(batch=20, grid_h=56, grid_w=56, window=7, d_in=576, mode="bf16", ln_eps=1e-5, fusion="mlp"),
