@@ -141,7 +141,7 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TA* __restrict__ dn, 
     constexpr int NACC = ACC_LDS ? 1 : MAXJ;
     // The chunks' sums: added as they come, or kept apart, whichever is faster (1280 floats, 50176 rows: 238 / 252 us;
     // 2048 floats, 8192 rows: 101 / 94).  The order is the same.
-    constexpr int NP = LPR == 64 && MAXJ < 8 ? 1 : MAXJ;
+    constexpr int NP = MAXJ >= 4 && MAXJ < 8 ? 1 : MAXJ;
     f4 ag[NACC], ab[NACC], ao[NACC], gg[MAXJ];
     float* wacc = lds + (ACC_LDS ? wave * 3 * D : 0);            // [dgamma | dbeta | colsum(out)] of this wavefront
 #pragma unroll
