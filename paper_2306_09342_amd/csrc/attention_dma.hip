@@ -11,9 +11,12 @@
 // change a bit of its results.
 //
 // What bounds them: vector ALU and latency (one exp2 and about ten other instructions per score, softmax statistics in the middle of
-// the chain); the tiles come from L2.  Two tiles in flight and workgroups of up to four wavefronts: a workgroup takes 16 KB
-// (32 features) to 42 KB of LDS and at most one wavefront of a SIMD, so three or four share a CU and their phases
-// overlap; three or four tiles in flight cost occupancy and time everywhere (197 tokens, 64 features: 27 -> 31 us).
+// the chain); the tiles come from L2.  The ring kernels keep two tiles in flight and have workgroups of up to four wavefronts,
+// one per SIMD, so that several share a CU and their phases overlap.  KB of LDS of a workgroup, beyond 64 tokens, and how
+// many share a CU (LDS, or registers), for 32, 64 and 80 features: forward and dQ 16, 33, 41 KB and 4, 4, 3 of them; dK and dV 17,
+// 34, 42 KB and 3, 3, 2; the pair 26, 50, 62 KB and 3, 2, 2.  (Half of it up to 64 tokens.)  Three or four tiles in flight
+// cost occupancy and time everywhere (197 tokens, 64 features: 27 -> 31 us).  attn_bwd_fused holds a whole head, 16 to 133 KB, in a
+// workgroup of up to eight wavefronts, two per SIMD.
 // Measured, us, before (padded LDS rows, a whole head loaded per workgroup or the next tile fetched through registers, 80
 // features padded to 96) and now.  Forward: 768 heads of 197 tokens, 64 features: 34 -> 27; 384 heads of 512: 66 -> 45;
 // 512 heads of 257, 80 features: 84 -> 37; 12288 windows of 49, 32 features: 53 -> 42.  Backward: 384 heads of 512 tokens: 148 ->

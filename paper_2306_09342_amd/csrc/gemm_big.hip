@@ -1,4 +1,4 @@
-// bf16 GEMM in 256x256 tiles, for launches whose tiles fill the chip in whole rounds:
+// bf16 GEMM in 256x256 tiles, for launches whose tiles fill most of the chip (big_tiles_pay, gemm_mfma.hip):
 //   C[M,N] (+epilogue) = A[M,K] * B[N,K]^T   or, with BKM,   A[M,K] * B[K,N];   M, N >= 256, K a multiple of 128.
 //
 // One workgroup of 8 wavefronts per CU, 128 output columns x 64 rows of the tile per wavefront (weights on the A port, so an

@@ -109,8 +109,8 @@ static bool big_tiles_pay(int M, int N, int K, int kind, BigRule rule, bool tall
 // 256x128 tiles (gemm_mid.hip), two workgroups per CU, whose epilogues run beside the other's products.  256x256, 160x128 or
 // 128x128 / 256x128, us:
 // The GELU epilogues over short contractions, from more than two rounds of 512 on.  GELU' M = 25216, N = 1536, K = 384
-// (1188 tiles): 72 / 63; N = 2048, K = 512: 110 / 94; M = 7289, N = 1536, K = 384 (348): 24.7 / 25.0; M = 12608, N = 3072, K = 768:
-// 97 / 85 alone, but next to the other stream's kernels a pass of Rev-ViT-B takes 9.16 ms with them and 9.00 without.  GELU
+// (1188 tiles): 72 / 63; N = 2048, K = 512: 110 / 94; M = 7289, N = 1536, K = 384 (348): 24.7 / 25.0; at K = 768 next to the other
+// stream's kernels a pass of Rev-ViT-B (M = 12608) takes 9.16 ms with them and 9.00 without.  GELU
 // M = 50000, N = 1024, K = 256: 82 / 71; M = 25216, N = 1536, K = 384: 69 / 67; N = 2048, K = 512: 98 / 99; M = 30000: 106 / 116.
 // The QKV maps of the same widths, from one and a half rounds on: K = 384, M = 25216 (891 tiles) 37.9 / 34.1, M = 12608 (450) 19.2 /
 // 19.9; K = 512, M = 25216 59.6 / 51.4; K = 192, M = 50176 30.0 / 24.4; K = 128, M = 96000 27.6 / 30.8; K = 768, M = 12608 53.7 / 58.1.
@@ -122,10 +122,10 @@ static bool mid_tiles_pay(int M, int N, int K, int kind, bool solo) {
     return t > 1024 && ((kind == EPI_GELU_BWD && K <= 512) || (kind == EPI_BIAS_GELU && K <= 384));
 }
 // The GELU epilogues of somewhat longer contractions, where 256x256 tiles would leave the last round partly empty and no other
-// stream's kernel takes those CUs.  256x256 / 256x128, us, GELU and GELU': M = 16384, N = 2560, K = 640 (640 tiles of 256x256) 93 / 78
-// and 97 / 89; M = 12608, N = 3072, K = 768 (600) 97 / 91 and 110 / 103; M = 16384 (768, three whole rounds) 112 / 116 and 126 /
-// 125; K = 1280, M = 8224, N = 5120 (660) GELU' 135 / 142.  The column sums of both tiles have the same bits, so that both
-// schedules still add the same ones.
+// stream's kernel takes those CUs.  256x256 / 256x128, us, three sets of buffers in turn, GELU and GELU' with column sums: M = 12608, N
+// = 3072, K = 768 (600 tiles of 256x256) 88 / 82 and 98 / 89; M = 16384 (768, three whole rounds) 95 / 104 and 110 / 112; N = 2560, K =
+// 640 (640) 82 / 89 and 95 / 86, together 177 / 175; K = 1280, M = 8224, N = 5120 (660) GELU' 135 / 139.  The column sums of both tiles have the same
+// bits, so that both schedules still add the same ones.
 static bool mid_fills_better(int M, int N, int K, const Epi& epi) {
     const int t256 = tiles_of(M, N, 256, 256);
     return epi.solo && (epi.kind == EPI_BIAS_GELU || epi.kind == EPI_GELU_BWD) && K <= 768 && t256 > 512 && t256 < 0.85 * 256 * ((t256 + 255) / 256);
