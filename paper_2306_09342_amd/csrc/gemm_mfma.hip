@@ -56,37 +56,40 @@ static GemmShape small_shape(int M, int N, int K) {
     return GS_128x128;
 }
 // What a launch takes by itself, in us, by tile: a stage of 64 of K, and what a round spends besides (first loads, epilogue) by
-// what the epilogue does.  Fitted to 1466 launches of M = 400 ... 40000, D = 128 ... 2048 (the products of a block and of a
-// transition; root mean square error 7 %).  A round is 512 workgroups, two per CU, of 128x128 or 160x128 tiles, 256 of 256x256
-// ones.  The workgroups of a launch that does not fill one round run faster, for they share less (two to a CU on some of them;
-// the power limit), and so do those of a last, partly filled round.
-//                                     bias  GELU  residual  GELU'  plain  float32
-static const double REST_128[] =      {5.0,  9.0,  12.0,     10.0,  6.0,   7.5};
-static const double REST_160[] =      {7.7,  13.2, 14.7,     13.2,  8.3,   9.5};
-static const double REST_256[] =      {10.0, 16.0, 22.0,     20.0,  10.5,  11.5};
+// what the epilogue does.  Fitted to 3235 launches of M = 400 ... 59100, D = 128 ... 2048 (the products of a block and of a
+// transition), weighted to tell the tiles apart where they are close; the times themselves are met to 6 to 9 %.  A round is 512
+// workgroups, two per CU, of 128x128 or 160x128 tiles, 256 of 256x256 ones.  The workgroups of a launch that does not fill one
+// round run faster, for they share less (two to a CU on some of them; the power limit), and so do those of a last, partly
+// filled round.
+//                                bias  GELU  residual  GELU'  plain  float32
+static const double REST_128[] = {4.1,  8.0,  10.0,     9.0,   4.7,   7.1};
+static const double REST_160[] = {7.6,  12.8, 15.3,     12.8,  8.4,   9.4};
+static const double REST_256[] = {10.5, 18.0, 22.0,     21.0,  10.4,  13.5};
 static double cost_128(int tiles, double st, int kind) {
     const int full = tiles / 512;
     const double x = tiles % 512 / 512.0;
-    const double last = x == 0 ? 0.0 : full ? 0.32 + 0.74 * x : x <= 0.5 ? 0.48 + 0.42 * x : 0.51 + 0.49 * x;
-    return (full + last) * (st * 0.98 + REST_128[kind]);
+    const double last = x == 0 ? 0.0 : full ? 0.40 + 0.70 * x : x <= 0.5 ? 0.54 + 0.36 * x : 0.62 + 0.36 * x;
+    return (full + last) * (st * 1.03 + REST_128[kind]);
 }
 static double cost_160(int tiles, double st, int kind) {
     const int full = tiles / 512;
     const double x = tiles % 512 / 512.0;
-    const double last = x == 0 ? 0.0 : full ? 0.57 + 0.53 * x : x <= 0.5 ? 0.65 + 0.26 * x : 0.58 + 0.48 * x;
-    return (full + last) * (st * 1.09 + REST_160[kind]);
+    const double last = x == 0 ? 0.0 : full ? 0.66 + 0.49 * x : x <= 0.5 ? 0.65 + 0.30 * x : 0.69 + 0.33 * x;
+    return (full + last) * (st * 1.04 + REST_160[kind]);
 }
 static double cost_256(int tiles, double st, int kind) {
     const int full = tiles / 256;
     const double x = tiles % 256 / 256.0, rest = REST_256[kind];
-    return full * (st * 1.43 + rest) + (x == 0 ? 0.0 : st * (0.66 + 0.77 * x) + rest * (0.71 + 0.29 * x));
+    return full * (st * 1.25 + rest) + (x == 0 ? 0.0 : st * (0.96 + 0.29 * x) + rest * (0.50 + 0.50 * x));
 }
 // 256x256 tiles (gemm_big.hip) for a launch by itself, where they save more than the costs above are off by.  Measured,
 // 128x128 or 160x128 / 256x256, us: M = 16384, N = 768, K = 3072: 92 / 64 (input gradient), 103 / 78 (residual); M = 8224, N = 1280, K =
 // 5120: 125 / 90, 156 / 104; M = 12608, N = K = 1024 (200 tiles), residual: 51 / 44.  Where they leave half of a round empty:
 // M = 1568, N = 2560, K = 1280 (70 tiles; 260 of 128x128): 17.8 / 25.0; M = 8192, N = 1024, K = 4096 (128; 512): 66 / 72; or take a
-// short second one: M = 4100, N = 4096, K = 1024 (272; 1056), GELU: 53 / 59.  Of the 1466 launches they take 589, 18 % faster in
-// the mean; ten of these are 3 to 11 % slower (four of them with column sums, see below).
+// short second one: M = 4100, N = 4096, K = 1024 (272; 1056), GELU: 53 / 59.  Of the 3235 launches they take 1587, 17 % faster in
+// the mean; 45 of these are 3 to 14 % slower, most of them residuals over short contractions from operands that had left the
+// caches, where a pass finds them there: D = 256, M = 50176, K = 256 32 / 35 by itself (59100: 34 / 43), but a forward block of it
+// 234 / 227 us.
 // Next to another stream's kernels a partly filled round costs only the CUs it takes, so there the work per CU decides (a tile's
 // time with the chip full of them), unless the launch by itself would take much longer.  Four blocks on two streams, 128x128 /
 // 256x256 tiles, us: D = 1024, M = 5122: 2349 / 2232; D = 1536, M = 4096: 3471 / 3178.
@@ -98,7 +101,7 @@ static bool big_tiles_pay(int M, int N, int K, int kind, BigRule rule, bool tall
     const double st = K / 64;
     const int t128 = tiles_of(M, N, 128, 128), t256 = tiles_of(M, N, 256, 256);
     const double small = cost_128(t128, st, kind), big = cost_256(t256, st, kind);
-    if (rule == BIG_ALONE) return big < 0.95 * (tall ? std::fmin(small, cost_160(tiles_of(M, N, 160, 128), st, kind)) : small);
+    if (rule == BIG_ALONE) return big < 0.98 * (tall ? std::fmin(small, cost_160(tiles_of(M, N, 160, 128), st, kind)) : small);
     // the constants of the two rules below are those that were fitted next to another stream's kernels
     static const double small_rest[] = {3.0, 7.0, 8.0, 7.0, 4.4, 8.0}, big_rest[] = {8.0, 15.0, 17.0, 18.0, 8.0, 17.0};
     const int rounds = (t256 + 255) / 256;
