@@ -148,8 +148,8 @@ struct Epi {
 };
 // rows of column-sum partials (strips of 32 or 64 token rows) that a bf16 GEMM writes
 int gemm_colsum_strips(int M, int N, int K);
-// tile of a bf16 GEMM launch: gemm_ring.hip (the first three), gemm_nt_dma.hip, gemm_mid.hip and gemm_big.hip (the last two)
-enum GemmShape { GS_32x32, GS_64x64, GS_64x128_RING, GS_64x128, GS_128x128, GS_160x128, GS_256x128, GS_256x256 };
+// tile of a bf16 GEMM launch: gemm_ring.hip (the first five), gemm_nt_dma.hip, gemm_mid.hip and gemm_big.hip (the last two)
+enum GemmShape { GS_32x32, GS_64x64, GS_64x128_RING, GS_128x128_RING, GS_192x128_RING, GS_128x128, GS_160x128, GS_256x128, GS_256x256 };
 
 // C[M,N] (+epilogue) = A[M,K] * B[N,K]^T.  A, B row-major with leading dims lda, ldb.
 // fp32 flavour: A, B float.  bf16 flavour: A, B bf16.

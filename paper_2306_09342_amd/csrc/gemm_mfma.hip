@@ -37,23 +37,34 @@ static bool tall_tiles_pay(int M, int N) {
 }
 
 // A launch that cannot give every CU a workgroup is bound by the serial chain of one tile and by the rate at
-// which one CU takes in operands; so it takes the smallest tile whose workgroups all run at once.  All tiles sum the products
-// of an output in the same order, so a sample's results do not depend on how many others are in its batch, and the lines
-// below are free to follow the clock.  Measured at 16 ... 7289 rows, N and K from 384 to 5120 (us, activation x weight):
-//   32x32 up to 288 tiles (a little over one per CU).  197 rows, N = K = 768 (168 tiles): 4.4, 64x64 5.5, 64x128 8.3; K = 3072:
-//     9.1, 12.3, 28.  At 456 tiles 5.9 against 6.1, and 6.6 against 5.8 for weights stored K x N.
-//   64x64 up to 384 tiles, and up to the 512 that run at once for short contractions.  1182 rows, N = 768, K = 3072 (228): 14.1,
-//     128x128 34.6.  2364 rows, N = K = 768 (444): 11.1, 64x128 11.7; K = 3072: 28.6 against 24.6.
-//   64x128 in the ring up to 256 tiles.  2364 rows, N = 768, K = 3072 (222): 24.6, the two-stage kernel 29.8.
-//   64x128 in two stages up to 440 tiles of long contractions.  2570 rows, N = 1280, K = 3840 (410): 39.8, 128x128 45.2; 4728
-//     rows, N = 640, K = 2560 (370): 29.4, 32.2; 5300 rows, N = 768, K = 2304 (498): 30.3, 29.6.  At K = 768 and 1024 the
-//     two are within 5 % of each other, either way.
-static GemmShape small_shape(int M, int N, int K) {
-    if (tiles_of(M, N, 32, 32) <= 288) return GS_32x32;
-    if (tiles_of(M, N, 64, 64) <= (K < 1536 ? 512 : 384)) return GS_64x64;
-    if (tiles_of(M, N, 64, 128) <= 256) return GS_64x128_RING;
-    if (tiles_of(M, N, 64, 128) <= 440 && K >= 1280) return GS_64x128;
-    return GS_128x128;
+// which one CU takes in operands; so it takes a tile whose workgroups all run at once, in the deep ring of gemm_ring.hip.  All tiles
+// sum the products of an output in the same order, so a sample's results do not depend on how many others are in its batch, and
+// the lines below are free to follow the clock.
+//
+// What a launch in the ring takes, in us: what it spends besides the stages by what the epilogue does, and a stage of 64 of K alone
+// and with the chip full of workgroups.  Fitted to 1760 launches of M = 100 ... 16384, D = 128 ... 1280 (the products of a block),
+// three times each; met to 6 to 11 %.  The two smallest tiles share a CU, two and two, beyond 256 workgroups.
+struct RingCost { GemmShape shape; int bm, bn, least, most; double rest[6], full, stage, stage_full; };
+static const RingCost RING[] = {
+    //                               bias GELU resid GELU' plain f32   fill   stage
+    {GS_32x32, 32, 32, 0, 256,       {4.3, 4.5, 4.0, 4.7, 3.9, 4.0},   0.0, 0.073, 0.025},
+    {GS_32x32, 32, 32, 256, 288,     {4.3, 4.5, 4.0, 4.7, 4.0, 4.0},   0.0, 0.071, 0.061},
+    {GS_64x64, 64, 64, 0, 256,       {4.2, 4.7, 4.3, 4.9, 3.9, 4.1},   0.0, 0.132, 0.052},
+    {GS_64x64, 64, 64, 256, 512,     {4.2, 4.8, 4.8, 5.2, 4.1, 4.4},   0.0, 0.239, 0.076},
+    {GS_64x128_RING, 64, 128, 0, 256, {4.1, 4.9, 4.5, 5.4, 3.9, 4.2},  0.5, 0.207, 0.106},
+    {GS_128x128_RING, 128, 128, 0, 256, {4.7, 6.3, 5.7, 7.1, 4.4, 5.0}, 1.2, 0.281, 0.223},
+    {GS_192x128_RING, 192, 128, 0, 256, {5.1, 7.8, 6.7, 8.7, 4.8, 5.7}, 2.2, 0.389, 0.309}};
+// the cheapest of them (up to 64x64 tiles with small_only), GS_128x128 if none holds the launch
+static GemmShape ring_shape(int M, int N, int K, int kind, bool small_only, double* us) {
+    GemmShape best = GS_128x128;
+    *us = 1e30;
+    for (const RingCost& r : RING) {
+        const int t = tiles_of(M, N, r.bm, r.bn);
+        if (t <= r.least || t > r.most || (small_only && r.bm > 64)) continue;
+        const double x = t / 256.0, c = r.rest[kind] + r.full * x + K / 64.0 * (r.stage + r.stage_full * x);
+        if (c < *us) { *us = c; best = r.shape; }
+    }
+    return best;
 }
 // What a launch takes by itself, in us, by tile: a stage of 64 of K, and what a round spends besides (first loads, epilogue) by
 // what the epilogue does.  Fitted to 3235 launches of M = 400 ... 59100, D = 128 ... 2048 (the products of a block and of a
@@ -140,14 +151,37 @@ static bool mid_shares_better(int M, int N, int K, const Epi& epi) {
     return !epi.solo && (epi.kind == EPI_RESIDUAL || epi.kind == EPI_PLAIN) && M >= 256 && N >= 128 && N <= 384 && K >= 192 && K % 64 == 0 &&
            tiles_of(M, N, 256, 128) > 256;
 }
-static GemmShape pick_gemm_shape(int M, int N, int K, const Epi& epi) {
-    const GemmShape sh = small_shape(M, N, K);
-    if (sh != GS_128x128) return sh;
+// The tiles of launches that fill the chip, two workgroups per CU or 256x256, and what one takes by itself.
+static GemmShape wide_shape(int M, int N, int K, const Epi& epi, double* us) {
+    *us = 0.0;                                                // (256x128 tiles: only where nothing else comes near)
     if (mid_tiles_pay(M, N, K, epi.kind, epi.solo)) return GS_256x128;
+    const double st = K / 64.0;
     const bool tall = epi.solo && epi.colsum == nullptr && K % 64 == 0 && tall_tiles_pay(M, N);
-    if (big_tiles_pay(M, N, K, epi.kind, epi.colsum ? BIG_SUMS : epi.solo ? BIG_ALONE : BIG_BESIDE, tall)) return mid_fills_better(M, N, K, epi) ? GS_256x128 : GS_256x256;
+    if (big_tiles_pay(M, N, K, epi.kind, epi.colsum ? BIG_SUMS : epi.solo ? BIG_ALONE : BIG_BESIDE, tall)) {
+        if (mid_fills_better(M, N, K, epi)) return GS_256x128;
+        *us = cost_256(tiles_of(M, N, 256, 256), st, epi.kind);
+        return GS_256x256;
+    }
     if (mid_shares_better(M, N, K, epi)) return GS_256x128;
-    return tall ? GS_160x128 : sh;
+    *us = tall ? cost_160(tiles_of(M, N, 160, 128), st, epi.kind) : cost_128(tiles_of(M, N, 128, 128), st, epi.kind);
+    return tall ? GS_160x128 : GS_128x128;
+}
+// Short contractions (K < 640), where a launch is mostly first loads and epilogue: tiles of up to 64x64 while their workgroups all
+// run at once, 64x128 up to one per CU, and two workgroups per CU from there on.  Longer ones: the cheapest tile of the ring where 64x64 tiles would
+// all run at once; beyond, if it undercuts the wide tiles by 3 %, for the fits are off by more than they differ below that.  us, the
+// tiles before (64x64 or 64x128 in the ring, 64x128 or 128x128 in two stages, 256x256) and the ring's: 1576 rows, N = 768, K = 3072, input
+// gradient: 23.2 / 16.6; 3152: 33.3 / 21.8; 7289: 42.8 / 35.1; 7289, N = 384, K = 1536: 19.6 / 13.7, residual 20.7 / 16.7; 3152, N = 384:
+// 15.7 / 11.1.  Of the 1760 launches 427 change tile, to 0.875 of the time in the mean; 11 are 4 to 9 % slower (M = 16384, N = 256, K
+// = 768, input gradient, 12.9 -> 14.0).
+static GemmShape pick_gemm_shape(int M, int N, int K, const Epi& epi) {
+    double ring_us, us;
+    const bool brief = K < 640;
+    const bool few = tiles_of(M, N, 32, 32) <= 288 || tiles_of(M, N, 64, 64) <= (K < 1536 ? 512 : 384);
+    const GemmShape ring = ring_shape(M, N, K, epi.kind, brief, &ring_us);
+    if (few) return ring;
+    if (brief && tiles_of(M, N, 64, 128) <= 256) return GS_64x128_RING;
+    const GemmShape wide = wide_shape(M, N, K, epi, &us);
+    return !brief && ring_us < 0.97 * us ? ring : wide;
 }
 
 int gemm_colsum_strips(int M, int N, int K) {
@@ -158,7 +192,9 @@ int gemm_colsum_strips(int M, int N, int K) {
     switch (pick_gemm_shape(M, N, K, e)) {
         case GS_256x256: case GS_256x128: return (M + 255) / 256 * 4;
         case GS_32x32: return (M + 31) / 32;
-        case GS_64x64: case GS_64x128_RING: case GS_64x128: return (M + 63) / 64;
+        case GS_64x64: case GS_64x128_RING: return (M + 63) / 64;
+        case GS_128x128_RING: return (M + 127) / 128;
+        case GS_192x128_RING: return (M + 191) / 192;
         default: return (M + 127) / 128 * 2;              // 64-row strips
     }
 }
@@ -183,7 +219,7 @@ static int gemm_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, i
     // Widths that are no multiple of 32 take GELU in its erf form.  The polynomial is off by up to 1.3e-4 in the value, more
     // than half a bf16 step below -2.1 (six of them at -3), and pays only where the epilogue is a large share of the launch.
     if (K % 32 && (epi.kind == EPI_BIAS_GELU || epi.kind == EPI_GELU_BWD)) epi.kind |= EPI_ERF;
-    if (shape == GS_32x32 || shape == GS_64x64 || shape == GS_64x128_RING) return gemm_bf16_ring(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
+    if (shape <= GS_192x128_RING) return gemm_bf16_ring(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
     if (shape == GS_256x128 && b_kmajor == (epi.kind == EPI_GELU_BWD || epi.kind == EPI_PLAIN)) return gemm_bf16_mid(s, A, lda, B, ldb, M, N, K, epi);
     if (shape == GS_256x256) return gemm_bf16_big(s, A, lda, B, ldb, M, N, K, epi, b_kmajor);
     return gemm_bf16_dma(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);

@@ -22,8 +22,7 @@
 //
 // Tile shapes: 128x128 with four wavefronts of 64x64 (two workgroups per CU, the general case); 160x128 with two
 // wavefronts of 160x64 (7 fragment reads per 10 products, one wavefront per SIMD), which a launch that
-// has the device to itself picks when 128-row tiles would leave a short, ragged last round of workgroups; 64x128 with
-// two wavefronts of 64x64 for launches that would leave CUs without a workgroup otherwise.
+// has the device to itself picks when 128-row tiles would leave a short, ragged last round of workgroups.
 #include "gemm_epilogue.h"
 #include <type_traits>
 
@@ -381,7 +380,6 @@ template <int EPI, bool BKM, bool TAIL>
 static int dispatch_dma(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
                         const Epi& epi, GemmShape shape) {
     switch (shape) {
-        case GS_64x128: return launch_dma<64, 128, 1, 2, 64, EPI, BKM, TAIL>(s, A, lda, B, ldb, M, N, K, epi);
         case GS_160x128:
             if constexpr (!TAIL) return launch_dma<160, 128, 1, 2, 64, EPI, BKM, false>(s, A, lda, B, ldb, M, N, K, epi);
             break;

@@ -7,20 +7,26 @@
 // stage's fragments are read while the products of the stage before run.  Every output element is the sum of the same
 // products in the same order as under every other tile, so the choice of the tile never changes a bit of the result.
 //
-// What bounds it: the rate at which a CU takes in operands, (BM + BN) * K * 2 bytes per workgroup at 50 to 80 GB/s, and for the
-// smallest tile the chain of its products; both behind about 2.5 us of launch, first latency and epilogue.  The steady
-// loop has no branch: with two per load and four per wait a stage took 0.38 us whatever its size, now 0.25.  Measured (197
-// rows, operands from the memory-side cache, us): N = 768, K = 768: 4.4; K = 3072: 9.1 (whole-K 64x128 tiles in two stages: 8.3
-// and 28; wavefronts that split K, whose sums depended on the row count: 3.6 and 7.0).  Six or eight stages measured the same or
-// worse than three or four.
+// What bounds it: the rate at which a CU takes in operands, (BM + BN) * K * 2 bytes per workgroup, the LDS reads of a wavefront (38
+// cycles each, whoever else reads), and for the smallest tile the chain of its products; all behind about 2.5 us of launch, first
+// latency and epilogue.  The requests of a stage and its reads are spread between the products, so that the three run
+// side by side; a fragment's registers are refilled as soon as its products are issued, one stage ahead, which leaves room for 96 rows
+// of sums and the epilogue's operand per wavefront.  64x128 tiles and larger have eight wavefronts, two per SIMD, and a CU to
+// themselves.
+// Measured (us, operands from the memory-side cache).  197 rows, N = 768, K = 3072: 8.4 (whole-K 64x128 tiles in two stages: 28; wavefronts that
+// split K, whose sums depended on the row count, 7.0); K = 768: 4.8.  One workgroup per CU or less against two-stage tiles, two
+// workgroups per CU, K = 3072, N = 768, input gradient: 1576 rows 64x128 16.6 (64x64 with four wavefronts 23.2); 3152 rows 128x128 21.8
+// (33.3); 6304 rows 192x128 32.6 (40.3).  Requests at the head of a stage: 128x128 23.9.  Three stages of 192x128 instead of four: 34.8.
+// 256x128 with three: as 128x128 tiles in two stages, not kept.
 #include "gemm_epilogue.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace rev {
 
 // SUB: 64-wide chunks of K per stage, NS: stages in the ring
 template <int TM, int TN, int WM, int WN, int SUB, int NS> struct RingCfg {
-    static constexpr int NW = 4;
+    static constexpr int NW = WM * WN > 4 ? WM * WN : 4;
     static constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
     static constexpr int LA = BM / 8, LB = BN / 8, LPC = LA + LB, LPW = SUB * LPC / NW;   // 1 KB loads: per chunk, per wavefront and stage
     static constexpr int A_BYTES = BM * 128, CHUNK = (BM + BN) * 128, STAGE = SUB * CHUNK;
@@ -31,8 +37,8 @@ template <int TM, int TN, int WM, int WN, int SUB, int NS> struct RingCfg {
 };
 
 template <int TM, int TN, int WM, int WN, int SUB, int NS, int EPI, bool BKM>
-__global__ __launch_bounds__(256) void gemm_ring_kernel(const bf16* __restrict__ A, int64_t lda, const bf16* __restrict__ B, int64_t ldb,
-                                                        int M, int N, int K, Epi epi) {
+__global__ __launch_bounds__((RingCfg<TM, TN, WM, WN, SUB, NS>::NW * 64)) void gemm_ring_kernel(
+    const bf16* __restrict__ A, int64_t lda, const bf16* __restrict__ B, int64_t ldb, int M, int N, int K, Epi epi, int n_fast) {
     using C = RingCfg<TM, TN, WM, WN, SUB, NS>;
     constexpr int KIND = EPI & ~EPI_ERF;
     constexpr int BM = C::BM, BN = C::BN, NW = C::NW, LPW = C::LPW;
@@ -42,10 +48,9 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const bf16* __restrict__
     const int g = lane >> 5, fr = lane & 31;
     const bool computes = wave < WM * WN;
     const int wm = wave / WN, wn = wave % WN;
-    // m fastest: an XCD's run of tiles then reads each slice of B once and the (small) A from its L2
-    const int tiles_m = (M + BM - 1) / BM;
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int tile = xcd_remap(blockIdx.x, gridDim.x);
-    const int n0 = (tile / tiles_m) * BN, m0 = (tile % tiles_m) * BM;
+    const int n0 = (n_fast ? tile % tiles_n : tile / tiles_m) * BN, m0 = (n_fast ? tile / tiles_n : tile % tiles_m) * BM;
     const unsigned lds0 = (unsigned)(uintptr_t)LDS_PTR(unsigned char, smem);
 
     // ---- this wavefront's loads of a stage: a scalar base per operand, advanced along K, and a 32-bit byte offset per lane.
@@ -76,10 +81,11 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const bf16* __restrict__
     const char* zero = reinterpret_cast<const char*>(g_zero_chunk);
     const int nst = (K + 64 * SUB - 1) / (64 * SUB);
     const int nfull = K / (64 * SUB);                           // stages that lie within K
-    auto issue = [&](int st, auto full_tag) {
+    // requests t0 .. t1 - 1 of the wavefront's LPW of a stage
+    auto issue = [&](int st, auto full_tag, int t0, int t1) {
         const unsigned sb = lds0 + ((unsigned)st % NS) * C::STAGE;
 #pragma unroll
-        for (int t = 0; t < LPW; ++t) {
+        for (int t = t0; t < t1; ++t) {
             const int sub = (NW * t) / C::LPC, k0 = (st * SUB + sub) * 64;
             const bool isA = (NW * t) % C::LPC < C::LA;
             const char* base = isA ? a_base + (int64_t)k0 * 2 : b_base + (BKM ? (int64_t)k0 * ldb * 2 : (int64_t)k0 * 2);
@@ -89,18 +95,19 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const bf16* __restrict__
         }
     };
     auto issue_any = [&](int st) {
-        if (st < nfull) issue(st, std::true_type{});
-        else if (st < nst) issue(st, std::false_type{});
+        if (st < nfull) issue(st, std::true_type{}, 0, LPW);
+        else if (st < nst) issue(st, std::false_type{}, 0, LPW);
     };
 
     // ---- epilogue geometry; its operands do not depend on the products: requested first, landed long before use ----
     constexpr int QPR = BN / 4, ROWS = NW * 64 / QPR, PASS = BM / ROWS;       // threads per row, rows per pass
     const int c4 = tid % QPR, rr = tid / QPR, n = n0 + 4 * c4;
+    constexpr bool AHEAD_OPND = PASS <= 16;
     f32x4_t bv = {0.f, 0.f, 0.f, 0.f}, opnd[PASS];
     if (n < N) {
         if (KIND == EPI_BIAS || KIND == EPI_BIAS_GELU || KIND == EPI_RESIDUAL)
             bv = ld_bf16x4(reinterpret_cast<const bf16*>(epi.bias) + n);
-        if (PASS <= 4)
+        if (AHEAD_OPND)
 #pragma unroll
             for (int p = 0; p < PASS; ++p) opnd[p] = epi_load4<KIND>(epi, min(m0 + rr + p * ROWS, M - 1), n);
     }
@@ -125,28 +132,23 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const bf16* __restrict__
             bt_off[j] = C::A_BYTES + r * (BN * 2) + (((c >> 3) ^ bswz(r)) << 4) + (c & 7) * 2;
         }
     }
-    struct Frags { bf16x8_t a[KK][TM], b[KK][TN]; };
-    auto read = [&](Frags& f, int st) {
-        const unsigned char* base = smem + ((unsigned)st % NS) * C::STAGE;
+    bf16x8_t fa[KK][TM], fb[KK][TN];
+    auto read = [&](int kk, int st) {
+        const unsigned char* p = smem + ((unsigned)st % NS) * C::STAGE + (kk >> 2) * C::CHUNK;
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            const unsigned char* p = base + (kk >> 2) * C::CHUNK;
+        for (int i = 0; i < TM; ++i) fa[kk][i] = *reinterpret_cast<const bf16x8_t*>(p + a_off[kk & 3] + i * 32 * 128);
 #pragma unroll
-            for (int i = 0; i < TM; ++i) f.a[kk][i] = *reinterpret_cast<const bf16x8_t*>(p + a_off[kk & 3] + i * 32 * 128);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                if (BKM) {
-                    const unsigned char* q = p + bt_off[j] + (kk & 3) * 16 * (BN * 2);
-                    union { struct { s16x4_t lo, hi; } s; bf16x8_t v; } u;
-                    u.s.lo = lds_tr16(reinterpret_cast<const uint16_t*>(q));
-                    u.s.hi = lds_tr16(reinterpret_cast<const uint16_t*>(q + 4 * (BN * 2)));
-                    f.b[kk][j] = u.v;
-                } else {
-                    f.b[kk][j] = *reinterpret_cast<const bf16x8_t*>(p + b_off[kk & 3] + j * 32 * 128);
-                }
+        for (int j = 0; j < TN; ++j) {
+            if (BKM) {
+                const unsigned char* q = p + bt_off[j] + (kk & 3) * 16 * (BN * 2);
+                union { struct { s16x4_t lo, hi; } s; bf16x8_t v; } u;
+                u.s.lo = lds_tr16(reinterpret_cast<const uint16_t*>(q));
+                u.s.hi = lds_tr16(reinterpret_cast<const uint16_t*>(q + 4 * (BN * 2)));
+                fb[kk][j] = u.v;
+            } else {
+                fb[kk][j] = *reinterpret_cast<const bf16x8_t*>(p + b_off[kk & 3] + j * 32 * 128);
             }
         }
-        __builtin_amdgcn_sched_barrier(0);
     };
     f32x16_t acc[TN][TM];
 #pragma unroll
@@ -155,15 +157,11 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const bf16* __restrict__
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][i][v] = 0.f;
-    auto products = [&](const Frags& f, int chunks) {           // of the first `chunks` chunks of a stage
+    auto products = [&](int kk) {
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            if (kk % 4 == 0 && kk / 4 >= chunks) break;
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int i = 0; i < TM; ++i) acc[j][i] = mfma32(f.b[kk][j], f.a[kk][i], acc[j][i]);
-        }
+            for (int i = 0; i < TM; ++i) acc[j][i] = mfma32(fb[kk][j], fa[kk][i], acc[j][i]);
     };
     // This wavefront's loads of a stage have landed, with those of the AHEAD stages after it still under way, and its LDS
     // reads have returned; then the same for everybody.
@@ -173,18 +171,27 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const bf16* __restrict__
         asm volatile("s_barrier" ::: "memory");
     };
     using Ahead = std::integral_constant<int, NS - 2>;
-    // a stage whose refill (of the stage read last, before the barrier) lies within K ...
-    auto step = [&](Frags& now, const Frags& before, int st) {
+    // A stage: step by step, the products of the stage before it, then the fragments for the next time in their place, then a
+    // share of the requests, which held up the reads behind them where all came first (64x64 tiles, two workgroups per CU: the
+    // other way round, 10.7 and 13.3 us at 197 rows, N = 768, K = 3072).
+    // A stage whose refill (of the stage read last, before the barrier) lies within K ...
+    constexpr bool SPREAD = C::NW > 4;
+    auto step = [&](int st) {
         landed(Ahead{});
-        issue(st + NS - 1, std::true_type{});
+        if (!SPREAD || !computes) issue(st + NS - 1, std::true_type{}, 0, LPW);
         if (computes) {
-            read(now, st);
-            products(before, SUB);
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                products(kk);
+                __builtin_amdgcn_sched_barrier(0);
+                read(kk, st);
+                if (SPREAD) issue(st + NS - 1, std::true_type{}, LPW * kk / KK, LPW * (kk + 1) / KK);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     };
-    // ... and one near the end
-    const int last_chunks = (K + 63) / 64 - (nst - 1) * SUB;    // of the last stage
-    auto end_step = [&](Frags& now, const Frags& before, int st) {
+    // ... and one near the end, or the first
+    auto end_step = [&](int st) {
         const int ahead = nst - 1 - st;
         if (ahead >= NS - 2) landed(Ahead{});
         else if (ahead >= (NS - 2) / 2) landed(std::integral_constant<int, (NS - 2) / 2>{});
@@ -192,25 +199,22 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const bf16* __restrict__
         else landed(std::integral_constant<int, 0>{});
         issue_any(st + NS - 1);
         if (computes) {
-            read(now, st);
-            if (st > 0) products(before, SUB);
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                if (st > 0) products(kk);
+                read(kk, st);
+            }
         }
     };
-    Frags f0, f1;
-    end_step(f0, f1, 0);
+    end_step(0);
     int st = 1;
-    for (; st + NS < nfull; st += 2) {
-        step(f1, f0, st);
-        step(f0, f1, st + 1);
-    }
-    for (; st + 1 < nst; st += 2) {
-        end_step(f1, f0, st);
-        end_step(f0, f1, st + 1);
-    }
-    if (st < nst) end_step(f1, f0, st);
+    for (; st + NS - 1 < nfull; ++st) step(st);
+    for (; st < nst; ++st) end_step(st);
     if (computes) {
-        if (nst & 1) products(f0, last_chunks);
-        else products(f1, last_chunks);
+        const int last_steps = ((K + 63) / 64 - (nst - 1) * SUB) * 4;          // of the last stage
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk)
+            if (kk < last_steps) products(kk);
     }
 
     // ---- the tile through LDS, out in full rows ----
@@ -234,7 +238,7 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const bf16* __restrict__
             const int r = rr + p * ROWS, m = m0 + r;
             if (m < M) {
                 const f32x4_t v = *reinterpret_cast<const f32x4_t*>(ct + r * C::PITCH + 4 * c4);
-                const f32x4_t x = PASS <= 4 ? opnd[p] : epi_load4<KIND>(epi, m, n);
+                const f32x4_t x = AHEAD_OPND ? opnd[p] : epi_load4<KIND>(epi, m, n);
                 const f32x4_t o = epi_store4<EPI>(epi, m, n, v, bv, x);
                 if (KIND == EPI_GELU_BWD) csum += o;
             }
@@ -259,8 +263,11 @@ static int launch_ring(hipStream_t s, const bf16* A, int64_t lda, const bf16* B,
     static LdsLimit lim;
     auto kern = gemm_ring_kernel<TM, TN, WM, WN, SUB, NS, EPI, BKM>;
     if (int rc = lim.ensure(reinterpret_cast<const void*>(kern), C::SHMEM)) return rc;
-    const int tiles = ((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
-    hipLaunchKernelGGL(kern, dim3(tiles), dim3(256), C::SHMEM, s, A, lda, B, ldb, M, N, K, epi);
+    // Which way an XCD's run of tiles goes: the one in which it reads fewer rows of A and B.  (7289 x 384, K = 1536: 19.9 us down
+    // the columns, 18.8 along the rows.)
+    const int tm = (M + C::BM - 1) / C::BM, tn = (N + C::BN - 1) / C::BN, run = (tm * tn + 7) / 8;
+    const int down = std::min(run, tm) * C::BM + (run + tm - 1) / tm * C::BN, along = std::min(run, tn) * C::BN + (run + tn - 1) / tn * C::BM;
+    hipLaunchKernelGGL(kern, dim3(tm * tn), dim3(C::NW * 64), C::SHMEM, s, A, lda, B, ldb, M, N, K, epi, (int)(along < down));
     REV_HIP(hipGetLastError());
     return REV_OK;
 }
@@ -269,9 +276,11 @@ template <int EPI, bool BKM>
 static int dispatch_ring(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
                          const Epi& epi, GemmShape shape) {
     switch (shape) {
-        case GS_32x32: return launch_ring<1, 1, 1, 1, 2, 4, EPI, BKM>(s, A, lda, B, ldb, M, N, K, epi);     // 64 to 72 KB of LDS:
-        case GS_64x64: return launch_ring<1, 1, 2, 2, 1, 4, EPI, BKM>(s, A, lda, B, ldb, M, N, K, epi);     // two workgroups
-        case GS_64x128_RING: return launch_ring<1, 2, 2, 2, 1, 3, EPI, BKM>(s, A, lda, B, ldb, M, N, K, epi);   // per CU
+        case GS_32x32: return launch_ring<1, 1, 1, 1, 2, 4, EPI, BKM>(s, A, lda, B, ldb, M, N, K, epi);     // 64 KB of LDS: two
+        case GS_64x64: return launch_ring<1, 1, 2, 2, 1, 4, EPI, BKM>(s, A, lda, B, ldb, M, N, K, epi);     // workgroups per CU
+        case GS_64x128_RING: return launch_ring<1, 1, 2, 4, 1, 4, EPI, BKM>(s, A, lda, B, ldb, M, N, K, epi);   // 96, 128 and 160 KB: one
+        case GS_128x128_RING: return launch_ring<2, 1, 2, 4, 1, 4, EPI, BKM>(s, A, lda, B, ldb, M, N, K, epi);
+        case GS_192x128_RING: return launch_ring<3, 1, 2, 4, 1, 4, EPI, BKM>(s, A, lda, B, ldb, M, N, K, epi);
         default: set_error("gemm_bf16: no such tile"); return REV_EINVAL;
     }
 }
