@@ -22,6 +22,7 @@
 // 512 heads of 257, 80 features: 84 -> 37; 12288 windows of 49, 32 features: 53 -> 42.  Backward: 384 heads of 512 tokens: 148 ->
 // 126; 512 heads of 257, 80 features: 146 -> 108; one image of 12 heads, 197 tokens: 18.0 -> 12.0.
 #include "attention.h"
+#include "gemm_wgrad_dma.h"
 
 namespace rev {
 
@@ -595,6 +596,18 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_pair_dma(BwdArgs a) {
     else bwd_dkv_rows<DH, true>(a, smem, xcd_remap(blk - n, n));
 }
 
+// The pair and, in the workgroups behind its `attn_blocks`, weight gradients over the same rows: the pair leaves most of the chip idle
+// for as long as they take.  12 heads of 197 tokens: 13.0 us, 17.0 with the three weight gradients of an MLP and a projection 768 wide, which
+// take 10.4 by themselves.
+template <int DH>
+__global__ __launch_bounds__(256, 2) void attn_bwd_pair_wgrad(BwdArgs a, WgradTail w, int attn_blocks) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int n = attn_blocks >> 1, blk = blockIdx.x;
+    if (blk < n) bwd_dq_rows<DH>(a, smem, xcd_remap(blk, n));
+    else if (blk < attn_blocks) bwd_dkv_rows<DH, true>(a, smem, xcd_remap(blk - n, n));
+    else wgrad_small_block(w.grp, w.M, w.steps, blk - attn_blocks);
+}
+
 #define RES_BARRIER(n) do { asm volatile("" ::: "memory"); res_wait(n); __builtin_amdgcn_s_barrier(); asm volatile("" ::: "memory"); } while (0)
 
 // ----------------------------------------------------------------------------------------
@@ -852,12 +865,16 @@ static int fwd_dma(hipStream_t s, const bf16* qkv, bf16* o, float* lse, int B, i
 // Workgroups of two wavefronts instead of four as long as every CU gets at most one of them (12 heads of 197 tokens: 12.0
 // against 12.3; 24 of 128, 64 features: 8.1 against 8.8; where a CU gets two, both use the same two SIMDs: 48 of 197, 14.5
 // against 12.7).
+static bool bwd_pair_pays(int heads, int T, int dh) {
+    const int tiles = (T + 31) / 32;
+    return dh == 64 && T <= 256 ? heads <= (tiles > 2 ? 128 : 256) : 2 * heads * ((tiles + 3) / 4) <= 768;
+}
 template <int DH>
 static int bwd_dma(hipStream_t s, BwdArgs a, int B) {
     const int heads = B * a.H, tiles = (a.T + 31) / 32;
     int nw;
     const bool fits = DH <= 64 && a.T <= 256;
-    if (fits && DH == 64 ? heads <= (tiles > 2 ? 128 : 256) : 2 * heads * ((tiles + 3) / 4) <= 768) {
+    if (bwd_pair_pays(heads, a.T, DH)) {
         split_rows(a.T, 2 * heads * ((tiles + 1) / 2) <= 256 ? 2 : 4, &a.nblk, &nw);
         a.delta = nullptr;
         const size_t lds = ring_lds<TileRing<DH, 3, 1>>(a.T) + nw * 128;
@@ -881,6 +898,31 @@ static int bwd_dma(hipStream_t s, BwdArgs a, int B) {
     hipLaunchKernelGGL(attn_bwd_dkv_dma<DH>, dim3(heads * a.nblk), dim3(nw * 64), lds2, s, a);
     REV_HIP(hipGetLastError());
     return REV_OK;
+}
+
+// with weight gradients: workgroups of four wavefronts, as theirs
+template <int DH>
+static int bwd_wgrad_dma(hipStream_t s, BwdArgs a, int B, const WgradTail& w) {
+    const int heads = B * a.H;
+    a.nblk = ((a.T + 31) / 32 + 3) / 4;
+    const int lds = std::max((int)(ring_lds<TileRing<DH, 3, 1>>(a.T) + 4 * 128), 2 * WD_STAGE), attn_blocks = 2 * heads * a.nblk;
+    static LdsLimit lim;
+    if (int rc = lim.ensure(reinterpret_cast<const void*>(attn_bwd_pair_wgrad<DH>), 2 * WD_STAGE)) return rc;
+    hipLaunchKernelGGL(attn_bwd_pair_wgrad<DH>, dim3(attn_blocks + w.grp.tile_blocks), dim3(256), lds, s, a, w, attn_blocks);
+    REV_HIP(hipGetLastError());
+    return REV_OK;
+}
+bool attention_takes_wgrad(int B, int T, int H, int dh) { return attention_dma_takes(dh) && bwd_pair_pays(B * H, T, dh); }
+int attention_backward_wgrad(hipStream_t s, const bf16* qkv, const bf16* o, const bf16* dout, const float* lse, bf16* dqkv, int B, int T,
+                             int H, int dh, const int* key_len, const WgradItem* items, int count) {
+    const BwdArgs a = {qkv, o, dout, lse, dqkv, nullptr, key_len, T, H, 0};
+    WgradTail w;
+    double flops = 8.0 * B * H * (double)T * T * dh;
+    if (int rc = gemm_wgrad_bf16_beside(items, count, B * T, &w, &flops)) return rc;
+    ProfScope ps(K_ATTN_BWD, s, flops);
+    if (dh == 32) return bwd_wgrad_dma<32>(s, a, B, w);
+    if (dh == 64) return bwd_wgrad_dma<64>(s, a, B, w);
+    return bwd_wgrad_dma<80>(s, a, B, w);
 }
 
 bool attention_dma_takes(int dh) { return dh == 32 || dh == 64 || dh == 80; }

@@ -179,9 +179,18 @@ struct WgradItem {
 int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int M, float* scratch, int64_t scratch_elems,
                           RedSeg* segs, int* nseg);
 int64_t wgrad_scratch_elems(int M, const int* N, const int* K, int count);   // floats of scratch it needs for these shapes
-// The float32 flavour: up to WGRAD_GROUP_MAX weight gradients in one launch, no pieces.
-struct WgradF32Item { const float* G; int64_t ldg; const float* A; int64_t lda; int N, K; float* dW; };
+// Rows up to which the column sums that ride in a launch of weight gradients come in one piece (sums.h): 1024 rows take about 7 us,
+// less than the products beside them.
+constexpr int COLSUM_ROWS = 1024;
+// The float32 flavour: up to WGRAD_GROUP_MAX weight gradients in one launch, no pieces; colsum (nullable, one of a group, up to
+// COLSUM_ROWS rows): the column sums of G.
+struct WgradF32Item { const float* G; int64_t ldg; const float* A; int64_t lda; int N, K; float* dW; float* colsum; };
 int gemm_wgrad_f32_group(hipStream_t s, const WgradF32Item* items, int count, int M);
+// C[M,N] = A[M,K] * B[K,N], weight gradients over the same M rows, and second stages of sums in one launch, for small blocks
+// (gemm_wgrad_f32_together)
+bool gemm_wgrad_f32_together(int M, int N, const int* wn, const int* wk, int count);
+int gemm_nn_wgrad_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, float* out, int64_t ldo,
+                      const WgradF32Item* items, int count, const RedSeg* segs, int nseg);
 // Column sums that ride in a weight-gradient launch: its last workgroups take 512 columns of one of `chunks` runs of `rows`
 // tokens each (n = 0: none); the chunks' sums go to out[chunk * n + column].
 // At most two cotangents; block0: the first of a cotangent's workgroups, counted from the first behind the tiles.
@@ -189,7 +198,16 @@ constexpr int WGRAD_SUMS_MAX = 2;
 struct WgradSums { const bf16* g; float* out; float* total; int64_t ld; int n, rows, chunks, block0; };
 // device-side description of the launch (gemm_wgrad_dma.hip)
 struct WgradProblem { const bf16* G; const bf16* A; float* out; int64_t ldg, lda, split_stride; int N, K, tile0; };
-struct WgradGroup { WgradProblem p[WGRAD_GROUP_MAX]; WgradSums sums[WGRAD_SUMS_MAX]; int count, tiles_total, tile_blocks, sum_blocks; };
+// tile: 64 (64x64), 128 (128x128) or 256 (256x128)
+struct WgradGroup { WgradProblem p[WGRAD_GROUP_MAX]; WgradSums sums[WGRAD_SUMS_MAX]; int count, tile, tiles_total, tile_blocks, sum_blocks; };
+// Weight gradients that ride in the last workgroups of another launch over the same M rows, where gemm_wgrad_bf16_together says so:
+// of the attention backward (attention_backward_wgrad), and, with second stages of sums too, of an input gradient out[M,N] =
+// A[M,K] * B[K,N].
+struct WgradTail { WgradGroup grp; int M, steps; };
+bool gemm_wgrad_bf16_together(int M, int N, int K, const int* wn, const int* wk, int count);
+int gemm_wgrad_bf16_beside(const WgradItem* items, int count, int M, WgradTail* out, double* flops);
+int gemm_nn_wgrad_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, bf16* out, int64_t ldo,
+                       const WgradItem* items, int count, const RedSeg* segs, int nseg);
 // The same in 256x256 tiles (gemm_wgrad_big.hip): `full` tiles run over all tokens, the others over `splits` ranges of them.
 struct WgradBigProblem { const bf16* G; const bf16* A; float* dW; int64_t ldg, lda; int N, K, tile0; };
 struct WgradBig {
@@ -240,5 +258,10 @@ template <typename TA>
 int attention_backward(hipStream_t s, const TA* qkv, const TA* o, const TA* dout, const float* lse,
                        TA* dqkv, float* delta, int B, int T, int H, int dh, const int* key_len = nullptr,
                        bool solo = false);     // solo: the launch has the device to itself (one stream)
+
+// The attention backward of bf16 heads and weight gradients over the same rows in one launch, where attention_takes_wgrad says so
+bool attention_takes_wgrad(int B, int T, int H, int dh);
+int attention_backward_wgrad(hipStream_t s, const bf16* qkv, const bf16* o, const bf16* dout, const float* lse, bf16* dqkv, int B, int T,
+                             int H, int dh, const int* key_len, const WgradItem* items, int count);
 
 }  // namespace rev

@@ -16,6 +16,7 @@
 // 32x32 tiles unless there are 512 of 64x64: below that the chip is not full and the shorter chain wins.  Both sum the
 // same products in the same order.  591 rows, 384 x 1536 (0.7 GFLOP): 8-9 us; 64x64 tiles on the vector units took 150-174.
 #include "gemm_epilogue.h"
+#include "sums.h"
 
 namespace rev {
 
@@ -207,9 +208,11 @@ __global__ __launch_bounds__(F_NW * 64) void gemm_f32_kernel(const float* __rest
 struct WgradF32Problem { const float* G; const float* A; float* out; int64_t ldg, lda; int N, K, tile0; };
 struct WgradF32Group { WgradF32Problem p[WGRAD_GROUP_MAX]; int count; };
 
+// The column sums of a cotangent ride in the last workgroups (sum_blocks of them).
+struct WgradF32Sums { const float* in; float* out; int64_t ld; int n, blocks; };
+
 template <int TM, int TN>
-__global__ __launch_bounds__(F_NW * 64) void wgrad_f32_kernel(WgradF32Group grp, int M) {
-    const int lin = xcd_remap(blockIdx.x, gridDim.x);
+__device__ __forceinline__ void wgrad_f32_block(const WgradF32Group& grp, int M, int lin) {
     int pi = 0;
 #pragma unroll
     for (int k = 1; k < WGRAD_GROUP_MAX; ++k)
@@ -219,6 +222,36 @@ __global__ __launch_bounds__(F_NW * 64) void wgrad_f32_kernel(WgradF32Group grp,
     Epi e = {};
     e.outf = q.out; e.ldo = q.K;
     gemm_f32_tile<TM, TN, EPI_PLAIN_F32, true, true>(q.G, q.ldg, q.A, q.lda, q.N, q.K, M, e, (t % tiles_n) * 32 * TM, (t / tiles_n) * 32 * TN);
+}
+template <int TM, int TN>
+__global__ __launch_bounds__(F_NW * 64) void wgrad_f32_kernel(WgradF32Group grp, int M, WgradF32Sums sums) {
+    const int tiles = gridDim.x - sums.blocks;
+    if ((int)blockIdx.x >= tiles) {
+        extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+        colsum_block<float>(sums.in, sums.ld, M, sums.n, sums.out, blockIdx.x - tiles, reinterpret_cast<float*>(smem));
+        return;
+    }
+    wgrad_f32_block<TM, TN>(grp, M, xcd_remap(blockIdx.x, tiles));
+}
+// C[M,N] = A[M,K] * B[K,N] and, in the workgroups behind its `gemm_blocks` tiles, weight gradients over the same M rows, the column
+// sums and second stages of sums: everything that a block's backward still has to do with the rows of A, and with partial sums
+// that earlier launches left.  For blocks whose launches do not fill the chip: each of the four costs 3 to 5 us by itself there,
+// whatever it does.  Four blocks of 32 rows, D = 64: 302 -> 264 us; three of 591 rows, D = 384: 503 -> 478.
+struct WgradF32Beside { WgradF32Group grp; WgradF32Sums sums; RedArgs red; int gemm_blocks, tile_blocks, M; };
+__global__ __launch_bounds__(F_NW * 64) void gemm_wgrad_f32_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ B,
+                                                                   int64_t ldb, int N, int K, Epi epi, WgradF32Beside w) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    int b = blockIdx.x;
+    if (b < w.gemm_blocks) {
+        const int tiles_m = (w.M + 31) / 32, tile = xcd_remap(b, w.gemm_blocks);
+        gemm_f32_tile<1, 1, EPI_PLAIN, false, true>(A, lda, B, ldb, w.M, N, K, epi, (tile % tiles_m) * 32, (tile / tiles_m) * 32);
+    } else if ((b -= w.gemm_blocks) < w.tile_blocks) {
+        wgrad_f32_block<1, 1>(w.grp, w.M, xcd_remap(b, w.tile_blocks));
+    } else if ((b -= w.tile_blocks) < w.sums.blocks) {
+        colsum_block<float>(w.sums.in, w.sums.ld, w.M, w.sums.n, w.sums.out, b, reinterpret_cast<float*>(smem));
+    } else {
+        reduce_block(w.red, b - w.sums.blocks, reinterpret_cast<float4*>(smem));
+    }
 }
 
 static inline int64_t f32_tiles(int M, int N, int b) { return (int64_t)((M + b - 1) / b) * ((N + b - 1) / b); }
@@ -263,35 +296,81 @@ int gemm_nn_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int6
     return gemm_f32<true>(s, A, lda, B, ldb, M, N, K, epi);
 }
 
-int gemm_wgrad_f32_group(hipStream_t s, const WgradF32Item* items, int count, int M) {
-    WgradF32Group grp = {};
-    grp.count = count;
+static int wgrad_f32_args(const WgradF32Item* items, int count, int M, WgradF32Group* grp, WgradF32Sums* sums, bool* wide, int* tiles, double* flops) {
     int64_t t64 = 0, t32 = 0;
-    double flops = 0;
+    grp->count = count;
     for (int k = 0; k < count; ++k) {
         const WgradF32Item& it = items[k];
-        if (it.N % 4 || it.K % 4 || (it.ldg & 3) || (it.lda & 3) || (((uintptr_t)it.G | (uintptr_t)it.A | (uintptr_t)it.dW) & 15)) {
+        if (it.N % 4 || it.K % 4 || (it.ldg & 3) || (it.lda & 3) ||
+            (((uintptr_t)it.G | (uintptr_t)it.A | (uintptr_t)it.dW | (uintptr_t)it.colsum) & 15)) {
             set_error("gemm_wgrad_f32: sizes must be multiples of 4 and every buffer 16-byte aligned");
             return REV_EINVAL;
         }
         t64 += f32_tiles(it.N, it.K, 64);
-        flops += 2.0 * M * it.N * it.K;
+        *flops += 2.0 * M * it.N * it.K;
+        if (it.colsum) {
+            if (sums->blocks) { set_error("gemm_wgrad_f32: column sums of one cotangent per launch"); return REV_EINVAL; }
+            *sums = {it.G, it.colsum, it.ldg, it.N, colsum_blocks(it.N)};
+        }
     }
-    const bool wide = t64 >= 512;
+    *wide = t64 >= 512;
     for (int k = 0; k < count; ++k) {
         const WgradF32Item& it = items[k];
-        grp.p[k] = {it.G, it.A, it.dW, it.ldg, it.lda, it.N, it.K, (int)t32};
-        t32 += f32_tiles(it.N, it.K, wide ? 64 : 32);
+        grp->p[k] = {it.G, it.A, it.dW, it.ldg, it.lda, it.N, it.K, (int)t32};
+        t32 += f32_tiles(it.N, it.K, *wide ? 64 : 32);
     }
+    *tiles = (int)t32;
+    return REV_OK;
+}
+
+int gemm_wgrad_f32_group(hipStream_t s, const WgradF32Item* items, int count, int M) {
+    WgradF32Group grp = {};
+    WgradF32Sums sums = {};
+    bool wide;
+    int tiles;
+    double flops = 0;
+    if (int rc = wgrad_f32_args(items, count, M, &grp, &sums, &wide, &tiles, &flops)) return rc;
     ProfScope ps(K_GEMM_WGRAD, s, flops);
     static LdsLimit lim1, lim2;
+    const dim3 grid((unsigned)(tiles + sums.blocks)), block(F_NW * 64);
     if (wide) {
         if (int rc = lim2.ensure(reinterpret_cast<const void*>(wgrad_f32_kernel<2, 2>), FCfg<2, 2>::SHMEM)) return rc;
-        hipLaunchKernelGGL((wgrad_f32_kernel<2, 2>), dim3((unsigned)t32), dim3(F_NW * 64), (FCfg<2, 2>::SHMEM), s, grp, M);
+        hipLaunchKernelGGL((wgrad_f32_kernel<2, 2>), grid, block, (FCfg<2, 2>::SHMEM), s, grp, M, sums);
     } else {
         if (int rc = lim1.ensure(reinterpret_cast<const void*>(wgrad_f32_kernel<1, 1>), FCfg<1, 1>::SHMEM)) return rc;
-        hipLaunchKernelGGL((wgrad_f32_kernel<1, 1>), dim3((unsigned)t32), dim3(F_NW * 64), (FCfg<1, 1>::SHMEM), s, grp, M);
+        hipLaunchKernelGGL((wgrad_f32_kernel<1, 1>), grid, block, (FCfg<1, 1>::SHMEM), s, grp, M, sums);
     }
+    REV_HIP(hipGetLastError());
+    return REV_OK;
+}
+
+// One launch for all of it as long as 32x32 tiles are what each of the two would take by itself, and the column sums come in one piece.
+bool gemm_wgrad_f32_together(int M, int N, const int* wn, const int* wk, int count) {
+    int64_t t64 = 0;
+    for (int k = 0; k < count; ++k) t64 += f32_tiles(wn[k], wk[k], 64);
+    return M <= COLSUM_ROWS && t64 < 512 && !f32_wide(M, N);
+}
+int gemm_nn_wgrad_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, float* out, int64_t ldo,
+                      const WgradF32Item* items, int count, const RedSeg* segs, int nseg) {
+    if (K % 4 || N % 4 || (lda & 3) || (ldb & 3) || ldo % 4 || (((uintptr_t)A | (uintptr_t)B | (uintptr_t)out) & 15)) {
+        set_error("gemm_f32: sizes must be multiples of 4 and every buffer 16-byte aligned");
+        return REV_EINVAL;
+    }
+    WgradF32Beside w = {};
+    bool wide;
+    double flops = 2.0 * M * N * K, bytes = 0;
+    if (int rc = wgrad_f32_args(items, count, M, &w.grp, &w.sums, &wide, &w.tile_blocks, &flops)) return rc;
+    const int red_blocks = reduce_args(segs, nseg, &w.red, &bytes);
+    if (red_blocks < 0) return red_blocks;
+    w.M = M;
+    w.gemm_blocks = (int)f32_tiles(M, N, 32);
+    Epi e = {};
+    e.out = out; e.ldo = ldo;
+    ProfScope ps(K_GEMM_WGRAD, s, flops);
+    static LdsLimit lim;
+    if (int rc = lim.ensure(reinterpret_cast<const void*>(gemm_wgrad_f32_kernel), FCfg<1, 1>::SHMEM)) return rc;
+    hipLaunchKernelGGL(gemm_wgrad_f32_kernel, dim3((unsigned)(w.gemm_blocks + w.tile_blocks + w.sums.blocks + red_blocks)), dim3(F_NW * 64),
+                       (FCfg<1, 1>::SHMEM), s, A, lda, B, ldb, N, K, e, w);
     REV_HIP(hipGetLastError());
     return REV_OK;
 }

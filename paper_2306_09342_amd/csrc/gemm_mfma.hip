@@ -6,6 +6,7 @@
 //            gemm_wgrad_big.hip) and the number of token ranges; the pieces of the ranges are summed afterwards in
 //            range order, so results do not depend on scheduling.
 #include "mfma.h"
+#include "sums.h"
 
 namespace rev {
 
@@ -249,6 +250,16 @@ constexpr int WG_BR = 64;             // tokens per step
 // weight.  Narrow layers with very many tokens (window-attention stages: a handful of tiles, thousands of steps) get up to
 // 128 ranges.
 //
+// 64x64 tiles in the ring where they all run at once and the tokens are few (COLSUM_ROWS): over all tokens, so that no second
+// stage is left.  us, the 128x128 tiles' ranges / these, the launch that adds the pieces not counted: 197 tokens, D = 128: 7.0 / 4.8; 591,
+// 384: 9.6 / 8.6; 1024, 256: 8.7 / 7.1; 1024, 384: 10.6 / 10.6.
+//
+// 256x128 tiles in the ring in the place of 128x128 ones where they run at once, one per CU, on most of the CUs, with at most a fifth
+// more of padding, over ranges of at least 40 steps: 6304 tokens, D = 512: 65 / 53; 768: 115 / 103; 25216, 384: 126 / 123 (of which the
+// column sums, which find no idle CU, take 12); below 40 steps the deeper fill costs what the operands save:
+// 6304, 384 (25 steps): 32.9 / 33.3;
+// 1576, 768 (25): 29.6 / 32.4; and so do CUs that stay idle: 3152, 640 (165 tiles): 44.7 / 46.3.
+//
 // 256x256 tiles (gemm_wgrad_big.hip): whole rounds of 256 tiles run over all tokens; what is left over (or a group with
 // fewer than 256 tiles) is cut into the number of ranges that keeps the CUs busiest, its pieces counted at the time of
 // writing and reading them.
@@ -260,7 +271,7 @@ constexpr int WG_BR = 64;             // tokens per step
 // 25216, 384 (134) and 1500, 1280 (84) take small tiles, where the two were within 7 % of each other.
 struct WgradPlan {
     bool big;
-    int S, sps;                       // 128x128: token ranges and steps per range
+    int tile, S, sps;                 // 64x64, 128x128, 256x128: token ranges and steps per range
     int tiles, full, splits, stages, stages_per_split;   // 256x256
     int tile_blocks;
     int64_t piece_elems, elems;       // floats of scratch: the pieces, and with the column sums' chunks
@@ -268,11 +279,15 @@ struct WgradPlan {
 // Column sums of n columns behind `blocks` tile workgroups of `steps` stages each: as many workgroups as the last round of
 // tiles leaves slots idle, but no more rows for one than it reads (at about 20 GB/s, 40 with 8 wavefronts) in the time of
 // a tile; in one chunk where that is short anyway.
-static WgradSums sums_plan(int M, int n, int blocks, int steps, bool big) {
+static WgradSums sums_plan(int M, int n, int blocks, int steps, bool big, bool one_per_cu) {
     WgradSums p = {};
-    const int slots = big ? 256 : 512, idle = (slots - blocks % slots) % slots, groups = (n + 511) / 512;
+    if (!one_per_cu && M <= COLSUM_ROWS) {                            // 64 columns a workgroup, no second stage
+        p.n = n; p.chunks = 1; p.rows = M;
+        return p;
+    }
+    const int slots = one_per_cu ? 256 : 512, idle = (slots - blocks % slots) % slots, groups = (n + 511) / 512;
     p.n = n;
-    const int most_rows = steps * (big ? 36 : 13), least = (M + most_rows - 1) / most_rows;
+    const int most_rows = steps * (one_per_cu ? 36 : 13), least = (M + most_rows - 1) / most_rows;
     p.chunks = M <= 256 ? 1 : (idle / groups > least ? idle / groups : least);
     // sums that the idle slots do not hold run after the tiles, with the chip to themselves: then in chunks that fill it (MLP
     // transition, 62720 rows, C = 576: 1672 -> 1629 us; two launches of their own: 1638)
@@ -286,9 +301,11 @@ static WgradSums sums_plan(int M, int n, int blocks, int steps, bool big) {
 static WgradPlan wgrad_plan(int M, const int* N, const int* K, int count) {
     WgradPlan p = {};
     const int steps = (M + WG_BR - 1) / WG_BR;
-    int t128 = 0;
+    int t128 = 0, t64 = 0, t256x128 = 0;
     int64_t nk = 0;
     for (int k = 0; k < count; ++k) {
+        t64 += tiles_of(N[k], K[k], 64, 64);
+        t256x128 += tiles_of(N[k], K[k], 256, 128);
         t128 += tiles_of(N[k], K[k], WG_BP, WG_BQ);
         p.tiles += tiles_of(N[k], K[k], 256, 256);
         nk += (int64_t)N[k] * K[k];
@@ -300,7 +317,8 @@ static WgradPlan wgrad_plan(int M, const int* N, const int* K, int count) {
         const int64_t cap = ((int64_t)64 << 20) / ((int64_t)N[k] * K[k] * 4);
         if (S > cap) S = (int)cap;
     }
-    if (S < 1) S = 1;
+    const bool few = M <= COLSUM_ROWS && t64 <= 512;
+    if (S < 1 || few) S = 1;
     p.sps = (steps + S - 1) / S;
     p.S = (steps + p.sps - 1) / p.sps;                         // no empty ranges
     const double small = 4.0 + (double)((t128 * p.S + 511) / 512) * p.sps + (p.S > 1 ? 4.0 + (double)p.S * nk / 16384 * 0.015 : 0.0);
@@ -319,24 +337,37 @@ static WgradPlan wgrad_plan(int M, const int* N, const int* K, int count) {
     }
     const double large = (double)(p.full / 256) * (7.0 + p.stages * 1.3) + best;
     p.tile_blocks = p.full + rem * p.splits;
-    p.big = M >= 64 && large < 0.95 * small;
+    p.big = !few && M >= 64 && large < 0.95 * small;
+    p.tile = few ? 64 : p.sps >= 40 && t256x128 * p.S <= 256 && t256x128 * p.S >= 180 && t256x128 * 5 <= t128 * 3 ? 256 : 128;
     p.piece_elems = p.big ? (p.splits > 1 ? (int64_t)rem * p.splits * 65536 : 0) : (p.S > 1 ? p.S * nk : 0);
-    if (!p.big) p.tile_blocks = t128 * p.S;
+    if (!p.big) p.tile_blocks = (p.tile == 64 ? t64 : p.tile == 256 ? t256x128 : t128) * p.S;
     p.elems = p.piece_elems;
-    for (int k = 0; k < count; ++k) p.elems += (int64_t)sums_plan(M, N[k], p.tile_blocks, p.big ? p.stages_per_split : p.sps, p.big).chunks * N[k];
+    for (int k = 0; k < count; ++k) p.elems += (int64_t)sums_plan(M, N[k], p.tile_blocks, p.big ? p.stages_per_split : p.sps, p.big, p.big || p.tile == 256).chunks * N[k];
     return p;
 }
 int64_t wgrad_scratch_elems(int M, const int* N, const int* K, int count) { return wgrad_plan(M, N, K, count).elems; }
 
 int launch_wgrad_dma_group(hipStream_t s, const WgradGroup& grp, int M, int sps);
 int launch_wgrad_big(hipStream_t s, const WgradBig& p);
+int launch_gemm_wgrad(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi,
+                      const WgradTail& tail, const RedSeg* segs, int nseg, GemmShape shape);
 
-int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int M, float* scratch, int64_t scratch_elems,
-                          RedSeg* segs, int* nseg) {
-    *nseg = 0;
+static GemmShape plain_shape(int M, int N, int K) {
+    Epi e = {};
+    e.kind = EPI_PLAIN;
+    e.solo = true;
+    return pick_gemm_shape(M, N, K, e);
+}
+// One launch for all of it where the input gradient takes the smallest tiles, which leave most of a CU free, and the weight gradients and column sums
+// come in one piece.
+bool gemm_wgrad_bf16_together(int M, int N, int K, const int* wn, const int* wk, int count) {
+    if (M > COLSUM_ROWS || plain_shape(M, N, K) > GS_64x64) return false;
+    const WgradPlan p = wgrad_plan(M, wn, wk, count);
+    return !p.big && p.S == 1;
+}
+
+static int check_wgrad_items(const WgradItem* items, int count, int M, int* N, int* K, double* flops) {
     if (count < 1 || count > WGRAD_GROUP_MAX) { set_error("gemm_wgrad_bf16: 1 to 4 weight gradients per launch"); return REV_EINVAL; }
-    int N[WGRAD_GROUP_MAX], K[WGRAD_GROUP_MAX];
-    double flops = 0;
     for (int k = 0; k < count; ++k) {
         const WgradItem& it = items[k];
         if ((it.ldg & 7) || (it.lda & 7) || (it.N & 7) || (it.K & 7) || (((uintptr_t)it.G | (uintptr_t)it.A | (uintptr_t)it.dW) & 15)) {
@@ -344,8 +375,58 @@ int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int 
             return REV_EINVAL;
         }
         N[k] = it.N; K[k] = it.K;
-        flops += 2.0 * M * it.N * it.K;
+        *flops += 2.0 * M * it.N * it.K;
     }
+    return REV_OK;
+}
+
+// 64x64 or 128x128 tiles over all of up to COLSUM_ROWS tokens, column sums in one piece: for the last workgroups of another launch
+int gemm_wgrad_bf16_beside(const WgradItem* items, int count, int M, WgradTail* out, double* flops) {
+    int N[WGRAD_GROUP_MAX], K[WGRAD_GROUP_MAX];
+    if (M > COLSUM_ROWS) { set_error("gemm_wgrad_bf16: too many rows to ride in another launch"); return REV_EINVAL; }
+    if (int rc = check_wgrad_items(items, count, M, N, K, flops)) return rc;
+    *out = {};
+    WgradGroup& g = out->grp;
+    int nsums = 0, t64 = 0;
+    for (int k = 0; k < count; ++k) t64 += tiles_of(N[k], K[k], 64, 64);
+    g.count = count;
+    g.tile = t64 <= 512 ? 64 : 128;
+    for (int k = 0; k < count; ++k) {
+        const WgradItem& it = items[k];
+        g.p[k] = {it.G, it.A, it.dW, it.ldg, it.lda, 0, it.N, it.K, g.tiles_total};
+        g.tiles_total += tiles_of(it.N, it.K, g.tile, g.tile);
+        if (!it.colsum) continue;
+        if (nsums == WGRAD_SUMS_MAX) { set_error("gemm_wgrad_bf16: too many column sums"); return REV_EINVAL; }
+        g.sums[nsums++] = {it.G, it.colsum, it.colsum, it.ldg, it.N, M, 1, g.sum_blocks};
+        g.sum_blocks += colsum_blocks(it.N);
+    }
+    for (int k = nsums; k < WGRAD_SUMS_MAX; ++k) g.sums[k].block0 = g.sum_blocks;
+    g.tile_blocks = g.tiles_total;
+    out->M = M;
+    out->steps = (M + WG_BR - 1) / WG_BR;
+    return REV_OK;
+}
+int gemm_nn_wgrad_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, bf16* out, int64_t ldo,
+                       const WgradItem* items, int count, const RedSeg* segs, int nseg) {
+    if (K % 8 || N % 8 || (lda & 7) || (ldb & 7) || ldo % 8 || (((uintptr_t)A | (uintptr_t)B | (uintptr_t)out) & 15)) {
+        set_error("gemm_bf16: sizes must be multiples of 8 and every buffer 16-byte aligned");
+        return REV_EINVAL;
+    }
+    WgradTail tail;
+    double flops = 2.0 * M * N * K;
+    if (int rc = gemm_wgrad_bf16_beside(items, count, M, &tail, &flops)) return rc;
+    Epi e = {};
+    e.kind = EPI_PLAIN; e.out = out; e.ldo = ldo;
+    ProfScope ps(K_GEMM_WGRAD, s, flops);
+    return launch_gemm_wgrad(s, A, lda, B, ldb, M, N, K, e, tail, segs, nseg, plain_shape(M, N, K));
+}
+
+int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int M, float* scratch, int64_t scratch_elems,
+                          RedSeg* segs, int* nseg) {
+    *nseg = 0;
+    int N[WGRAD_GROUP_MAX], K[WGRAD_GROUP_MAX];
+    double flops = 0;
+    if (int rc = check_wgrad_items(items, count, M, N, K, &flops)) return rc;
     const WgradPlan pl = wgrad_plan(M, N, K, count);
     if (pl.elems > 0 && (scratch == nullptr || scratch_elems < pl.elems)) {
         set_error("gemm_wgrad_bf16: scratch too small");
@@ -358,11 +439,11 @@ int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int 
         if (items[k].colsum) {
             if (nsums == WGRAD_SUMS_MAX) { set_error("gemm_wgrad_bf16: too many column sums"); return REV_EINVAL; }
             WgradSums& q = sums[nsums++];
-            q = sums_plan(M, N[k], pl.tile_blocks, pl.big ? pl.stages_per_split : pl.sps, pl.big);
+            q = sums_plan(M, N[k], pl.tile_blocks, pl.big ? pl.stages_per_split : pl.sps, pl.big, pl.big || pl.tile == 256);
             q.g = items[k].G; q.ld = items[k].ldg; q.total = items[k].colsum; q.block0 = sum_blocks;
             q.out = pl.big || q.chunks > 1 ? sums_scratch : q.total;
             sums_scratch += (int64_t)q.chunks * q.n;
-            sum_blocks += q.chunks * ((q.n + 511) / 512);
+            sum_blocks += !pl.big && pl.tile != 256 && q.chunks == 1 ? colsum_blocks(q.n) : q.chunks * ((q.n + 511) / 512);
         }
     for (int k = nsums; k < WGRAD_SUMS_MAX; ++k) sums[k].block0 = sum_blocks;
     ProfScope ps(K_GEMM_WGRAD, s, flops);
@@ -380,14 +461,15 @@ int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int 
         return launch_wgrad_big(s, b);
     }
     WgradGroup grp = {};
-    grp.count = count; grp.tile_blocks = pl.tile_blocks; grp.sum_blocks = sum_blocks;
+    grp.count = count; grp.tile = pl.tile; grp.tile_blocks = pl.tile_blocks; grp.sum_blocks = sum_blocks;
+    const int bp = pl.tile, bq = pl.tile == 64 ? 64 : 128;
     for (int k = 0; k < WGRAD_SUMS_MAX; ++k) grp.sums[k] = sums[k];
     float* part = scratch;
     for (int k = 0; k < count; ++k) {
         const WgradItem& it = items[k];
         const int64_t nk = (int64_t)it.N * it.K;
         grp.p[k] = {it.G, it.A, pl.S > 1 ? part : it.dW, it.ldg, it.lda, nk, it.N, it.K, grp.tiles_total};
-        grp.tiles_total += tiles_of(it.N, it.K, WG_BP, WG_BQ);
+        grp.tiles_total += tiles_of(it.N, it.K, bp, bq);
         if (pl.S > 1) {
             segs[(*nseg)++] = {part, it.dW, nullptr, nk, nk, nk, pl.S};
             part += pl.S * nk;

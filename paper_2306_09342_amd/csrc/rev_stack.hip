@@ -6,6 +6,7 @@
 #include "common.h"
 
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 namespace rev {
@@ -167,7 +168,7 @@ static Layout make_layout(const rev_cfg& c, bool compact) {
     {
         // [0]: fc1 bias gradient (column-sum strips of the GELU' epilogue); [1]: float32 mode, the QKV bias gradients
         const int64_t e0 = (int64_t)(c.mode == REV_MODE_BF16 ? gemm_colsum_strips((int)M, (int)Dm, (int)D) : gemm_f32_colsum_strips((int)M, (int)Dm)) * Dm;
-        const int64_t e1 = c.mode == REV_MODE_BF16 ? 0 : colsum_partial_elems((int)M, (int)(3 * D));
+        const int64_t e1 = c.mode == REV_MODE_BF16 || M <= COLSUM_ROWS ? 0 : colsum_partial_elems((int)M, (int)(3 * D));
         L.part_col[0] = take(e0 * 4);
         L.part_col[1] = take(e1 * 4);
     }
@@ -312,8 +313,30 @@ struct Runner {
     // done_dqkv (nullable): recorded on s when dh, gY1 and dqkv are complete.
     T* gy1_act(int blk, float* o1) const { return kBf16 ? at<T>(L.gy1b[blk & 1]) : reinterpret_cast<T*>(o1); }
 
+    using Item = typename std::conditional<kBf16, WgradItem, WgradF32Item>::type;
+    struct Items { Item p[4]; };
+    Items w_items(int blk, const T* d2b, float* o1) const {
+        Slot sl = slot(blk);
+        T* dhb = at<T>(L.dh[blk & 1]);
+        T* dqkv = at<T>(L.dqkv[blk & 1]);
+        T* gy1b = gy1_act(blk, o1);
+        return {{{d2b, D, sl.a, Dm, D, Dm, G(blk, T_WFC2), nullptr}, {dhb, Dm, sl.n2, D, Dm, D, G(blk, T_WFC1), nullptr},
+                 {gy1b, D, sl.o, D, D, D, G(blk, T_WPROJ), nullptr},
+                 {dqkv, 3 * D, sl.n1, D, 3 * D, D, G(blk, T_WQKV), sums_ride() ? G(blk, T_BQKV) : nullptr}}};
+    }
+    // QKV's bias gradient (column sums of dqkv) in the launch of the weight gradients, which reads dqkv anyway
+    bool sums_ride() const { return kBf16 || M <= COLSUM_ROWS; }
+    // Small blocks on one stream: QKV's input gradient, the weight gradients, the column sums and the second stages of the
+    // sums that the launches before left, in one launch.
+    bool all_ride() const {
+        const int nn[4] = {D, Dm, D, 3 * D}, kk[4] = {Dm, D, D, D};
+        return kBf16 ? gemm_wgrad_bf16_together(M, D, 3 * D, nn, kk, 4) : gemm_wgrad_f32_together(M, D, nn, kk, 4);
+    }
+
+    // together: grad_w's work is done here too, with the launch that ends the attention branch, and what segs holds by then
+    // (with what the block above left there) is summed; the last LayerNorm's sums are left in segs.
     int grad_d(hipStream_t s, int blk, const float* y1, const float* x2, const float* d1, const float* d2,
-               const T* d2b, float* o1, float* o2, T* o2b, hipEvent_t done_dqkv, RedSeg* segs, int* n) {
+               const T* d2b, float* o1, float* o2, T* o2b, hipEvent_t done_dqkv, RedSeg* segs, int* n, bool together) {
         Slot sl = slot(blk);
         T* dhb = at<T>(L.dh[blk & 1]);
         T* dqkv = at<T>(L.dqkv[blk & 1]);
@@ -338,12 +361,24 @@ struct Runner {
         // ---- F branch
         Epi q = epi0(); q.kind = EPI_PLAIN; q.out = dO; q.ldo = D;
         RC(dgrad(s, blk, T_WPROJ, gy1b, D, D, q));
-        RC((attention_backward<T>(s, sl.qkv, sl.o, dO, sl.lse, dqkv, at<float>(L.delta), B, Tn, H, dh, key_len, solo)));
+        const Items w = w_items(blk, d2b, o1);
+        int begun = 0;                                       // weight gradients whose operands are ready before dqkv
+        if constexpr (kBf16) {
+            if (together && attention_takes_wgrad(B, Tn, H, dh)) begun = 3;
+            if (begun) RC(attention_backward_wgrad(s, sl.qkv, sl.o, dO, sl.lse, dqkv, B, Tn, H, dh, key_len, w.p, begun));
+        }
+        if (!begun) RC((attention_backward<T>(s, sl.qkv, sl.o, dO, sl.lse, dqkv, at<float>(L.delta), B, Tn, H, dh, key_len, solo)));
         if (done_dqkv) REV_HIP(hipEventRecord(done_dqkv, s));
-        Epi r = epi0(); r.kind = EPI_PLAIN; r.out = dn; r.ldo = D;
-        RC(dgrad(s, blk, T_WQKV, dqkv, 3 * D, D, r));
-        // (bf16: the weight-gradient kernel, which reads dqkv anyway, sums its columns)
-        if constexpr (!kBf16) RC(colsum<T>(s, dqkv, 3 * D, M, 3 * D, G(blk, T_BQKV), at<float>(L.part_col[1]), &segs[nseg++]));
+        if (together) {
+            if constexpr (kBf16) RC(gemm_nn_wgrad_bf16(s, dqkv, 3 * D, P(blk, T_WQKV), D, M, D, 3 * D, dn, D, w.p + begun, 4 - begun, segs, nseg));
+            else RC(gemm_nn_wgrad_f32(s, dqkv, 3 * D, P(blk, T_WQKV), D, M, D, 3 * D, dn, D, w.p, 4, segs, nseg));
+            nseg = 0;
+        } else {
+            Epi r = epi0(); r.kind = EPI_PLAIN; r.out = dn; r.ldo = D;
+            RC(dgrad(s, blk, T_WQKV, dqkv, 3 * D, D, r));
+            if constexpr (!kBf16)
+                if (!sums_ride()) RC(colsum<T>(s, dqkv, 3 * D, M, 3 * D, G(blk, T_BQKV), at<float>(L.part_col[1]), &segs[nseg++]));
+        }
         // dX2 = dY2 + LN1bwd(dn); dX2 is the block below's dY2, so its column sums are that block's
         // fc2 bias gradient
         RC((ln_backward<T, T>(s, dn, x2, sl.st1, P(blk, T_LN1G), d2, o2, kBf16 ? o2b : nullptr,
@@ -353,28 +388,16 @@ struct Runner {
     }
 
     int grad_w(hipStream_t s, int blk, const T* d2b, float* o1, RedSeg* segs, int* nseg) {
-        Slot sl = slot(blk);
-        T* dhb = at<T>(L.dh[blk & 1]);
-        T* dqkv = at<T>(L.dqkv[blk & 1]);
-        T* gy1b = gy1_act(blk, o1);
+        const Items w = w_items(blk, d2b, o1);
         if constexpr (kBf16) {
             // all four in one launch: together their tiles fill the device without cutting the token range (or with
             // fewer cuts), which saves the float32 pieces and most of their reduction
-            const WgradItem items[4] = {{d2b, D, sl.a, Dm, D, Dm, G(blk, T_WFC2), nullptr},
-                                        {dhb, Dm, sl.n2, D, Dm, D, G(blk, T_WFC1), nullptr},
-                                        {gy1b, D, sl.o, D, D, D, G(blk, T_WPROJ), nullptr},
-                                        {dqkv, 3 * D, sl.n1, D, 3 * D, D, G(blk, T_WQKV), G(blk, T_BQKV)}};
             int n = 0;
-            RC(gemm_wgrad_bf16_group(s, items, 4, M, at<float>(L.part_wg), L.part_wg_elems, segs + *nseg, &n));
+            RC(gemm_wgrad_bf16_group(s, w.p, 4, M, at<float>(L.part_wg), L.part_wg_elems, segs + *nseg, &n));
             *nseg += n;
             return REV_OK;
         }
-        if constexpr (!kBf16) {
-            const WgradF32Item items[4] = {{d2b, D, sl.a, Dm, D, Dm, G(blk, T_WFC2)}, {dhb, Dm, sl.n2, D, Dm, D, G(blk, T_WFC1)},
-                                           {gy1b, D, sl.o, D, D, D, G(blk, T_WPROJ)},
-                                           {dqkv, 3 * D, sl.n1, D, 3 * D, D, G(blk, T_WQKV)}};
-            return gemm_wgrad_f32_group(s, items, 4, M);
-        }
+        else return gemm_wgrad_f32_group(s, w.p, 4, M);
     }
 
     // Two streams cost the host three events and three waits per block, so where the line lies depends on the host's speed.
@@ -421,6 +444,7 @@ struct Runner {
         std::vector<hipEvent_t>& ev = lease.ev;
         auto E = [&](int i, int k) { return ev[(i - 1) * EPB + k]; };
         const bool two = schedule == 1 && !one_stream_is_faster();
+        const bool together = !two && all_ride();
         const int per = two ? EPB * N : 0;
         const hipStream_t sv_caller = sv;
         if (schedule == 1) {
@@ -466,7 +490,7 @@ struct Runner {
             float* o2 = (i == 1) ? dX2 : at<float>(L.cot[(i - 1) & 1][1]);
             T* o2b = nullptr;
             if constexpr (kBf16) o2b = (i == 1) ? nullptr : at<T>(L.cot2b[(i - 1) % 3]);
-            return grad_d(sv, i - 1, y1, x2, d1, d2, d2b_of(i), o1_of(i), o2, o2b, done_dqkv, segs, &nseg);
+            return grad_d(sv, i - 1, y1, x2, d1, d2, d2b_of(i), o1_of(i), o2, o2b, done_dqkv, segs, &nseg, together);
         };
         if (two) {
             RC(run_R(N));
@@ -496,10 +520,12 @@ struct Runner {
                 if (doR) RC(run_R(i));
                 if (doV) {
                     RC(run_D(i, nullptr));
+                    if (together) continue;
                     RC(grad_w(sv, i - 1, d2b_of(i), o1_of(i), segs, &nseg));
                     RC(reduce(sv, segs, &nseg));
                 }
             }
+            RC(reduce(sv, segs, &nseg));
         }
         if (schedule == 1) {
             REV_HIP(hipEventRecord(ev[per + 1], sr));             // join

@@ -1,0 +1,45 @@
+"""Small blocks on one stream: QKV's input gradient, the weight gradients, the column sums and the second stages of sums in one
+launch, on both sides of the rules that choose it, against the oracle; the two-stream schedule, which issues them apart, must give
+the same bits.  Three blocks, so that sums of one block are finished by the launch of the next."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import rev_oracle as O
+from paper_2306_09342_amd import binding as B
+
+from parity_util import TOL, compare_backward, gpu_cfg, make_case, takes_two_streams, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# (mode, width, heads, hidden, tokens, samples)
+CASES = [
+    ("fp32", 72, 3, 200, 1, 1),            # one row
+    ("fp32", 136, 17, 520, 32, 32),         # 1024 rows, the last whose column sums come in one piece; ragged widths
+    ("fp32", 136, 17, 520, 41, 25),         # 1025 rows
+    ("fp32", 384, 6, 1536, 33, 3),         # weight gradients of 432 64x64 tiles, together still
+    ("fp32", 512, 8, 1536, 33, 3),         # 640: apart
+    ("bf16", 72, 3, 200, 1, 1),            # 32x32 tiles
+    ("bf16", 136, 17, 520, 41, 25),        # 1025 rows: two ranges of tokens
+    ("bf16", 264, 11, 1032, 32, 32),       # 1024 rows, 64x64 tiles
+    ("bf16", 768, 12, 3072, 197, 1),       # 32x32 tiles, the rest fills the chip
+    ("bf16", 1024, 16, 4096, 197, 4),      # larger tiles: apart
+]
+
+
+@pytest.mark.parametrize("mode,width,heads,hidden,tokens,batch", CASES)
+def test_one_launch_or_several(mode, width, heads, hidden, tokens, batch):
+    cfg = dict(n_blocks=3, d_model=width, n_heads=heads, d_mlp=hidden, seq_len=tokens, batch=batch, mode=mode)
+    print(f"[case] {cfg} two streams: {takes_two_streams(cfg)}", flush=True)
+    flat, blocks, x, dy1, dy2 = make_case(cfg, seed=19)
+    c = gpu_cfg(cfg)
+    params = to_dev(flat, B.param_dtype(c))
+    args = [to_dev(a) for a in (x, x[:, ::-1].copy(), dy1, dy2)]
+    rep = B.rev_stack_backward_reprop(c, params, *args, want_inputs=True)
+    again = B.rev_stack_backward_reprop(c, params, *args, want_inputs=True)
+    par = B.rev_stack_backward_pareprop(c, params, *args, torch.cuda.Stream(), want_inputs=True)
+    torch.cuda.synchronize()
+    for k in ("dX1", "dX2", "X1", "X2", "dparams"):
+        assert torch.equal(rep[k], par[k]) and torch.equal(rep[k], again[k]), k
+    ref = O.stack_backward_reversible_chunked(x.astype(np.float64), x[:, ::-1].astype(np.float64), blocks, heads, dy1, dy2, chunk=8)
+    compare_backward(cfg, rep, ref, TOL[mode], what=str(cfg))
