@@ -163,8 +163,16 @@ def param_dtype(cfg: RevCfg):
     return torch.bfloat16 if cfg.mode == REV_MODE_BF16 else torch.float32
 
 
+SMALL_ROWS = 1024                              # COLSUM_ROWS of csrc/common.h
+
+
 def alloc_workspace(cfg: RevCfg, device="cuda", reprop_only: bool = False) -> torch.Tensor:
-    n = rev_stack_workspace_bytes_reprop(cfg) if reprop_only else rev_stack_workspace_bytes(cfg)
+    """Workspace for every entry point, or with reprop_only for the sequential schedule and the forward map, which need
+    rev_stack_workspace_bytes_reprop.  Stacks of up to SMALL_ROWS rows get rev_stack_workspace_bytes either way: in that the
+    sequential schedule runs their two chains side by side."""
+    n = rev_stack_workspace_bytes_reprop(cfg)
+    if not reprop_only or cfg.batch * cfg.seq_len <= SMALL_ROWS:
+        n = rev_stack_workspace_bytes(cfg)
     return torch.empty(n, dtype=torch.uint8, device=device)
 
 

@@ -208,14 +208,23 @@ struct TileRing {
 };
 
 // ---- forward ----------------------------------------------------------------------------------------------------------
+struct FwdArgs {
+    const bf16* qkv;
+    bf16* o;
+    float* lse;
+    const int* key_len;
+    int T, H, nblk;              // nblk workgroups per head
+};
 template <int DH, int TR>
-__global__ __launch_bounds__(256, DH == 80 ? 3 : 4) void attn_fwd_dma(const bf16* __restrict__ qkv, bf16* __restrict__ o, float* __restrict__ lse,
-                                                    const int* __restrict__ key_len, int T, int H, int nblk) {
+__device__ __forceinline__ void fwd_rows(const FwdArgs& a, unsigned char* smem, int blk) {
     constexpr int KS = DH / 16, DT = (DH + 31) / 32, ROWB = 2 * DH, NT = TR / 32;
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const bf16* __restrict__ qkv = a.qkv;
+    bf16* __restrict__ o = a.o;
+    float* __restrict__ lse = a.lse;
+    const int* __restrict__ key_len = a.key_len;
+    const int T = a.T, H = a.H, nblk = a.nblk;
     const int lane = threadIdx.x & 63, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
-    const int blk = xcd_remap(blockIdx.x, gridDim.x);
     const int bh = blk / nblk, b = bh / H, h = bh - b * H;
     const int D = H * DH;
     const int64_t ld = 3 * (int64_t)D;
@@ -322,6 +331,12 @@ __global__ __launch_bounds__(256, DH == 80 ? 3 : 4) void attn_fwd_dma(const bf16
             }
         if (g == 0) lse[(int64_t)bh * T + q] = (m + __log2f(l)) * 0.6931471805599453f;   // back to natural log
     }
+}
+
+template <int DH, int TR>
+__global__ __launch_bounds__(256, DH == 80 ? 3 : 4) void attn_fwd_dma(FwdArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    fwd_rows<DH, TR>(a, smem, xcd_remap(blockIdx.x, gridDim.x));
 }
 
 // ---- backward pass 1: dQ and delta ----------------------------------------------------------------------------------------
@@ -598,14 +613,16 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_pair_dma(BwdArgs a) {
 
 // The pair and, in the workgroups behind its `attn_blocks`, weight gradients over the same rows: the pair leaves most of the chip idle
 // for as long as they take.  12 heads of 197 tokens: 13.0 us, 17.0 with the three weight gradients of an MLP and a projection 768 wide, which
-// take 10.4 by themselves.
-template <int DH>
-__global__ __launch_bounds__(256, 2) void attn_bwd_pair_wgrad(BwdArgs a, WgradTail w, int attn_blocks) {
+// take 10.4 by themselves.  FWD: the attention forward of the other chain (rev_stack.hip), in `fwd_blocks` before the weight gradients.
+template <int DH, bool FWD>
+__global__ __launch_bounds__(256, 2) void attn_bwd_pair_wgrad(BwdArgs a, WgradTail w, int attn_blocks, FwdArgs f, int fwd_blocks) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    const int n = attn_blocks >> 1, blk = blockIdx.x;
+    const int n = attn_blocks >> 1;
+    int blk = blockIdx.x;
     if (blk < n) bwd_dq_rows<DH>(a, smem, xcd_remap(blk, n));
     else if (blk < attn_blocks) bwd_dkv_rows<DH, true>(a, smem, xcd_remap(blk - n, n));
-    else wgrad_small_block(w.grp, w.M, w.steps, blk - attn_blocks);
+    else if (FWD && (blk -= attn_blocks) < fwd_blocks) fwd_rows<DH, 64>(f, smem, xcd_remap(blk, fwd_blocks));
+    else wgrad_small_block(w.grp, w.M, w.steps, blk - (FWD ? fwd_blocks : attn_blocks));
 }
 
 #define RES_BARRIER(n) do { asm volatile("" ::: "memory"); res_wait(n); __builtin_amdgcn_s_barrier(); asm volatile("" ::: "memory"); } while (0)
@@ -847,7 +864,7 @@ static int fwd_dma(hipStream_t s, const bf16* qkv, bf16* o, float* lse, int B, i
     int nblk, nw;
     split_rows(T, 4, &nblk, &nw);
     const size_t lds = ring_lds<TileRing<DH, 2, 0, TR>>(T);
-    hipLaunchKernelGGL((attn_fwd_dma<DH, TR>), dim3(nblk * B * H), dim3(nw * 64), lds, s, qkv, o, lse, key_len, T, H, nblk);
+    hipLaunchKernelGGL((attn_fwd_dma<DH, TR>), dim3(nblk * B * H), dim3(nw * 64), lds, s, FwdArgs{qkv, o, lse, key_len, T, H, nblk});
     REV_HIP(hipGetLastError());
     return REV_OK;
 }
@@ -902,27 +919,32 @@ static int bwd_dma(hipStream_t s, BwdArgs a, int B) {
 
 // with weight gradients: workgroups of four wavefronts, as theirs
 template <int DH>
-static int bwd_wgrad_dma(hipStream_t s, BwdArgs a, int B, const WgradTail& w) {
+static int bwd_wgrad_dma(hipStream_t s, BwdArgs a, int B, const WgradTail& w, const AttnFwdCall<bf16>* beside) {
     const int heads = B * a.H;
     a.nblk = ((a.T + 31) / 32 + 3) / 4;
     const int lds = std::max((int)(ring_lds<TileRing<DH, 3, 1>>(a.T) + 4 * 128), 2 * WD_STAGE), attn_blocks = 2 * heads * a.nblk;
-    static LdsLimit lim;
-    if (int rc = lim.ensure(reinterpret_cast<const void*>(attn_bwd_pair_wgrad<DH>), 2 * WD_STAGE)) return rc;
-    hipLaunchKernelGGL(attn_bwd_pair_wgrad<DH>, dim3(attn_blocks + w.grp.tile_blocks), dim3(256), lds, s, a, w, attn_blocks);
-    REV_HIP(hipGetLastError());
-    return REV_OK;
+    static_assert(2 * TileRing<DH, 2, 0, 64>::SLOT + 64 <= 2 * WD_STAGE, "the forward's ring");
+    auto go = [&](auto kern, const FwdArgs& f, int fwd_blocks, LdsLimit& lim) -> int {
+        if (int rc = lim.ensure(reinterpret_cast<const void*>(kern), 2 * WD_STAGE)) return rc;
+        hipLaunchKernelGGL(kern, dim3(attn_blocks + fwd_blocks + w.grp.tile_blocks), dim3(256), lds, s, a, w, attn_blocks, f, fwd_blocks);
+        REV_HIP(hipGetLastError());
+        return REV_OK;
+    };
+    static LdsLimit lim, lim_fwd;
+    if (!beside) return go(attn_bwd_pair_wgrad<DH, false>, FwdArgs{}, 0, lim);
+    return go(attn_bwd_pair_wgrad<DH, true>, FwdArgs{beside->qkv, beside->o, beside->lse, a.key_len, a.T, a.H, a.nblk}, heads * a.nblk, lim_fwd);
 }
 bool attention_takes_wgrad(int B, int T, int H, int dh) { return attention_dma_takes(dh) && bwd_pair_pays(B * H, T, dh); }
 int attention_backward_wgrad(hipStream_t s, const bf16* qkv, const bf16* o, const bf16* dout, const float* lse, bf16* dqkv, int B, int T,
-                             int H, int dh, const int* key_len, const WgradItem* items, int count) {
+                             int H, int dh, const int* key_len, const WgradItem* items, int count, const AttnFwdCall<bf16>* beside) {
     const BwdArgs a = {qkv, o, dout, lse, dqkv, nullptr, key_len, T, H, 0};
     WgradTail w;
-    double flops = 8.0 * B * H * (double)T * T * dh;
+    double flops = (beside ? 12.0 : 8.0) * B * H * (double)T * T * dh;
     if (int rc = gemm_wgrad_bf16_beside(items, count, B * T, &w, &flops)) return rc;
     ProfScope ps(K_ATTN_BWD, s, flops);
-    if (dh == 32) return bwd_wgrad_dma<32>(s, a, B, w);
-    if (dh == 64) return bwd_wgrad_dma<64>(s, a, B, w);
-    return bwd_wgrad_dma<80>(s, a, B, w);
+    if (dh == 32) return bwd_wgrad_dma<32>(s, a, B, w, beside);
+    if (dh == 64) return bwd_wgrad_dma<64>(s, a, B, w, beside);
+    return bwd_wgrad_dma<80>(s, a, B, w, beside);
 }
 
 bool attention_dma_takes(int dh) { return dh == 32 || dh == 64 || dh == 80; }

@@ -11,6 +11,7 @@
 // rows 8*(v/4) + 4g + v%4.
 #include "mfma.h"
 #include "rowwise.h"
+#include <algorithm>
 
 namespace rev {
 
@@ -81,17 +82,19 @@ __device__ __forceinline__ void store_tile(T* row, int dt, int dh, int lane, con
     }
 }
 
+// the rows q0 .. q0 + 31 of head bh
+template <int DHP> constexpr int AF_FWD_LDS = AF_NW * (DHP / 32 * AF_SLOT + 64) * 4;
 template <int DHP>
-__global__ __launch_bounds__(AF_NW * 64) void attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ o, float* __restrict__ lse,
-                                                           const int* __restrict__ key_len, int T, int H, int dh) {
+__device__ __forceinline__ void fwd_rows_f32(const float* __restrict__ qkv, float* __restrict__ o, float* __restrict__ lse,
+                                             const int* __restrict__ key_len, int T, int H, int dh, int q0, int bh, float* lds) {
     constexpr int DT = DHP / 32;
-    __shared__ float tiles[AF_NW][DT][AF_SLOT];
-    __shared__ float sm[AF_NW][32], sl[AF_NW][32];
+    float (*tiles)[DT][AF_SLOT] = reinterpret_cast<float (*)[DT][AF_SLOT]>(lds);
+    float (*sm)[32] = reinterpret_cast<float (*)[32]>(lds + AF_NW * DT * AF_SLOT), (*sl)[32] = sm + AF_NW;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 5;
-    const int bh = blockIdx.y, b = bh / H, h = bh % H, D = H * dh;
+    const int b = bh / H, h = bh % H, D = H * dh;
     const int64_t ld = 3 * (int64_t)D;
     const float* base = qkv + (int64_t)b * T * ld + h * dh;
-    const int q0 = blockIdx.x * 32, q = q0 + (lane & 31);
+    const int q = q0 + (lane & 31);
     const float scale = rsqrtf((float)dh);
     const int Tk = key_len ? min(max(key_len[b], 1), T) : T;     // keys beyond take no part in the softmax
 
@@ -157,21 +160,27 @@ __global__ __launch_bounds__(AF_NW * 64) void attn_fwd_f32(const float* __restri
     }
 }
 
-// blockIdx.z = 0: dQ of 32 query rows;  1: dK and dV of 32 key rows
+template <int DHP>
+__global__ __launch_bounds__(AF_NW * 64) void attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ o, float* __restrict__ lse,
+                                                           const int* __restrict__ key_len, int T, int H, int dh) {
+    __shared__ float lds[AF_FWD_LDS<DHP> / 4];
+    fwd_rows_f32<DHP>(qkv, o, lse, key_len, T, H, dh, blockIdx.x * 32, blockIdx.y, lds);
+}
+
+// pass 0: dQ of the 32 query rows from r0 on, head bh;  1: dK and dV of 32 key rows.  tiles: [AF_NW][2 * DT][AF_SLOT]
 template <int DHP, typename T>
-__global__ __launch_bounds__(AF_NW * 64) void attn_bwd_f32(const T* __restrict__ qkv, const T* __restrict__ o, const T* __restrict__ dout,
-                                                           const float* __restrict__ lse, T* __restrict__ dqkv,
-                                                           const int* __restrict__ key_len, int Tn, int H, int dh) {
+__device__ __forceinline__ void bwd_rows_f32(const T* __restrict__ qkv, const T* __restrict__ o, const T* __restrict__ dout,
+                                             const float* __restrict__ lse, T* __restrict__ dqkv, const int* __restrict__ key_len, int Tn,
+                                             int H, int dh, int r0, int bh, int pass, float* tiles) {
     constexpr int DT = DHP / 32;
-    extern __shared__ __attribute__((aligned(16))) float tiles[];      // [AF_NW][2 * DT][AF_SLOT]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 5;
-    const int bh = blockIdx.y, b = bh / H, h = bh % H, D = H * dh;
+    const int b = bh / H, h = bh % H, D = H * dh;
     const int64_t ld = 3 * (int64_t)D;
     const T* base = qkv + (int64_t)b * Tn * ld + h * dh;
     const T* dob = dout + (int64_t)b * Tn * D + h * dh;
     const T* ob = o + (int64_t)b * Tn * D + h * dh;
     const float* lrow = lse + (int64_t)bh * Tn;
-    const int r0 = blockIdx.x * 32, own = r0 + (lane & 31);
+    const int own = r0 + (lane & 31);
     const float scale = rsqrtf((float)dh);
     const int Tk = key_len ? min(max(key_len[b], 1), Tn) : Tn;
     // delta of rows t0 + l%32: sum over features of dO * O; the two lane groups hold complementary features
@@ -188,7 +197,7 @@ __global__ __launch_bounds__(AF_NW * 64) void attn_bwd_f32(const T* __restrict__
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
 
-    if (blockIdx.z == 0) {
+    if (pass == 0) {
         float bq[DHP / 2], bdo[DHP / 2];
         rows_frag<DHP>(base, ld, r0, Tn, dh, lane, bq);
         rows_frag<DHP>(dob, D, r0, Tn, dh, lane, bdo);
@@ -232,22 +241,40 @@ __global__ __launch_bounds__(AF_NW * 64) void attn_bwd_f32(const T* __restrict__
             }
         }
     }
-    const int nt = blockIdx.z == 0 ? DT : 2 * DT;
+    const int nt = pass == 0 ? DT : 2 * DT;
 #pragma unroll
     for (int t = 0; t < 2 * DT; ++t)
         if (t < nt) put_tile(tiles + (wave * 2 * DT + t) * AF_SLOT, acc[t], lane);
     __syncthreads();
     if (own >= Tn) return;
     T* row = dqkv + ((int64_t)b * Tn + own) * ld + h * dh;
-    const bool masked = blockIdx.z == 1 && own >= Tk;                    // a masked key: no query looked at it
+    const bool masked = pass == 1 && own >= Tk;                    // a masked key: no query looked at it
     for (int t = wave; t < nt; t += AF_NW) {
         f32x16_t s = sum_tiles(tiles + t * AF_SLOT, 2 * DT * AF_SLOT, lane);
         if (masked)
 #pragma unroll
             for (int v = 0; v < 16; ++v) s[v] = 0.f;
-        T* dst = blockIdx.z == 0 ? row : (t < DT ? row + D : row + 2 * D);
+        T* dst = pass == 0 ? row : (t < DT ? row + D : row + 2 * D);
         store_tile(dst, t < DT ? t : t - DT, dh, lane, s, 1.f);
     }
+}
+
+template <int DHP, typename T>
+__global__ __launch_bounds__(AF_NW * 64) void attn_bwd_f32(const T* __restrict__ qkv, const T* __restrict__ o, const T* __restrict__ dout,
+                                                           const float* __restrict__ lse, T* __restrict__ dqkv,
+                                                           const int* __restrict__ key_len, int Tn, int H, int dh) {
+    extern __shared__ __attribute__((aligned(16))) float tiles[];
+    bwd_rows_f32<DHP, T>(qkv, o, dout, lse, dqkv, key_len, Tn, H, dh, blockIdx.x * 32, blockIdx.y, blockIdx.z, tiles);
+}
+// Its two passes and, as blockIdx.z = 2, the forward of the other chain of a small stack (rev_stack.hip).
+template <int DHP>
+__global__ __launch_bounds__(AF_NW * 64) void attn_pair_f32(const float* __restrict__ qkv, const float* __restrict__ o,
+                                                            const float* __restrict__ dout, const float* __restrict__ lse,
+                                                            float* __restrict__ dqkv, const int* __restrict__ key_len, int Tn, int H, int dh,
+                                                            AttnFwdCall<float> f) {
+    extern __shared__ __attribute__((aligned(16))) float tiles[];
+    if (blockIdx.z < 2) bwd_rows_f32<DHP, float>(qkv, o, dout, lse, dqkv, key_len, Tn, H, dh, blockIdx.x * 32, blockIdx.y, blockIdx.z, tiles);
+    else fwd_rows_f32<DHP>(f.qkv, f.o, f.lse, key_len, Tn, H, dh, blockIdx.x * 32, blockIdx.y, tiles);
 }
 
 int attention_forward_f32(hipStream_t s, const float* qkv, float* o, float* lse, int B, int T, int H, int dh, const int* key_len) {
@@ -274,6 +301,24 @@ int attention_backward_f32(hipStream_t s, const T* qkv, const T* o, const T* dou
         static LdsLimit lim;                                                                                                \
         if (int rc = lim.ensure(reinterpret_cast<const void*>(attn_bwd_f32<32 * J, T>), bytes)) return rc;                  \
         hipLaunchKernelGGL((attn_bwd_f32<32 * J, T>), grid, block, bytes, s, qkv, o, dout, lse, dqkv, key_len, Tn, H, dh);  \
+        break; }
+        CASE(1) CASE(2) CASE(3) CASE(4)
+#undef CASE
+        default: set_error("attention: head_dim too large"); return REV_EINVAL;
+    }
+    REV_HIP(hipGetLastError());
+    return REV_OK;
+}
+int attention_pair_f32(hipStream_t s, const float* qkv, const float* o, const float* dout, const float* lse, float* dqkv, int B, int T, int H,
+                       int dh, const int* key_len, const AttnFwdCall<float>& fwd) {
+    ProfScope ps(K_ATTN_BWD, s, 12.0 * B * H * (double)T * T * dh);
+    const dim3 grid((T + 31) / 32, B * H, 3), block(AF_NW * 64);
+    switch ((dh + 31) / 32) {
+#define CASE(J) case J: {                                                                                                   \
+        constexpr int bytes = std::max(AF_NW * 2 * J * AF_SLOT * 4, AF_FWD_LDS<32 * J>);                                    \
+        static LdsLimit lim;                                                                                                \
+        if (int rc = lim.ensure(reinterpret_cast<const void*>(attn_pair_f32<32 * J>), bytes)) return rc;                    \
+        hipLaunchKernelGGL((attn_pair_f32<32 * J>), grid, block, bytes, s, qkv, o, dout, lse, dqkv, key_len, T, H, dh, fwd); \
         break; }
         CASE(1) CASE(2) CASE(3) CASE(4)
 #undef CASE

@@ -162,6 +162,11 @@ int gemm_nn_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64
                  int M, int N, int K, const Epi& epi);
 int gemm_nn_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb,
                 int M, int N, int K, const Epi& epi);
+// An input gradient A[M,K] * B[K,N] (GELU' or plain) and a map of the other chain A[M,K] * B[N,K]^T (GELU, residual or bias, in
+// this order of the pairs), which do not depend on each other: one launch where neither fills the chip, two otherwise.
+template <typename T> struct GemmCall { const T* A; int64_t lda; const T* B; int64_t ldb; int N, K; Epi epi; };
+int gemm_pair(hipStream_t s, const GemmCall<bf16>& nn, const GemmCall<bf16>& nt, int M);
+int gemm_pair(hipStream_t s, const GemmCall<float>& nn, const GemmCall<float>& nt, int M);
 // rows of column-sum partials a float32 GEMM with an [M, N] output writes
 int gemm_f32_colsum_strips(int M, int N);
 // dW[N,K] (float32, ld = K) = G[M,N]^T * A[M,K], reduction over the M tokens: up to WGRAD_GROUP_MAX of them over the same
@@ -187,10 +192,10 @@ constexpr int COLSUM_ROWS = 1024;
 struct WgradF32Item { const float* G; int64_t ldg; const float* A; int64_t lda; int N, K; float* dW; float* colsum; };
 int gemm_wgrad_f32_group(hipStream_t s, const WgradF32Item* items, int count, int M);
 // C[M,N] = A[M,K] * B[K,N], weight gradients over the same M rows, and second stages of sums in one launch, for small blocks
-// (gemm_wgrad_f32_together)
+// (gemm_wgrad_f32_together); beside (nullable): a residual map of the other chain, in the same launch
 bool gemm_wgrad_f32_together(int M, int N, const int* wn, const int* wk, int count);
-int gemm_nn_wgrad_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, float* out, int64_t ldo,
-                      const WgradF32Item* items, int count, const RedSeg* segs, int nseg);
+int gemm_nn_wgrad_f32(hipStream_t s, const GemmCall<float>& nn, int M, const WgradF32Item* items, int count, const RedSeg* segs, int nseg,
+                      const GemmCall<float>* beside);
 // Column sums that ride in a weight-gradient launch: its last workgroups take 512 columns of one of `chunks` runs of `rows`
 // tokens each (n = 0: none); the chunks' sums go to out[chunk * n + column].
 // At most two cotangents; block0: the first of a cotangent's workgroups, counted from the first behind the tiles.
@@ -202,12 +207,12 @@ struct WgradProblem { const bf16* G; const bf16* A; float* out; int64_t ldg, lda
 struct WgradGroup { WgradProblem p[WGRAD_GROUP_MAX]; WgradSums sums[WGRAD_SUMS_MAX]; int count, tile, tiles_total, tile_blocks, sum_blocks; };
 // Weight gradients that ride in the last workgroups of another launch over the same M rows, where gemm_wgrad_bf16_together says so:
 // of the attention backward (attention_backward_wgrad), and, with second stages of sums too, of an input gradient out[M,N] =
-// A[M,K] * B[K,N].
+// A[M,K] * B[K,N], where a residual map of the other chain may ride too (beside, nullable).
 struct WgradTail { WgradGroup grp; int M, steps; };
-bool gemm_wgrad_bf16_together(int M, int N, int K, const int* wn, const int* wk, int count);
+bool gemm_wgrad_bf16_together(int M, const int* wn, const int* wk, int count, bool as_apart);
 int gemm_wgrad_bf16_beside(const WgradItem* items, int count, int M, WgradTail* out, double* flops);
-int gemm_nn_wgrad_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, bf16* out, int64_t ldo,
-                       const WgradItem* items, int count, const RedSeg* segs, int nseg);
+int gemm_nn_wgrad_bf16(hipStream_t s, const GemmCall<bf16>& nn, int M, const WgradItem* items, int count, const RedSeg* segs, int nseg,
+                       const GemmCall<bf16>* beside);
 // The same in 256x256 tiles (gemm_wgrad_big.hip): `full` tiles run over all tokens, the others over `splits` ranges of them.
 struct WgradBigProblem { const bf16* G; const bf16* A; float* dW; int64_t ldg, lda; int N, K, tile0; };
 struct WgradBig {
@@ -236,6 +241,15 @@ int ln_backward(hipStream_t s, const TA* dn, const float* x, const float* stats,
                 const float* r, float* out, TA* outb, float* dgb, float* dbias,
                 float* partial, int M, int D, RedSeg* defer = nullptr);
 int64_t ln_bwd_partial_elems(int M, int D);
+// Two launches that do not depend on each other as one, where neither fills the chip (two otherwise); the arguments of
+// ln_backward and ln_forward, with the same results.
+template <typename TA, typename TP>
+struct LnBwdCall {
+    const TA* dn; const float *x, *stats; const TP* g; const float* r; float* out; TA* outb; float *dgb, *dbias, *partial;
+};
+template <typename TA, typename TP> struct LnFwdCall { const float* x; const TP *g, *b; float eps; TA* y; float* stats; };
+template <typename TA, typename TP>
+int ln_pair(hipStream_t s, const LnBwdCall<TA, TP>& b, const LnFwdCall<TA, TP>& f, int M, int D, RedSeg* defer);
 
 // out[n] = sum_m in[m, n]   (float32 out, fixed summation order).  With `defer` the second stage is not
 // launched: its description is returned for a later reduce_multi.
@@ -259,9 +273,14 @@ int attention_backward(hipStream_t s, const TA* qkv, const TA* o, const TA* dout
                        TA* dqkv, float* delta, int B, int T, int H, int dh, const int* key_len = nullptr,
                        bool solo = false);     // solo: the launch has the device to itself (one stream)
 
-// The attention backward of bf16 heads and weight gradients over the same rows in one launch, where attention_takes_wgrad says so
+// The attention backward of bf16 heads and weight gradients over the same rows in one launch, where attention_takes_wgrad says so;
+// beside (nullable): with the attention forward of the other chain
+template <typename T> struct AttnFwdCall { const T* qkv; T* o; float* lse; };
 bool attention_takes_wgrad(int B, int T, int H, int dh);
 int attention_backward_wgrad(hipStream_t s, const bf16* qkv, const bf16* o, const bf16* dout, const float* lse, bf16* dqkv, int B, int T,
-                             int H, int dh, const int* key_len, const WgradItem* items, int count);
+                             int H, int dh, const int* key_len, const WgradItem* items, int count, const AttnFwdCall<bf16>* beside = nullptr);
+// float32: the backward and the forward of the other chain in one launch
+int attention_pair_f32(hipStream_t s, const float* qkv, const float* o, const float* dout, const float* lse, float* dqkv, int B, int T, int H,
+                       int dh, const int* key_len, const AttnFwdCall<float>& fwd);
 
 }  // namespace rev

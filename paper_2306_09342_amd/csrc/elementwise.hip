@@ -15,13 +15,11 @@ namespace rev {
 // requested before either is reduced, so it has two independent memory round trips in flight.  Bound by HBM.  200704 rows
 // of 96: 49 us with a wavefront per row (24 of 64 lanes at work), now 28; 100000 rows of 64: 22 -> 9.6.
 template <typename TA, typename TP, int LPR, int MAXJ>
-__global__ __launch_bounds__(256) void ln_fwd_kernel(const float* __restrict__ x, const TP* __restrict__ g,
-                                                     const TP* __restrict__ b, float eps,
-                                                     TA* __restrict__ y, float* __restrict__ stats,
-                                                     int M, int D) {
-    const int lane = threadIdx.x & (LPR - 1);
+__device__ __forceinline__ void ln_fwd_rows(const float* __restrict__ x, const TP* __restrict__ g, const TP* __restrict__ b, float eps,
+                                            TA* __restrict__ y, float* __restrict__ stats, int M, int D, int thread) {
+    const int lane = thread & (LPR - 1);
     const int half = (M + 1) >> 1;
-    const int r0 = (blockIdx.x * 256 + threadIdx.x) / LPR;         // rows r0 and r0 + half
+    const int r0 = thread / LPR;                                   // rows r0 and r0 + half
     if (r0 >= half) return;
     const int nch = D >> 2;
     int rows[2] = {r0, r0 + half};
@@ -77,6 +75,14 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float* __restrict__ x
     }
 }
 
+template <typename TA, typename TP, int LPR, int MAXJ>
+__global__ __launch_bounds__(256) void ln_fwd_kernel(const float* __restrict__ x, const TP* __restrict__ g,
+                                                     const TP* __restrict__ b, float eps,
+                                                     TA* __restrict__ y, float* __restrict__ stats,
+                                                     int M, int D) {
+    ln_fwd_rows<TA, TP, LPR, MAXJ>(x, g, b, eps, y, stats, M, D, blockIdx.x * 256 + threadIdx.x);
+}
+
 template <typename TA, typename TP>
 int ln_forward(hipStream_t s, const float* x, const TP* g, const TP* b, float eps,
                TA* y, float* stats, int M, int D) {
@@ -122,6 +128,14 @@ static int ln_bwd_rows_per_block(int M, int D) {
     if (ln_bwd_shares(M, D)) rpb = (rpb + 31) / 32 * 32;
     return rpb;
 }
+
+// A chunk's products, with the rounding spelled out: left to the compiler, which products it fuses into the sums behind them changes
+// from kernel to kernel, and a row must have the same bits in all of them.
+__device__ __forceinline__ f4 mul4(const f4& a, const f4& b) {
+#pragma clang fp contract(off)
+    return {a.x * b.x, a.y * b.y, a.z * b.z, a.w * b.w};
+}
+__device__ __forceinline__ float dot4(const f4& a, const f4& b) { return fmaf(a.x, b.x, a.y * b.y) + fmaf(a.z, b.z, a.w * b.w); }
 
 // Rows of 1024 floats and more (4+ register chunks per lane): the three column accumulators of a
 // wavefront live in its own slice of LDS instead of registers (lane-private slots, no synchronisation),
@@ -192,9 +206,9 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TA* __restrict__ dn, 
                     ag[j % NACC].x += d.x * xh[j].x; ag[j % NACC].y += d.y * xh[j].y;
                     ag[j % NACC].z += d.z * xh[j].z; ag[j % NACC].w += d.w * xh[j].w;
                 }
-                dh[j] = {d.x * gg[j].x, d.y * gg[j].y, d.z * gg[j].z, d.w * gg[j].w};
-                const float s1 = (dh[j].x + dh[j].y) + (dh[j].z + dh[j].w);
-                const float s2 = (dh[j].x * xh[j].x + dh[j].y * xh[j].y) + (dh[j].z * xh[j].z + dh[j].w * xh[j].w);
+                dh[j] = mul4(d, gg[j]);
+                const float s1 = dot4(d, gg[j]);
+                const float s2 = dot4(dh[j], xh[j]);
                 p1[j % NP] = NP == 1 ? p1[0] + s1 : s1;
                 p2[j % NP] = NP == 1 ? p2[0] + s2 : s2;
             }
@@ -277,13 +291,12 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TA* __restrict__ dn, 
 // 2000 rows 10.8 / 8.5, 4096 15.2 / 15.7, 6144 24.2 / 25.4, 8192 33.1 / 34.0.
 constexpr int LNB_SMALL_MAXD = 1280;
 template <typename TA, typename TP, int MAXJ>
-__global__ __launch_bounds__(512) void ln_bwd_small_kernel(const TA* __restrict__ dn, const float* __restrict__ x,
-                                                           const float* __restrict__ stats, const TP* __restrict__ g,
-                                                           const float* __restrict__ r, float* __restrict__ out,
-                                                           TA* __restrict__ outb, float* __restrict__ partial, int M, int D) {
+__device__ __forceinline__ void ln_bwd_small_rows(const TA* __restrict__ dn, const float* __restrict__ x, const float* __restrict__ stats,
+                                                  const TP* __restrict__ g, const float* __restrict__ r, float* __restrict__ out,
+                                                  TA* __restrict__ outb, float* __restrict__ partial, int M, int D, int block) {
     extern __shared__ float lds[];   // [8][3 * D]
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nch = D >> 2;
-    const int row = blockIdx.x * 8 + wave;
+    const int row = block * 8 + wave;
     float* slot = lds + wave * 3 * D;
     const f4 z = {0.f, 0.f, 0.f, 0.f};
     if (row < M) {
@@ -301,9 +314,9 @@ __global__ __launch_bounds__(512) void ln_bwd_small_kernel(const TA* __restrict_
         for (int j = 0; j < MAXJ; ++j) {
             const int c = lane + 64 * j;
             xv[j] = {(xv[j].x - mean) * rstd, (xv[j].y - mean) * rstd, (xv[j].z - mean) * rstd, (xv[j].w - mean) * rstd};
-            const f4 h = {d[j].x * gg[j].x, d[j].y * gg[j].y, d[j].z * gg[j].z, d[j].w * gg[j].w};
-            c1 += (h.x + h.y) + (h.z + h.w);
-            c2 += (h.x * xv[j].x + h.y * xv[j].y) + (h.z * xv[j].z + h.w * xv[j].w);
+            const f4 h = mul4(d[j], gg[j]);
+            c1 += dot4(d[j], gg[j]);
+            c2 += dot4(h, xv[j]);
             if (c < nch) {
                 store4(slot + 4 * c, f4{d[j].x * xv[j].x, d[j].y * xv[j].y, d[j].z * xv[j].z, d[j].w * xv[j].w});
                 store4(slot + D + 4 * c, d[j]);
@@ -337,8 +350,22 @@ __global__ __launch_bounds__(512) void ln_bwd_small_kernel(const TA* __restrict_
             const f4 v = load4(lds + w * 3 * D + 4 * c);
             s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
         }
-        store4(partial + (int64_t)blockIdx.x * 3 * D + 4 * c, s);
+        store4(partial + (int64_t)block * 3 * D + 4 * c, s);
     }
+}
+template <typename TA, typename TP, int MAXJ>
+__global__ __launch_bounds__(512) void ln_bwd_small_kernel(const TA* __restrict__ dn, const float* __restrict__ x,
+                                                           const float* __restrict__ stats, const TP* __restrict__ g,
+                                                           const float* __restrict__ r, float* __restrict__ out,
+                                                           TA* __restrict__ outb, float* __restrict__ partial, int M, int D) {
+    ln_bwd_small_rows<TA, TP, MAXJ>(dn, x, stats, g, r, out, outb, partial, M, D, blockIdx.x);
+}
+// It and, in the workgroups behind its own, the LayerNorm forward of other rows of the same width: the two chains of a small stack
+// side by side (rev_stack.hip).
+template <typename TA, typename TP, int MAXJ>
+__global__ __launch_bounds__(512) void ln_pair_kernel(LnBwdCall<TA, TP> b, LnFwdCall<TA, TP> f, int M, int D, int bwd_blocks) {
+    if ((int)blockIdx.x < bwd_blocks) ln_bwd_small_rows<TA, TP, MAXJ>(b.dn, b.x, b.stats, b.g, b.r, b.out, b.outb, b.partial, M, D, blockIdx.x);
+    else ln_fwd_rows<TA, TP, 64, MAXJ>(f.x, f.g, f.b, f.eps, f.y, f.stats, M, D, (blockIdx.x - bwd_blocks) * 512 + threadIdx.x);
 }
 
 // ---- several fixed-order reductions in one launch ----------------------------------------------------
@@ -364,6 +391,9 @@ int64_t ln_bwd_partial_elems(int M, int D) {
     return (int64_t)((M + rpb - 1) / rpb) * 3 * D;
 }
 
+static bool ln_bwd_small(int M, int D) {
+    return ln_bwd_rows_per_block(M, D) == 8 && D <= LNB_SMALL_MAXD && !(M > 2048 && D > 848 && D <= 1024);
+}
 template <typename TA, typename TP>
 int ln_backward(hipStream_t s, const TA* dn, const float* x, const float* stats, const TP* g,
                 const float* r, float* out, TA* outb, float* dgb, float* dbias,
@@ -373,7 +403,7 @@ int ln_backward(hipStream_t s, const TA* dn, const float* x, const float* stats,
     {
         ProfScope ps(K_LN_BWD, s, (double)M * D * (sizeof(TA) + 4 + 4 + 4 + (outb ? sizeof(TA) : 0)));
         dim3 grid(nblk), block(256);
-        const bool small = rpb == 8 && D <= LNB_SMALL_MAXD && !(M > 2048 && D > 848 && D <= 1024);
+        const bool small = ln_bwd_small(M, D);
         const RowSplit rs = pick_row(D, ln_bwd_shares(M, D));
 #define SMALL(J) if (rs.maxj == J) {                                                                                   \
             auto kern = ln_bwd_small_kernel<TA, TP, J>;                                                                 \
@@ -402,6 +432,33 @@ int ln_backward(hipStream_t s, const TA* dn, const float* x, const float* stats,
 }
 template int ln_backward<float, float>(hipStream_t, const float*, const float*, const float*, const float*, const float*, float*, float*, float*, float*, float*, int, int, RedSeg*);
 template int ln_backward<bf16, bf16>(hipStream_t, const bf16*, const float*, const float*, const bf16*, const float*, float*, bf16*, float*, float*, float*, int, int, RedSeg*);
+
+template <typename TA, typename TP>
+int ln_pair(hipStream_t s, const LnBwdCall<TA, TP>& b, const LnFwdCall<TA, TP>& f, int M, int D, RedSeg* defer) {
+    if (!ln_bwd_small(M, D)) {
+        if (int rc = ln_backward<TA, TP>(s, b.dn, b.x, b.stats, b.g, b.r, b.out, b.outb, b.dgb, b.dbias, b.partial, M, D, defer)) return rc;
+        return ln_forward<TA, TP>(s, f.x, f.g, f.b, f.eps, f.y, f.stats, M, D);
+    }
+    const int nblk = (M + 7) / 8;
+    ProfScope ps(K_LN_BWD, s, (double)M * D * (16 + sizeof(TA) * (b.outb ? 3 : 2)));
+    const dim3 grid(nblk + ((M + 1) / 2 + 7) / 8), block(512);
+    switch (pick_maxj(D)) {
+#define CASE(J) case J: {                                                                                              \
+            auto kern = ln_pair_kernel<TA, TP, J>;                                                                      \
+            static LdsLimit lim;                                                                                        \
+            if (int rc = lim.ensure(reinterpret_cast<const void*>(kern), 96 * LNB_SMALL_MAXD)) return rc;               \
+            hipLaunchKernelGGL(kern, grid, block, (size_t)96 * D, s, b, f, M, D, nblk);                                 \
+            break; }
+        CASE(2) CASE(3) CASE(4) CASE(5)
+#undef CASE
+        default: set_error("ln_pair: d_model too large"); return REV_EINVAL;
+    }
+    REV_HIP(hipGetLastError());
+    *defer = {b.partial, b.dgb, b.dbias, 3 * (int64_t)D, 3 * (int64_t)D, 2 * (int64_t)D, nblk};
+    return REV_OK;
+}
+template int ln_pair<float, float>(hipStream_t, const LnBwdCall<float, float>&, const LnFwdCall<float, float>&, int, int, RedSeg*);
+template int ln_pair<bf16, bf16>(hipStream_t, const LnBwdCall<bf16, bf16>&, const LnFwdCall<bf16, bf16>&, int, int, RedSeg*);
 
 // ---- column sums (bias gradients) --------------------------------------------------------
 // grid (column tiles of 256, row chunks); each wavefront sums a quarter of the

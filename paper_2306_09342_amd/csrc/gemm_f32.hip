@@ -205,6 +205,21 @@ __global__ __launch_bounds__(F_NW * 64) void gemm_f32_kernel(const float* __rest
     gemm_f32_tile<TM, TN, KIND, false, BKM>(A, lda, B, ldb, M, N, K, epi, (tile % tiles_m) * 32 * TM, (tile / tiles_m) * 32 * TN);
 }
 
+// One of the products of a launch that holds several, in 32x32 tiles
+struct F32Part { const float *A, *B; int64_t lda, ldb; int N, K, blocks; Epi epi; };
+template <int KIND, bool BKM>
+__device__ __forceinline__ void f32_part(const F32Part& p, int M, int block) {
+    const int tiles_m = (M + 31) / 32, tile = xcd_remap(block, p.blocks);
+    gemm_f32_tile<1, 1, KIND, false, BKM>(p.A, p.lda, p.B, p.ldb, M, p.N, p.K, p.epi, (tile % tiles_m) * 32, (tile / tiles_m) * 32);
+}
+// An input gradient and, behind its tiles, a map of the other chain of a small stack (rev_stack.hip): two products that do not
+// depend on each other, neither of which fills the chip.
+template <int KIND_NN, int KIND_NT>
+__global__ __launch_bounds__(F_NW * 64) void gemm_pair_f32_kernel(F32Part nn, F32Part nt, int M) {
+    if ((int)blockIdx.x < nn.blocks) f32_part<KIND_NN, true>(nn, M, blockIdx.x);
+    else f32_part<KIND_NT, false>(nt, M, blockIdx.x - nn.blocks);
+}
+
 struct WgradF32Problem { const float* G; const float* A; float* out; int64_t ldg, lda; int N, K, tile0; };
 struct WgradF32Group { WgradF32Problem p[WGRAD_GROUP_MAX]; int count; };
 
@@ -237,15 +252,16 @@ __global__ __launch_bounds__(F_NW * 64) void wgrad_f32_kernel(WgradF32Group grp,
 // sums and second stages of sums: everything that a block's backward still has to do with the rows of A, and with partial sums
 // that earlier launches left.  For blocks whose launches do not fill the chip: each of the four costs 3 to 5 us by itself there,
 // whatever it does.  Four blocks of 32 rows, D = 64: 302 -> 264 us; three of 591 rows, D = 384: 503 -> 478.
-struct WgradF32Beside { WgradF32Group grp; WgradF32Sums sums; RedArgs red; int gemm_blocks, tile_blocks, M; };
-__global__ __launch_bounds__(F_NW * 64) void gemm_wgrad_f32_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ B,
-                                                                   int64_t ldb, int N, int K, Epi epi, WgradF32Beside w) {
+// A residual map of the other chain comes between the input gradient's tiles and the weight gradients; without one it has no workgroups.
+struct WgradF32Beside { WgradF32Group grp; WgradF32Sums sums; RedArgs red; F32Part nn, nt; int tile_blocks, M; };
+__global__ __launch_bounds__(F_NW * 64) void gemm_wgrad_f32_kernel(WgradF32Beside w) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     int b = blockIdx.x;
-    if (b < w.gemm_blocks) {
-        const int tiles_m = (w.M + 31) / 32, tile = xcd_remap(b, w.gemm_blocks);
-        gemm_f32_tile<1, 1, EPI_PLAIN, false, true>(A, lda, B, ldb, w.M, N, K, epi, (tile % tiles_m) * 32, (tile / tiles_m) * 32);
-    } else if ((b -= w.gemm_blocks) < w.tile_blocks) {
+    if (b < w.nn.blocks) {
+        f32_part<EPI_PLAIN, true>(w.nn, w.M, b);
+    } else if ((b -= w.nn.blocks) < w.nt.blocks) {
+        f32_part<EPI_RESIDUAL, false>(w.nt, w.M, b);
+    } else if ((b -= w.nt.blocks) < w.tile_blocks) {
         wgrad_f32_block<1, 1>(w.grp, w.M, xcd_remap(b, w.tile_blocks));
     } else if ((b -= w.tile_blocks) < w.sums.blocks) {
         colsum_block<float>(w.sums.in, w.sums.ld, w.M, w.sums.n, w.sums.out, b, reinterpret_cast<float*>(smem));
@@ -270,14 +286,19 @@ static int launch_f32(hipStream_t s, const float* A, int64_t lda, const float* B
     return REV_OK;
 }
 
-template <bool BKM>
-static int gemm_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, const Epi& epi) {
+static int check_gemm_f32(const float* A, int64_t lda, const float* B, int64_t ldb, int N, int K, const Epi& epi) {
     const uintptr_t ptrs = (uintptr_t)A | (uintptr_t)B | (uintptr_t)epi.out | (uintptr_t)epi.out2 | (uintptr_t)epi.outf |
                            (uintptr_t)epi.bias | (uintptr_t)epi.res | (uintptr_t)epi.aux | (uintptr_t)epi.colsum;
     if (K % 4 || N % 4 || (lda & 3) || (ldb & 3) || epi.ldo % 4 || (ptrs & 15)) {
         set_error("gemm_f32: sizes must be multiples of 4 and every buffer 16-byte aligned");
         return REV_EINVAL;
     }
+    return REV_OK;
+}
+
+template <bool BKM>
+static int gemm_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, const Epi& epi) {
+    if (int rc = check_gemm_f32(A, lda, B, ldb, N, K, epi)) return rc;
     ProfScope ps(K_GEMM_NT, s, 2.0 * M * N * K);
     const bool wide = f32_wide(M, N);
     switch (epi.kind) {
@@ -294,6 +315,34 @@ int gemm_nt_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int6
 }
 int gemm_nn_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, const Epi& epi) {
     return gemm_f32<true>(s, A, lda, B, ldb, M, N, K, epi);
+}
+
+static F32Part f32_part_of(const GemmCall<float>& c, int M) {
+    return {c.A, c.B, c.lda, c.ldb, c.N, c.K, (int)f32_tiles(M, c.N, 32), c.epi};
+}
+// One launch where both take 32x32 tiles by themselves.
+int gemm_pair(hipStream_t s, const GemmCall<float>& nn, const GemmCall<float>& nt, int M) {
+    if (f32_wide(M, nn.N) || f32_wide(M, nt.N)) {
+        if (int rc = gemm_nn_f32(s, nn.A, nn.lda, nn.B, nn.ldb, M, nn.N, nn.K, nn.epi)) return rc;
+        return gemm_nt_f32(s, nt.A, nt.lda, nt.B, nt.ldb, M, nt.N, nt.K, nt.epi);
+    }
+    if (int rc = check_gemm_f32(nn.A, nn.lda, nn.B, nn.ldb, nn.N, nn.K, nn.epi)) return rc;
+    if (int rc = check_gemm_f32(nt.A, nt.lda, nt.B, nt.ldb, nt.N, nt.K, nt.epi)) return rc;
+    ProfScope ps(K_GEMM_NT, s, 2.0 * M * ((double)nn.N * nn.K + (double)nt.N * nt.K));
+    const F32Part a = f32_part_of(nn, M), b = f32_part_of(nt, M);
+    constexpr int lds = FCfg<1, 1>::SHMEM;
+    const dim3 grid((unsigned)(a.blocks + b.blocks)), block(F_NW * 64);
+#define PAIR(X, Y) if (nn.epi.kind == X && nt.epi.kind == Y) {                                                             \
+        static LdsLimit lim;                                                                                               \
+        if (int rc = lim.ensure(reinterpret_cast<const void*>(gemm_pair_f32_kernel<X, Y>), lds)) return rc;                \
+        hipLaunchKernelGGL((gemm_pair_f32_kernel<X, Y>), grid, block, lds, s, a, b, M);                                    \
+        REV_HIP(hipGetLastError());                                                                                        \
+        return REV_OK;                                                                                                     \
+    }
+    PAIR(EPI_GELU_BWD, EPI_BIAS_GELU) PAIR(EPI_PLAIN, EPI_RESIDUAL) PAIR(EPI_PLAIN, EPI_BIAS)
+#undef PAIR
+    set_error("gemm_pair: no such pair of epilogues");
+    return REV_EINVAL;
 }
 
 static int wgrad_f32_args(const WgradF32Item* items, int count, int M, WgradF32Group* grp, WgradF32Sums* sums, bool* wide, int* tiles, double* flops) {
@@ -350,27 +399,33 @@ bool gemm_wgrad_f32_together(int M, int N, const int* wn, const int* wk, int cou
     for (int k = 0; k < count; ++k) t64 += f32_tiles(wn[k], wk[k], 64);
     return M <= COLSUM_ROWS && t64 < 512 && !f32_wide(M, N);
 }
-int gemm_nn_wgrad_f32(hipStream_t s, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, float* out, int64_t ldo,
-                      const WgradF32Item* items, int count, const RedSeg* segs, int nseg) {
-    if (K % 4 || N % 4 || (lda & 3) || (ldb & 3) || ldo % 4 || (((uintptr_t)A | (uintptr_t)B | (uintptr_t)out) & 15)) {
-        set_error("gemm_f32: sizes must be multiples of 4 and every buffer 16-byte aligned");
-        return REV_EINVAL;
+int gemm_nn_wgrad_f32(hipStream_t s, const GemmCall<float>& nn, int M, const WgradF32Item* items, int count, const RedSeg* segs, int nseg,
+                      const GemmCall<float>* beside) {
+    if (int rc = check_gemm_f32(nn.A, nn.lda, nn.B, nn.ldb, nn.N, nn.K, nn.epi)) return rc;
+    if (beside) {
+        if (int rc = check_gemm_f32(beside->A, beside->lda, beside->B, beside->ldb, beside->N, beside->K, beside->epi)) return rc;
+        if (f32_wide(M, beside->N)) {                          // a launch of its own
+            if (int rc = gemm_nt_f32(s, beside->A, beside->lda, beside->B, beside->ldb, M, beside->N, beside->K, beside->epi)) return rc;
+            beside = nullptr;
+        }
     }
     WgradF32Beside w = {};
     bool wide;
-    double flops = 2.0 * M * N * K, bytes = 0;
+    double flops = 2.0 * M * nn.N * nn.K, bytes = 0;
     if (int rc = wgrad_f32_args(items, count, M, &w.grp, &w.sums, &wide, &w.tile_blocks, &flops)) return rc;
     const int red_blocks = reduce_args(segs, nseg, &w.red, &bytes);
     if (red_blocks < 0) return red_blocks;
     w.M = M;
-    w.gemm_blocks = (int)f32_tiles(M, N, 32);
-    Epi e = {};
-    e.out = out; e.ldo = ldo;
+    w.nn = f32_part_of(nn, M);
+    if (beside) {
+        w.nt = f32_part_of(*beside, M);
+        flops += 2.0 * M * beside->N * beside->K;
+    }
     ProfScope ps(K_GEMM_WGRAD, s, flops);
     static LdsLimit lim;
     if (int rc = lim.ensure(reinterpret_cast<const void*>(gemm_wgrad_f32_kernel), FCfg<1, 1>::SHMEM)) return rc;
-    hipLaunchKernelGGL(gemm_wgrad_f32_kernel, dim3((unsigned)(w.gemm_blocks + w.tile_blocks + w.sums.blocks + red_blocks)), dim3(F_NW * 64),
-                       (FCfg<1, 1>::SHMEM), s, A, lda, B, ldb, N, K, e, w);
+    hipLaunchKernelGGL(gemm_wgrad_f32_kernel, dim3((unsigned)(w.nn.blocks + w.nt.blocks + w.tile_blocks + w.sums.blocks + red_blocks)),
+                       dim3(F_NW * 64), (FCfg<1, 1>::SHMEM), s, w);
     REV_HIP(hipGetLastError());
     return REV_OK;
 }

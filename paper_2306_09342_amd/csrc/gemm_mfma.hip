@@ -174,6 +174,10 @@ static GemmShape wide_shape(int M, int N, int K, const Epi& epi, double* us) {
 // gradient: 23.2 / 16.6; 3152: 33.3 / 21.8; 7289: 42.8 / 35.1; 7289, N = 384, K = 1536: 19.6 / 13.7, residual 20.7 / 16.7; 3152, N = 384:
 // 15.7 / 11.1.  Of the 1760 launches 427 change tile, to 0.875 of the time in the mean; 11 are 4 to 9 % slower (M = 16384, N = 256, K
 // = 768, input gradient, 12.9 -> 14.0).
+// Beside another stream's kernels 128x128 tiles of the ring, one per CU on nearly all of them, keep those out for a short
+// contraction (and so do launches with column sums, whose tile is the same under both schedules): two-stream passes of four blocks, D = 1024, two-stage
+// tiles / these, us: 1024 rows 735 / 773, 1000 rows 795 / 825; one stream 848 / 842.  Longer contractions and fewer tiles gain all the same:
+// D = 1024, 3152 rows (200 tiles) 1602 / 1475; D = 1280, 3152 rows (250, K = 5120) 2361 / 2196.
 static GemmShape pick_gemm_shape(int M, int N, int K, const Epi& epi) {
     double ring_us, us;
     const bool brief = K < 640;
@@ -182,6 +186,7 @@ static GemmShape pick_gemm_shape(int M, int N, int K, const Epi& epi) {
     if (few) return ring;
     if (brief && tiles_of(M, N, 64, 128) <= 256) return GS_64x128_RING;
     const GemmShape wide = wide_shape(M, N, K, epi, &us);
+    if (!brief && ring == GS_128x128_RING && K <= 1024 && tiles_of(M, N, 128, 128) > 224 && (!epi.solo || epi.colsum)) return wide;
     return !brief && ring_us < 0.97 * us ? ring : wide;
 }
 
@@ -207,19 +212,27 @@ int gemm_bf16_mid(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int6
 int gemm_bf16_ring(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
                    const Epi& epi, bool b_kmajor, GemmShape shape);
 
-static int gemm_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
-                     Epi epi, bool b_kmajor) {
+int gemm_bf16_ring_pair(hipStream_t s, const GemmCall<bf16>& nn, const GemmCall<bf16>& nt, int M, GemmShape shape);
+
+static int check_gemm(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int N, int K, const Epi& epi) {
     const uintptr_t ptrs = (uintptr_t)A | (uintptr_t)B | (uintptr_t)epi.out | (uintptr_t)epi.out2 | (uintptr_t)epi.outf |
                            (uintptr_t)epi.bias | (uintptr_t)epi.res | (uintptr_t)epi.aux | (uintptr_t)epi.colsum;
     if (K % 8 || N % 8 || (lda & 7) || (ldb & 7) || epi.ldo % 8 || (ptrs & 15)) {
         set_error("gemm_bf16: sizes must be multiples of 8 and every buffer 16-byte aligned");
         return REV_EINVAL;
     }
+    return REV_OK;
+}
+// Widths that are no multiple of 32 take GELU in its erf form.  The polynomial is off by up to 1.3e-4 in the value, more
+// than half a bf16 step below -2.1 (six of them at -3), and pays only where the epilogue is a large share of the launch.
+static bool takes_erf(int K, int kind) { return K % 32 && (kind == EPI_BIAS_GELU || kind == EPI_GELU_BWD); }
+
+static int gemm_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
+                     Epi epi, bool b_kmajor) {
+    if (int rc = check_gemm(A, lda, B, ldb, N, K, epi)) return rc;
     ProfScope ps(K_GEMM_NT, s, 2.0 * M * N * K);
     const GemmShape shape = pick_gemm_shape(M, N, K, epi);
-    // Widths that are no multiple of 32 take GELU in its erf form.  The polynomial is off by up to 1.3e-4 in the value, more
-    // than half a bf16 step below -2.1 (six of them at -3), and pays only where the epilogue is a large share of the launch.
-    if (K % 32 && (epi.kind == EPI_BIAS_GELU || epi.kind == EPI_GELU_BWD)) epi.kind |= EPI_ERF;
+    if (takes_erf(K, epi.kind)) epi.kind |= EPI_ERF;
     if (shape <= GS_192x128_RING) return gemm_bf16_ring(s, A, lda, B, ldb, M, N, K, epi, b_kmajor, shape);
     if (shape == GS_256x128 && b_kmajor == (epi.kind == EPI_GELU_BWD || epi.kind == EPI_PLAIN)) return gemm_bf16_mid(s, A, lda, B, ldb, M, N, K, epi);
     if (shape == GS_256x256) return gemm_bf16_big(s, A, lda, B, ldb, M, N, K, epi, b_kmajor);
@@ -234,6 +247,36 @@ int gemm_nn_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64
 int gemm_nt_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb,
                  int M, int N, int K, const Epi& epi) {
     return gemm_bf16(s, A, lda, B, ldb, M, N, K, epi, false);
+}
+// The tile of two products in one launch: the cheapest of the ring for the workgroups of both together (up to 64x64 with
+// small_only), GS_128x128 if none holds them.
+static GemmShape pair_shape(const GemmCall<bf16>& nn, const GemmCall<bf16>& nt, int M, bool small_only) {
+    GemmShape best = GS_128x128;
+    double us = 1e30;
+    for (const RingCost& r : RING) {
+        const int t = tiles_of(M, nn.N, r.bm, r.bn) + tiles_of(M, nt.N, r.bm, r.bn);
+        if (t <= r.least || t > r.most || (small_only && r.bm > 64)) continue;
+        const double x = t / 256.0, step = r.stage + r.stage_full * x;
+        const double c = r.full * x + std::fmax(r.rest[nn.epi.kind] + nn.K / 64.0 * step, r.rest[nt.epi.kind] + nt.K / 64.0 * step);
+        if (c < us) { us = c; best = r.shape; }
+    }
+    return best;
+}
+// One launch where a tile of the ring holds both.  An input gradient with column sums keeps the tile that it has by itself, which
+// their strips depend on, and takes as many rounds of it as it needs.
+int gemm_pair(hipStream_t s, const GemmCall<bf16>& nn, const GemmCall<bf16>& nt, int M) {
+    const GemmShape shape = nn.epi.colsum ? pick_gemm_shape(M, nn.N, nn.K, nn.epi) : pair_shape(nn, nt, M, false);
+    if (shape > GS_192x128_RING) {
+        if (int rc = gemm_nn_bf16(s, nn.A, nn.lda, nn.B, nn.ldb, M, nn.N, nn.K, nn.epi)) return rc;
+        return gemm_nt_bf16(s, nt.A, nt.lda, nt.B, nt.ldb, M, nt.N, nt.K, nt.epi);
+    }
+    if (int rc = check_gemm(nn.A, nn.lda, nn.B, nn.ldb, nn.N, nn.K, nn.epi)) return rc;
+    if (int rc = check_gemm(nt.A, nt.lda, nt.B, nt.ldb, nt.N, nt.K, nt.epi)) return rc;
+    ProfScope ps(K_GEMM_NT, s, 2.0 * M * ((double)nn.N * nn.K + (double)nt.N * nt.K));
+    GemmCall<bf16> p = nn, q = nt;
+    if (takes_erf(p.K, p.epi.kind)) p.epi.kind |= EPI_ERF;
+    if (takes_erf(q.K, q.epi.kind)) q.epi.kind |= EPI_ERF;
+    return gemm_bf16_ring_pair(s, p, q, M, shape);
 }
 
 // ----------------------------------------------------------------------------------------
@@ -349,21 +392,15 @@ int64_t wgrad_scratch_elems(int M, const int* N, const int* K, int count) { retu
 
 int launch_wgrad_dma_group(hipStream_t s, const WgradGroup& grp, int M, int sps);
 int launch_wgrad_big(hipStream_t s, const WgradBig& p);
-int launch_gemm_wgrad(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi,
-                      const WgradTail& tail, const RedSeg* segs, int nseg, GemmShape shape);
+int launch_gemm_wgrad(hipStream_t s, const GemmCall<bf16>& nn, int M, const WgradTail& tail, const RedSeg* segs, int nseg, GemmShape shape,
+                      const GemmCall<bf16>* nt);
 
-static GemmShape plain_shape(int M, int N, int K) {
-    Epi e = {};
-    e.kind = EPI_PLAIN;
-    e.solo = true;
-    return pick_gemm_shape(M, N, K, e);
-}
-// One launch for all of it where the input gradient takes the smallest tiles, which leave most of a CU free, and the weight gradients and column sums
-// come in one piece.
-bool gemm_wgrad_bf16_together(int M, int N, int K, const int* wn, const int* wk, int count) {
-    if (M > COLSUM_ROWS || plain_shape(M, N, K) > GS_64x64) return false;
+// One launch for all of it where the column sums come in one piece and 256x256 tiles would not be the better ones for the weight
+// gradients.  as_apart: only where a launch of their own would sum them in one piece too, which is what two streams take.
+bool gemm_wgrad_bf16_together(int M, const int* wn, const int* wk, int count, bool as_apart) {
+    if (M > COLSUM_ROWS) return false;
     const WgradPlan p = wgrad_plan(M, wn, wk, count);
-    return !p.big && p.S == 1;
+    return !p.big && (!as_apart || p.S == 1);
 }
 
 static int check_wgrad_items(const WgradItem* items, int count, int M, int* N, int* K, double* flops) {
@@ -406,19 +443,18 @@ int gemm_wgrad_bf16_beside(const WgradItem* items, int count, int M, WgradTail* 
     out->steps = (M + WG_BR - 1) / WG_BR;
     return REV_OK;
 }
-int gemm_nn_wgrad_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, bf16* out, int64_t ldo,
-                       const WgradItem* items, int count, const RedSeg* segs, int nseg) {
-    if (K % 8 || N % 8 || (lda & 7) || (ldb & 7) || ldo % 8 || (((uintptr_t)A | (uintptr_t)B | (uintptr_t)out) & 15)) {
-        set_error("gemm_bf16: sizes must be multiples of 8 and every buffer 16-byte aligned");
-        return REV_EINVAL;
-    }
+int gemm_nn_wgrad_bf16(hipStream_t s, const GemmCall<bf16>& nn, int M, const WgradItem* items, int count, const RedSeg* segs, int nseg,
+                       const GemmCall<bf16>* beside) {
+    if (int rc = check_gemm(nn.A, nn.lda, nn.B, nn.ldb, nn.N, nn.K, nn.epi)) return rc;
+    if (beside)
+        if (int rc = check_gemm(beside->A, beside->lda, beside->B, beside->ldb, beside->N, beside->K, beside->epi)) return rc;
     WgradTail tail;
-    double flops = 2.0 * M * N * K;
+    double flops = 2.0 * M * ((double)nn.N * nn.K + (beside ? (double)beside->N * beside->K : 0.0)), us;
     if (int rc = gemm_wgrad_bf16_beside(items, count, M, &tail, &flops)) return rc;
-    Epi e = {};
-    e.kind = EPI_PLAIN; e.out = out; e.ldo = ldo;
     ProfScope ps(K_GEMM_WGRAD, s, flops);
-    return launch_gemm_wgrad(s, A, lda, B, ldb, M, N, K, e, tail, segs, nseg, plain_shape(M, N, K));
+    // 64x64 tiles from more than 32x32 ones hold at once
+    const GemmShape shape = beside ? pair_shape(nn, *beside, M, true) : ring_shape(M, nn.N, nn.K, EPI_PLAIN, true, &us);
+    return launch_gemm_wgrad(s, nn, M, tail, segs, nseg, shape, beside);
 }
 
 int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int M, float* scratch, int64_t scratch_elems,

@@ -35,6 +35,8 @@ template <int TM, int TN, int WM, int WN, int SUB, int NS> struct RingCfg {
     static constexpr int OUT_BYTES = BM * PITCH * 4, RING_BYTES = NS * STAGE;
     static constexpr int SHMEM = RING_BYTES > OUT_BYTES ? RING_BYTES : OUT_BYTES;
     static_assert(LA % NW == 0 && LB % NW == 0 && WM * WN <= NW && (NS - 2) * LPW < 64, "RingCfg");
+    template <int EPI, bool AKM, bool BKM>                      // gemm_ring_tile
+    __device__ __forceinline__ static void tile(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K, const Epi& epi, int m0, int n0);
 };
 
 // The tile at (m0, n0), multiples of its size (the same for all threads).  AKM, BKM: the operand is stored contraction-major, [K, ld].
@@ -262,6 +264,12 @@ __device__ __forceinline__ void gemm_ring_tile(const bf16* __restrict__ A, int64
     }
 }
 
+template <int TM, int TN, int WM, int WN, int SUB, int NS> template <int EPI, bool AKM, bool BKM>
+__device__ __forceinline__ void RingCfg<TM, TN, WM, WN, SUB, NS>::tile(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
+                                                                       const Epi& epi, int m0, int n0) {
+    gemm_ring_tile<TM, TN, WM, WN, SUB, NS, EPI, AKM, BKM>(A, lda, B, ldb, M, N, K, epi, m0, n0);
+}
+
 // Which way an XCD's run of tiles goes: the one in which it reads fewer rows of A and B.  (7289 x 384, K = 1536: 19.9 us down
 // the columns, 18.8 along the rows.)
 inline int ring_n_fast(int M, int N, int bm, int bn) {
@@ -277,5 +285,16 @@ __device__ __forceinline__ void ring_tile_at(int M, int N, int n_fast, int block
 }
 using Ring32 = RingCfg<1, 1, 1, 1, 2, 4>;                      // 64 KB of LDS: two workgroups per CU
 using Ring64 = RingCfg<1, 1, 2, 2, 1, 4>;
+
+// One of the products of a launch that holds several.
+struct RingPart { const bf16 *A, *B; int64_t lda, ldb; int N, K, n_fast, blocks; Epi epi; };
+template <typename C, int EPI, bool BKM> __device__ __forceinline__ void ring_part(const RingPart& p, int M, int block) {
+    int m0, n0;
+    ring_tile_at<C>(M, p.N, p.n_fast, block, p.blocks, &m0, &n0);
+    C::template tile<EPI, false, BKM>(p.A, p.lda, p.B, p.ldb, M, p.N, p.K, p.epi, m0, n0);
+}
+template <typename C> RingPart ring_part_of(const GemmCall<bf16>& c, int M) {
+    return {c.A, c.B, c.lda, c.ldb, c.N, c.K, ring_n_fast(M, c.N, C::BM, C::BN), ((M + C::BM - 1) / C::BM) * ((c.N + C::BN - 1) / C::BN), c.epi};
+}
 
 }  // namespace rev

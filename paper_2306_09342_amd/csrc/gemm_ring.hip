@@ -49,4 +49,38 @@ int gemm_bf16_ring(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int
     return REV_EINVAL;
 }
 
+// Two products that do not depend on each other, one tile per workgroup: an input gradient, and behind its tiles a map of the other
+// chain of a small stack (rev_stack.hip), in tiles of one shape: neither fills the chip, and both are latency for most of their time.
+template <typename C, int EPI_NN, int EPI_NT>
+__global__ __launch_bounds__((C::NW * 64)) void gemm_pair_kernel(RingPart nn, RingPart nt, int M) {
+    if ((int)blockIdx.x < nn.blocks) ring_part<C, EPI_NN, true>(nn, M, blockIdx.x);
+    else ring_part<C, EPI_NT, false>(nt, M, blockIdx.x - nn.blocks);
+}
+template <typename C>
+static int dispatch_pair(hipStream_t s, const GemmCall<bf16>& nn, const GemmCall<bf16>& nt, int M) {
+    const RingPart a = ring_part_of<C>(nn, M), b = ring_part_of<C>(nt, M);
+#define PAIR(X, Y) if (nn.epi.kind == (X) && nt.epi.kind == (Y)) {                                                      \
+        static LdsLimit lim;                                                                                            \
+        if (int rc = lim.ensure(reinterpret_cast<const void*>(gemm_pair_kernel<C, X, Y>), C::SHMEM)) return rc;         \
+        hipLaunchKernelGGL((gemm_pair_kernel<C, X, Y>), dim3(a.blocks + b.blocks), dim3(C::NW * 64), C::SHMEM, s, a, b, M); \
+        REV_HIP(hipGetLastError());                                                                                     \
+        return REV_OK;                                                                                                  \
+    }
+    PAIR(EPI_GELU_BWD, EPI_BIAS_GELU) PAIR((EPI_GELU_BWD | EPI_ERF), (EPI_BIAS_GELU | EPI_ERF))
+    PAIR(EPI_PLAIN, EPI_RESIDUAL) PAIR(EPI_PLAIN, EPI_BIAS)
+#undef PAIR
+    set_error("gemm_pair: no such pair of epilogues");
+    return REV_EINVAL;
+}
+int gemm_bf16_ring_pair(hipStream_t s, const GemmCall<bf16>& nn, const GemmCall<bf16>& nt, int M, GemmShape shape) {
+    switch (shape) {
+        case GS_32x32: return dispatch_pair<Ring32>(s, nn, nt, M);
+        case GS_64x64: return dispatch_pair<Ring64>(s, nn, nt, M);
+        case GS_64x128_RING: return dispatch_pair<RingCfg<1, 1, 2, 4, 1, 4>>(s, nn, nt, M);
+        case GS_128x128_RING: return dispatch_pair<RingCfg<2, 1, 2, 4, 1, 4>>(s, nn, nt, M);
+        case GS_192x128_RING: return dispatch_pair<RingCfg<3, 1, 2, 4, 1, 4>>(s, nn, nt, M);
+        default: set_error("gemm_bf16: no such tile"); return REV_EINVAL;
+    }
+}
+
 }  // namespace rev

@@ -226,6 +226,31 @@ static int gemm_nt(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int
     return gemm_nt_bf16(s, A, lda, B, ldb, M, N, K, e);
 }
 
+static double forward_flops(const rev_cfg& c) {               // of a block
+    const double M = (double)c.batch * c.seq_len, D = c.d_model;
+    return 2.0 * M * D * (4.0 * D + 2.0 * c.d_mlp) + 4.0 * M * c.seq_len * D;
+}
+// Blocks whose launches are mostly latency: on one stream, QKV's input gradient, the weight gradients, the column sums and the
+// second stages of the sums that the launches before left are one launch, and where the workspace holds the layout of two streams
+// the two chains are issued side by side, each launch of R_{i-1} in one of D_i (grad_d).  Four blocks, us a call: one stream, one chain
+// after the other / one stream, side by side / two streams, and in brackets side by side with the fork and the join of the parallel
+// schedule, which cost about 45 us:
+//                        197 rows                394                     788                     1000
+//     D =  256           309 / 201 / 404 (255)   339 / 214 / 418 (267)   344 / 227 / 420 (280)   423 / 278 / 428 (329)
+//     D =  768           433 / 305 / 357 (324)   507 / 352 / 439 (400)   601 / 520 / 515 (556)   701 / 597 / 600 (640)
+//     D = 1280           706 / 547 / 598 (565)   914 / 736 / 720 (776)   1228 / 1045 / 995 (1090)
+//     float32, D = 256   440 / 293 / 412 (349)   476 / 340 / 429 (394)   554 / 444 / 511 (495)   702 / 567 / 658 (615)
+// So the parallel schedule takes two streams from about 8e9 FLOP of a block's forward on (float32: 2.2e9; beyond it too much of the
+// chip is busy).  Two to 24 blocks: the same lines.
+static bool side_by_side_is_faster(const rev_cfg& c) { return forward_flops(c) < (c.mode == REV_MODE_BF16 ? 8e9 : 2.2e9); }
+// Both schedules and any number of blocks must sum the weight gradients in as many pieces: where two streams would be taken, only what
+// they sum in one.
+static bool blocks_ride(const rev_cfg& c) {
+    const int M = c.batch * c.seq_len, D = c.d_model, Dm = c.d_mlp;
+    const int nn[4] = {D, Dm, D, 3 * D}, kk[4] = {Dm, D, D, D};
+    return c.mode == REV_MODE_BF16 ? gemm_wgrad_bf16_together(M, nn, kk, 4, c.n_blocks == 1 || !side_by_side_is_faster(c)) : gemm_wgrad_f32_together(M, D, nn, kk, 4);
+}
+
 template <typename T>
 struct Runner {
     static constexpr bool kBf16 = sizeof(T) == 2;
@@ -236,10 +261,11 @@ struct Runner {
     float* dparams;
     int M, D, Dm, H, dh, B, Tn;
     bool solo;      // one stream: every kernel has the device to itself
+    bool side_by_side;   // one stream, in the layout of two: small blocks issue the two chains side by side
     const int* key_len = nullptr;   // optional key-padding mask: valid keys per sample (device, [batch])
 
-    Runner(const rev_cfg& cfg, const void* p, float* dp, void* w, bool compact)
-        : c(cfg), L(make_layout(cfg, compact)), ws((char*)w), params((const T*)p), dparams(dp), solo(compact) {
+    Runner(const rev_cfg& cfg, const void* p, float* dp, void* w, bool compact, bool one_stream)
+        : c(cfg), L(make_layout(cfg, compact)), ws((char*)w), params((const T*)p), dparams(dp), solo(one_stream), side_by_side(!compact) {
         M = c.batch * c.seq_len; D = c.d_model; Dm = c.d_mlp; H = c.n_heads; dh = D / H; B = c.batch; Tn = c.seq_len;
     }
     Epi epi0() const { Epi e = {}; e.solo = solo; return e; }
@@ -253,34 +279,52 @@ struct Runner {
                 at<T>(b + L.s_o), at<float>(b + L.s_lse), at<float>(b + L.s_st1), at<float>(b + L.s_st2)};
     }
 
-    // F branch pieces up to the projection input: n1, qkv, o, lse from x2
-    int f_pre(hipStream_t s, int blk, const float* x2, const Slot& sl) {
-        RC((ln_forward<T, T>(s, x2, P(blk, T_LN1G), P(blk, T_LN1B), c.ln_eps, sl.n1, sl.st1, M, D)));
+    // ---- the launches of a block's two maps ----
+    using Gemm = GemmCall<T>;
+    using Ln = LnFwdCall<T, T>;
+    Ln ln1(int blk, const float* x2, const Slot& sl) const { return {x2, P(blk, T_LN1G), P(blk, T_LN1B), c.ln_eps, sl.n1, sl.st1}; }
+    Ln ln2(int blk, const float* y1, const Slot& sl) const { return {y1, P(blk, T_LN2G), P(blk, T_LN2B), c.ln_eps, sl.n2, sl.st2}; }
+    Gemm qkv_map(int blk, const Slot& sl) const {
         Epi e = epi0(); e.kind = EPI_BIAS; e.out = sl.qkv; e.bias = P(blk, T_BQKV); e.ldo = 3 * D;
-        RC(gemm_nt(s, sl.n1, D, P(blk, T_WQKV), D, M, 3 * D, D, e));
-        RC((attention_forward<T>(s, sl.qkv, sl.o, sl.lse, B, Tn, H, dh, key_len)));
-        return REV_OK;
+        return {sl.n1, D, P(blk, T_WQKV), D, 3 * D, D, e};
     }
     // out1 = in1 + sign * (o Wp^T + bp)
-    int f_post(hipStream_t s, int blk, const Slot& sl, const float* in1, float* out1, float sign) {
+    Gemm proj_map(int blk, const Slot& sl, const float* in1, float* out1, float sign) const {
         Epi e = epi0(); e.kind = EPI_RESIDUAL; e.outf = out1; e.res = in1; e.bias = P(blk, T_BPROJ); e.sign = sign; e.ldo = D;
-        return gemm_nt(s, sl.o, D, P(blk, T_WPROJ), D, M, D, D, e);
+        return {sl.o, D, P(blk, T_WPROJ), D, D, D, e};
     }
-    // out2 = in2 + sign * G(y1); the pre-activation of the MLP is kept only where a backward step will read it
+    // the pre-activation of the MLP is kept only where a backward step will read it
+    Gemm fc1_map(int blk, const Slot& sl, bool keep_h) const {
+        Epi e = epi0(); e.kind = EPI_BIAS_GELU; e.out = keep_h ? sl.h : nullptr; e.out2 = sl.a; e.bias = P(blk, T_BFC1); e.ldo = Dm;
+        return {sl.n2, D, P(blk, T_WFC1), D, Dm, D, e};
+    }
+    // out2 = in2 + sign * (a W2^T + b2)
+    Gemm fc2_map(int blk, const Slot& sl, const float* in2, float* out2, float sign) const {
+        Epi r = epi0(); r.kind = EPI_RESIDUAL; r.outf = out2; r.res = in2; r.bias = P(blk, T_BFC2); r.sign = sign; r.ldo = D;
+        return {sl.a, Dm, P(blk, T_WFC2), Dm, D, Dm, r};
+    }
+    int run(hipStream_t s, const Ln& l) { return ln_forward<T, T>(s, l.x, l.g, l.b, l.eps, l.y, l.stats, M, D); }
+    int run(hipStream_t s, const Gemm& g) { return gemm_nt(s, g.A, g.lda, g.B, g.ldb, M, g.N, g.K, g.epi); }
+
+    // F branch pieces up to the projection input: n1, qkv, o, lse from x2
+    int f_pre(hipStream_t s, int blk, const float* x2, const Slot& sl) {
+        RC(run(s, ln1(blk, x2, sl)));
+        RC(run(s, qkv_map(blk, sl)));
+        return attention_forward<T>(s, sl.qkv, sl.o, sl.lse, B, Tn, H, dh, key_len);
+    }
+    // out2 = in2 + sign * G(y1)
     int g_branch(hipStream_t s, int blk, const float* y1, const Slot& sl, const float* in2, float* out2, float sign,
                  bool keep_h = true) {
-        RC((ln_forward<T, T>(s, y1, P(blk, T_LN2G), P(blk, T_LN2B), c.ln_eps, sl.n2, sl.st2, M, D)));
-        Epi e = epi0(); e.kind = EPI_BIAS_GELU; e.out = keep_h ? sl.h : nullptr; e.out2 = sl.a; e.bias = P(blk, T_BFC1); e.ldo = Dm;
-        RC(gemm_nt(s, sl.n2, D, P(blk, T_WFC1), D, M, Dm, D, e));
-        Epi r = epi0(); r.kind = EPI_RESIDUAL; r.outf = out2; r.res = in2; r.bias = P(blk, T_BFC2); r.sign = sign; r.ldo = D;
-        return gemm_nt(s, sl.a, Dm, P(blk, T_WFC2), Dm, M, D, Dm, r);
+        RC(run(s, ln2(blk, y1, sl)));
+        RC(run(s, fc1_map(blk, sl, keep_h)));
+        return run(s, fc2_map(blk, sl, in2, out2, sign));
     }
 
     // forward of block blk (0-based): (x1,x2) -> (y1,y2)
     int forward_block(hipStream_t s, int blk, const float* x1, const float* x2, float* y1, float* y2) {
         Slot sl = slot(0);
         RC(f_pre(s, blk, x2, sl));
-        RC(f_post(s, blk, sl, x1, y1, 1.f));
+        RC(run(s, proj_map(blk, sl, x1, y1, 1.f)));
         return g_branch(s, blk, y1, sl, x2, y2, 1.f, false);
     }
 
@@ -289,16 +333,22 @@ struct Runner {
         Slot sl = slot(blk);
         RC(g_branch(s, blk, y1, sl, y2, x2, -1.f));
         RC(f_pre(s, blk, x2, sl));
-        return f_post(s, blk, sl, y1, x1, -1.f);
+        return run(s, proj_map(blk, sl, y1, x1, -1.f));
     }
 
-    // dA[M,Kin] = dC[M,Nout] * W[Nout,Kin], the weight read as it is stored
-    int dgrad(hipStream_t s, int blk, int wt, const T* dC, int Nout, int Kin, const Epi& e) {
+    // dA[M,Kin] = dC[M,Nout] * W[Nout,Kin], the weight read as it is stored; with a map of the block below beside it where there is one
+    int dgrad(hipStream_t s, int blk, int wt, const T* dC, int Nout, int Kin, const Epi& e, bool paired, const Gemm& beside) {
+        if (paired) return gemm_pair(s, {dC, Nout, P(blk, wt), Kin, Kin, Nout, e}, beside, M);
         if constexpr (kBf16) {
             return gemm_nn_bf16(s, dC, Nout, P(blk, wt), Kin, M, Kin, Nout, e);
         } else {
             return gemm_nn_f32(s, dC, Nout, P(blk, wt), Kin, M, Kin, Nout, e);
         }
+    }
+    // LayerNorm backward, with the LayerNorm forward of the block below beside it where there is one
+    int ln_back(hipStream_t s, const LnBwdCall<T, T>& b, bool paired, const Ln& beside, RedSeg* seg) {
+        if (paired) return ln_pair<T, T>(s, b, beside, M, D, seg);
+        return ln_backward<T, T>(s, b.dn, b.x, b.stats, b.g, b.r, b.out, b.outb, b.dgb, b.dbias, b.partial, M, D, seg);
     }
 
     // V_i is issued as two kernel sequences.
@@ -326,18 +376,20 @@ struct Runner {
     }
     // QKV's bias gradient (column sums of dqkv) in the launch of the weight gradients, which reads dqkv anyway
     bool sums_ride() const { return kBf16 || M <= COLSUM_ROWS; }
-    // Small blocks on one stream: QKV's input gradient, the weight gradients, the column sums and the second stages of the
-    // sums that the launches before left, in one launch.
-    bool all_ride() const {
-        const int nn[4] = {D, Dm, D, 3 * D}, kk[4] = {Dm, D, D, D};
-        return kBf16 ? gemm_wgrad_bf16_together(M, D, 3 * D, nn, kk, 4) : gemm_wgrad_f32_together(M, D, nn, kk, 4);
-    }
+    bool all_ride() const { return blocks_ride(c); }
 
     // together: grad_w's work is done here too, with the launch that ends the attention branch, and what segs holds by then
     // (with what the block above left there) is summed; the last LayerNorm's sums are left in segs.
+    // below (nullable, with together): the recomputation of the block below, whose seven launches have the order and the kinds of D_i's,
+    // one launch on, and depend on none of them: each rides in one of D_i's.  Its first LayerNorm is done before; the last launch takes
+    // that of the block below it.
+    struct Below { const float *y1, *y2; float *x1, *x2; };
     int grad_d(hipStream_t s, int blk, const float* y1, const float* x2, const float* d1, const float* d2,
-               const T* d2b, float* o1, float* o2, T* o2b, hipEvent_t done_dqkv, RedSeg* segs, int* n, bool together) {
-        Slot sl = slot(blk);
+               const T* d2b, float* o1, float* o2, T* o2b, hipEvent_t done_dqkv, RedSeg* segs, int* n, bool together, const Below* below) {
+        Slot sl = slot(blk), lo = slot(blk + 1);             // (the other one)
+        const Below w = below ? *below : Below{};
+        const bool pair = below != nullptr;
+        const int lb = pair ? blk - 1 : 0;
         T* dhb = at<T>(L.dh[blk & 1]);
         T* dqkv = at<T>(L.dqkv[blk & 1]);
         T* dn = at<T>(L.dn);
@@ -350,41 +402,47 @@ struct Runner {
         // in the epilogue
         Epi e = epi0(); e.kind = EPI_GELU_BWD; e.out = dhb; e.aux = sl.h; e.ldo = Dm;
         e.colsum = pcol0;
-        RC(dgrad(s, blk, T_WFC2, d2b, D, Dm, e));
+        RC(dgrad(s, blk, T_WFC2, d2b, D, Dm, e, pair, fc1_map(lb, lo, true)));
         segs[nseg++] = {pcol0, G(blk, T_BFC1), nullptr, (int64_t)Dm, (int64_t)Dm, (int64_t)Dm,
                         kBf16 ? gemm_colsum_strips(M, Dm, D) : gemm_f32_colsum_strips(M, Dm)};
         Epi p = epi0(); p.kind = EPI_PLAIN; p.out = dn; p.ldo = D;
-        RC(dgrad(s, blk, T_WFC1, dhb, Dm, D, p));
+        RC(dgrad(s, blk, T_WFC1, dhb, Dm, D, p, pair, fc2_map(lb, lo, w.y2, w.x2, -1.f)));
         // gY1 = dY1 + LN2bwd(dn); its column sums are the bias gradient of the projection
-        RC((ln_backward<T, T>(s, dn, y1, sl.st2, P(blk, T_LN2G), d1, o1, kBf16 ? gy1b : nullptr,
-                              G(blk, T_LN2G), G(blk, T_BPROJ), at<float>(L.part_ln[0]), M, D, &segs[nseg++])));
+        RC(ln_back(s, {dn, y1, sl.st2, P(blk, T_LN2G), d1, o1, kBf16 ? gy1b : nullptr, G(blk, T_LN2G), G(blk, T_BPROJ), at<float>(L.part_ln[0])},
+                   pair, ln1(lb, w.x2, lo), &segs[nseg++]));
         // ---- F branch
         Epi q = epi0(); q.kind = EPI_PLAIN; q.out = dO; q.ldo = D;
-        RC(dgrad(s, blk, T_WPROJ, gy1b, D, D, q));
-        const Items w = w_items(blk, d2b, o1);
+        RC(dgrad(s, blk, T_WPROJ, gy1b, D, D, q, pair, qkv_map(lb, lo)));
+        const Items wi = w_items(blk, d2b, o1);
+        const AttnFwdCall<T> fwd = {lo.qkv, lo.o, lo.lse};
         int begun = 0;                                       // weight gradients whose operands are ready before dqkv
+        bool attended = !pair;                               // the block below has had its attention
         if constexpr (kBf16) {
             if (together && attention_takes_wgrad(B, Tn, H, dh)) begun = 3;
-            if (begun) RC(attention_backward_wgrad(s, sl.qkv, sl.o, dO, sl.lse, dqkv, B, Tn, H, dh, key_len, w.p, begun));
+            if (begun) RC(attention_backward_wgrad(s, sl.qkv, sl.o, dO, sl.lse, dqkv, B, Tn, H, dh, key_len, wi.p, begun, pair ? &fwd : nullptr));
+            attended |= begun > 0;
+        } else if (pair) {
+            RC(attention_pair_f32(s, sl.qkv, sl.o, dO, sl.lse, dqkv, B, Tn, H, dh, key_len, fwd));
+            attended = true;
         }
-        if (!begun) RC((attention_backward<T>(s, sl.qkv, sl.o, dO, sl.lse, dqkv, at<float>(L.delta), B, Tn, H, dh, key_len, solo)));
+        if (!begun && (kBf16 || !pair)) RC((attention_backward<T>(s, sl.qkv, sl.o, dO, sl.lse, dqkv, at<float>(L.delta), B, Tn, H, dh, key_len, solo)));
+        if (!attended) RC(attention_forward<T>(s, fwd.qkv, fwd.o, fwd.lse, B, Tn, H, dh, key_len));
         if (done_dqkv) REV_HIP(hipEventRecord(done_dqkv, s));
+        Epi r = epi0(); r.kind = EPI_PLAIN; r.out = dn; r.ldo = D;
         if (together) {
-            if constexpr (kBf16) RC(gemm_nn_wgrad_bf16(s, dqkv, 3 * D, P(blk, T_WQKV), D, M, D, 3 * D, dn, D, w.p + begun, 4 - begun, segs, nseg));
-            else RC(gemm_nn_wgrad_f32(s, dqkv, 3 * D, P(blk, T_WQKV), D, M, D, 3 * D, dn, D, w.p, 4, segs, nseg));
+            const Gemm input = {dqkv, 3 * D, P(blk, T_WQKV), D, D, 3 * D, r}, proj = proj_map(lb, lo, w.y1, w.x1, -1.f), *beside = pair ? &proj : nullptr;
+            if constexpr (kBf16) RC(gemm_nn_wgrad_bf16(s, input, M, wi.p + begun, 4 - begun, segs, nseg, beside));
+            else RC(gemm_nn_wgrad_f32(s, input, M, wi.p, 4, segs, nseg, beside));
             nseg = 0;
         } else {
-            Epi r = epi0(); r.kind = EPI_PLAIN; r.out = dn; r.ldo = D;
-            RC(dgrad(s, blk, T_WQKV, dqkv, 3 * D, D, r));
+            RC(dgrad(s, blk, T_WQKV, dqkv, 3 * D, D, r, false, {}));
             if constexpr (!kBf16)
                 if (!sums_ride()) RC(colsum<T>(s, dqkv, 3 * D, M, 3 * D, G(blk, T_BQKV), at<float>(L.part_col[1]), &segs[nseg++]));
         }
         // dX2 = dY2 + LN1bwd(dn); dX2 is the block below's dY2, so its column sums are that block's
         // fc2 bias gradient
-        RC((ln_backward<T, T>(s, dn, x2, sl.st1, P(blk, T_LN1G), d2, o2, kBf16 ? o2b : nullptr,
-                              G(blk, T_LN1G), blk > 0 ? G(blk - 1, T_BFC2) : nullptr, at<float>(L.part_ln[1]), M, D,
-                              &segs[nseg++])));
-        return REV_OK;
+        return ln_back(s, {dn, x2, sl.st1, P(blk, T_LN1G), d2, o2, kBf16 ? o2b : nullptr, G(blk, T_LN1G), blk > 0 ? G(blk - 1, T_BFC2) : nullptr,
+                           at<float>(L.part_ln[1])}, pair && blk >= 2, pair && blk >= 2 ? ln2(blk - 2, w.x1, sl) : Ln{}, &segs[nseg++]);
     }
 
     int grad_w(hipStream_t s, int blk, const T* d2b, float* o1, RedSeg* segs, int* nseg) {
@@ -409,8 +467,9 @@ struct Runner {
     //    5.5e7      1039 / 1010      1164 / 1241        522 / 435      608 / 503
     //    9.7e7      1202 /  976      1296 / 1270        635 / 460      724 / 546
     //    2.0e8      1240 / 1043      1418 / 1241        657 / 465      796 / 618
-    // From 8e7 on two streams win on both.  Same kernels in the same order, so the same results.
-    bool one_stream_is_faster() const { return 2.0 * M * D * (4.0 * D + 2.0 * Dm) + 4.0 * M * (double)Tn * D < 8e7; }
+    // From 8e7 on two streams win on both, where the chains cannot be issued side by side on one.  Same kernels in the same order, so
+    // the same results.
+    bool one_stream_is_faster() const { return forward_flops(c) < 8e7 || (c.n_blocks > 1 && all_ride() && side_by_side_is_faster(c)); }
 
     // residual level `lvl` (0..N): stream s1/s2 pointers
     struct Ptrs { const float* in1; const float* in2; float* out1; float* out2; };
@@ -482,7 +541,7 @@ struct Runner {
             else return reinterpret_cast<const T*>((i == N) ? dY2 : at<float>(L.cot[i & 1][1]));
         };
         auto o1_of = [&](int i) -> float* { return (i == 1) ? dX1 : at<float>(L.cot[(i - 1) & 1][0]); };
-        auto run_D = [&](int i, hipEvent_t done_dqkv) -> int {
+        auto run_D = [&](int i, hipEvent_t done_dqkv, const Below* below = nullptr) -> int {
             const float* y1 = (i == N) ? Y1 : res(i, 0, X1o, X2o);
             const float* x2 = res(i - 1, 1, X1o, X2o);
             const float* d1 = (i == N) ? dY1 : at<float>(L.cot[i & 1][0]);
@@ -490,7 +549,7 @@ struct Runner {
             float* o2 = (i == 1) ? dX2 : at<float>(L.cot[(i - 1) & 1][1]);
             T* o2b = nullptr;
             if constexpr (kBf16) o2b = (i == 1) ? nullptr : at<T>(L.cot2b[(i - 1) % 3]);
-            return grad_d(sv, i - 1, y1, x2, d1, d2, d2b_of(i), o1_of(i), o2, o2b, done_dqkv, segs, &nseg, together);
+            return grad_d(sv, i - 1, y1, x2, d1, d2, d2b_of(i), o1_of(i), o2, o2b, done_dqkv, segs, &nseg, together, below);
         };
         if (two) {
             RC(run_R(N));
@@ -515,6 +574,15 @@ struct Runner {
                 RC(reduce(sr, wsegs, &nw));
                 if (!kBf16 && i > 1) REV_HIP(hipEventRecord(E(i, E_W), sr));
             }
+        } else if (together && side_by_side && doR && doV) {
+            RC(run_R(N));
+            if (N > 1) RC(run(sv, ln2(N - 2, res(N - 1, 0, X1o, X2o), slot(N - 2))));
+            for (int i = N; i >= 1; --i) {
+                const Below below = {res(i - 1, 0, X1o, X2o), res(i - 1, 1, X1o, X2o), i > 1 ? res(i - 2, 0, X1o, X2o) : nullptr,
+                                     i > 1 ? res(i - 2, 1, X1o, X2o) : nullptr};
+                RC(run_D(i, nullptr, i > 1 ? &below : nullptr));
+            }
+            RC(reduce(sv, segs, &nseg));
         } else {
             for (int i = N; i >= 1; --i) {
                 if (doR) RC(run_R(i));
@@ -576,12 +644,15 @@ static int backward_entry(int schedule, const rev_cfg* cfg, const void* params, 
     }
     if (schedule == 1 && sv == sr) { set_error("PaReprop needs two different streams"); return REV_EINVAL; }
     if (((uintptr_t)key_len & 3) != 0) { set_error("key_len must be 4-byte aligned"); return REV_EINVAL; }
+    // A sequential pass takes the layout of the parallel one where it fits and the blocks are small, for it issues both chains side
+    // by side then.
+    const bool small = compact && !(ws_bytes >= make_layout(*cfg, false).total && blocks_ride(*cfg));
     if (cfg->mode == REV_MODE_BF16) {
-        Runner<bf16> r(*cfg, params, dparams, ws, compact);
+        Runner<bf16> r(*cfg, params, dparams, ws, small, compact);
         r.key_len = key_len;
         return r.backward(schedule, Y1, Y2, dY1, dY2, dX1, dX2, X1o, X2o, (hipStream_t)sv, (hipStream_t)sr);
     }
-    Runner<float> r(*cfg, params, dparams, ws, compact);
+    Runner<float> r(*cfg, params, dparams, ws, small, compact);
     r.key_len = key_len;
     return r.backward(schedule, Y1, Y2, dY1, dY2, dX1, dX2, X1o, X2o, (hipStream_t)sv, (hipStream_t)sr);
 }
@@ -664,11 +735,11 @@ static int forward_entry(const rev_cfg* cfg, const void* params, const float* X1
     }
     if (((uintptr_t)key_len & 3) != 0) { set_error("key_len must be 4-byte aligned"); return REV_EINVAL; }
     if (cfg->mode == REV_MODE_BF16) {
-        Runner<bf16> r(*cfg, params, nullptr, ws, true);
+        Runner<bf16> r(*cfg, params, nullptr, ws, true, true);
         r.key_len = key_len;
         return r.forward(X1, X2, Y1, Y2, (hipStream_t)stream);
     }
-    Runner<float> r(*cfg, params, nullptr, ws, true);
+    Runner<float> r(*cfg, params, nullptr, ws, true, true);
     r.key_len = key_len;
     return r.forward(X1, X2, Y1, Y2, (hipStream_t)stream);
 }
