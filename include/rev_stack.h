@@ -119,11 +119,12 @@ int64_t rev_stack_workspace_bytes(const rev_cfg* cfg);
  * produced while block i is still being consumed, so ONE activation slot, two
  * residual-stream levels and single gradient temporaries suffice.  The
  * difference to rev_stack_workspace_bytes is the extra memory the parallel
- * schedule pays for its speed (Sec. 3.3; memory trends, Sec. 4.2).  Stacks of up
- * to 1024 rows (batch*seq_len) are faster (up to 1.8 times) in a backward call
- * that is given rev_stack_workspace_bytes: it then issues the two chains side by
- * side, the launches of R_{i-1} within those of V_i, with the same results bit
- * for bit.  Host only. */
+ * schedule pays for its speed (Sec. 3.3; memory trends, Sec. 4.2).  Stacks of
+ * small blocks (up to 1024 rows, batch*seq_len, or about 1e10 FLOP of a block's
+ * forward) are faster, up to 1.8 times, in a backward call that is given
+ * rev_stack_workspace_bytes: it then issues the two chains side by side, the
+ * launches of R_{i-1} within those of V_i, with the same results bit for bit.
+ * Host only. */
 int64_t rev_stack_workspace_bytes_reprop(const rev_cfg* cfg);
 
 /* Bytes of one activation slot: the intermediates of ONE block that a gradient

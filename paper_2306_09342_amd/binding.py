@@ -163,15 +163,19 @@ def param_dtype(cfg: RevCfg):
     return torch.bfloat16 if cfg.mode == REV_MODE_BF16 else torch.float32
 
 
-SMALL_ROWS = 1024                              # COLSUM_ROWS of csrc/common.h
+def _small_blocks(cfg: RevCfg) -> bool:
+    """Stacks whose chains a sequential backward may run side by side (at least those: the lines are in csrc/rev_stack.hip)."""
+    rows, D = cfg.batch * cfg.seq_len, cfg.d_model
+    flops = 2.0 * rows * D * (4.0 * D + 2.0 * cfg.d_mlp) + 4.0 * rows * cfg.seq_len * D
+    return rows <= 1024 or flops < (8e9 if cfg.mode == REV_MODE_BF16 else 1.2e10)
 
 
 def alloc_workspace(cfg: RevCfg, device="cuda", reprop_only: bool = False) -> torch.Tensor:
     """Workspace for every entry point, or with reprop_only for the sequential schedule and the forward map, which need
-    rev_stack_workspace_bytes_reprop.  Stacks of up to SMALL_ROWS rows get rev_stack_workspace_bytes either way: in that the
-    sequential schedule runs their two chains side by side."""
+    rev_stack_workspace_bytes_reprop.  Stacks of small blocks get rev_stack_workspace_bytes either way: in that the sequential
+    schedule runs their two chains side by side."""
     n = rev_stack_workspace_bytes_reprop(cfg)
-    if not reprop_only or cfg.batch * cfg.seq_len <= SMALL_ROWS:
+    if not reprop_only or _small_blocks(cfg):
         n = rev_stack_workspace_bytes(cfg)
     return torch.empty(n, dtype=torch.uint8, device=device)
 

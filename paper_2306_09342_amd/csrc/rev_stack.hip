@@ -243,6 +243,14 @@ static double forward_flops(const rev_cfg& c) {               // of a block
 // So the parallel schedule takes two streams from about 8e9 FLOP of a block's forward on (float32: 2.2e9; beyond it too much of the
 // chip is busy).  Two to 24 blocks: the same lines.
 static bool side_by_side_is_faster(const rev_cfg& c) { return forward_flops(c) < (c.mode == REV_MODE_BF16 ? 8e9 : 2.2e9); }
+// The same without the common launch of the weight gradients, beyond 1024 rows or 512 64x64 tiles of them.  Four blocks, us a call: one
+// stream, in turn / side by side / two streams.  bf16, D = 64: 1576 rows 281 / 233 / 364, 12608 423 / 396 / 518; D = 128: 3152 rows 366 / 308 /
+// 382, 6304 434 / 396 / 416, 12608 (6e9 FLOP) 578 / 581 / 528; D = 256: 3152 473 / 445 / 424; D = 512: 1576 (1e10) 559 / 534 / 478, 3152 (2e10)
+// 767 / 770 / 877.  float32, D = 64: 3152 464 / 402 / 570; D = 256: 1576 824 / 760 / 753; D = 384: 3152 (1.2e10) 2463 / 2424 / 2323.
+static bool apart_side_by_side_is_faster(const rev_cfg& c, bool two_streams) {
+    const bool bf = c.mode == REV_MODE_BF16;
+    return forward_flops(c) < (two_streams ? (bf ? 2e9 : 5e8) : (bf ? 8e9 : 1.2e10));
+}
 // Both schedules and any number of blocks must sum the weight gradients in as many pieces: where two streams would be taken, only what
 // they sum in one.
 static bool blocks_ride(const rev_cfg& c) {
@@ -380,9 +388,9 @@ struct Runner {
 
     // together: grad_w's work is done here too, with the launch that ends the attention branch, and what segs holds by then
     // (with what the block above left there) is summed; the last LayerNorm's sums are left in segs.
-    // below (nullable, with together): the recomputation of the block below, whose seven launches have the order and the kinds of D_i's,
+    // below (nullable): the recomputation of the block below, whose seven launches have the order and the kinds of D_i's,
     // one launch on, and depend on none of them: each rides in one of D_i's.  Its first LayerNorm is done before; the last launch takes
-    // that of the block below it.
+    // that of the block below it, in the slot of this block, whose grad_w is therefore done before it.
     struct Below { const float *y1, *y2; float *x1, *x2; };
     int grad_d(hipStream_t s, int blk, const float* y1, const float* x2, const float* d1, const float* d2,
                const T* d2b, float* o1, float* o2, T* o2b, hipEvent_t done_dqkv, RedSeg* segs, int* n, bool together, const Below* below) {
@@ -435,9 +443,10 @@ struct Runner {
             else RC(gemm_nn_wgrad_f32(s, input, M, wi.p, 4, segs, nseg, beside));
             nseg = 0;
         } else {
-            RC(dgrad(s, blk, T_WQKV, dqkv, 3 * D, D, r, false, {}));
+            RC(dgrad(s, blk, T_WQKV, dqkv, 3 * D, D, r, pair, proj_map(lb, lo, w.y1, w.x1, -1.f)));
             if constexpr (!kBf16)
                 if (!sums_ride()) RC(colsum<T>(s, dqkv, 3 * D, M, 3 * D, G(blk, T_BQKV), at<float>(L.part_col[1]), &segs[nseg++]));
+            if (pair) RC(grad_w(s, blk, d2b, o1, segs, n));      // before the last launch overwrites n2 of this slot
         }
         // dX2 = dY2 + LN1bwd(dn); dX2 is the block below's dY2, so its column sums are that block's
         // fc2 bias gradient
@@ -469,7 +478,7 @@ struct Runner {
     //    2.0e8      1240 / 1043      1418 / 1241        657 / 465      796 / 618
     // From 8e7 on two streams win on both, where the chains cannot be issued side by side on one.  Same kernels in the same order, so
     // the same results.
-    bool one_stream_is_faster() const { return forward_flops(c) < 8e7 || (c.n_blocks > 1 && all_ride() && side_by_side_is_faster(c)); }
+    bool one_stream_is_faster() const { return forward_flops(c) < 8e7 || (c.n_blocks > 1 && (all_ride() ? side_by_side_is_faster(c) : apart_side_by_side_is_faster(c, true))); }
 
     // residual level `lvl` (0..N): stream s1/s2 pointers
     struct Ptrs { const float* in1; const float* in2; float* out1; float* out2; };
@@ -574,13 +583,16 @@ struct Runner {
                 RC(reduce(sr, wsegs, &nw));
                 if (!kBf16 && i > 1) REV_HIP(hipEventRecord(E(i, E_W), sr));
             }
-        } else if (together && side_by_side && doR && doV) {
+        } else if (side_by_side && doR && doV) {
             RC(run_R(N));
             if (N > 1) RC(run(sv, ln2(N - 2, res(N - 1, 0, X1o, X2o), slot(N - 2))));
             for (int i = N; i >= 1; --i) {
                 const Below below = {res(i - 1, 0, X1o, X2o), res(i - 1, 1, X1o, X2o), i > 1 ? res(i - 2, 0, X1o, X2o) : nullptr,
                                      i > 1 ? res(i - 2, 1, X1o, X2o) : nullptr};
                 RC(run_D(i, nullptr, i > 1 ? &below : nullptr));
+                if (together) continue;
+                if (i == 1) RC(grad_w(sv, 0, d2b_of(1), o1_of(1), segs, &nseg));
+                RC(reduce(sv, segs, &nseg));
             }
             RC(reduce(sv, segs, &nseg));
         } else {
@@ -646,7 +658,7 @@ static int backward_entry(int schedule, const rev_cfg* cfg, const void* params, 
     if (((uintptr_t)key_len & 3) != 0) { set_error("key_len must be 4-byte aligned"); return REV_EINVAL; }
     // A sequential pass takes the layout of the parallel one where it fits and the blocks are small, for it issues both chains side
     // by side then.
-    const bool small = compact && !(ws_bytes >= make_layout(*cfg, false).total && blocks_ride(*cfg));
+    const bool small = compact && !(ws_bytes >= make_layout(*cfg, false).total && (blocks_ride(*cfg) || apart_side_by_side_is_faster(*cfg, false)));
     if (cfg->mode == REV_MODE_BF16) {
         Runner<bf16> r(*cfg, params, dparams, ws, small, compact);
         r.key_len = key_len;

@@ -29,7 +29,11 @@ CASES = [
     ("bf16", 3, 512, 8, 2048, 250, 4, False),      # weight gradients in 128x128 tiles that two ranges would share; 1000 rows
     ("bf16", 2, 1288, 23, 2576, 20, 3, False),     # rows too wide for the LayerNorm pair
     ("bf16", 2, 1024, 16, 4096, 100, 4, False),    # eight-wavefront tiles
-    ("bf16", 3, 256, 4, 1024, 41, 25, False),      # 1025 rows: in turn
+    ("bf16", 3, 256, 4, 1024, 41, 25, False),      # 1025 rows: weight gradients in a launch of their own
+    ("bf16", 3, 96, 3, 384, 49, 45, True),         # 2205 rows, attention of a launch per chain
+    ("bf16", 2, 64, 1, 256, 60, 140, False),       # 8400 rows: beyond the LayerNorm pair
+    ("fp32", 3, 512, 8, 1536, 33, 3, False),       # weight gradients of 640 tiles
+    ("fp32", 3, 64, 2, 264, 43, 25, True),         # 1075 rows
 ]
 
 
@@ -70,10 +74,10 @@ def test_side_by_side_or_in_turn(mode, blocks, width, heads, hidden, tokens, bat
         compare_backward(cfg, rep, ref, TOL[mode], what=str(cfg))
 
 
-# 1100 rows and 1e8 FLOP of a block's forward: beyond both lines
+# 8000 rows and 3.3e9 FLOP of a block's forward: beyond every line
 @pytest.mark.parametrize("mode", ["bf16", "fp32"])
 def test_two_streams_keep_their_order_under_capture_and_with_late_outputs(mode):
-    cfg = dict(n_blocks=6, d_model=64, n_heads=2, d_mlp=256, seq_len=50, batch=22, mode=mode)
+    cfg = dict(n_blocks=4, d_model=128, n_heads=2, d_mlp=512, seq_len=50, batch=160, mode=mode)
     flat, _, x, dy1, dy2 = make_case(cfg, seed=29)
     c = gpu_cfg(cfg)
     params = to_dev(flat, B.param_dtype(c))
