@@ -361,7 +361,7 @@ __global__ __launch_bounds__(512) void ln_bwd_small_kernel(const TA* __restrict_
     ln_bwd_small_rows<TA, TP, MAXJ>(dn, x, stats, g, r, out, outb, partial, M, D, blockIdx.x);
 }
 // It and, in the workgroups behind its own, the LayerNorm forward of other rows of the same width: the two chains of a small stack
-// side by side (rev_stack.hip).
+// side by side (rev_stack.hip).  197 rows of 768: 4.6 and 4.5 us by themselves, 4.8 together.
 template <typename TA, typename TP, int MAXJ>
 __global__ __launch_bounds__(512) void ln_pair_kernel(LnBwdCall<TA, TP> b, LnFwdCall<TA, TP> f, int M, int D, int bwd_blocks) {
     if ((int)blockIdx.x < bwd_blocks) ln_bwd_small_rows<TA, TP, MAXJ>(b.dn, b.x, b.stats, b.g, b.r, b.out, b.outb, b.partial, M, D, blockIdx.x);
