@@ -316,7 +316,7 @@ struct WgradPlan {
     bool big;
     int tile, S, sps;                 // 64x64, 128x128, 256x128: token ranges and steps per range
     int tiles, full, splits, stages, stages_per_split;   // 256x256
-    int tile_blocks;
+    int tile_blocks, blocks128;       // workgroups, and those that 128x128 tiles would have over the same ranges
     int64_t piece_elems, elems;       // floats of scratch: the pieces, and with the column sums' chunks
 };
 // Column sums of n columns behind `blocks` tile workgroups of `steps` stages each: as many workgroups as the last round of
@@ -340,6 +340,16 @@ static WgradSums sums_plan(int M, int n, int blocks, int steps, bool big, bool o
     p.rows = (M + p.chunks - 1) / p.chunks;
     p.chunks = (M + p.rows - 1) / p.rows;
     return p;
+}
+// Column sums of n columns under a plan.  Those behind 256x128 tiles take no more chunks than behind 128x128 ones, so that the choice
+// between the two never asks for more scratch; that is still enough chunks to end with the tiles, for it is at least the 128x128
+// tiles' `least`, which is larger.
+static WgradSums sums_of(const WgradPlan& p, int M, int n) {
+    if (p.big) return sums_plan(M, n, p.tile_blocks, p.stages_per_split, true, true);
+    const WgradSums q = sums_plan(M, n, p.tile_blocks, p.sps, false, p.tile == 256);
+    if (p.tile != 256) return q;
+    const WgradSums cap = sums_plan(M, n, p.blocks128, p.sps, false, false);
+    return q.chunks > cap.chunks ? cap : q;
 }
 static WgradPlan wgrad_plan(int M, const int* N, const int* K, int count) {
     WgradPlan p = {};
@@ -383,9 +393,10 @@ static WgradPlan wgrad_plan(int M, const int* N, const int* K, int count) {
     p.big = !few && M >= 64 && large < 0.95 * small;
     p.tile = few ? 64 : p.sps >= 40 && t256x128 * p.S <= 256 && t256x128 * p.S >= 180 && t256x128 * 5 <= t128 * 3 ? 256 : 128;
     p.piece_elems = p.big ? (p.splits > 1 ? (int64_t)rem * p.splits * 65536 : 0) : (p.S > 1 ? p.S * nk : 0);
+    p.blocks128 = t128 * p.S;
     if (!p.big) p.tile_blocks = (p.tile == 64 ? t64 : p.tile == 256 ? t256x128 : t128) * p.S;
     p.elems = p.piece_elems;
-    for (int k = 0; k < count; ++k) p.elems += (int64_t)sums_plan(M, N[k], p.tile_blocks, p.big ? p.stages_per_split : p.sps, p.big, p.big || p.tile == 256).chunks * N[k];
+    for (int k = 0; k < count; ++k) p.elems += (int64_t)sums_of(p, M, N[k]).chunks * N[k];
     return p;
 }
 int64_t wgrad_scratch_elems(int M, const int* N, const int* K, int count) { return wgrad_plan(M, N, K, count).elems; }
@@ -475,7 +486,7 @@ int gemm_wgrad_bf16_group(hipStream_t s, const WgradItem* items, int count, int 
         if (items[k].colsum) {
             if (nsums == WGRAD_SUMS_MAX) { set_error("gemm_wgrad_bf16: too many column sums"); return REV_EINVAL; }
             WgradSums& q = sums[nsums++];
-            q = sums_plan(M, N[k], pl.tile_blocks, pl.big ? pl.stages_per_split : pl.sps, pl.big, pl.big || pl.tile == 256);
+            q = sums_of(pl, M, N[k]);
             q.g = items[k].G; q.ld = items[k].ldg; q.total = items[k].colsum; q.block0 = sum_blocks;
             q.out = pl.big || q.chunks > 1 ? sums_scratch : q.total;
             sums_scratch += (int64_t)q.chunks * q.n;

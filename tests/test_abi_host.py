@@ -67,6 +67,28 @@ def test_workspace_sizes_of_the_two_schedules(name):
     assert full - small == extra and small % 256 == 0
 
 
+# Workspaces that callers have sized already stay large enough: (width, heads, hidden, tokens, samples) with the bytes that sufficed
+# for the two schedules, and (images, grid, grid, window, width, fusion) with those of the transition, at shapes whose weight
+# gradients take 256x128 tiles, which leave other numbers of workgroups for the column sums than the 128x128 tiles before them.
+SIZED = [((1040, 13, 1032, 142, 39), 594377728, 398440960), ((880, 110, 2480, 512, 5), 285307904, 182969344),
+         ((896, 28, 2456, 35, 92), 359415808, 230769920), ((640, 10, 616, 7, 1261), 604846592, 413547520),
+         ((360, 3, 1440, 718, 14), 526240512, 337783808), ((384, 6, 1536, 198, 52), 576509440, 370506752)]
+SIZED_MERGES = [((19, 36, 40, 1, 672, "average"), 139302912), ((43, 42, 42, 7, 648, "mlp"), 1044309760),
+                ((16, 12, 52, 2, 848, "mlp"), 195677952)]
+
+
+@pytest.mark.parametrize("shape,full,small", SIZED)
+def test_workspaces_that_sufficed_suffice(shape, full, small):
+    D, H, Dm, T, b = shape
+    c = B.make_cfg(n_blocks=2, d_model=D, n_heads=H, d_mlp=Dm, seq_len=T, batch=b, mode="bf16")
+    assert B.rev_stack_workspace_bytes(c) <= full and B.rev_stack_workspace_bytes_reprop(c) <= small
+
+
+@pytest.mark.parametrize("shape,size", SIZED_MERGES)
+def test_transition_workspaces_that_sufficed_suffice(shape, size):
+    assert B.rev_merge_workspace_bytes(B.make_merge_cfg(*shape[:5], "bf16", fusion=shape[5])) <= size
+
+
 def test_bad_configs_are_rejected():
     good = dict(synth.CONFIGS["tiny"])
     assert B.rev_stack_check_cfg(B.make_cfg(**good)) == 0
