@@ -252,11 +252,12 @@ static bool apart_side_by_side_is_faster(const rev_cfg& c, bool two_streams) {
     return forward_flops(c) < (two_streams ? (bf ? 2e9 : 5e8) : (bf ? 8e9 : 1.2e10));
 }
 // Both schedules and any number of blocks must sum the weight gradients in as many pieces: where two streams would be taken, only what
-// they sum in one.
+// they sum in one.  A single block has nothing to put side by side, but goes in one stream all the same where the weight gradients
+// ride, which costs it nothing: 1000 rows of 512, two streams and two pieces / one stream, 159 / 149 us, of 256 124 / 120.
 static bool blocks_ride(const rev_cfg& c) {
     const int M = c.batch * c.seq_len, D = c.d_model, Dm = c.d_mlp;
     const int nn[4] = {D, Dm, D, 3 * D}, kk[4] = {Dm, D, D, D};
-    return c.mode == REV_MODE_BF16 ? gemm_wgrad_bf16_together(M, nn, kk, 4, c.n_blocks == 1 || !side_by_side_is_faster(c)) : gemm_wgrad_f32_together(M, D, nn, kk, 4);
+    return c.mode == REV_MODE_BF16 ? gemm_wgrad_bf16_together(M, nn, kk, 4, !side_by_side_is_faster(c)) : gemm_wgrad_f32_together(M, D, nn, kk, 4);
 }
 
 template <typename T>
@@ -478,7 +479,7 @@ struct Runner {
     //    2.0e8      1240 / 1043      1418 / 1241        657 / 465      796 / 618
     // From 8e7 on two streams win on both, where the chains cannot be issued side by side on one.  Same kernels in the same order, so
     // the same results.
-    bool one_stream_is_faster() const { return forward_flops(c) < 8e7 || (c.n_blocks > 1 && (all_ride() ? side_by_side_is_faster(c) : apart_side_by_side_is_faster(c, true))); }
+    bool one_stream_is_faster() const { return forward_flops(c) < 8e7 || (all_ride() ? side_by_side_is_faster(c) : c.n_blocks > 1 && apart_side_by_side_is_faster(c, true)); }
 
     // residual level `lvl` (0..N): stream s1/s2 pointers
     struct Ptrs { const float* in1; const float* in2; float* out1; float* out2; };

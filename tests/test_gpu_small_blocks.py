@@ -43,3 +43,22 @@ def test_one_launch_or_several(mode, width, heads, hidden, tokens, batch):
         assert torch.equal(rep[k], par[k]) and torch.equal(rep[k], again[k]), k
     ref = O.stack_backward_reversible_chunked(x.astype(np.float64), x[:, ::-1].astype(np.float64), blocks, heads, dy1, dy2, chunk=8)
     compare_backward(cfg, rep, ref, TOL[mode], what=str(cfg))
+
+
+# 1000 rows of 512: weight gradients that a launch of their own would sum in two ranges, in one piece for any number of blocks
+@pytest.mark.parametrize("mode,width,heads,hidden,tokens,batch", [
+    ("bf16", 512, 8, 2048, 250, 4), ("bf16", 768, 12, 3072, 197, 1), ("bf16", 136, 17, 520, 41, 25), ("fp32", 136, 17, 520, 32, 32)])
+def test_a_block_has_the_same_gradients_in_a_stack_of_any_depth(mode, width, heads, hidden, tokens, batch):
+    cfg = dict(n_blocks=3, d_model=width, n_heads=heads, d_mlp=hidden, seq_len=tokens, batch=batch, mode=mode)
+    print(f"[case] {cfg}", flush=True)
+    flat, _, x, dy1, dy2 = make_case(cfg, seed=37)
+    deep, one = gpu_cfg(cfg), gpu_cfg(dict(cfg, n_blocks=1))
+    params = to_dev(flat, B.param_dtype(deep))
+    per = B.rev_stack_param_count(one)
+    args = [to_dev(a) for a in (x, x[:, ::-1].copy(), dy1, dy2)]
+    top = params[-per:].clone()
+    ref = B.rev_stack_backward_reprop(deep, params, *args)["dparams"][-per:]
+    rep = B.rev_stack_backward_reprop(one, top, *args)["dparams"]
+    par = B.rev_stack_backward_pareprop(one, top, *args, torch.cuda.Stream())["dparams"]
+    torch.cuda.synchronize()
+    assert torch.equal(rep, ref) and torch.equal(par, ref)
