@@ -127,6 +127,15 @@ int64_t rev_stack_workspace_bytes(const rev_cfg* cfg);
  * Host only. */
 int64_t rev_stack_workspace_bytes_reprop(const rev_cfg* cfg);
 
+/* How a backward call issues the two chains of its blocks with a workspace of
+ * that many bytes (pareprop: 0 for the sequential schedule, 1 for the parallel
+ * one): in turn on one stream, side by side on one stream, or on two streams.
+ * The same results bit for bit.  Host only. */
+#define REV_ORDER_IN_TURN      0
+#define REV_ORDER_SIDE_BY_SIDE 1
+#define REV_ORDER_TWO_STREAMS  2
+int rev_stack_backward_order(const rev_cfg* cfg, int32_t pareprop, int64_t workspace_bytes);
+
 /* Bytes of one activation slot: the intermediates of ONE block that a gradient
  * step consumes (normalised inputs, QKV, attention output and row statistics,
  * MLP pre-activation and activation).  Backpropagation without recomputation

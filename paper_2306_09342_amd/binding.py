@@ -18,10 +18,11 @@ LIB_PATH = os.path.join(_HERE, "librevstack.so")
 REV_MODE_FP32 = 0
 REV_MODE_BF16 = 1
 MODES = {"fp32": REV_MODE_FP32, "bf16": REV_MODE_BF16}
+REV_ORDER_IN_TURN, REV_ORDER_SIDE_BY_SIDE, REV_ORDER_TWO_STREAMS = 0, 1, 2
 
 EXPORTS = (
     "rev_stack_check_cfg", "rev_stack_param_count", "rev_stack_param_offset", "rev_stack_workspace_bytes",
-    "rev_stack_workspace_bytes_reprop", "rev_stack_slot_bytes",
+    "rev_stack_workspace_bytes_reprop", "rev_stack_slot_bytes", "rev_stack_backward_order",
     "rev_stack_forward", "rev_stack_backward_reprop", "rev_stack_backward_pareprop", "rev_stack_backward_chain",
     "rev_stack_backward_reprop_static",
     "rev_stack_forward_masked", "rev_stack_backward_reprop_masked", "rev_stack_backward_pareprop_masked",
@@ -69,6 +70,8 @@ def lib():
         for n in ("rev_stack_workspace_bytes", "rev_stack_workspace_bytes_reprop", "rev_stack_slot_bytes"):
             getattr(L, n).argtypes = [cp]
             getattr(L, n).restype = i64
+        L.rev_stack_backward_order.argtypes = [cp, i32, i64]
+        L.rev_stack_backward_order.restype = ctypes.c_int
         L.rev_stack_forward.argtypes = [cp, vp, vp, vp, vp, vp, vp, i64, vp]
         L.rev_stack_forward.restype = ctypes.c_int
         bw = [cp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, i64]
@@ -157,6 +160,10 @@ def rev_stack_workspace_bytes_reprop(cfg: RevCfg) -> int:
 
 def rev_stack_slot_bytes(cfg: RevCfg) -> int:
     return _check(lib().rev_stack_slot_bytes(ctypes.byref(cfg)))
+
+
+def rev_stack_backward_order(cfg: RevCfg, pareprop: bool, workspace_bytes: int) -> int:
+    return _check(lib().rev_stack_backward_order(ctypes.byref(cfg), int(pareprop), workspace_bytes))
 
 
 def param_dtype(cfg: RevCfg):

@@ -226,6 +226,9 @@ static int gemm_nt(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int
     return gemm_nt_bf16(s, A, lda, B, ldb, M, N, K, e);
 }
 
+// How a backward call issues the two chains of its blocks.
+enum Order { IN_TURN = REV_ORDER_IN_TURN, SIDE_BY_SIDE = REV_ORDER_SIDE_BY_SIDE, TWO_STREAMS = REV_ORDER_TWO_STREAMS };
+
 static double forward_flops(const rev_cfg& c) {               // of a block
     const double M = (double)c.batch * c.seq_len, D = c.d_model;
     return 2.0 * M * D * (4.0 * D + 2.0 * c.d_mlp) + 4.0 * M * c.seq_len * D;
@@ -260,6 +263,29 @@ static bool blocks_ride(const rev_cfg& c) {
     return c.mode == REV_MODE_BF16 ? gemm_wgrad_bf16_together(M, nn, kk, 4, !side_by_side_is_faster(c)) : gemm_wgrad_f32_together(M, D, nn, kk, 4);
 }
 
+// Two streams cost the host three events and three waits per block, so where the line lies depends on the host's speed.
+// Measured (us a call, one stream / two, calls back to back) on a slow host, 12 blocks, and on a fast one, 6 blocks, by FLOP
+// of a block's forward:
+//              slow: bf16         float32         fast: bf16      float32
+//    6.6e6       769 / 1018       848 / 1249        450 / 443      537 / 478
+//    2.9e7      1047 / 1006      1142 / 1262        538 / 453      616 / 500
+//    5.5e7      1039 / 1010      1164 / 1241        522 / 435      608 / 503
+//    9.7e7      1202 /  976      1296 / 1270        635 / 460      724 / 546
+//    2.0e8      1240 / 1043      1418 / 1241        657 / 465      796 / 618
+// From 8e7 on two streams win on both, where the chains cannot be issued side by side on one.  Same kernels in the same order, so
+// the same results under every order.
+// A sequential pass takes the layout of the parallel one where the workspace holds it and the blocks are small, for it issues both chains
+// side by side then.  schedule: 0 = Reprop, 1 = PaReprop, others: one chain alone
+static Order issue_order(const rev_cfg& c, int schedule, int64_t ws_bytes) {
+    if (schedule > 1) return IN_TURN;
+    const bool ride = blocks_ride(c), several = c.n_blocks > 1;
+    if (schedule == 0)
+        return several && (ride || apart_side_by_side_is_faster(c, false)) && ws_bytes >= make_layout(c, false).total ? SIDE_BY_SIDE : IN_TURN;
+    if (forward_flops(c) < 8e7 || (ride ? side_by_side_is_faster(c) : several && apart_side_by_side_is_faster(c, true)))
+        return several ? SIDE_BY_SIDE : IN_TURN;
+    return TWO_STREAMS;
+}
+
 template <typename T>
 struct Runner {
     static constexpr bool kBf16 = sizeof(T) == 2;
@@ -270,11 +296,11 @@ struct Runner {
     float* dparams;
     int M, D, Dm, H, dh, B, Tn;
     bool solo;      // one stream: every kernel has the device to itself
-    bool side_by_side;   // one stream, in the layout of two: small blocks issue the two chains side by side
+    Order order;
     const int* key_len = nullptr;   // optional key-padding mask: valid keys per sample (device, [batch])
 
-    Runner(const rev_cfg& cfg, const void* p, float* dp, void* w, bool compact, bool one_stream)
-        : c(cfg), L(make_layout(cfg, compact)), ws((char*)w), params((const T*)p), dparams(dp), solo(one_stream), side_by_side(!compact) {
+    Runner(const rev_cfg& cfg, const void* p, float* dp, void* w, bool compact, bool one_stream, Order o)
+        : c(cfg), L(make_layout(cfg, compact)), ws((char*)w), params((const T*)p), dparams(dp), solo(one_stream), order(o) {
         M = c.batch * c.seq_len; D = c.d_model; Dm = c.d_mlp; H = c.n_heads; dh = D / H; B = c.batch; Tn = c.seq_len;
     }
     Epi epi0() const { Epi e = {}; e.solo = solo; return e; }
@@ -468,19 +494,6 @@ struct Runner {
         else return gemm_wgrad_f32_group(s, w.p, 4, M);
     }
 
-    // Two streams cost the host three events and three waits per block, so where the line lies depends on the host's speed.
-    // Measured (us a call, one stream / two, calls back to back) on a slow host, 12 blocks, and on a fast one, 6 blocks, by FLOP
-    // of a block's forward:
-    //              slow: bf16         float32         fast: bf16      float32
-    //    6.6e6       769 / 1018       848 / 1249        450 / 443      537 / 478
-    //    2.9e7      1047 / 1006      1142 / 1262        538 / 453      616 / 500
-    //    5.5e7      1039 / 1010      1164 / 1241        522 / 435      608 / 503
-    //    9.7e7      1202 /  976      1296 / 1270        635 / 460      724 / 546
-    //    2.0e8      1240 / 1043      1418 / 1241        657 / 465      796 / 618
-    // From 8e7 on two streams win on both, where the chains cannot be issued side by side on one.  Same kernels in the same order, so
-    // the same results.
-    bool one_stream_is_faster() const { return forward_flops(c) < 8e7 || (all_ride() ? side_by_side_is_faster(c) : c.n_blocks > 1 && apart_side_by_side_is_faster(c, true)); }
-
     // residual level `lvl` (0..N): stream s1/s2 pointers
     struct Ptrs { const float* in1; const float* in2; float* out1; float* out2; };
     float* res(int lvl, int st, float* x_out1, float* x_out2) const {
@@ -512,7 +525,7 @@ struct Runner {
         EventLease lease;
         std::vector<hipEvent_t>& ev = lease.ev;
         auto E = [&](int i, int k) { return ev[(i - 1) * EPB + k]; };
-        const bool two = schedule == 1 && !one_stream_is_faster();
+        const bool two = order == TWO_STREAMS;
         const bool together = !two && all_ride();
         const int per = two ? EPB * N : 0;
         const hipStream_t sv_caller = sv;
@@ -584,9 +597,9 @@ struct Runner {
                 RC(reduce(sr, wsegs, &nw));
                 if (!kBf16 && i > 1) REV_HIP(hipEventRecord(E(i, E_W), sr));
             }
-        } else if (side_by_side && doR && doV) {
+        } else if (order == SIDE_BY_SIDE) {
             RC(run_R(N));
-            if (N > 1) RC(run(sv, ln2(N - 2, res(N - 1, 0, X1o, X2o), slot(N - 2))));
+            RC(run(sv, ln2(N - 2, res(N - 1, 0, X1o, X2o), slot(N - 2))));
             for (int i = N; i >= 1; --i) {
                 const Below below = {res(i - 1, 0, X1o, X2o), res(i - 1, 1, X1o, X2o), i > 1 ? res(i - 2, 0, X1o, X2o) : nullptr,
                                      i > 1 ? res(i - 2, 1, X1o, X2o) : nullptr};
@@ -657,15 +670,14 @@ static int backward_entry(int schedule, const rev_cfg* cfg, const void* params, 
     }
     if (schedule == 1 && sv == sr) { set_error("PaReprop needs two different streams"); return REV_EINVAL; }
     if (((uintptr_t)key_len & 3) != 0) { set_error("key_len must be 4-byte aligned"); return REV_EINVAL; }
-    // A sequential pass takes the layout of the parallel one where it fits and the blocks are small, for it issues both chains side
-    // by side then.
-    const bool small = compact && !(ws_bytes >= make_layout(*cfg, false).total && (blocks_ride(*cfg) || apart_side_by_side_is_faster(*cfg, false)));
+    const Order order = issue_order(*cfg, schedule, ws_bytes);
+    const bool one_slot = compact && order == IN_TURN;
     if (cfg->mode == REV_MODE_BF16) {
-        Runner<bf16> r(*cfg, params, dparams, ws, small, compact);
+        Runner<bf16> r(*cfg, params, dparams, ws, one_slot, compact, order);
         r.key_len = key_len;
         return r.backward(schedule, Y1, Y2, dY1, dY2, dX1, dX2, X1o, X2o, (hipStream_t)sv, (hipStream_t)sr);
     }
-    Runner<float> r(*cfg, params, dparams, ws, small, compact);
+    Runner<float> r(*cfg, params, dparams, ws, one_slot, compact, order);
     r.key_len = key_len;
     return r.backward(schedule, Y1, Y2, dY1, dY2, dX1, dX2, X1o, X2o, (hipStream_t)sv, (hipStream_t)sr);
 }
@@ -739,6 +751,12 @@ int64_t rev_stack_slot_bytes(const rev_cfg* cfg) {
     return make_layout(*cfg, true).slot_bytes;
 }
 
+int rev_stack_backward_order(const rev_cfg* cfg, int32_t pareprop, int64_t ws_bytes) {
+    RC(check_cfg(cfg));
+    if (ws_bytes < make_layout(*cfg, !pareprop).total) { set_error("backward_order: workspace too small"); return REV_EWORKSPACE; }
+    return issue_order(*cfg, pareprop ? 1 : 0, ws_bytes);
+}
+
 static int forward_entry(const rev_cfg* cfg, const void* params, const float* X1, const float* X2, float* Y1, float* Y2,
                          void* ws, int64_t ws_bytes, void* stream, const int32_t* key_len) {
     RC(check_common(cfg, ws, ws_bytes, true));
@@ -748,11 +766,11 @@ static int forward_entry(const rev_cfg* cfg, const void* params, const float* X1
     }
     if (((uintptr_t)key_len & 3) != 0) { set_error("key_len must be 4-byte aligned"); return REV_EINVAL; }
     if (cfg->mode == REV_MODE_BF16) {
-        Runner<bf16> r(*cfg, params, nullptr, ws, true, true);
+        Runner<bf16> r(*cfg, params, nullptr, ws, true, true, IN_TURN);
         r.key_len = key_len;
         return r.forward(X1, X2, Y1, Y2, (hipStream_t)stream);
     }
-    Runner<float> r(*cfg, params, nullptr, ws, true, true);
+    Runner<float> r(*cfg, params, nullptr, ws, true, true, IN_TURN);
     r.key_len = key_len;
     return r.forward(X1, X2, Y1, Y2, (hipStream_t)stream);
 }

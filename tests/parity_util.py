@@ -44,11 +44,10 @@ def oracle_forward(cfg, blocks, x1, x2, chunk=8):
 
 
 def takes_two_streams(cfg):
-    """Whether a block has 8e7 FLOP forward: smaller ones never take two streams under the parallel schedule.  Larger ones do,
-    unless the chains of several blocks run side by side on one stream (up to 1024 rows and 8e9 FLOP, float32 2.2e9, or any rows and
-    2e9, float32 5e8); test_gpu_side_by_side.py has the cross-stream ordering of a stack that is larger than that."""
-    rows, D, Dm = cfg["batch"] * cfg["seq_len"], cfg["d_model"], cfg["d_mlp"]
-    return 2.0 * rows * D * (4.0 * D + 2.0 * Dm) + 4.0 * rows * cfg["seq_len"] * D >= 8e7
+    """Whether the parallel schedule issues this stack on both streams, as the library says.  Tests of the cross-stream
+    ordering assert it, so that they cannot become comparisons of two serial runs."""
+    c = gpu_cfg(cfg)
+    return B.rev_stack_backward_order(c, True, B.rev_stack_workspace_bytes(c)) == B.REV_ORDER_TWO_STREAMS
 
 
 def to_dev(a, dtype=torch.float32):

@@ -89,6 +89,28 @@ def test_transition_workspaces_that_sufficed_suffice(shape, size):
     assert B.rev_merge_workspace_bytes(B.make_merge_cfg(*shape[:5], "bf16", fusion=shape[5])) <= size
 
 
+def _orders(**cfg):
+    c = B.make_cfg(**cfg)
+    full, small = B.rev_stack_workspace_bytes(c), B.rev_stack_workspace_bytes_reprop(c)
+    assert B.rev_stack_backward_order(c, False, small) == B.REV_ORDER_IN_TURN
+    for pareprop, short in ((False, small - 1), (True, full - 1)):
+        with pytest.raises(B.RevError, match="workspace too small"):
+            B.rev_stack_backward_order(c, pareprop, short)
+    return B.rev_stack_backward_order(c, False, full), B.rev_stack_backward_order(c, True, full)
+
+
+def test_orders_of_the_two_chains():
+    """Reprop and PaReprop, with the workspace of two streams: small blocks side by side on one stream under both, larger ones on two
+    under PaReprop; a single block has nothing to put beside itself."""
+    base = dict(n_blocks=4, d_model=768, n_heads=12, d_mlp=3072, seq_len=197, mode="bf16")
+    turn, side, two = B.REV_ORDER_IN_TURN, B.REV_ORDER_SIDE_BY_SIDE, B.REV_ORDER_TWO_STREAMS
+    assert _orders(**base, batch=1) == (side, side)
+    assert _orders(**base, batch=4) == (side, two)
+    assert _orders(**base, batch=64) == (turn, two)
+    assert _orders(**dict(base, n_blocks=1), batch=1) == (turn, turn)
+    assert _orders(**dict(base, n_blocks=1), batch=64) == (turn, two)
+
+
 def test_bad_configs_are_rejected():
     good = dict(synth.CONFIGS["tiny"])
     assert B.rev_stack_check_cfg(B.make_cfg(**good)) == 0

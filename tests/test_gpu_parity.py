@@ -23,9 +23,11 @@ SHAPES = {
     "dh128_T1": dict(n_blocks=2, d_model=256, n_heads=2, d_mlp=264, seq_len=1, batch=5),
     "vit_s_slice": dict(n_blocks=3, d_model=384, n_heads=6, d_mlp=1536, seq_len=197, batch=3),
     "one_sample_T300": dict(n_blocks=1, d_model=64, n_heads=2, d_mlp=64, seq_len=300, batch=1),
-    # six blocks on two streams: every buffer that the streams hand each other is used again (in float32 mode a cotangent
-    # level, from the fourth block on)
+    # six blocks, side by side on one stream, and with more samples on two: every buffer that the chains or the streams hand
+    # each other is used again (in float32 mode a cotangent level, from the fourth block on)
     "six_blocks": dict(n_blocks=6, d_model=256, n_heads=4, d_mlp=1024, seq_len=197, batch=2),
+    "six_blocks_two_streams": dict(n_blocks=6, d_model=256, n_heads=4, d_mlp=1024, seq_len=197, batch=8),
+    "vit_s_two_streams": dict(n_blocks=3, d_model=384, n_heads=6, d_mlp=1536, seq_len=197, batch=6),
     # window-attention shaped stages (49 tokens, head_dim 32): narrow first stage, many-headed last stage
     "window_stage1": dict(n_blocks=2, d_model=96, n_heads=3, d_mlp=384, seq_len=49, batch=7),
     "window_stage4": dict(n_blocks=1, d_model=768, n_heads=24, d_mlp=3072, seq_len=49, batch=2),
@@ -83,8 +85,10 @@ def test_fp32_mode_matches_oracle(name):
 
 
 def test_shapes_of_several_blocks_lie_on_both_sides_of_the_two_stream_line():
-    several = {n: takes_two_streams(s) for n, s in SHAPES.items() if s["n_blocks"] > 1}
-    assert several["six_blocks"] and several["vit_s_slice"] and not several["tiny"], several
+    for mode in ("fp32", "bf16"):
+        several = {n: takes_two_streams(dict(s, mode=mode)) for n, s in SHAPES.items() if s["n_blocks"] > 1}
+        assert several["six_blocks_two_streams"] and several["vit_s_two_streams"], (mode, several)
+        assert not several["tiny"] and not several["six_blocks"], (mode, several)
 
 
 @pytest.mark.parametrize("name", list(SHAPES))
@@ -128,7 +132,7 @@ def test_paper_recipe_inputs_tiny_fp32():
 
 def test_outputs_do_not_depend_on_stale_workspace_or_repeat():
     """Two calls in a row on a workspace filled with NaN bytes give identical bits."""
-    cfg = dict(SHAPES["six_blocks"], mode="bf16")
+    cfg = dict(SHAPES["six_blocks_two_streams"], mode="bf16")
     assert takes_two_streams(cfg)
     flat, blocks, x, dy1, dy2 = make_case(cfg, seed=3)
     c = gpu_cfg(cfg)
@@ -194,7 +198,7 @@ def test_pareprop_call_can_be_captured_into_a_graph_and_replayed(mode):
     """The two-stream call enqueues only kernels and event waits, so a caller may capture it into a
     HIP graph (both streams join the capture through the call's own fork / join events).  Replays,
     with eager work and a scrambled workspace in between, reproduce the eager bits."""
-    cfg = dict(SHAPES["six_blocks"], mode=mode)
+    cfg = dict(SHAPES["six_blocks_two_streams"], mode=mode)
     assert takes_two_streams(cfg)
     flat, blocks, x, dy1, dy2 = make_case(cfg, seed=7)
     c = gpu_cfg(cfg)
@@ -273,7 +277,7 @@ def test_two_host_threads_issue_pareprop_calls_concurrently():
     at the same time (each call leases its own events): every result equals, bit for bit, what the same call
     returns when it is the only one in flight."""
     import threading
-    cfgs = [dict(SHAPES["six_blocks"], mode="bf16"), dict(SHAPES["vit_s_slice"], mode="bf16")]
+    cfgs = [dict(SHAPES["six_blocks_two_streams"], mode="bf16"), dict(SHAPES["vit_s_two_streams"], mode="bf16")]
     assert all(takes_two_streams(cfg) for cfg in cfgs)
     jobs = []
     for i, cfg in enumerate(cfgs):
@@ -317,7 +321,7 @@ def test_two_host_threads_issue_pareprop_calls_concurrently():
                 assert torch.equal(r[k], v), k
 
 
-@pytest.mark.parametrize("name", ["tiny", "vit_s_slice"])
+@pytest.mark.parametrize("name", ["tiny", "vit_s_two_streams"])
 def test_pareprop_keeps_its_order_with_work_on_the_recompute_stream(name):
     """The outputs Y1, Y2 are produced late on the recompute stream, and the recomputed inputs are read there right after the
     call; blocks small enough to be issued on one stream keep the same order as larger ones."""

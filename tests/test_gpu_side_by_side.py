@@ -9,7 +9,7 @@ import torch
 from oracle import rev_oracle as O
 from paper_2306_09342_amd import binding as B
 
-from parity_util import TOL, compare_backward, gpu_cfg, make_case, to_dev
+from parity_util import TOL, compare_backward, gpu_cfg, make_case, takes_two_streams, to_dev
 
 pytestmark = pytest.mark.gpu
 KEYS = ("dX1", "dX2", "X1", "X2", "dparams")
@@ -78,6 +78,7 @@ def test_side_by_side_or_in_turn(mode, blocks, width, heads, hidden, tokens, bat
 @pytest.mark.parametrize("mode", ["bf16", "fp32"])
 def test_two_streams_keep_their_order_under_capture_and_with_late_outputs(mode):
     cfg = dict(n_blocks=4, d_model=128, n_heads=2, d_mlp=512, seq_len=50, batch=160, mode=mode)
+    assert takes_two_streams(cfg)
     flat, _, x, dy1, dy2 = make_case(cfg, seed=29)
     c = gpu_cfg(cfg)
     params = to_dev(flat, B.param_dtype(c))
