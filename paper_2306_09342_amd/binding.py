@@ -170,20 +170,13 @@ def param_dtype(cfg: RevCfg):
     return torch.bfloat16 if cfg.mode == REV_MODE_BF16 else torch.float32
 
 
-def _small_blocks(cfg: RevCfg) -> bool:
-    """Stacks whose chains a sequential backward may run side by side (at least those: the lines are in csrc/rev_stack.hip)."""
-    rows, D = cfg.batch * cfg.seq_len, cfg.d_model
-    flops = 2.0 * rows * D * (4.0 * D + 2.0 * cfg.d_mlp) + 4.0 * rows * cfg.seq_len * D
-    return rows <= 1024 or flops < (8e9 if cfg.mode == REV_MODE_BF16 else 1.2e10)
-
-
-def alloc_workspace(cfg: RevCfg, device="cuda", reprop_only: bool = False) -> torch.Tensor:
-    """Workspace for every entry point, or with reprop_only for the sequential schedule and the forward map, which need
-    rev_stack_workspace_bytes_reprop.  Stacks of small blocks get rev_stack_workspace_bytes either way: in that the sequential
-    schedule runs their two chains side by side."""
-    n = rev_stack_workspace_bytes_reprop(cfg)
-    if not reprop_only or _small_blocks(cfg):
-        n = rev_stack_workspace_bytes(cfg)
+def alloc_workspace(cfg: RevCfg, device="cuda", reprop_only: bool = False, forward_only: bool = False) -> torch.Tensor:
+    """Workspace for every entry point (rev_stack_workspace_bytes); with reprop_only for the sequential schedule and the forward map,
+    with forward_only for the forward map alone.  Those two need rev_stack_workspace_bytes_reprop, and reprop_only gives the larger
+    size only to the stacks whose chains the sequential schedule runs side by side in it, up to 1.8 times as fast."""
+    n = rev_stack_workspace_bytes(cfg)
+    if forward_only or reprop_only and rev_stack_backward_order(cfg, False, n) == REV_ORDER_IN_TURN:
+        n = rev_stack_workspace_bytes_reprop(cfg)
     return torch.empty(n, dtype=torch.uint8, device=device)
 
 

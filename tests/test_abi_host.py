@@ -111,6 +111,22 @@ def test_orders_of_the_two_chains():
     assert _orders(**dict(base, n_blocks=1), batch=64) == (turn, two)
 
 
+def test_alloc_workspace_gives_the_larger_size_only_where_it_is_used():
+    base = dict(n_blocks=4, d_model=768, n_heads=12, d_mlp=3072, seq_len=197, batch=1, mode="bf16")
+
+    def size(cfg, **how):
+        c = B.make_cfg(**cfg)
+        n = B.alloc_workspace(c, device="cpu", **how).numel()
+        return {B.rev_stack_workspace_bytes(c): "two slots", B.rev_stack_workspace_bytes_reprop(c): "one slot"}[n]
+
+    assert size(base) == "two slots" and size(base, reprop_only=True) == "two slots"          # side by side
+    assert size(base, forward_only=True) == size(base, forward_only=True, reprop_only=True) == "one slot"
+    assert size(dict(base, n_blocks=1), reprop_only=True) == "one slot"                       # nothing to put side by side
+    # 1024 rows whose weight gradients take 256x256 tiles; rows beyond the lines
+    assert size(dict(base, d_model=4096, n_heads=64, d_mlp=16384, seq_len=1024), reprop_only=True) == "one slot"
+    assert size(dict(base, batch=64), reprop_only=True) == "one slot" and size(dict(base, batch=64)) == "two slots"
+
+
 def test_bad_configs_are_rejected():
     good = dict(synth.CONFIGS["tiny"])
     assert B.rev_stack_check_cfg(B.make_cfg(**good)) == 0
