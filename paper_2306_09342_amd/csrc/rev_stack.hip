@@ -244,15 +244,23 @@ static double forward_flops(const rev_cfg& c) {               // of a block
 //     D = 1280           706 / 547 / 598 (565)   914 / 736 / 720 (776)   1228 / 1045 / 995 (1090)
 //     float32, D = 256   440 / 293 / 412 (349)   476 / 340 / 429 (394)   554 / 444 / 511 (495)   702 / 567 / 658 (615)
 // So the parallel schedule takes two streams from about 8e9 FLOP of a block's forward on (float32: 2.2e9; beyond it too much of the
-// chip is busy).  Two to 24 blocks: the same lines.
-static bool side_by_side_is_faster(const rev_cfg& c) { return forward_flops(c) < (c.mode == REV_MODE_BF16 ? 8e9 : 2.2e9); }
+// chip is busy).  Two to 24 blocks: the same lines.  Rows of more than 1280 floats are too wide for the LayerNorm pair, and two streams are
+// faster from the first row on; just below, from 3e9 FLOP on.  Side by side with the fork and the join / two streams, us: D = 1280, 32
+// blocks, 50 rows (2e9) 3073 / 3223, 100 (4e9) 3725 / 3432, 128 3975 / 3685, 197 (8e9) 4095 / 4117; three blocks, D = 1216, 200 rows (7.3e9)
+// 417 / 428; D = 1344, 16 rows (7e8) 384 / 349, 150 (6.6e9) 470 / 415; D = 1536, 100 rows 543 / 479; D = 4096, 16 rows 1854 / 1742.
+static bool side_by_side_is_faster(const rev_cfg& c) {
+    if (c.mode != REV_MODE_BF16) return forward_flops(c) < 2.2e9;
+    return c.d_model <= 1280 && forward_flops(c) < (c.d_model <= 1216 ? 8e9 : 3e9);
+}
 // The same without the common launch of the weight gradients, beyond 1024 rows or 512 64x64 tiles of them.  Four blocks, us a call: one
 // stream, in turn / side by side / two streams.  bf16, D = 64: 1576 rows 281 / 233 / 364, 12608 423 / 396 / 518; D = 128: 3152 rows 366 / 308 /
 // 382, 6304 434 / 396 / 416, 12608 (6e9 FLOP) 578 / 581 / 528; D = 256: 3152 473 / 445 / 424; D = 512: 1576 (1e10) 559 / 534 / 478, 3152 (2e10)
-// 767 / 770 / 877.  float32, D = 64: 3152 464 / 402 / 570; D = 256: 1576 824 / 760 / 753; D = 384: 3152 (1.2e10) 2463 / 2424 / 2323.
+// 767 / 770 / 877.  float32, D = 64: 3152 464 / 402 / 570; D = 256: 1576 824 / 760 / 753; D = 384: 3152 (1.2e10) 2463 / 2424 / 2323; three
+// blocks of 16 rows, side by side / two streams: D = 512 331 / 361, D = 640 387 / 374, D = 768 437 / 430.
 static bool apart_side_by_side_is_faster(const rev_cfg& c, bool two_streams) {
     const bool bf = c.mode == REV_MODE_BF16;
-    return forward_flops(c) < (two_streams ? (bf ? 2e9 : 5e8) : (bf ? 8e9 : 1.2e10));
+    if (two_streams) return c.d_model <= (bf ? 1280 : 512) && forward_flops(c) < (bf ? 2e9 : 5e8);
+    return forward_flops(c) < (bf ? 8e9 : 1.2e10);
 }
 // Both schedules and any number of blocks must sum the weight gradients in as many pieces: where two streams would be taken, only what
 // they sum in one.  A single block has nothing to put side by side, but goes in one stream all the same where the weight gradients

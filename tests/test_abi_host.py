@@ -107,6 +107,11 @@ def test_orders_of_the_two_chains():
     assert _orders(**base, batch=1) == (side, side)
     assert _orders(**base, batch=4) == (side, two)
     assert _orders(**base, batch=64) == (turn, two)
+    # rows of more than 1280 floats have no LayerNorm pair: two streams from the first row on, just below from 3e9 FLOP on
+    wide = lambda D, T, mode="bf16": _orders(n_blocks=4, d_model=D, n_heads=D // 64, d_mlp=4 * D, seq_len=T, batch=1, mode=mode)
+    assert wide(1216, 200) == wide(1280, 50) == (side, side)
+    assert wide(1280, 100) == wide(1344, 16) == wide(1536, 100) == wide(1792, 100) == (side, two)
+    assert wide(512, 16, "fp32") == (side, side) and wide(640, 16, "fp32") == (side, two)
     assert _orders(**dict(base, n_blocks=1), batch=1) == (turn, turn)
     assert _orders(**dict(base, n_blocks=1), batch=64) == (turn, two)
 
