@@ -262,13 +262,23 @@ static bool apart_side_by_side_is_faster(const rev_cfg& c, bool two_streams) {
     if (two_streams) return c.d_model <= (bf ? 1280 : 512) && forward_flops(c) < (bf ? 2e9 : 5e8);
     return forward_flops(c) < (bf ? 8e9 : 1.2e10);
 }
+// Blocks of 4.5e7 to 1.3e8 weights, which the memory-side cache does not keep from pass to pass, and few rows: a launch of one product in
+// 32x32 tiles has as many loads under way as one of two products in the 64x64 tiles that hold both, and the chains take turns.  Three blocks, one
+// stream, in turn / side by side, us: D = 2048, 100 rows (1e10 FLOP) 692 / 735, 125 722 / 770, 150 (1.5e10) 821 / 827, 200 852 / 837; D = 2560, 16
+// rows 915 / 952, 50 962 / 1039, 75 (1.2e10) 1027 / 1068, 100 (1.6e10) 1186 / 1165; D = 3072, 50 rows 1178 / 1270, 75 (1.7e10) 1382 / 1356.  Smaller
+// and larger blocks: D = 1792, 16 rows 552 / 526, 100 609 / 616, 200 772 / 698; D = 3584, 16 rows 1600 / 1513, 50 1656 / 1617.
+static bool turns_are_faster(const rev_cfg& c) {
+    const double weights = (double)block_params(c);
+    return c.mode == REV_MODE_BF16 && weights > 4.5e7 && weights < 1.3e8 && forward_flops(c) < 1.4e10;
+}
 // Both schedules and any number of blocks must sum the weight gradients in as many pieces: where two streams would be taken, only what
 // they sum in one.  A single block has nothing to put side by side, but goes in one stream all the same where the weight gradients
 // ride, which costs it nothing: 1000 rows of 512, two streams and two pieces / one stream, 159 / 149 us, of 256 124 / 120.
 static bool blocks_ride(const rev_cfg& c) {
     const int M = c.batch * c.seq_len, D = c.d_model, Dm = c.d_mlp;
     const int nn[4] = {D, Dm, D, 3 * D}, kk[4] = {Dm, D, D, D};
-    return c.mode == REV_MODE_BF16 ? gemm_wgrad_bf16_together(M, nn, kk, 4, !side_by_side_is_faster(c)) : gemm_wgrad_f32_together(M, D, nn, kk, 4);
+    if (c.mode != REV_MODE_BF16) return gemm_wgrad_f32_together(M, D, nn, kk, 4);
+    return !turns_are_faster(c) && gemm_wgrad_bf16_together(M, nn, kk, 4, !side_by_side_is_faster(c));
 }
 
 // Two streams cost the host three events and three waits per block, so where the line lies depends on the host's speed.
@@ -288,7 +298,7 @@ static Order issue_order(const rev_cfg& c, int schedule, int64_t ws_bytes) {
     if (schedule > 1) return IN_TURN;
     const bool ride = blocks_ride(c), several = c.n_blocks > 1;
     if (schedule == 0)
-        return several && (ride || apart_side_by_side_is_faster(c, false)) && ws_bytes >= make_layout(c, false).total ? SIDE_BY_SIDE : IN_TURN;
+        return several && !turns_are_faster(c) && (ride || apart_side_by_side_is_faster(c, false)) && ws_bytes >= make_layout(c, false).total ? SIDE_BY_SIDE : IN_TURN;
     if (forward_flops(c) < 8e7 || (ride ? side_by_side_is_faster(c) : several && apart_side_by_side_is_faster(c, true)))
         return several ? SIDE_BY_SIDE : IN_TURN;
     return TWO_STREAMS;

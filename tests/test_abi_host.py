@@ -111,6 +111,9 @@ def test_orders_of_the_two_chains():
     wide = lambda D, T, mode="bf16": _orders(n_blocks=4, d_model=D, n_heads=D // 64, d_mlp=4 * D, seq_len=T, batch=1, mode=mode)
     assert wide(1216, 200) == wide(1280, 50) == (side, side)
     assert wide(1280, 100) == wide(1344, 16) == wide(1536, 100) == wide(1792, 100) == (side, two)
+    # weights beyond the memory-side cache and few rows: in turn
+    assert wide(2048, 100) == wide(2560, 50) == wide(3072, 16) == (turn, two)
+    assert wide(1792, 50) == wide(2048, 200) == wide(3072, 100) == wide(4096, 16) == (side, two)
     assert wide(512, 16, "fp32") == (side, side) and wide(640, 16, "fp32") == (side, two)
     assert _orders(**dict(base, n_blocks=1), batch=1) == (turn, turn)
     assert _orders(**dict(base, n_blocks=1), batch=64) == (turn, two)

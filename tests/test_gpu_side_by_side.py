@@ -28,6 +28,7 @@ CASES = [
     ("bf16", 3, 768, 12, 3072, 197, 1, False),
     ("bf16", 3, 512, 8, 2048, 250, 4, False),      # weight gradients in 128x128 tiles that two ranges would share; 1000 rows
     ("bf16", 2, 1288, 23, 2576, 20, 3, False),     # rows too wide for the LayerNorm pair
+    ("bf16", 2, 2048, 16, 8192, 9, 2, False),      # weights beyond the memory-side cache: in turn
     ("bf16", 2, 1024, 16, 4096, 100, 4, False),    # eight-wavefront tiles
     ("bf16", 3, 256, 4, 1024, 41, 25, False),      # 1025 rows: weight gradients in a launch of their own
     ("bf16", 3, 96, 3, 384, 49, 45, True),         # 2205 rows, attention of a launch per chain
