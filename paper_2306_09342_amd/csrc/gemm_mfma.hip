@@ -178,11 +178,15 @@ static GemmShape wide_shape(int M, int N, int K, const Epi& epi, double* us) {
 // contraction (and so do launches with column sums, whose tile is the same under both schedules): two-stream passes of four blocks, D = 1024, two-stage
 // tiles / these, us: 1024 rows 735 / 773, 1000 rows 795 / 825; one stream 848 / 842.  Longer contractions and fewer tiles gain all the same:
 // D = 1024, 3152 rows (200 tiles) 1602 / 1475; D = 1280, 3152 rows (250, K = 5120) 2361 / 2196.
+// So do 64x128 tiles where 64x64 ones would all run at once, two per CU, and the rows are few: passes of two streams, those / 64x64 tiles, us:
+// four blocks, D = 1280, 200 rows 588 / 574, D = 1536, 200 rows 751 / 715; 32 blocks, D = 1280, 197 rows 4299 / 4144, and one stream, side by side,
+// 3959 / 3854.  More rows gain from them all the same: four blocks, D = 1280, 400 rows 693 / 707, 500 728 / 757; D = 1536, 1000 rows 1322 / 1347.
 static GemmShape pick_gemm_shape(int M, int N, int K, const Epi& epi) {
     double ring_us, us;
     const bool brief = K < 640;
     const bool few = tiles_of(M, N, 32, 32) <= 288 || tiles_of(M, N, 64, 64) <= (K < 1536 ? 512 : 384);
     const GemmShape ring = ring_shape(M, N, K, epi.kind, brief, &ring_us);
+    if (few && ring == GS_64x128_RING && M <= 320 && (!epi.solo || epi.colsum)) return GS_64x64;
     if (few) return ring;
     if (brief && tiles_of(M, N, 64, 128) <= 256) return GS_64x128_RING;
     const GemmShape wide = wide_shape(M, N, K, epi, &us);
