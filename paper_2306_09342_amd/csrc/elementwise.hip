@@ -9,6 +9,14 @@
 
 namespace rev {
 
+// A chunk's products, with the rounding spelled out: left to the compiler, which products it fuses into the sums behind them changes
+// from kernel to kernel, and a row must have the same bits in all of them.
+__device__ __forceinline__ f4 mul4(const f4& a, const f4& b) {
+#pragma clang fp contract(off)
+    return {a.x * b.x, a.y * b.y, a.z * b.z, a.w * b.w};
+}
+__device__ __forceinline__ float dot4(const f4& a, const f4& b) { return fmaf(a.x, b.x, a.y * b.y) + fmaf(a.z, b.z, a.w * b.w); }
+
 // ---- LayerNorm forward -----------------------------------------------------------
 // LPR lanes hold a row: lane l of them the 4-element chunks l, l + LPR, ... (MAXJ of them).  Rows of up to 256 floats share a
 // wavefront (pick_row), wider ones have it to themselves.  Every lane handles two rows, half of all rows apart and both
@@ -48,11 +56,9 @@ __device__ __forceinline__ void ln_fwd_rows(const float* __restrict__ x, const T
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
             int c = lane + LPR * j;
-            q[j] = 0.f;
-            if (c < nch) {
-                float a0 = v[k][j].x - mean, a1 = v[k][j].y - mean, a2 = v[k][j].z - mean, a3 = v[k][j].w - mean;
-                q[j] = (a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3);
-            }
+            const f4 a = {v[k][j].x - mean, v[k][j].y - mean, v[k][j].z - mean, v[k][j].w - mean};
+            const float d = dot4(a, a);
+            q[j] = c < nch ? d : 0.f;
         }
         const float rstd = 1.0f / sqrtf(row_sum<LPR, MAXJ>(q) / (float)D + eps);
         TA* yr = y + (int64_t)rows[k] * D;
@@ -128,14 +134,6 @@ static int ln_bwd_rows_per_block(int M, int D) {
     if (ln_bwd_shares(M, D)) rpb = (rpb + 31) / 32 * 32;
     return rpb;
 }
-
-// A chunk's products, with the rounding spelled out: left to the compiler, which products it fuses into the sums behind them changes
-// from kernel to kernel, and a row must have the same bits in all of them.
-__device__ __forceinline__ f4 mul4(const f4& a, const f4& b) {
-#pragma clang fp contract(off)
-    return {a.x * b.x, a.y * b.y, a.z * b.z, a.w * b.w};
-}
-__device__ __forceinline__ float dot4(const f4& a, const f4& b) { return fmaf(a.x, b.x, a.y * b.y) + fmaf(a.z, b.z, a.w * b.w); }
 
 // Rows of 1024 floats and more (4+ register chunks per lane): the three column accumulators of a
 // wavefront live in its own slice of LDS instead of registers (lane-private slots, no synchronisation),
