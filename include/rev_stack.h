@@ -352,7 +352,10 @@ int rev_merge_backward(const rev_merge_cfg* cfg, const void* params,
  * recording.  rev_profile_get() returns, for family `kind` (0 <=
  * kind < rev_profile_kinds()), its name, total milliseconds, launch count and
  * the algorithmic work of those launches (flops for matrix-core families, HBM
- * bytes for the others; see rev_profile_is_flops).  Totals accumulate until
+ * bytes for the others; see rev_profile_is_flops).  The launches of small blocks
+ * that hold the work of several families are families of their own: "mixed"
+ * (products and attention, with column sums and second stages of sums beside
+ * them) and "ln_pair" (LayerNorm backward and forward).  Totals accumulate until
  * rev_profile_begin() is called again.  Not thread safe. */
 int         rev_profile_begin(void);
 int         rev_profile_end(void);

@@ -942,7 +942,7 @@ int attention_backward_wgrad(hipStream_t s, const bf16* qkv, const bf16* o, cons
     WgradTail w;
     double flops = (beside ? 12.0 : 8.0) * B * H * (double)T * T * dh;
     if (int rc = gemm_wgrad_bf16_beside(items, count, B * T, &w, &flops)) return rc;
-    ProfScope ps(K_ATTN_BWD, s, flops);
+    ProfScope ps(K_MIXED, s, flops);
     if (dh == 32) return bwd_wgrad_dma<32>(s, a, B, w, beside);
     if (dh == 64) return bwd_wgrad_dma<64>(s, a, B, w, beside);
     return bwd_wgrad_dma<80>(s, a, B, w, beside);

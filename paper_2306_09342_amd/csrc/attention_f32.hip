@@ -311,7 +311,7 @@ int attention_backward_f32(hipStream_t s, const T* qkv, const T* o, const T* dou
 }
 int attention_pair_f32(hipStream_t s, const float* qkv, const float* o, const float* dout, const float* lse, float* dqkv, int B, int T, int H,
                        int dh, const int* key_len, const AttnFwdCall<float>& fwd) {
-    ProfScope ps(K_ATTN_BWD, s, 12.0 * B * H * (double)T * T * dh);
+    ProfScope ps(K_MIXED, s, 12.0 * B * H * (double)T * T * dh);
     const dim3 grid((T + 31) / 32, B * H, 3), block(AF_NW * 64);
     switch ((dh + 31) / 32) {
 #define CASE(J) case J: {                                                                                                   \

@@ -48,6 +48,8 @@ enum Kind {
     K_REDUCE,        // fixed-order second stage of column sums / split reductions
     K_CONVERT,       // dtype conversion
     K_OPTIM,         // optimizer update
+    K_MIXED,         // launches of small blocks that hold products of several of the families above
+    K_LN_PAIR,       // LayerNorm backward of one block with LayerNorm forward of another
     K_COUNT
 };
 

@@ -438,7 +438,7 @@ int ln_pair(hipStream_t s, const LnBwdCall<TA, TP>& b, const LnFwdCall<TA, TP>& 
         return ln_forward<TA, TP>(s, f.x, f.g, f.b, f.eps, f.y, f.stats, M, D);
     }
     const int nblk = (M + 7) / 8;
-    ProfScope ps(K_LN_BWD, s, (double)M * D * (16 + sizeof(TA) * (b.outb ? 3 : 2)));
+    ProfScope ps(K_LN_PAIR, s, (double)M * D * (16 + sizeof(TA) * (b.outb ? 3 : 2)));
     const dim3 grid(nblk + ((M + 1) / 2 + 7) / 8), block(512);
     switch (pick_maxj(D)) {
 #define CASE(J) case J: {                                                                                              \

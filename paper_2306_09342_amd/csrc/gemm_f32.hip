@@ -411,9 +411,9 @@ int gemm_nn_wgrad_f32(hipStream_t s, const GemmCall<float>& nn, int M, const Wgr
     }
     WgradF32Beside w = {};
     bool wide;
-    double flops = 2.0 * M * nn.N * nn.K, bytes = 0;
+    double flops = 2.0 * M * nn.N * nn.K;
     if (int rc = wgrad_f32_args(items, count, M, &w.grp, &w.sums, &wide, &w.tile_blocks, &flops)) return rc;
-    const int red_blocks = reduce_args(segs, nseg, &w.red, &bytes);
+    const int red_blocks = reduce_args(segs, nseg, &w.red, nullptr);
     if (red_blocks < 0) return red_blocks;
     w.M = M;
     w.nn = f32_part_of(nn, M);
@@ -421,7 +421,7 @@ int gemm_nn_wgrad_f32(hipStream_t s, const GemmCall<float>& nn, int M, const Wgr
         w.nt = f32_part_of(*beside, M);
         flops += 2.0 * M * beside->N * beside->K;
     }
-    ProfScope ps(K_GEMM_WGRAD, s, flops);
+    ProfScope ps(K_MIXED, s, flops);
     static LdsLimit lim;
     if (int rc = lim.ensure(reinterpret_cast<const void*>(gemm_wgrad_f32_kernel), FCfg<1, 1>::SHMEM)) return rc;
     hipLaunchKernelGGL(gemm_wgrad_f32_kernel, dim3((unsigned)(w.nn.blocks + w.nt.blocks + w.tile_blocks + w.sums.blocks + red_blocks)),

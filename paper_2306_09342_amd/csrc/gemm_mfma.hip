@@ -466,7 +466,7 @@ int gemm_nn_wgrad_bf16(hipStream_t s, const GemmCall<bf16>& nn, int M, const Wgr
     WgradTail tail;
     double flops = 2.0 * M * ((double)nn.N * nn.K + (beside ? (double)beside->N * beside->K : 0.0)), us;
     if (int rc = gemm_wgrad_bf16_beside(items, count, M, &tail, &flops)) return rc;
-    ProfScope ps(K_GEMM_WGRAD, s, flops);
+    ProfScope ps(K_MIXED, s, flops);
     // 64x64 tiles from more than 32x32 ones hold at once
     const GemmShape shape = beside ? pair_shape(nn, *beside, M, true) : ring_shape(M, nn.N, nn.K, EPI_PLAIN, true, &us);
     return launch_gemm_wgrad(s, nn, M, tail, segs, nseg, shape, beside);

@@ -52,8 +52,7 @@ __global__ __launch_bounds__(256) void gemm_wgrad_kernel(WgradBeside w) {
 template <typename C>
 static int gemm_wgrad(hipStream_t s, const GemmCall<bf16>& nn, int M, const WgradTail& tail, const RedSeg* segs, int nseg, const GemmCall<bf16>* nt) {
     WgradBeside w = {};
-    double bytes = 0;
-    const int red_blocks = reduce_args(segs, nseg, &w.red, &bytes);
+    const int red_blocks = reduce_args(segs, nseg, &w.red, nullptr);
     if (red_blocks < 0) return red_blocks;
     w.t = tail;
     w.nn = ring_part_of<C>(nn, M);

@@ -31,8 +31,8 @@ static double g_prof_ms[K_COUNT];
 static int64_t g_prof_n[K_COUNT];
 static double g_prof_work[K_COUNT];
 static const char* g_kind_names[K_COUNT] = {"gemm_nt", "gemm_wgrad", "attn_fwd", "attn_bwd", "ln_fwd",
-                                            "ln_bwd", "colsum", "reduce", "convert", "optimizer"};
-static const int g_kind_flops[K_COUNT] = {1, 1, 1, 1, 0, 0, 0, 0, 0, 0};
+                                            "ln_bwd", "colsum", "reduce", "convert", "optimizer", "mixed", "ln_pair"};
+static const int g_kind_flops[K_COUNT] = {1, 1, 1, 1, 0, 0, 0, 0, 0, 0, 1, 0};
 
 bool profiling() { return g_prof_on; }
 

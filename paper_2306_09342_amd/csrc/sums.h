@@ -73,7 +73,7 @@ __device__ __forceinline__ void reduce_block(const RedArgs& a, int block, float4
     }
 }
 
-// Fills the device description; the number of workgroups, or an error.
+// Fills the device description; the number of workgroups, or an error.  bytes: nullable
 inline int reduce_args(const RedSeg* segs, int nseg, RedArgs* a, double* bytes) {
     if (nseg > RED_MAX_SEGS) { set_error("reduce_multi: too many segments"); return REV_EINVAL; }
     a->nseg = nseg;
@@ -84,7 +84,7 @@ inline int reduce_args(const RedSeg* segs, int nseg, RedArgs* a, double* bytes) 
         const int64_t n4 = g.n / 4;
         a->seg[k] = {g.partial, g.out, g.out2, g.stride, n4, g.split / 4, g.P, blocks};
         blocks += (int)(reduce_by_lanes(g.P, n4) ? (n4 + 15) / 16 : (n4 + 255) / 256);
-        *bytes += (double)(g.P + 1) * g.n * 4;
+        if (bytes) *bytes += (double)(g.P + 1) * g.n * 4;
     }
     return blocks;
 }

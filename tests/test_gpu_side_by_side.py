@@ -115,3 +115,33 @@ def test_two_streams_keep_their_order_under_capture_and_with_late_outputs(mode):
         for k in KEYS:
             assert torch.equal(out[k], ref[k]), (rep, k)
         assert torch.equal(eager["dparams"], ref["dparams"])
+
+
+# Launches of several families are families of their own, and hold what the others lose: the same products under every order
+@pytest.mark.parametrize("mode", ["bf16", "fp32"])
+def test_timed_families_hold_their_own_work_under_every_order(mode):
+    cfg = dict(n_blocks=3, d_model=128, n_heads=2, d_mlp=512, seq_len=50, batch=4, mode=mode)
+    flat, _, x, dy1, dy2 = make_case(cfg, seed=41)
+    c = gpu_cfg(cfg)
+    params = to_dev(flat, B.param_dtype(c))
+    args = [to_dev(a) for a in (x, x, dy1, dy2)]
+
+    def families(nbytes):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        B.rev_profile_begin()
+        B.rev_stack_backward_reprop(c, params, *args, workspace=ws)
+        return B.rev_profile_end()
+
+    turn, side = families(B.rev_stack_workspace_bytes_reprop(c)), families(B.rev_stack_workspace_bytes(c))
+    rows, D = cfg["batch"] * cfg["seq_len"], cfg["d_model"]
+    products = 2.0 * rows * D * (4 * D + 2 * cfg["d_mlp"])           # of a block's forward; its backward has twice as much
+    attention = 4.0 * rows * cfg["seq_len"] * D
+    for f in (turn, side):
+        assert sum(w for _, _, w, flops in f.values() if flops) == cfg["n_blocks"] * 3 * (products + attention)
+    assert [turn[k][1] for k in ("ln_fwd", "ln_bwd", "ln_pair")] == [6, 6, 0]
+    assert [side[k][1] for k in ("ln_fwd", "ln_bwd", "ln_pair")] == [3, 3, 3]
+    # in turn: the attention forward by itself; side by side only that of the top block, and the attention backward of the bottom one
+    # shares its launch with weight gradients (bf16)
+    assert turn["attn_fwd"][1:3] == (3, 3 * attention) and side["attn_fwd"][1:3] == (1, attention)
+    assert side["attn_bwd"][1:3] == ((0, 0.0) if mode == "bf16" else (1, 2 * attention))
+    assert turn["gemm_wgrad"][1] == side["gemm_wgrad"][1] == 0 and side["mixed"][1] == (6 if mode == "bf16" else 5)
