@@ -55,7 +55,7 @@ static const RingCost RING[] = {
     {GS_64x128_RING, 64, 128, 0, 256, {4.1, 4.9, 4.5, 5.4, 3.9, 4.2},  0.5, 0.207, 0.106},
     {GS_128x128_RING, 128, 128, 0, 256, {4.7, 6.3, 5.7, 7.1, 4.4, 5.0}, 1.2, 0.281, 0.223},
     {GS_192x128_RING, 192, 128, 0, 256, {5.1, 7.8, 6.7, 8.7, 4.8, 5.7}, 2.2, 0.389, 0.309}};
-// the cheapest of them (up to 64x64 tiles with small_only), GS_128x128 if none holds the launch
+// the cheapest of them (tiles of up to 64 rows with small_only), GS_128x128 if none holds the launch
 static GemmShape ring_shape(int M, int N, int K, int kind, bool small_only, double* us) {
     GemmShape best = GS_128x128;
     *us = 1e30;
@@ -167,7 +167,7 @@ static GemmShape wide_shape(int M, int N, int K, const Epi& epi, double* us) {
     *us = tall ? cost_160(tiles_of(M, N, 160, 128), st, epi.kind) : cost_128(tiles_of(M, N, 128, 128), st, epi.kind);
     return tall ? GS_160x128 : GS_128x128;
 }
-// Short contractions (K < 640), where a launch is mostly first loads and epilogue: tiles of up to 64x64 while their workgroups all
+// Short contractions (K < 640), where a launch is mostly first loads and epilogue: tiles of up to 64 rows while 64x64 ones would all
 // run at once, 64x128 up to one per CU, and two workgroups per CU from there on.  Longer ones: the cheapest tile of the ring where 64x64 tiles would
 // all run at once; beyond, if it undercuts the wide tiles by 3 %, for the fits are off by more than they differ below that.  us, the
 // tiles before (64x64 or 64x128 in the ring, 64x128 or 128x128 in two stages, 256x256) and the ring's: 1576 rows, N = 768, K = 3072, input
@@ -252,7 +252,7 @@ int gemm_nt_bf16(hipStream_t s, const bf16* A, int64_t lda, const bf16* B, int64
                  int M, int N, int K, const Epi& epi) {
     return gemm_bf16(s, A, lda, B, ldb, M, N, K, epi, false);
 }
-// The tile of two products in one launch: the cheapest of the ring for the workgroups of both together (up to 64x64 with
+// The tile of two products in one launch: the cheapest of the ring for the workgroups of both together (up to 64 rows with
 // small_only), GS_128x128 if none holds them.
 static GemmShape pair_shape(const GemmCall<bf16>& nn, const GemmCall<bf16>& nt, int M, bool small_only) {
     GemmShape best = GS_128x128;
@@ -467,7 +467,7 @@ int gemm_nn_wgrad_bf16(hipStream_t s, const GemmCall<bf16>& nn, int M, const Wgr
     double flops = 2.0 * M * ((double)nn.N * nn.K + (beside ? (double)beside->N * beside->K : 0.0)), us;
     if (int rc = gemm_wgrad_bf16_beside(items, count, M, &tail, &flops)) return rc;
     ProfScope ps(K_MIXED, s, flops);
-    // 64x64 tiles from more than 32x32 ones hold at once
+    // 64x64 tiles where 32x32 ones do not all run at once, or cost more
     const GemmShape shape = beside ? pair_shape(nn, *beside, M, true) : ring_shape(M, nn.N, nn.K, EPI_PLAIN, true, &us);
     return launch_gemm_wgrad(s, nn, M, tail, segs, nseg, shape, beside);
 }
