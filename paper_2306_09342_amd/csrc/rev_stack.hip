@@ -245,12 +245,13 @@ static double forward_flops(const rev_cfg& c) {               // of a block
 //     float32, D = 256   440 / 293 / 412 (349)   476 / 340 / 429 (394)   554 / 444 / 511 (495)   702 / 567 / 658 (615)
 // So the parallel schedule takes two streams from about 8e9 FLOP of a block's forward on (float32: 2.2e9; beyond it too much of the
 // chip is busy).  Two to 24 blocks: the same lines.  Rows of more than 1280 floats are too wide for the LayerNorm pair, and two streams are
-// faster from the first row on; just below, from 3e9 FLOP on.  Side by side with the fork and the join / two streams, us: D = 1280, 32
-// blocks, 50 rows (2e9) 3073 / 3223, 100 (4e9) 3725 / 3432, 128 3975 / 3685, 197 (8e9) 4095 / 4117; three blocks, D = 1216, 200 rows (7.3e9)
-// 417 / 428; D = 1344, 16 rows (7e8) 384 / 349, 150 (6.6e9) 470 / 415; D = 1536, 100 rows 543 / 479; D = 4096, 16 rows 1854 / 1742.
+// faster from the first row on; just below, from where 32x32 tiles no longer hold two products of that width (288 of them) on.  Side by side with
+// the fork and the join / two streams, us: D = 1280, 32 blocks, 50 rows 3073 / 3223, 100 3725 / 3432, 128 3975 / 3685, 197 (8e9 FLOP) 4095 / 4117;
+// 24 blocks, 77 rows (240 tiles) 2376 / 2533; D = 1248, 100 rows (312 tiles) 2828 / 2606; D = 1216, 197 rows 2820 / 2871; three blocks, D = 1344, 16 rows (7e8) 384 / 349, 150 (6.6e9) 470 / 415; D = 1536, 100 rows 543 / 479; D = 4096, 16 rows 1854 / 1742.
 static bool side_by_side_is_faster(const rev_cfg& c) {
     if (c.mode != REV_MODE_BF16) return forward_flops(c) < 2.2e9;
-    return c.d_model <= 1280 && forward_flops(c) < (c.d_model <= 1216 ? 8e9 : 3e9);
+    const int rows = c.batch * c.seq_len, pair_tiles = 2 * ((rows + 31) / 32) * ((c.d_model + 31) / 32);
+    return forward_flops(c) < 8e9 && c.d_model <= 1280 && (c.d_model <= 1216 || pair_tiles <= 288);
 }
 // The same without the common launch of the weight gradients, beyond 1024 rows or 512 64x64 tiles of them.  Four blocks, us a call: one
 // stream, in turn / side by side / two streams.  bf16, D = 64: 1576 rows 281 / 233 / 364, 12608 423 / 396 / 518; D = 128: 3152 rows 366 / 308 /

@@ -107,10 +107,11 @@ def test_orders_of_the_two_chains():
     assert _orders(**base, batch=1) == (side, side)
     assert _orders(**base, batch=4) == (side, two)
     assert _orders(**base, batch=64) == (turn, two)
-    # rows of more than 1280 floats have no LayerNorm pair: two streams from the first row on, just below from 3e9 FLOP on
-    wide = lambda D, T, mode="bf16": _orders(n_blocks=4, d_model=D, n_heads=D // 64, d_mlp=4 * D, seq_len=T, batch=1, mode=mode)
-    assert wide(1216, 200) == wide(1280, 50) == (side, side)
-    assert wide(1280, 100) == wide(1344, 16) == wide(1536, 100) == wide(1792, 100) == (side, two)
+    # rows of more than 1280 floats have no LayerNorm pair: two streams from the first row on, just below from where
+    # two products of that width are more than 288 tiles of 32x32
+    wide = lambda D, T, mode="bf16": _orders(n_blocks=4, d_model=D, n_heads=D // 32, d_mlp=4 * D, seq_len=T, batch=1, mode=mode)
+    assert wide(1216, 200) == wide(1280, 50) == wide(1280, 96) == (side, side)
+    assert wide(1280, 97) == wide(1248, 100) == wide(1344, 16) == wide(1536, 100) == wide(1792, 100) == (side, two)
     # weights beyond the memory-side cache and few rows: in turn
     assert wide(2048, 100) == wide(2560, 50) == wide(3072, 16) == (turn, two)
     assert wide(1792, 50) == wide(2048, 200) == wide(3072, 100) == wide(4096, 16) == (side, two)
