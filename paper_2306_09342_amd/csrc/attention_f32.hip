@@ -309,8 +309,16 @@ int attention_backward_f32(hipStream_t s, const T* qkv, const T* o, const T* dou
     REV_HIP(hipGetLastError());
     return REV_OK;
 }
+// One launch up to 768 workgroups of each pass.  Beyond, the forward's workgroups, which hold the LDS of the backward's there, have too few
+// beside them.  Two launches against one, 220 stacks of four blocks, geometric mean of the pass by workgroups of a pass: 257 to 384 0.96, 513 to
+// 768 0.98, 769 to 1024 1.01, 1537 to 2048 1.02, 2049 to 4096 1.03, more 1.04.
+constexpr int AF_PAIR_MOST = 768;
 int attention_pair_f32(hipStream_t s, const float* qkv, const float* o, const float* dout, const float* lse, float* dqkv, int B, int T, int H,
                        int dh, const int* key_len, const AttnFwdCall<float>& fwd) {
+    if ((int64_t)((T + 31) / 32) * B * H > AF_PAIR_MOST) {
+        if (int rc = attention_backward_f32<float>(s, qkv, o, dout, lse, dqkv, B, T, H, dh, key_len)) return rc;
+        return attention_forward_f32(s, fwd.qkv, fwd.o, fwd.lse, B, T, H, dh, key_len);
+    }
     ProfScope ps(K_MIXED, s, 12.0 * B * H * (double)T * T * dh);
     const dim3 grid((T + 31) / 32, B * H, 3), block(AF_NW * 64);
     switch ((dh + 31) / 32) {

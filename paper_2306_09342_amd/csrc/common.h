@@ -281,7 +281,7 @@ template <typename T> struct AttnFwdCall { const T* qkv; T* o; float* lse; };
 bool attention_takes_wgrad(int B, int T, int H, int dh);
 int attention_backward_wgrad(hipStream_t s, const bf16* qkv, const bf16* o, const bf16* dout, const float* lse, bf16* dqkv, int B, int T,
                              int H, int dh, const int* key_len, const WgradItem* items, int count, const AttnFwdCall<bf16>* beside = nullptr);
-// float32: the backward and the forward of the other chain in one launch
+// float32: the backward and the forward of the other chain, in one launch while both leave the chip idle
 int attention_pair_f32(hipStream_t s, const float* qkv, const float* o, const float* dout, const float* lse, float* dqkv, int B, int T, int H,
                        int dh, const int* key_len, const AttnFwdCall<float>& fwd);
 

@@ -35,6 +35,8 @@ CASES = [
     ("bf16", 2, 64, 1, 256, 60, 140, False),       # 8400 rows: beyond the LayerNorm pair
     ("fp32", 3, 512, 8, 1536, 33, 3, False),       # weight gradients of 640 tiles
     ("fp32", 3, 64, 2, 264, 43, 25, True),         # 1075 rows
+    ("fp32", 2, 64, 4, 128, 3, 192, False),        # 768 heads: the last whose attention goes in one launch
+    ("fp32", 2, 64, 4, 128, 3, 193, True),         # 772: apart
 ]
 
 
