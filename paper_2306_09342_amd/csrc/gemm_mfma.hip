@@ -174,10 +174,13 @@ static GemmShape wide_shape(int M, int N, int K, const Epi& epi, double* us) {
 // gradient: 23.2 / 16.6; 3152: 33.3 / 21.8; 7289: 42.8 / 35.1; 7289, N = 384, K = 1536: 19.6 / 13.7, residual 20.7 / 16.7; 3152, N = 384:
 // 15.7 / 11.1.  Of the 1760 launches 427 change tile, to 0.875 of the time in the mean; 11 are 4 to 9 % slower (M = 16384, N = 256, K
 // = 768, input gradient, 12.9 -> 14.0).
-// Beside another stream's kernels 128x128 tiles of the ring, one per CU on nearly all of them, keep those out for a short
-// contraction (and so do launches with column sums, whose tile is the same under both schedules): two-stream passes of four blocks, D = 1024, two-stage
-// tiles / these, us: 1024 rows 735 / 773, 1000 rows 795 / 825; one stream 848 / 842.  Longer contractions and fewer tiles gain all the same:
-// D = 1024, 3152 rows (200 tiles) 1602 / 1475; D = 1280, 3152 rows (250, K = 5120) 2361 / 2196.
+// Beside another stream's kernels the eight-wavefront tiles of the ring, one per CU on most of them, keep those out for a short
+// contraction (and so do launches with column sums, whose tile is the same under both schedules): up to 2048 rows from 161 of them on, where it is
+// the wide products (QKV, fc1 and its transpose) that take them.  Two-stream passes of four blocks, these / two-stage tiles, us: D = 1024, 800 rows
+// 775 / 758, 1000 rows 870 / 844, 1024 rows 886 / 862; D = 896, 1100 rows 832 / 799; D = 768, 1150 rows 736 / 710; D = 640, 1200 rows 670 /
+// 634; one stream, by the launch with column sums alone: D = 1024, 800 rows 903 / 913, 1000 rows 1020 / 1021, D = 768, 1100 rows 626 / 634.  With
+// more rows so many tiles are products of D x D, which gain: two streams, D = 768, 4000 rows 1245 / 1269, D = 1024, 2600 rows 1560 / 1597; from 225
+// tiles of 128x128 on they do not.  Longer contractions gain all the same: D = 1280, 3152 rows (250, K = 5120) 2196 / 2361.
 // So do 64x128 tiles where 64x64 ones would all run at once, two per CU, and the rows are few: passes of two streams, those / 64x64 tiles, us:
 // four blocks, D = 1280, 200 rows 588 / 574, D = 1536, 200 rows 751 / 715; 32 blocks, D = 1280, 197 rows 4299 / 4144, and one stream, side by side,
 // 3959 / 3854.  More rows gain from them all the same: four blocks, D = 1280, 400 rows 693 / 707, 500 728 / 757; D = 1536, 1000 rows 1322 / 1347.
@@ -190,7 +193,10 @@ static GemmShape pick_gemm_shape(int M, int N, int K, const Epi& epi) {
     if (few) return ring;
     if (brief && tiles_of(M, N, 64, 128) <= 256) return GS_64x128_RING;
     const GemmShape wide = wide_shape(M, N, K, epi, &us);
-    if (!brief && ring == GS_128x128_RING && K <= 1024 && tiles_of(M, N, 128, 128) > 224 && (!epi.solo || epi.colsum)) return wide;
+    if (!brief && K <= 1024 && (!epi.solo || epi.colsum)) {
+        const int tiles = ring == GS_192x128_RING ? tiles_of(M, N, 192, 128) : tiles_of(M, N, 128, 128);
+        if (M <= 2048 ? tiles > 160 : ring == GS_128x128_RING && tiles > 224) return wide;
+    }
     return !brief && ring_us < 0.97 * us ? ring : wide;
 }
 

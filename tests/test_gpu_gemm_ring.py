@@ -14,9 +14,10 @@ pytestmark = pytest.mark.gpu
 # (width, heads, hidden, tokens, samples).  2607 rows, contractions of 648 and 1304 (a last chunk of 8, of 24): 64x128, and 128x128 for fc1
 # and its transpose; 1900 rows, 1288 wide: 128x128 for all but QKV; 6305 rows, 760 wide: 192x128; 3204 rows: 192x128 with column
 # sums, 1160 wide, 1544 hidden; 2560 rows, 880 wide: weight gradients in 256x128 tiles, whose column sums are held to the chunks that
-# 128x128 tiles would have; 201 and 335 rows, 1160 wide: on both sides of the line up to which 64x64 tiles stand in for 64x128
+# 128x128 tiles would have; 201 and 335 rows, 1160 wide: on both sides of the line up to which 64x64 tiles stand in for 64x128; 1067 rows, 960
+# wide, and 2051 rows, 640 wide: on both sides of the line up to which more than 160 eight-wavefront tiles give way on two streams
 CASES = [(648, 9, 1304, 79, 33), (1288, 23, 1288, 95, 20), (760, 19, 2056, 65, 97), (1160, 29, 1544, 89, 36), (880, 11, 2480, 32, 80),
-         (1160, 29, 4648, 67, 3), (1160, 29, 4648, 67, 5)]
+         (1160, 29, 4648, 67, 3), (1160, 29, 4648, 67, 5), (960, 12, 3840, 97, 11), (640, 8, 2560, 293, 7)]
 
 
 @pytest.mark.parametrize("width,heads,hidden,tokens,batch", CASES)
