@@ -258,10 +258,18 @@ static bool side_by_side_is_faster(const rev_cfg& c) {
 // 382, 6304 434 / 396 / 416, 12608 (6e9 FLOP) 578 / 581 / 528; D = 256: 3152 473 / 445 / 424; D = 512: 1576 (1e10) 559 / 534 / 478, 3152 (2e10)
 // 767 / 770 / 877.  float32, D = 64: 3152 464 / 402 / 570; D = 256: 1576 824 / 760 / 753; D = 384: 3152 (1.2e10) 2463 / 2424 / 2323; three
 // blocks of 16 rows, side by side / two streams: D = 512 331 / 361, D = 640 387 / 374, D = 768 437 / 430.
+// Narrow blocks of very many rows have as few FLOP, but what limits them is memory: with the intermediates of two blocks in turn the memory-side
+// cache keeps less of either, and two streams fill the chip.  By rows times width, over 550 stacks of 2 to 12 blocks.  One stream, in turn / side by side:
+// bf16, 11866 x 128 (1.5e6) 1046 / 1008, 18100 x 96 (1.7e6) 278 / 277, 31552 x 64 (2.0e6) 282 / 298, 34742 x 64 (2.2e6) 1327 / 1416; float32, 9062 x 64
+// 974 / 913, 9828 x 128 (1.26e6) 3599 / 3527, 13489 x 128 (1.7e6) 4593 / 4672, 34580 x 64 (2.2e6) 5393 / 5590.  Two streams, two streams / side by
+// side: bf16, 8029 x 64 (5.1e5) 222 / 174, 6765 x 80 (5.4e5) 239 / 257, 8680 x 80 (6.9e5) 608 / 699, 11390 x 64 (7.3e5) 481 / 382, 15617 x 64
+// (1e6) 600 / 652, 42780 x 32 (1.4e6) 837 / 1043: from 5.2e5 to 1.2e6 the two are even in the mean; float32, 1440 x 64 505 / 459, 1125 x 128 (1.44e5)
+// 328 / 286, 2006 x 80 (1.6e5) 728 / 773, 9174 x 32 (2.9e5) 560 / 630.
 static bool apart_side_by_side_is_faster(const rev_cfg& c, bool two_streams) {
     const bool bf = c.mode == REV_MODE_BF16;
-    if (two_streams) return c.d_model <= (bf ? 1280 : 512) && forward_flops(c) < (bf ? 2e9 : 5e8);
-    return forward_flops(c) < (bf ? 8e9 : 1.2e10);
+    const double floats = (double)c.batch * c.seq_len * c.d_model;
+    if (two_streams) return c.d_model <= (bf ? 1280 : 512) && forward_flops(c) < (bf ? 2e9 : 5e8) && floats <= (bf ? 5.2e5 : 1.55e5);
+    return forward_flops(c) < (bf ? 8e9 : 1.2e10) && floats <= (bf ? 1.8e6 : 1.3e6);
 }
 // Blocks of 4.5e7 to 1.3e8 weights, which the memory-side cache does not keep from pass to pass, and few rows: a launch of one product in
 // 32x32 tiles has as many loads under way as one of two products in the 64x64 tiles that hold both, and the chains take turns.  Three blocks, one

@@ -116,6 +116,12 @@ def test_orders_of_the_two_chains():
     assert wide(2048, 100) == wide(2560, 50) == wide(3072, 16) == (turn, two)
     assert wide(1792, 50) == wide(2048, 200) == wide(3072, 100) == wide(4096, 16) == (side, two)
     assert wide(512, 16, "fp32") == (side, side) and wide(640, 16, "fp32") == (side, two)
+    # narrow blocks of very many rows: two streams from 520 000 floats of a residual level on (float32 155 000), in turn from 1.8 (1.3) million
+    narrow = lambda rows, mode: _orders(n_blocks=2, d_model=64, n_heads=1, d_mlp=256, seq_len=32, batch=rows // 32, mode=mode)
+    assert narrow(8096, "bf16") == (side, side) and narrow(8160, "bf16") == narrow(28096, "bf16") == (side, two)
+    assert narrow(28160, "bf16") == (turn, two)
+    assert narrow(2400, "fp32") == (side, side) and narrow(2432, "fp32") == narrow(20288, "fp32") == (side, two)
+    assert narrow(20352, "fp32") == (turn, two)
     assert _orders(**dict(base, n_blocks=1), batch=1) == (turn, turn)
     assert _orders(**dict(base, n_blocks=1), batch=64) == (turn, two)
 
