@@ -38,21 +38,31 @@ __device__ __forceinline__ f32x16_t rows_product(const float (&a)[DHP / 2], cons
     return acc;
 }
 // acc[d, owned] += sum over the tile's rows r of X[r0 + r][32*dt + d] * p[r, owned]; p in accumulator order.  Rows from `rows`
-// on count as zeros whatever they hold: their p is 0, but 0 times an infinity or a NaN would not be.
+// on count as zeros whatever they hold: their p is 0, but 0 times an infinity or a NaN would not be.  The columns are requested
+// before the first product: left to the compiler, which of its loops wait for every element by itself changes from kernel to kernel.
+// Four float32 blocks, both passes of the backward / the forward, us, left to it and this way: 54732 heads of one token, 32 features 4915 / 895 and
+// 4500 / 825; 161 of 503 tokens, 32 features 1351 / 326 and 1261 / 332; 394 of 46, 80 features 438 / 114 and 395 / 110; three blocks, 80 of 100, 128
+// features 259 / 139 and 202 / 80; 18 of 197, 64 features 84 / 47 and 79 / 40.
+template <typename T>
+__device__ __forceinline__ void cols_frag(const T* __restrict__ base, int64_t ld, int r0, int rows, int dh, int dt, int lane, T (&x)[16]) {
+    const int c = min(dt * 32 + (lane & 31), dh - 1), g = lane >> 5;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) x[v] = base[(int64_t)min(r0 + 8 * (v >> 2) + 4 * g + (v & 3), rows - 1) * ld + c];
+    __builtin_amdgcn_sched_barrier(0);
+}
+template <typename T>
+__device__ __forceinline__ f32x16_t cols_product(const T (&x)[16], int r0, int rows, int lane, const float (&p)[16], f32x16_t acc) {
+    const int g = lane >> 5;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc = mfma_f32(r0 + 8 * (v >> 2) + 4 * g + (v & 3) < rows ? to_f(x[v]) : 0.f, p[v], acc);
+    return acc;
+}
 template <typename T>
 __device__ __forceinline__ f32x16_t cols_product(const T* __restrict__ base, int64_t ld, int r0, int rows, int dh, int dt, int lane,
                                                  const float (&p)[16], f32x16_t acc) {
-    const int c = min(dt * 32 + (lane & 31), dh - 1), g = lane >> 5;
-    float x[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int r = r0 + 8 * (v >> 2) + 4 * g + (v & 3);
-        const float y = to_f(base[(int64_t)min(r, rows - 1) * ld + c]);
-        x[v] = r < rows ? y : 0.f;
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc = mfma_f32(x[v], p[v], acc);
-    return acc;
+    T x[16];
+    cols_frag(base, ld, r0, rows, dh, dt, lane, x);
+    return cols_product(x, r0, rows, lane, p, acc);
 }
 // Sum over the workgroup's wavefronts of an accumulator, in wavefront order: every wavefront puts its tile to LDS
 // (lane-major, conflict-free), wavefront dt % AF_NW then owns tile dt.
@@ -109,6 +119,9 @@ __device__ __forceinline__ void fwd_rows_f32(const float* __restrict__ qkv, floa
     for (int k0 = wave * 32; k0 < Tk; k0 += AF_NW * 32) {
         float ak[DHP / 2];
         rows_frag<DHP>(base + D, ld, k0, T, dh, lane, ak);
+        float xv[16];
+        constexpr bool EARLY = DT <= 2;                          // beyond 64 features a second workgroup needs the registers
+        if (EARLY) cols_frag(base + 2 * D, ld, k0, Tk, dh, 0, lane, xv);
         const f32x16_t s = rows_product<DHP>(ak, bq);
         float p[16], mloc = -INFINITY;
 #pragma unroll
@@ -131,7 +144,8 @@ __device__ __forceinline__ void fwd_rows_f32(const float* __restrict__ qkv, floa
         for (int dt = 0; dt < DT; ++dt) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[dt][v] *= corr;
-            acc[dt] = cols_product(base + 2 * D, ld, k0, Tk, dh, dt, lane, p, acc[dt]);
+            if (!EARLY || dt > 0) cols_frag(base + 2 * D, ld, k0, Tk, dh, dt, lane, xv);
+            acc[dt] = cols_product(xv, k0, Tk, lane, p, acc[dt]);
         }
     }
     if (g == 0) { sm[wave][lane] = m; sl[wave][lane] = l; }
